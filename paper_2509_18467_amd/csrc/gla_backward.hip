@@ -18,6 +18,9 @@
 //   dk_i = [ R~ v_i + R~z + sum_{h, s>=i} Q'_s ( (dO_s . v_i) / den_s + dden_s ) ] / E_i
 //   dv_i = K'_i R~ + sum_{h, s>=i} (Q'_s . K'_i / den_s) dO_s
 //   R~ <- R~ + sum_h Q'^T d^   (times alpha of the block's first token when the block before it begins)
+// A token whose operands or denominator are not finite may spoil only what the equations say: the sums above run over
+// masked matrices, where a zero weight times an infinity is a NaN.  So a chunk with such a token (or with a key too large
+// to be divided by E) is walked in blocks of one token, and what a block reads of other tokens is cleared.
 // Five launches (three where there are few segments, whose contributions the sweeps fold themselves): the segments' contributions to the state (walked backwards, so that the walk stops once nothing
 // earlier can reach the segment's end), their scan, the forward sweep (dq, dden, and the segments' contributions to
 // the gradient that flows backwards), its scan, the reverse sweep (dk, dv, dg).  The gate's sum over all later tokens
@@ -52,7 +55,7 @@ struct BwdArgs {
   float *dS0, *dz0;
   float* dden;       // [heads][chunks][group][16]
   float* qdq;        // sum_h q (.) dq in the patch layout: [heads][chunks][D / 16][64 lanes][4 tokens]
-  int* blocks;       // [heads][chunks]: into how many blocks the chunk is cut
+  int* blocks;       // [heads][chunks]: into how many blocks the reverse sweep cuts the chunk
   float* slots_f;    // [heads][nseg][D*D + 2D]: forward contributions, then start states
   float* slots_r;    // the same for Gr, segments in reverse order
   int *live_f, *live_r;   // [heads][nseg]: 0 = the segment's total decay is exactly zero in every channel
@@ -275,38 +278,54 @@ __global__ void __launch_bounds__(4 * D, 2) bwd_forward_kernel(const BwdArgs a) 
 
   const int nchunk = (rows + kC - 1) / kC;
   int ci = 0, blk = 0, hb = 0, nblk = 1, cut = 1, lo = 0, hi = kC;
+  bool bad = false;      // a token of the chunk has operands or a denominator that are not finite
   Decay d;
   float kk[4], kp[4], zt[4], wf = 0.f;
   if (nchunk > 0) fetch(0, 0);
   while (ci < nchunk) {
     const int row0 = ci * kC;
     const size_t chunk = (size_t)bh * a.chunks + (s0 + row0) / kC;
-    // ---- rows to LDS, gates
-    if (hb == 0) {
-      St::template to_lds<D>(sm + L::oV, g, n, 16 * w, rv);
-      if (blk == 0) {
-        float gl[4];
-        St::patch(qd, rg, gl);
-        St::patch(qd, rk, kk);
+    // ---- rows to LDS (the block's tokens), gates
+    auto rows_to_lds = [&] {
+      const bool part = hi - lo < kC;
+      if (hb == 0) St::template to_lds<D>(sm + L::oV, g, n, 16 * w, part ? St::keep(rv, g, n, lo, hi) : rv);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) d.al[i] = row0 + 4 * g + i < rows ? alpha_of(gl[i], a.gate_scale) : 1.f;
-        cut = whole_chunk<Wide<T>>(d, ln, g);
-        if (l == 0) reinterpret_cast<int*>(sm + L::oFlag)[w] = cut;
+      for (int h = 0; h < HB; ++h) St::template to_lds<D>(sm + h * L::kSet, g, n, 16 * w, part ? St::keep(ro[h], g, n, lo, hi) : ro[h]);
+      if (tid < HB * kC) reinterpret_cast<float*>(sm + L::oDen)[tid] = (tid & 15) >= lo && (tid & 15) < hi ? inverse<T>(rden) : 0.f;
+    };
+    const bool fresh = hb == 0 && blk == 0;      // the chunk's first block is not known yet
+    lo = fresh ? 0 : blk * (kC / nblk);
+    hi = fresh ? kC : lo + kC / nblk;
+    if (fresh) {
+      float gl[4];
+      St::patch(qd, rg, gl);
+      St::patch(qd, rk, kk);
+      bool tame = true;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        d.al[i] = row0 + 4 * g + i < rows ? alpha_of(gl[i], a.gate_scale) : 1.f;
+        tame = tame && fabsf(kk[i]) < kTame;
       }
+      cut = whole_chunk<Wide<T>>(d, ln, g);
+      if (__builtin_amdgcn_ballot_w64(!tame) != 0) cut = kC;
+      if (l == 0) reinterpret_cast<int*>(sm + L::oFlag)[w] = cut;
+      bad = false;
     }
-#pragma unroll
-    for (int h = 0; h < HB; ++h) St::template to_lds<D>(sm + h * L::kSet, g, n, 16 * w, ro[h]);
-    if (tid < HB * kC) reinterpret_cast<float*>(sm + L::oDen)[tid] = inverse<T>(rden);
+    rows_to_lds();
     float qq[HB][4];
 #pragma unroll
     for (int h = 0; h < HB; ++h) St::patch(qd, rq[h], qq[h]);
     __syncthreads();
-    if (hb == 0 && blk == 0) {
+    if (fresh) {
       int m = 1;
 #pragma unroll
       for (int j = 0; j < NW; ++j) m = max(m, reinterpret_cast<const int*>(sm + L::oFlag)[j]);
       nblk = __builtin_amdgcn_readfirstlane(m);
-      if (tid == 0) a.blocks[chunk] = nblk;
+      if (nblk > 1) {
+        hi = kC / nblk;
+        rows_to_lds();
+        __syncthreads();
+      }
     }
     const int hb1 = hb + 1 < nb ? hb + 1 : 0;
     const int blk1 = hb1 ? blk : (blk + 1 < nblk ? blk + 1 : 0);
@@ -314,8 +333,6 @@ __global__ void __launch_bounds__(4 * D, 2) bwd_forward_kernel(const BwdArgs a) 
     if (ci1 < nchunk) fetch(ci1, hb1);
     // ---- once per block: decays, K', the state decayed up to the first token, z_t
     if (hb == 0) {
-      lo = blk * (kC / nblk);
-      hi = lo + kC / nblk;
       if (nblk > 1) block_of_chunk<Wide<T>>(d, ln, g, lo, hi);
       const float f = d.first * pend;
 #pragma unroll
@@ -394,12 +411,15 @@ __global__ void __launch_bounds__(4 * D, 2) bwd_forward_kernel(const BwdArgs a) 
       }
     }
     Rz += rz;
+    // q and dO reach rz through dden, and a denominator of zero does: what is not finite in any of them shows here
+    bad = bad || __builtin_amdgcn_ballot_w64(!(rz - rz == 0)) != 0;
     if (seg > 0 && carries) accumulate<T, D, HB>(R, sm, g, n, qw);
     if (last_head) {
       float kp1[1][4] = {{kp[0], kp[1], kp[2], kp[3]}};
       accumulate<T, D, 1>(X, sm + L::oV, g, n, kp1);
       if (blk + 1 == nblk) {
         *reinterpret_cast<floatx4*>(a.qdq + ((chunk * NW + w) * 64 + l) * 4) = floatx4{qdq[0], qdq[1], qdq[2], qdq[3]};
+        if (tid == 0) a.blocks[chunk] = bad ? kC : nblk;
 #pragma unroll
         for (int i = 0; i < 4; ++i) qdq[i] = 0.f;
       }
@@ -540,12 +560,15 @@ __global__ void __launch_bounds__(4 * D, 2) bwd_reverse_kernel(const BwdArgs a) 
       }
       St::template to_lds<D>(sm + L::oV, g, n, 16 * w, rv);
     }
+    // the block's tokens only (v: every token's row stays its own)
+    const bool part = hi - lo < kC;
 #pragma unroll
-    for (int h = 0; h < HB; ++h) St::template to_lds<D>(sm + h * L::kSet, g, n, 16 * w, ro[h]);
+    for (int h = 0; h < HB; ++h) St::template to_lds<D>(sm + h * L::kSet, g, n, 16 * w, part ? St::keep(ro[h], g, n, lo, hi) : ro[h]);
     float* den = reinterpret_cast<float*>(sm + L::oDen);
     if (tid < HB * kC) {
-      den[tid] = inverse<T>(rden);
-      den[HB * kC + tid] = rdd;
+      const bool in = (tid & 15) >= lo && (tid & 15) < hi;
+      den[tid] = in ? inverse<T>(rden) : 0.f;
+      den[HB * kC + tid] = in ? rdd : 0.f;
     }
     float qp[HB][4];
 #pragma unroll
@@ -650,21 +673,25 @@ __global__ void __launch_bounds__(4 * D, 2) bwd_reverse_kernel(const BwdArgs a) 
       }
     }
     if (hb + 1 == nb) {
-      // ---- outputs of the block; the gate's sum over this token and all later ones: an upper triangle of ones
+      // ---- outputs of the block; the gate's sum over this token and all later ones (by additions: no later token's sum
+      // holds an earlier token's term, finite or not)
       float dkv[4], dvv[4], dgv[4];
-      float ones[4], x[4];
+      Wide<T> x[4];
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         const int t = 4 * g + i;
         dkv[i] = (dk0[i] + dk[i]) * rE[i];
         dvv[i] = dv0[i] + dv[i];
         x[i] = (t >= lo && t < hi) ? fmaf(-kk[i], dkv[i], qdq[i]) : 0.f;
-        ones[i] = row <= t ? 1.f : 0.f;
       }
-      const floatx4 gs = token_steps<kWide>(ones, x, floatx4{later, later, later, later});
-      later = lane_get(ln.n4, gs[0]);
 #pragma unroll
-      for (int i = 0; i < 4; ++i) dgv[i] = gs[i] * a.gate_scale * sig[i];
+      for (int i = 2; i >= 0; --i) x[i] += x[i + 1];
+      const Wide<T> x1 = lane_get(ln.x1, x[0]), x2 = lane_get(ln.x2, x[0]), x3 = lane_get(ln.x3, x[0]);
+      const Wide<T> after = (g & 2) ? ((g & 1) ? Wide<T>(0) : x1) : ((g & 1) ? x2 + x3 : x1 + (x2 + x3));
+      const Wide<T> rest = after + (Wide<T>)later;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) dgv[i] = (float)(x[i] + rest) * a.gate_scale * sig[i];
+      later = lane_get(ln.n4, (float)(x[0] + rest));
       St::store(dK, qd, offk, row0, g, n, lo, hi, dkv);
       St::store(dV, qd, offk, row0, g, n, lo, hi, dvv);
       St::store(dG, qd, offk, row0, g, n, lo, hi, dgv);

@@ -71,10 +71,6 @@ struct WalkLds {
   static constexpr int kBytes = oFlag + 32;
 };
 
-// Larger keys would overflow divided by a block's decay (2^-64 at least), and a zero weight times an infinity or a NaN
-// would reach tokens that must not see it: chunks with such values are walked token by token.
-constexpr float kTame = 1.152921504606847e18f;   // 2^60
-
 // one element of a row as stored
 template <typename T>
 __device__ inline float load_one(const Rows& r, unsigned off) {
