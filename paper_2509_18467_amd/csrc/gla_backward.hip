@@ -278,7 +278,8 @@ __global__ void __launch_bounds__(4 * D, 2) bwd_forward_kernel(const BwdArgs a) 
 
   const int nchunk = (rows + kC - 1) / kC;
   int ci = 0, blk = 0, hb = 0, nblk = 1, cut = 1, lo = 0, hi = kC;
-  bool bad = false;      // a token of the chunk has operands or a denominator that are not finite
+  constexpr int kBad = 256;
+  bool bad = false;      // a token of the chunk has a query too large, or operands or a denominator that are not finite
   Decay d;
   float kk[4], kp[4], zt[4], wf = 0.f;
   if (nchunk > 0) fetch(0, 0);
@@ -308,18 +309,25 @@ __global__ void __launch_bounds__(4 * D, 2) bwd_forward_kernel(const BwdArgs a) 
       }
       cut = whole_chunk<Wide<T>>(d, ln, g);
       if (__builtin_amdgcn_ballot_w64(!tame) != 0) cut = kC;
-      if (l == 0) reinterpret_cast<int*>(sm + L::oFlag)[w] = cut;
       bad = false;
     }
     rows_to_lds();
     float qq[HB][4];
 #pragma unroll
     for (int h = 0; h < HB; ++h) St::patch(qd, rq[h], qq[h]);
+    float top = 0.f;       // largest |q|
+#pragma unroll
+    for (int h = 0; h < HB; ++h)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) top = fmaxf(top, fabsf(qq[h][i]));
+    bad = bad || __builtin_amdgcn_ballot_w64(!(top < kTame)) != 0;
+    int* flags = reinterpret_cast<int*>(sm + L::oFlag);      // per wave: the cut of its channels, and whether its part is bad
+    if (l == 0) flags[w] = cut | (bad ? kBad : 0);
     __syncthreads();
     if (fresh) {
       int m = 1;
 #pragma unroll
-      for (int j = 0; j < NW; ++j) m = max(m, reinterpret_cast<const int*>(sm + L::oFlag)[j]);
+      for (int j = 0; j < NW; ++j) m = max(m, flags[j] & (kBad - 1));
       nblk = __builtin_amdgcn_readfirstlane(m);
       if (nblk > 1) {
         hi = kC / nblk;
@@ -334,6 +342,7 @@ __global__ void __launch_bounds__(4 * D, 2) bwd_forward_kernel(const BwdArgs a) 
     // ---- once per block: decays, K', the state decayed up to the first token, z_t
     if (hb == 0) {
       if (nblk > 1) block_of_chunk<Wide<T>>(d, ln, g, lo, hi);
+      center(d);
       const float f = d.first * pend;
 #pragma unroll
       for (int jt = 0; jt < D / 16; ++jt)
@@ -353,7 +362,7 @@ __global__ void __launch_bounds__(4 * D, 2) bwd_forward_kernel(const BwdArgs a) 
       for (int i = 0; i < 4; ++i) zt[i] = d.E[i] * pz[i];
       z = lane_get(ln.n4 + 192, pz[3]);      // all of the block's tokens
       wf = P * d.first;
-      P = wf * d.last;
+      P *= d.first * d.last;
       pend = d.last;
     }
     // ---- u_t = E_t ( S~ dO_t + sum_{i <= t} (dO_t . v_i) K'_i )
@@ -419,7 +428,12 @@ __global__ void __launch_bounds__(4 * D, 2) bwd_forward_kernel(const BwdArgs a) 
       accumulate<T, D, 1>(X, sm + L::oV, g, n, kp1);
       if (blk + 1 == nblk) {
         *reinterpret_cast<floatx4*>(a.qdq + ((chunk * NW + w) * 64 + l) * 4) = floatx4{qdq[0], qdq[1], qdq[2], qdq[3]};
-        if (tid == 0) a.blocks[chunk] = bad ? kC : nblk;
+        if (tid == 0) {
+          int any = bad ? kBad : 0;
+#pragma unroll
+          for (int j = 0; j < NW; ++j) any |= flags[j];
+          a.blocks[chunk] = (any & kBad) ? kC : nblk;
+        }
 #pragma unroll
         for (int i = 0; i < 4; ++i) qdq[i] = 0.f;
       }
@@ -542,6 +556,7 @@ __global__ void __launch_bounds__(4 * D, 2) bwd_reverse_kernel(const BwdArgs a) 
       lo = blk * (kC / nblk);
       hi = lo + kC / nblk;
       if (nblk > 1) block_of_chunk<Wide<T>>(d, ln, g, lo, hi);
+      center(d);
       const float f = d.last * pend;
       pend = d.first;
       Rz *= f;

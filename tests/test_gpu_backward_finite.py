@@ -101,3 +101,34 @@ def test_a_key_too_large_to_be_divided_by_a_decay(oracle, shape):
     got = _run(wl, *x, den, *start)
     assert all(np.isfinite(a).all() for a in got.values())
     _check(wl, got, ref, "before the key", dq=before)
+
+
+@pytest.mark.parametrize("which", ["q", "k", "v", "dO"])
+@pytest.mark.parametrize("sign", [1, -1])
+@pytest.mark.parametrize("shape", [SHAPES[0], SHAPES[2], SHAPES[4]], ids=str)
+def test_tiny_and_huge_values_in_channels_that_nearly_close(oracle, shape, which, sign):
+    """Chunks that decay by nearly 2^-64, and operands scaled by a power of two: the gradients scale by powers of two as the
+    equations say (eps = 0).  2^80 in fp32 storage; 2^64 in bf16 storage, whose products need 16 bits below an fp32 value."""
+    power = sign * (80 if shape[3] == "fp32" else 64)
+    wl, (q, k, v, g, dO), _ = _inputs(*shape[:5], False)
+    g[:, :, 0] = H.host(torch.tensor(-2.6875))
+    print("backward, scaled operand", wl, which, power, flush=True)
+    den = oracle.gla_prefill(q, k, v, g, 1.0, 0.0)["den"].astype(np.float32)
+    ref = _run(wl, q, k, v, g, dO, den, None, None)
+    f = np.float32(2.0) ** np.float32(power)
+    got = {"q": lambda: _run(wl, q * f, k, v, g, dO, den * f, None, None), "k": lambda: _run(wl, q, k * f, v, g, dO, den * f, None, None),
+           "v": lambda: _run(wl, q, k, v * f, g, dO, den, None, None), "dO": lambda: _run(wl, q, k, v, g, dO * f, den, None, None)}[which]()
+    scales = {"q": dict(dq=-1), "k": dict(dk=-1), "v": dict(dq=1, dk=1, dg=1), "dO": dict(dq=1, dk=1, dv=1, dg=1)}[which]
+    # dg: a sum over the later tokens of differences of these, which nearly cancel; dq is such a difference itself, of terms
+    # two to three times its size, and 2^-18 of those is 1e-5 of the RMS
+    G = wl.Hq // wl.Hkv
+    terms = np.abs(q * ref["dq"]).reshape(1, wl.T, wl.Hkv, G, wl.d).sum(axis=3) + np.abs(k * ref["dk"])
+    terms = {"dg": np.cumsum(terms[:, ::-1], axis=1)[:, ::-1]}
+    for n in ref:
+        back = got[n] * 2.0 ** (-power * scales.get(n, 0))
+        # powers of two change no rounding; a chunk walked in other blocks does: 64 fp32 ulps of the terms, and an ulp of
+        # storage where they lie between two bf16 values
+        lim = 1e-5 * H.rms(ref[n]) + H.FP32_REL * terms.get(n, 0.0) + (2 * H.BF16_HALF_ULP * np.abs(ref[n]) if wl.dtype == "bf16" else 0.0)
+        ratio = np.abs(back - ref[n]) / lim
+        print(f"  {n}: {ratio.max():.3f} of its bar", flush=True)
+        assert ratio.max() <= 1.0, n
