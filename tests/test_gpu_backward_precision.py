@@ -47,3 +47,72 @@ def test_decay(gate_scale, scale, dtype):
     print(f"  RMS error {err[0]:.3f} units of 2^-24, with library functions {err[1]:.3f}", flush=True)
     # sixteen thousand values: either RMS is known to about one percent
     assert err[0] <= 1.02 * err[1]
+
+
+def _token_by_token(q, k, v, g, dO, den, gate_scale, S0, z0):
+    """The adjoint as the recurrence gives it, token by token in fp32."""
+    B, T, Hq, d = q.shape
+    Hkv = k.shape[2]
+    G = Hq // Hkv
+    al = torch.sigmoid(g) if gate_scale == 1.0 else torch.exp(gate_scale * torch.nn.functional.logsigmoid(g))
+    rd = 1.0 / den
+    dn = (dO * rd[..., None]).reshape(B, T, Hkv, G, d)
+    q, rd = q.reshape(B, T, Hkv, G, d), rd.reshape(B, T, Hkv, G)
+    S, z, dq, dd = S0, z0, torch.empty_like(q), torch.empty_like(rd)
+    for t in range(T):
+        S = torch.addcmul(k[:, t, :, :, None] * v[:, t, :, None, :], al[:, t, :, :, None], S)
+        z = torch.addcmul(k[:, t], al[:, t], z)
+        for h in range(G):
+            u = (S * dn[:, t, :, h, None, :]).sum(-1)
+            dd[:, t, :, h] = -(q[:, t, :, h] * u).sum(-1) * rd[:, t, :, h]
+            dq[:, t, :, h] = torch.addcmul(u, z, dd[:, t, :, h, None])
+    X, xz, later = torch.zeros_like(S0), torch.zeros_like(z0), torch.zeros_like(z0)
+    dk, dv, dg = torch.empty_like(k), torch.empty_like(v), torch.empty_like(g)
+    for t in reversed(range(T)):
+        for h in range(G):
+            X = torch.addcmul(X, q[:, t, :, h, :, None], dn[:, t, :, h, None, :])
+            xz = torch.addcmul(xz, q[:, t, :, h], dd[:, t, :, h, None])
+        dk[:, t] = (X * v[:, t, :, None, :]).sum(-1) + xz
+        dv[:, t] = (X * k[:, t, :, :, None]).sum(-2)
+        later = later + ((q[:, t] * dq[:, t]).sum(2) - k[:, t] * dk[:, t])
+        dg[:, t] = later * gate_scale * torch.sigmoid(-g[:, t])
+        X, xz = X * al[:, t, :, :, None], xz * al[:, t]
+    return dict(dq=dq.reshape(B, T, Hq, d), dk=dk, dv=dv, dg=dg, dS0=X, dz0=xz)
+
+
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+@pytest.mark.parametrize("gate_scale", [1.0, 0.0625])
+@pytest.mark.parametrize("d,G", [(64, 1), (64, 4), (64, 8), (128, 2)])
+def test_gradients(oracle, d, G, gate_scale, dtype):
+    """2-norms of the errors of the start state's gradient, which is stored in fp32."""
+    wl = Workload("precision", B=128, T=18, Hq=2 * G, Hkv=2, d=d, dtype=dtype)
+    print("gradients", wl, gate_scale, flush=True)
+    rng = np.random.default_rng(72)
+    dt = H.tdtype(wl)
+
+    def store(a):
+        return H.host(H.dev(a.astype(np.float32), dt)).astype(np.float32)
+
+    def phi(a):
+        return np.where(a > 0, 1 + a, np.exp(np.minimum(a, 0)))
+
+    q, k = (store(phi(rng.standard_normal((wl.B, wl.T, h, d)) * 0.125)) for h in (wl.Hq, 2))
+    v, g, dO = (store(rng.standard_normal((wl.B, wl.T, h, d)) * s) for h, s in ((2, 0.125), (2, 1.0), (wl.Hq, 0.5)))
+    S0 = (rng.standard_normal((wl.B, 2, d, d)) * 0.25).astype(np.float32)
+    z0 = (np.abs(rng.standard_normal((wl.B, 2, d)) * 2) + 4).astype(np.float32)
+    den = oracle.gla_prefill(q, k, v, g, gate_scale, 0.0, S0, z0)["den"].astype(np.float32)
+    ref = oracle.gla_backward(q, k, v, g, dO, gate_scale, 0.0, S0, z0)
+    ins = [H.dev(a, dt) for a in (q, k, v, g)]
+    outs = [torch.empty_like(t) for t in ins] + [torch.empty(wl.B, 2, d, d, device="cuda"), torch.empty(wl.B, 2, d, device="cuda")]
+    desc = H.desc_for(wl, gate_scale=gate_scale)
+    lawcat.gla_backward(desc, *ins, H.dev(den), H.dev(dO, dt), H.dev(S0), H.dev(z0), *outs, lawcat.alloc_workspace(desc, lawcat.CALL_GLA_BACKWARD))
+    torch.cuda.synchronize()
+    names = ("dq", "dk", "dv", "dg", "dS0", "dz0")
+    rec = _token_by_token(*(H.dev(a) for a in (q, k, v, g, dO, den)), gate_scale, H.dev(S0), H.dev(z0))
+    for n, t in zip(names, outs):
+        if n[1] not in "Sz":
+            continue
+        err = [np.linalg.norm(H.host(a) - ref[n]) / np.linalg.norm(ref[n]) for a in (t, rec[n])]
+        print(f"  {n}: {err[0]:.3e}, token by token {err[1]:.3e}", flush=True)
+        # the norm of thousands of independent errors: known to one percent
+        assert err[0] <= 1.02 * err[1], n
