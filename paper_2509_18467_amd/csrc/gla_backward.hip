@@ -212,7 +212,7 @@ struct Sweep {
   static constexpr int oU = oK + kC * f32_row_bytes<D>();
   static constexpr int kU = (D > HB * kC ? D : HB * kC) * f32_row_bytes<D>();
   static constexpr int oSc = oU + kU;
-  static constexpr int kScore = sizeof(T) == 2 ? 3 * 512 : 1024;  // per head: three terms of 8 bytes per lane, or one fp32 tile
+  static constexpr int kScore = sizeof(T) == 2 ? 3 * 512 : 2048;  // per head: three terms of 8 bytes per lane, or one fp64 tile
   static constexpr int kReverse = oSc + HB * kScore;
 };
 
@@ -549,6 +549,7 @@ __global__ void __launch_bounds__(4 * D, 2) bwd_reverse_kernel(const BwdArgs a) 
   Decay d;
   float kk[4], kp[4], rE[4], sig[4], qdq[4];
   floatx4 dk0, dk, dv0, dv;     // from after the block (state products), within it
+  doublex4 dvw;                 // fp32 storage: dv0 + dv
   if (ci >= 0) fetch(ci, 0);
   while (ci >= 0) {
     const int row0 = ci * kC;
@@ -620,6 +621,7 @@ __global__ void __launch_bounds__(4 * D, 2) bwd_reverse_kernel(const BwdArgs a) 
       contract<T, D, 1>(R, sm + L::oV, g, n, acc);
       dk0 = acc[0];
       dk = dv0 = dv = floatx4{0.f, 0.f, 0.f, 0.f};
+      dvw = kZero64;
 #pragma unroll
       for (int ct = 0; ct < D / 16; ++ct) {
         const floatx4 f = f32_row_frag<D>(sm + L::oK, g, row, ct);
@@ -629,7 +631,12 @@ __global__ void __launch_bounds__(4 * D, 2) bwd_reverse_kernel(const BwdArgs a) 
           fa[i] = f[i];
           r[i] = *reinterpret_cast<const float*>(sm + L::oU + (16 * ct + 4 * g + i) * f32_row_bytes<D>() + c * 4);
         }
-        dv0 = token_steps<kWide>(fa, r, dv0);
+        if constexpr (kWide) {
+#pragma unroll
+          for (int i = 0; i < 4; ++i) dvw = mfma_f64(fa[i], r[i], dvw);
+        } else {
+          dv0 = token_steps<false>(fa, r, dv0);
+        }
       }
       __syncthreads();
     }
@@ -638,17 +645,21 @@ __global__ void __launch_bounds__(4 * D, 2) bwd_reverse_kernel(const BwdArgs a) 
     __syncthreads();
     // ---- scores of head w: Q'_s . K'_i / den_s for i <= s, shared through LDS (in the terms the product below uses)
     if (w < HB) {
-      floatx4 sc = dot_rows<float, D, kWide>(sm + L::oU + w * kC * f32_row_bytes<D>(), sm + L::oK, g, n);   // [s][`row`]
+      const unsigned char* qrows = sm + L::oU + w * kC * f32_row_bytes<D>();
       const floatx4 rd = *reinterpret_cast<const floatx4*>(sm + L::oDen + (w * kC + 4 * g) * 4);
-#pragma unroll
-      for (int i = 0; i < 4; ++i) sc[i] = row <= 4 * g + i ? sc[i] * rd[i] : 0.f;
       unsigned char* p = sm + L::oSc + w * L::kScore;
       if constexpr (sizeof(T) == 2) {
+        floatx4 sc = dot_rows<float, D>(qrows, sm + L::oK, g, n);   // [s][`row`]
+#pragma unroll
+        for (int i = 0; i < 4; ++i) sc[i] = row <= 4 * g + i ? sc[i] * rd[i] : 0.f;
         const Split4 s = split4(sc[0], sc[1], sc[2], sc[3]);
 #pragma unroll
         for (int k = 0; k < 3; ++k) *reinterpret_cast<uint2*>(p + k * 512 + l * 8) = s.t[k];
       } else {
-        *reinterpret_cast<floatx4*>(p + l * 16) = sc;
+        doublex4 sc = dot_rows64<D>(qrows, sm + L::oK, g, n);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) sc[i] = row <= 4 * g + i ? sc[i] * (double)rd[i] : 0.0;
+        *reinterpret_cast<doublex4*>(p + l * 32) = sc;
       }
     }
     // ---- dk within the block, and what the block adds to the gradient flowing on
@@ -696,10 +707,10 @@ __global__ void __launch_bounds__(4 * D, 2) bwd_reverse_kernel(const BwdArgs a) 
     } else {
 #pragma unroll
       for (int h = 0; h < HB; ++h) {
-        const floatx4 sc = *reinterpret_cast<const floatx4*>(sm + L::oSc + h * L::kScore + l * 16);
+        const doublex4 sc = *reinterpret_cast<const doublex4*>(sm + L::oSc + h * L::kScore + l * 32);
         const floatx4 f = f32_col_frag<D>(sm + h * L::kSet, g, n, w);
-        const float sa[4] = {sc[0], sc[1], sc[2], sc[3]}, fa[4] = {f[0], f[1], f[2], f[3]};
-        dv = token_steps<kWide>(sa, fa, dv);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) dvw = mfma_f64(sc[i], f[i], dvw);
       }
     }
     if (hb + 1 == nb) {
@@ -711,7 +722,7 @@ __global__ void __launch_bounds__(4 * D, 2) bwd_reverse_kernel(const BwdArgs a) 
       for (int i = 0; i < 4; ++i) {
         const int t = 4 * g + i;
         dkv[i] = (dk0[i] + dk[i]) * rE[i];
-        dvv[i] = dv0[i] + dv[i];
+        dvv[i] = kWide ? (float)dvw[i] : dv0[i] + dv[i];
         x[i] = (t >= lo && t < hi) ? fmaf(-kk[i], dkv[i], qdq[i]) : 0.f;
       }
 #pragma unroll

@@ -84,7 +84,7 @@ def _token_by_token(q, k, v, g, dO, den, gate_scale, S0, z0):
 @pytest.mark.parametrize("gate_scale", [1.0, 0.0625])
 @pytest.mark.parametrize("d,G", [(64, 1), (64, 4), (64, 8), (128, 2)])
 def test_gradients(oracle, d, G, gate_scale, dtype):
-    """2-norms of the errors of the start state's gradient, which is stored in fp32."""
+    """2-norms of the errors of the outputs that are stored in fp32."""
     wl = Workload("precision", B=128, T=18, Hq=2 * G, Hkv=2, d=d, dtype=dtype)
     print("gradients", wl, gate_scale, flush=True)
     rng = np.random.default_rng(72)
@@ -110,7 +110,7 @@ def test_gradients(oracle, d, G, gate_scale, dtype):
     names = ("dq", "dk", "dv", "dg", "dS0", "dz0")
     rec = _token_by_token(*(H.dev(a) for a in (q, k, v, g, dO, den)), gate_scale, H.dev(S0), H.dev(z0))
     for n, t in zip(names, outs):
-        if n[1] not in "Sz":
+        if t.dtype != torch.float32:
             continue
         err = [np.linalg.norm(H.host(a) - ref[n]) / np.linalg.norm(ref[n]) for a in (t, rec[n])]
         print(f"  {n}: {err[0]:.3e}, token by token {err[1]:.3e}", flush=True)
