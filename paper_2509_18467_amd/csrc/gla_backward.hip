@@ -53,10 +53,11 @@ struct BwdArgs {
   const float *S0, *z0;
   void *dq, *dk, *dv, *dg;
   float *dS0, *dz0;
-  float* dden;       // [heads][chunks][group][16]
-  float* qdq;        // sum_h q (.) dq in the patch layout: [heads][chunks][D / 16][64 lanes][4 tokens]
-  int* blocks;       // [heads][chunks]: into how many blocks the reverse sweep cuts the chunk
-  float* slots_f;    // [heads][nseg][D*D + 2D]: forward contributions, then start states
+  float* dden;       // [heads][tokens][group], a chunk's as [group][its tokens]
+  float* qdq;        // sum_h q (.) dq: [heads][tokens][D], a chunk's in the patch layout ([D / 16][64 lanes][4 tokens]), or, of
+                     // fewer than 16 tokens, as [D][its tokens]
+  uint8_t* blocks;   // [heads][chunks]: into how many blocks the reverse sweep cuts the chunk
+  float* slots_f;    // [heads][nseg - 1][D*D + 2D]: forward contributions, then the states after the segments
   float* slots_r;    // the same for Gr, segments in reverse order
   int *live_f, *live_r;   // [heads][nseg]: 0 = the segment's total decay is exactly zero in every channel
   int B, T, Hq, Hkv, group, seg_len, nseg, chunks;
@@ -64,35 +65,24 @@ struct BwdArgs {
   float gate_scale;
 };
 
-// Any of the segments of this head passes its start state on (otherwise the scan left the contributions where they
-// were, and a segment starts from its predecessor's).  Uniform; contains a barrier.
-__device__ inline bool scan_ran(const int* live, int nseg) {
-  int any = 0;
-  for (int j = threadIdx.x; j < nseg - 1; j += blockDim.x) any |= live[j];
-  return __syncthreads_or(any) != 0;
-}
-
 template <int D> constexpr int slot_floats() { return D * D + 2 * D; }
 
-// This lane's part (channel c, value columns 16 jt + 4 g ..) of the state before segment `seg`: what the scan left, or, with few
+// This lane's part (channel c, value columns 16 jt + 4 g ..) of the state before segment `seg`: what the scan left (it leaves the
+// contributions as they are where no segment passes its start state on: they are the states after them then), or, with few
 // segments, the contributions before it folded here, from after the last segment whose total decay is exactly zero.
-// slots, live: of this head; S0, z0: its start state or null.  Uniform; contains a barrier unless folding.
+// slots, live: of this head; S0, z0: its start state or null.  Uniform.
 template <int D>
-__device__ inline void start_state(const float* slots, const int* live, int nseg, bool fold, int seg, const float* S0, const float* z0,
+__device__ inline void start_state(const float* slots, const int* live, bool fold, int seg, const float* S0, const float* z0,
                                    int c, int g, floatx4 (&X)[D / 16], float& z) {
-  int first = 0;                             // first segment whose contribution is still to be added
+  int first = seg;                           // first segment whose contribution is still to be added
   const float *src = nullptr, *zsrc = nullptr;
   if (fold) {
     const int l = threadIdx.x & 63;
     const unsigned long long m = __builtin_amdgcn_ballot_w64(l < seg && live[l] == 0);
     first = m ? 64 - __builtin_clzll(m) : 0;
-    if (first > 0) src = slots + (size_t)(first - 1) * slot_floats<D>();
-  } else {
-    const bool scanned = nseg > 1 && scan_ran(live, nseg);
-    if (scanned || seg > 0) src = slots + (size_t)(scanned ? seg : seg - 1) * slot_floats<D>();
-    first = seg;
   }
-  if (src) {
+  if (first > 0) {
+    src = slots + (size_t)(first - 1) * slot_floats<D>();
     zsrc = src + D * D;
   } else {
     src = S0;
@@ -181,7 +171,7 @@ __global__ void __launch_bounds__(4 * D) bwd_state_kernel(const BwdArgs a) {
     if (!more) break;
     __syncthreads();
   }
-  float* slot = a.slots_f + ((size_t)bh * a.nseg + seg) * slot_floats<D>();
+  float* slot = a.slots_f + ((size_t)bh * (a.nseg - 1) + seg) * slot_floats<D>();
   const int c = 16 * w + n;
 #pragma unroll
   for (int jt = 0; jt < D / 16; ++jt) *reinterpret_cast<floatx4*>(slot + (size_t)c * D + 16 * jt + 4 * g) = X[jt];
@@ -246,7 +236,7 @@ __global__ void __launch_bounds__(4 * D, 2) bwd_forward_kernel(const BwdArgs a) 
   floatx4 X[D / 16], R[D / 16];
   float z = 0.f;
   double Rz = 0.0;       // a long sum of signed terms: 64 bits
-  start_state<D>(a.slots_f + (size_t)bh * a.nseg * slot_floats<D>(), a.live_f + (size_t)bh * a.nseg, a.nseg, a.fold, seg,
+  start_state<D>(a.slots_f + (size_t)bh * (a.nseg - 1) * slot_floats<D>(), a.live_f + (size_t)bh * a.nseg, a.fold, seg,
                  a.S0 ? a.S0 + (size_t)bh * D * D : nullptr, a.z0 ? a.z0 + (size_t)bh * D : nullptr, c, g, X, z);
 #pragma unroll
   for (int jt = 0; jt < D / 16; ++jt) R[jt] = floatx4{0.f, 0.f, 0.f, 0.f};
@@ -285,7 +275,8 @@ __global__ void __launch_bounds__(4 * D, 2) bwd_forward_kernel(const BwdArgs a) 
   if (nchunk > 0) fetch(0, 0);
   while (ci < nchunk) {
     const int row0 = ci * kC;
-    const size_t chunk = (size_t)bh * a.chunks + (s0 + row0) / kC;
+    const size_t chunk = (size_t)bh * a.chunks + (s0 + row0) / kC, token = (size_t)bh * a.T + s0 + row0;
+    const int len = min(kC, rows - row0);        // the chunk's tokens
     // ---- rows to LDS (the block's tokens), gates
     auto rows_to_lds = [&] {
       const bool part = hi - lo < kC;
@@ -400,15 +391,14 @@ __global__ void __launch_bounds__(4 * D, 2) bwd_forward_kernel(const BwdArgs a) 
     // lane forming all of its row's sixteen, in fp32: 489 us for the call at 32768 tokens, this 471)
     float mine;
     {
-      const int at = ((n >> 2) & (HB - 1)) * kC + 4 * g + (n & 3);
+      const int h = (n >> 2) & (HB - 1), t = 4 * g + (n & 3), at = h * kC + t;
       double s = 0.0;
 #pragma unroll
       for (int j = 0; j < NW; ++j) s += (double)part[j * HB * kC + at];
       const float* den = reinterpret_cast<const float*>(sm + L::oDen);
       const double r = den[at], rr = r + r * (1.0 - (double)den[HB * kC + at] * r);
       mine = (float)(-(s * rr) * rr);
-      const int t = 4 * g + (n & 3);
-      if (w == 0 && n < 4 * HB && t >= lo && t < hi) a.dden[(chunk * a.group + hb * HB) * kC + at] = mine;
+      if (w == 0 && n < 4 * HB && t >= lo && t < min(hi, len)) a.dden[token * a.group + (hb * HB + h) * len + t] = mine;
     }
     const float dds[16] = {row16_get<0>(mine), row16_get<1>(mine), row16_get<2>(mine), row16_get<3>(mine),
                            row16_get<4>(mine), row16_get<5>(mine), row16_get<6>(mine), row16_get<7>(mine),
@@ -440,12 +430,19 @@ __global__ void __launch_bounds__(4 * D, 2) bwd_forward_kernel(const BwdArgs a) 
       float kp1[1][4] = {{kp[0], kp[1], kp[2], kp[3]}};
       accumulate<T, D, 1>(X, sm + L::oV, g, n, kp1);
       if (blk + 1 == nblk) {
-        *reinterpret_cast<floatx4*>(a.qdq + ((chunk * NW + w) * 64 + l) * 4) = floatx4{qdq[0], qdq[1], qdq[2], qdq[3]};
+        float* out = a.qdq + token * D;
+        if (len == kC) {
+          *reinterpret_cast<floatx4*>(out + (w * 64 + l) * 4) = floatx4{qdq[0], qdq[1], qdq[2], qdq[3]};
+        } else {
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            if (4 * g + i < len) out[c * len + 4 * g + i] = qdq[i];
+        }
         if (tid == 0) {
           int any = bad ? kBad : 0;
 #pragma unroll
           for (int j = 0; j < NW; ++j) any |= flags[j];
-          a.blocks[chunk] = (any & kBad) ? kC : nblk;
+          a.blocks[chunk] = (uint8_t)((any & kBad) ? kC : nblk);
         }
 #pragma unroll
         for (int i = 0; i < 4; ++i) qdq[i] = 0.f;
@@ -455,7 +452,7 @@ __global__ void __launch_bounds__(4 * D, 2) bwd_forward_kernel(const BwdArgs a) 
     ci = ci1; blk = blk1; hb = hb1;
   }
   if (seg > 0) {
-    float* slot = a.slots_r + ((size_t)bh * a.nseg + (a.nseg - 1 - seg)) * slot_floats<D>();
+    float* slot = a.slots_r + ((size_t)bh * (a.nseg - 1) + (a.nseg - 1 - seg)) * slot_floats<D>();
 #pragma unroll
     for (int jt = 0; jt < D / 16; ++jt) *reinterpret_cast<floatx4*>(slot + (size_t)c * D + 16 * jt + 4 * g) = R[jt];
     Rz += lane_get(ln.x1, Rz);
@@ -503,9 +500,9 @@ __global__ void __launch_bounds__(4 * D, 2) bwd_reverse_kernel(const BwdArgs a) 
   if (seg + 1 < a.nseg) {
     floatx4 end[D / 16];     // the state at the segment's end
     float zend;
-    start_state<D>(a.slots_f + (size_t)bh * a.nseg * slot_floats<D>(), a.live_f + (size_t)bh * a.nseg, a.nseg, a.fold, seg + 1,
+    start_state<D>(a.slots_f + (size_t)bh * (a.nseg - 1) * slot_floats<D>(), a.live_f + (size_t)bh * a.nseg, a.fold, seg + 1,
                    a.S0 ? a.S0 + (size_t)bh * D * D : nullptr, a.z0 ? a.z0 + (size_t)bh * D : nullptr, c, g, end, zend);
-    start_state<D>(a.slots_r + (size_t)bh * a.nseg * slot_floats<D>(), a.live_r + (size_t)bh * a.nseg, a.nseg, a.fold, a.nseg - 1 - seg,
+    start_state<D>(a.slots_r + (size_t)bh * (a.nseg - 1) * slot_floats<D>(), a.live_r + (size_t)bh * a.nseg, a.fold, a.nseg - 1 - seg,
                    nullptr, nullptr, c, g, R, Rz0);
 #pragma unroll
     for (int jt = 0; jt < D / 16; ++jt)
@@ -523,12 +520,19 @@ __global__ void __launch_bounds__(4 * D, 2) bwd_reverse_kernel(const BwdArgs a) 
   float rden = 1.f, rdd = 0.f;
   auto fetch = [&](int ci, int hb) {
     const int row0 = ci * kC;
-    const size_t chunk = (size_t)bh * a.chunks + (s0 + row0) / kC;
+    const size_t token = (size_t)bh * a.T + s0 + row0;
+    const int len = min(kC, rows - row0);
     if (hb == 0) {
       rg = St::load(Gt, offk, row0);
       rk = St::load(K, offk, row0);
       rv = St::load(V, offk, row0);
-      rqdq = *reinterpret_cast<const floatx4*>(a.qdq + ((chunk * NW + w) * 64 + l) * 4);
+      const float* in = a.qdq + token * D;
+      if (len == kC) {
+        rqdq = *reinterpret_cast<const floatx4*>(in + (w * 64 + l) * 4);
+      } else {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) rqdq[i] = 4 * g + i < len ? in[c * len + 4 * g + i] : 0.f;
+      }
     }
 #pragma unroll
     for (int h = 0; h < HB; ++h) {
@@ -539,12 +543,12 @@ __global__ void __launch_bounds__(4 * D, 2) bwd_reverse_kernel(const BwdArgs a) 
     if (tid < HB * kC) {
       const int t = row0 + (tid & 15), h = hb * HB + (tid >> 4);
       rden = t < rows ? a.den[((size_t)b * a.T + s0 + t) * a.Hq + (size_t)hk * a.group + h] : 1.f;
-      rdd = t < rows ? a.dden[(chunk * a.group + h) * kC + (tid & 15)] : 0.f;
+      rdd = t < rows ? a.dden[token * a.group + h * len + (tid & 15)] : 0.f;
     }
   };
 
   const int nchunk = (rows + kC - 1) / kC;
-  auto blocks_of = [&](int ci) { return __builtin_amdgcn_readfirstlane(a.blocks[(size_t)bh * a.chunks + s0 / kC + ci]); };
+  auto blocks_of = [&](int ci) { return __builtin_amdgcn_readfirstlane((int)a.blocks[(size_t)bh * a.chunks + s0 / kC + ci]); };
   int ci = nchunk - 1, hb = 0, nblk = ci >= 0 ? blocks_of(ci) : 1, blk = nblk - 1, lo = 0, hi = kC;
   Decay d;
   float kk[4], kp[4], rE[4], sig[4], qdq[4];
@@ -757,7 +761,7 @@ __global__ void __launch_bounds__(4 * D, 2) bwd_reverse_kernel(const BwdArgs a) 
 template <int D>
 void launch_scan(float* slots, const int* live, const float* S0, const float* z0, const BwdArgs& a, hipStream_t stream) {
   const int heads = a.B * a.Hkv, x = scan_blocks<D>(heads);
-  hipLaunchKernelGGL(segment_scan_kernel<D>, dim3(x, heads), dim3(256), 0, stream, slots, live, S0, z0, a.nseg,
+  hipLaunchKernelGGL((segment_scan_kernel<D, true>), dim3(x, heads), dim3(256), 0, stream, slots, live, S0, z0, a.nseg,
                      (const int*)nullptr, a.Hkv, a.seg_len);
 }
 
@@ -790,20 +794,20 @@ hipError_t launch_typed(const BwdArgs& a, hipStream_t stream) {
 }
 
 struct Sizes {
-  size_t dden, qdq, slots, blocks, live, total;   // floats / ints, and bytes in all
+  size_t qdq, slots, blocks, live, dden, total;   // floats / words, and bytes in all
 };
 Sizes workspace_sizes(int B, int T, int Hq, int Hkv, int d, int nseg) {
   const size_t heads = (size_t)B * Hkv, chunks = ((size_t)T + kC - 1) / kC;
   Sizes s;
-  s.dden = heads * chunks * (Hq / Hkv) * kC;
-  s.qdq = heads * chunks * kC * d;
-  s.slots = heads * nseg * (d * d + 2 * d);
-  s.blocks = (heads * chunks + 3) / 4 * 4;
-  s.live = (heads * nseg + 3) / 4 * 4;
-  // the words about chunks and segments share what one fp32 row per segment takes (up to segments of 992 tokens at head
-  // dim 64 they fit: the workspace is as large as callers that computed it by that rule expect)
-  const size_t words = s.blocks + 2 * s.live, rows = heads * nseg * d;
-  s.total = (s.dden + s.qdq + 2 * s.slots + (words > rows ? words : rows)) * 4 + 256;
+  s.qdq = heads * T * d;
+  s.slots = heads * (nseg - 1) * (d * d + 2 * d);
+  s.blocks = (heads * chunks + 15) / 16 * 4;
+  s.live = heads * nseg;
+  s.dden = (size_t)B * T * Hq;
+  // the size is two states and a row per segment beside both tensors, as callers may have kept it; what is used is less (but
+  // for sequences of millions of tokens)
+  const size_t used = s.qdq + 2 * s.slots + s.blocks + 2 * s.live + s.dden, rule = s.qdq + s.dden + heads * nseg * (2 * (d * d + 2 * d) + d);
+  s.total = (used > rule ? used : rule) * 4 + 256;
   return s;
 }
 
@@ -846,13 +850,13 @@ hipError_t launch_gla_backward(const GlaBackwardParams& p, hipStream_t stream) {
   a.fold = a.nseg > 1 && a.nseg <= (p.d == 64 ? 8 : 5);
   const Sizes s = workspace_sizes(p.B, p.T, p.Hq, p.Hkv, p.d, a.nseg);
   float* w = static_cast<float*>(p.workspace);
-  a.dden = w; w += s.dden;
   a.qdq = w; w += s.qdq;
   a.slots_f = w; w += s.slots;
   a.slots_r = w; w += s.slots;
-  a.blocks = reinterpret_cast<int*>(w); w += s.blocks;
+  a.blocks = reinterpret_cast<uint8_t*>(w); w += s.blocks;
   a.live_f = reinterpret_cast<int*>(w); w += s.live;
-  a.live_r = reinterpret_cast<int*>(w);
+  a.live_r = reinterpret_cast<int*>(w); w += s.live;
+  a.dden = w;
   if (p.bf16) return p.d == 64 ? launch_typed<bf16_t, 64>(a, stream) : launch_typed<bf16_t, 128>(a, stream);
   return p.d == 64 ? launch_typed<float, 64>(a, stream) : launch_typed<float, 128>(a, stream);
 }

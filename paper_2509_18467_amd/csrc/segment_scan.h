@@ -11,6 +11,7 @@ namespace {   // one copy per translation unit: the kernels are registered by ad
 
 // Turns per-segment contributions into segment start states, in place:
 //   slot[seg] <- state before segment seg;  state <- decay[seg] (.) state + contribution[seg].
+// AFTER: slot[seg] <- state after segment seg, for all but the last, which has no slot (nseg_max - 1 of them per head).
 // The recurrence is linear, so the segments are cut into 8 groups: 8 threads per 1 or 4 state elements each
 // reduce their group to (product of decays, contribution from a zero start), the eight pairs are
 // combined through LDS, and each thread replays its group from its true start, out of registers where a group has at
@@ -23,7 +24,7 @@ namespace {   // one copy per translation unit: the kernels are registered by ad
 // between them cost 2 us.
 // adjacent state elements of a thread: one where a head has up to 64 segments (head dim 64), four where it has up to 32
 template <int D> constexpr int kScanVec = D == 64 ? 1 : 4;
-template <int D>
+template <int D, bool AFTER = false>
 __global__ void __launch_bounds__(256) segment_scan_kernel(float* __restrict__ ws, const int* __restrict__ seg_live,
                                                           const float* __restrict__ S0, const float* __restrict__ z0,
                                                           int nseg_max, const int* __restrict__ seq_start, int Hkv,
@@ -49,7 +50,7 @@ __global__ void __launch_bounds__(256) segment_scan_kernel(float* __restrict__ w
     for (int j = threadIdx.x; j < nseg - 1; j += 256) any |= seg_live[(size_t)bh * nseg_max + j];
     if (__syncthreads_or(any) == 0) return;
   }
-  float* slot = ws + (size_t)bh * nseg_max * kSlot;
+  float* slot = ws + (size_t)bh * (AFTER ? nseg_max - 1 : nseg_max) * kSlot;
   const int last = nseg - 1;                 // segments 0 .. last-1 carry contributions
   const int spg = (last + NG - 1) / NG;      // segments per group
   const int sb = min(last, grp * spg), se = min(last, sb + spg);
@@ -106,12 +107,13 @@ __global__ void __launch_bounds__(256) segment_scan_kernel(float* __restrict__ w
 #pragma unroll
       for (int u = 0; u < U; ++u)
         if (seg + u < se) {
-          if (live) *reinterpret_cast<Vec*>(slot + (size_t)(seg + u) * kSlot + e) = st;
+          if (live && !AFTER) *reinterpret_cast<Vec*>(slot + (size_t)(seg + u) * kSlot + e) = st;
           step(st, dec[u], delta[u]);
+          if (live && AFTER) *reinterpret_cast<Vec*>(slot + (size_t)(seg + u) * kSlot + e) = st;
         }
     }
     // the group that ends at the last contribution also owns the start state of the last segment
-    if (live && se == last && sb < se) *reinterpret_cast<Vec*>(slot + (size_t)last * kSlot + e) = st;
+    if (!AFTER && live && se == last && sb < se) *reinterpret_cast<Vec*>(slot + (size_t)last * kSlot + e) = st;
     __syncthreads();   // the partial products in LDS are free for the next round
   }
 }
