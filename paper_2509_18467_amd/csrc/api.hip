@@ -100,7 +100,7 @@ size_t workspace_bytes_checked(const lawcat_desc* d, int which) {
              align_up(inner, 256);
     }
     case LAWCAT_CALL_GLA_BACKWARD:
-      return gla_backward_workspace_bytes(d->B, d->T, d->Hq, d->Hkv, d->dk);
+      return gla_backward_workspace_bytes(d->B, d->T, d->Hq, d->Hkv, d->dk, d->dtype == LAWCAT_DTYPE_BF16);
     case LAWCAT_CALL_CONV1D_BACKWARD:
       return conv_backward_workspace_bytes(d->B, d->T, d->Hq, d->dk, d->conv_width);
     default:

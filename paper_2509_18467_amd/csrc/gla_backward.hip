@@ -815,12 +815,16 @@ Sizes workspace_sizes(int B, int T, int Hq, int Hkv, int d, int nseg) {
 
 bool gla_backward_supports(int d, int group) { return group * d <= 2048 && group <= d; }
 
-// Segments of the sequence: about four workgroups of four waves per compute unit over all (batch, kv head) pairs at
-// head dim 64, two of eight waves at 128 (what registers and LDS allow to be resident), a multiple of 64 tokens.  A
-// segment's rows are addressed with 32-bit offsets from its first row.
-void gla_backward_plan(int B, int T, int Hq, int Hkv, int d, int* seg_len, int* nseg) {
-  const long long heads = (long long)B * Hkv;
-  long long want = (d == 64 ? 1024 : 512) / heads;                 // segments per head
+// Segments of the sequence, a multiple of 64 tokens: as many as make one round of the workgroups that the chip holds over all
+// (batch, kv head) pairs, which is what the sweeps' registers allow: at head dim 64 two per compute unit (of four waves), three
+// with one query head per pass in bf16 storage, at 128 one (of eight).  bf16, 32 / 8 heads, 32768 tokens of 64 430 us, 16384 of
+// 128 617; in two rounds, with twice the contributions and start states, 470 and 663.  Two rounds where one would leave many
+// places empty (300 pairs: two rounds of a third of the sequence, not one of all of it).  A segment's rows are addressed with
+// 32-bit offsets from its first row.
+void gla_backward_plan(int B, int T, int Hq, int Hkv, int d, int bf16, int* seg_len, int* nseg) {
+  const long long heads = (long long)B * Hkv, places = d == 128 ? 256 : (bf16 && (Hq / Hkv) % 2 ? 768 : 512);
+  const long long one = places / heads, two = (places < 512 ? 512 : 1024) / heads;   // segments per head
+  long long want = 10 * two > 22 * one ? two : one;
   if (want < 1) want = 1;
   long long len = (T + want - 1) / want;
   const long long most = (1ll << 31) / ((long long)Hq * d * 4) / 64 * 64;
@@ -830,9 +834,9 @@ void gla_backward_plan(int B, int T, int Hq, int Hkv, int d, int* seg_len, int* 
   *nseg = (int)((T + len - 1) / len);
 }
 
-size_t gla_backward_workspace_bytes(int B, int T, int Hq, int Hkv, int d) {
+size_t gla_backward_workspace_bytes(int B, int T, int Hq, int Hkv, int d, int bf16) {
   int seg_len, nseg;
-  gla_backward_plan(B, T, Hq, Hkv, d, &seg_len, &nseg);
+  gla_backward_plan(B, T, Hq, Hkv, d, bf16, &seg_len, &nseg);
   return workspace_sizes(B, T, Hq, Hkv, d, nseg).total;
 }
 
@@ -843,7 +847,7 @@ hipError_t launch_gla_backward(const GlaBackwardParams& p, hipStream_t stream) {
   a.B = p.B; a.T = p.T; a.Hq = p.Hq; a.Hkv = p.Hkv; a.group = p.Hq / p.Hkv;
   a.gate_scale = p.gate_scale;
   a.chunks = (p.T + kC - 1) / kC;
-  gla_backward_plan(p.B, p.T, p.Hq, p.Hkv, p.d, &a.seg_len, &a.nseg);
+  gla_backward_plan(p.B, p.T, p.Hq, p.Hkv, p.d, p.bf16, &a.seg_len, &a.nseg);
   if (!gla_backward_supports(p.d, a.group)) return hipErrorInvalidValue;
   // Fold / scan, us a call: head dim 64, fp32, 2 heads, 4 segments 40.0 / 45.3, 8 segments 44.0 / 46.0, bf16, 8 kv heads, 16
   // segments 72.4 / 67.1; head dim 128, 5 segments 106.2 / 107.0, 8 segments 119.4 / 110.6

@@ -40,7 +40,7 @@ struct GlaBackwardParams {
   int bf16;
 };
 bool gla_backward_supports(int d, int group);
-size_t gla_backward_workspace_bytes(int B, int T, int Hq, int Hkv, int d);
+size_t gla_backward_workspace_bytes(int B, int T, int Hq, int Hkv, int d, int bf16);
 hipError_t launch_gla_backward(const GlaBackwardParams& p, hipStream_t stream);
 
 // Adjoint of launch_conv1d (conv + pointwise feature map): dx, dw (fp32, [H,d,W]) and dhalo from dy.
