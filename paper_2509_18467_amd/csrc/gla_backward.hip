@@ -195,15 +195,21 @@ struct Sweep {
   static constexpr int oDen = oV + kSet;
   static constexpr int oFlag = oDen + 2 * HB * kC * 4;
   static constexpr int oEnd = oFlag + 32;
-  // forward: partial q . u of every wave
-  static constexpr int kForward = oEnd + NW * HB * kC * 4;
+  // fp32 storage at head dim 64: dO . v (and the scores) formed by each wave over its own channels and added up, where otherwise
+  // every wave forms all of it (32768 tokens of 32 / 8 heads: 1077 us and 1256); at 128 the tiles would not fit
+  static constexpr bool kParts = sizeof(T) == 4 && D == 64;
+  static constexpr int kTile = 2048;
+  // forward: partial q . u of every wave | parts of dO . v
+  static constexpr int oDa = oEnd + NW * HB * kC * 4;
+  static constexpr int kForward = oDa + (kParts ? NW * HB * kTile : 0);
   // reverse: K' rows | R~ [channel][value column], later Q' rows of HB heads | scores
   static constexpr int oK = oEnd;
   static constexpr int oU = oK + kC * f32_row_bytes<D>();
   static constexpr int kU = (D > HB * kC ? D : HB * kC) * f32_row_bytes<D>();
   static constexpr int oSc = oU + kU;
   static constexpr int kScore = sizeof(T) == 2 ? 3 * 512 : 2048;  // per head: three terms of 8 bytes per lane, or one fp64 tile
-  static constexpr int kReverse = oSc + HB * kScore;
+  // (or parts of the scores, then of dO . v)
+  static constexpr int kReverse = oSc + (kParts ? 2 * NW * HB * kTile : HB * kScore);
 };
 
 // ---- forward sweep: dq, dden, sum_h q (.) dq, and the segment's contribution to the gradient flowing backwards.
@@ -283,6 +289,11 @@ __global__ void __launch_bounds__(4 * D, 2) bwd_forward_kernel(const BwdArgs a) 
       if (hb == 0) St::template to_lds<D>(sm + L::oV, g, n, 16 * w, part ? St::keep(rv, g, n, lo, hi) : rv);
 #pragma unroll
       for (int h = 0; h < HB; ++h) St::template to_lds<D>(sm + h * L::kSet, g, n, 16 * w, part ? St::keep(ro[h], g, n, lo, hi) : ro[h]);
+      if constexpr (L::kParts) {
+        __builtin_amdgcn_wave_barrier();   // LDS serves one wave's requests in order: its rows are complete below
+#pragma unroll
+        for (int h = 0; h < HB; ++h) dot_part64<D>(sm + L::oV, sm + h * L::kSet, w, g, n, sm + L::oDa + (w * HB + h) * L::kTile);
+      }
       if (tid < HB * kC) {
         const bool in = (tid & 15) >= lo && (tid & 15) < hi;
         float* den = reinterpret_cast<float*>(sm + L::oDen);
@@ -369,7 +380,9 @@ __global__ void __launch_bounds__(4 * D, 2) bwd_forward_kernel(const BwdArgs a) 
     float* part = reinterpret_cast<float*>(sm + L::oEnd);
 #pragma unroll
     for (int h = 0; h < HB; ++h) {
-      const floatx4 da = dot_rows<T, D, kWide>(sm + L::oV, sm + h * L::kSet, g, n);    // [token i of v][token `row` of dO]
+      floatx4 da;    // [token i of v][token `row` of dO]
+      if constexpr (L::kParts) da = add64(floatx4{0.f, 0.f, 0.f, 0.f}, sum_parts64<NW>(sm + L::oDa + h * L::kTile, HB * L::kTile, g, n));
+      else da = dot_rows<T, D, kWide>(sm + L::oV, sm + h * L::kSet, g, n);
       float am[4];
 #pragma unroll
       for (int i = 0; i < 4; ++i) am[i] = 4 * g + i <= row ? da[i] : 0.f;
@@ -597,6 +610,12 @@ __global__ void __launch_bounds__(4 * D, 2) bwd_reverse_kernel(const BwdArgs a) 
     const bool part = hi - lo < kC;
 #pragma unroll
     for (int h = 0; h < HB; ++h) St::template to_lds<D>(sm + h * L::kSet, g, n, 16 * w, part ? St::keep(ro[h], g, n, lo, hi) : ro[h]);
+    unsigned char* das = sm + L::oSc + NW * HB * L::kTile;     // parts of dO . v
+    if constexpr (L::kParts) {
+      __builtin_amdgcn_wave_barrier();
+#pragma unroll
+      for (int h = 0; h < HB; ++h) dot_part64<D>(sm + h * L::kSet, sm + L::oV, w, g, n, das + (w * HB + h) * L::kTile);
+    }
     float* den = reinterpret_cast<float*>(sm + L::oDen);
     if (tid < HB * kC) {
       const bool in = (tid & 15) >= lo && (tid & 15) < hi;
@@ -646,9 +665,14 @@ __global__ void __launch_bounds__(4 * D, 2) bwd_reverse_kernel(const BwdArgs a) 
     }
 #pragma unroll
     for (int h = 0; h < HB; ++h) f32_to_lds<D>(sm + L::oU + h * kC * f32_row_bytes<D>(), g, n, 16 * w, qp[h]);
+    if constexpr (L::kParts) {
+      __builtin_amdgcn_wave_barrier();
+#pragma unroll
+      for (int h = 0; h < HB; ++h) dot_part64<D>(sm + L::oU + h * kC * f32_row_bytes<D>(), sm + L::oK, w, g, n, sm + L::oSc + (w * HB + h) * L::kTile);
+    }
     __syncthreads();
     // ---- scores of head w: Q'_s . K'_i / den_s for i <= s, shared through LDS (in the terms the product below uses)
-    if (w < HB) {
+    if (!L::kParts && w < HB) {
       const unsigned char* qrows = sm + L::oU + w * kC * f32_row_bytes<D>();
       const floatx4 rd = *reinterpret_cast<const floatx4*>(sm + L::oDen + (w * kC + 4 * g) * 4);
       unsigned char* p = sm + L::oSc + w * L::kScore;
@@ -673,7 +697,9 @@ __global__ void __launch_bounds__(4 * D, 2) bwd_reverse_kernel(const BwdArgs a) 
     for (int h = 0; h < HB; ++h) {
       const floatx4 rd = *reinterpret_cast<const floatx4*>(sm + L::oDen + (h * kC + 4 * g) * 4);
       const floatx4 dd = *reinterpret_cast<const floatx4*>(sm + L::oDen + ((HB + h) * kC + 4 * g) * 4);
-      const floatx4 da = dot_rows<T, D, kWide>(sm + h * L::kSet, sm + L::oV, g, n);    // [token s of dO][token `row` of v]
+      floatx4 da;    // [token s of dO][token `row` of v]
+      if constexpr (L::kParts) da = add64(floatx4{0.f, 0.f, 0.f, 0.f}, sum_parts64<NW>(das + h * L::kTile, HB * L::kTile, g, n));
+      else da = dot_rows<T, D, kWide>(sm + h * L::kSet, sm + L::oV, g, n);
       float am[4];
 #pragma unroll
       for (int i = 0; i < 4; ++i) am[i] = row <= 4 * g + i ? fmaf(da[i], rd[i], dd[i]) : 0.f;
@@ -690,7 +716,7 @@ __global__ void __launch_bounds__(4 * D, 2) bwd_reverse_kernel(const BwdArgs a) 
     rz += lane_get(ln.x1, rz);
     rz += lane_get(ln.x2, rz);
     Rz += rz;
-    __syncthreads();
+    if constexpr (!L::kParts) __syncthreads();
     // ---- dv within the block: this wave's 16 value columns
     if constexpr (sizeof(T) == 2) {
       if constexpr (HB == 1) {
@@ -711,7 +737,15 @@ __global__ void __launch_bounds__(4 * D, 2) bwd_reverse_kernel(const BwdArgs a) 
     } else {
 #pragma unroll
       for (int h = 0; h < HB; ++h) {
-        const doublex4 sc = *reinterpret_cast<const doublex4*>(sm + L::oSc + h * L::kScore + l * 32);
+        doublex4 sc;
+        if constexpr (L::kParts) {
+          const floatx4 rd = *reinterpret_cast<const floatx4*>(sm + L::oDen + (h * kC + 4 * g) * 4);
+          sc = sum_parts64<NW>(sm + L::oSc + h * L::kTile, HB * L::kTile, g, n);
+#pragma unroll
+          for (int i = 0; i < 4; ++i) sc[i] = row <= 4 * g + i ? sc[i] * (double)rd[i] : 0.0;
+        } else {
+          sc = *reinterpret_cast<const doublex4*>(sm + L::oSc + h * L::kScore + l * 32);
+        }
         const floatx4 f = f32_col_frag<D>(sm + h * L::kSet, g, n, w);
 #pragma unroll
         for (int i = 0; i < 4; ++i) dvw = mfma_f64(sc[i], f[i], dvw);
