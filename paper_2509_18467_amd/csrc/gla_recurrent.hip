@@ -1,9 +1,9 @@
 // Normalized gated linear attention (paper section 4.2) in fp32 accuracy:
 //   S_t = diag(alpha_t) S_{t-1} + k_t^T v_t,  z_t = alpha_t (.) z_{t-1} + k_t,
 //   o_t = q_t S_t / (q_t . z_t + eps)
-// Two kernels: gla_walk_kernel walks a whole sequence (prefill with fp32 storage, where bf16 matrix-core operands would not
-// meet the fp32 error bound, and blocks of decode steps), gla_step_kernel is the decode step (lawcat_gla_step, one token,
-// state updated in place).
+// Three kernels: gla_walk_kernel walks a whole sequence (prefill with fp32 storage, where bf16 matrix-core operands would not
+// meet the fp32 error bound, and blocks of decode steps), gla_few_kernel takes a few tokens one after the other (the same
+// calls), gla_step_kernel is the decode step (lawcat_gla_step, one token, state updated in place).
 //
 // gla_walk_kernel: 16 tokens at a time on the matrix cores.  Within a block of up to 16 tokens, with E_t the decay after the
 // block's first token up to t, Q' = q (.) E, K' = k / E and S~, z~ the state decayed by the first token's alpha:
@@ -24,6 +24,8 @@
 // What bounds it: the serial chain of one workgroup (gates, lane exchanges, LDS round trips, dependent MFMAs), about 4 us per
 // chunk in fp32 storage and 6 for four query heads in bf16, at head dim 64.  8 sequences of 32 tokens, 32 query heads on 8 kv
 // heads, bf16: 18 us, fp32, 256 tokens, 2 heads: 67 us; token by token on the vector ALUs the same took 115 and 235.
+#include <algorithm>
+
 #include "chunk_f32.h"
 
 namespace lawcat {
@@ -402,6 +404,92 @@ __global__ void __launch_bounds__(256) gla_step_kernel(const T* __restrict__ q, 
   }
 }
 
+// grid (B * Hkv, parts), 4 D threads.  A few tokens, one after the other, the state in registers in 64 bits and rounded once at the end, as the walk rounds it once
+// a chunk.  A thread owns value column t % D and a quarter of its key channels; the next token's rows are requested a token ahead;
+// a part takes `heads` of the group's query heads, and part 0 stores the state.  The sums of the outputs are 64-bit ones where the outputs are stored in fp32.  With one part S_out, z_out may be S0, z0:
+// a thread reads and writes the same elements of both.
+template <typename T, int D>
+__global__ void __launch_bounds__(4 * D) gla_few_kernel(const WalkArgs a) {
+  typedef std::conditional_t<sizeof(T) == 4, double, float> Acc;
+  constexpr int NPART = 4, RPT = D / NPART, HT = 4, NWD = D / 64;
+  __shared__ float sh_a[D], sh_k[D], sh_q[HT][D];
+  __shared__ double sh_z[2][D];
+  __shared__ Acc sh_part[HT][NPART][D], sh_den[HT][NWD];
+  const int tid = threadIdx.x, col = tid % D, part = tid / D;
+  const int bh = blockIdx.x, b = bh / a.Hkv, hk = bh % a.Hkv;
+  const int hq0 = hk * a.group + blockIdx.y * a.heads;      // first query head
+  const T* q = static_cast<const T*>(a.q) + ((size_t)b * a.T * a.Hq + hq0) * D;
+  const size_t kv1 = ((size_t)b * a.T * a.Hkv + hk) * D, kvs = (size_t)a.Hkv * D, qs = (size_t)a.Hq * D;
+  const T *k = static_cast<const T*>(a.k) + kv1, *v = static_cast<const T*>(a.v) + kv1, *g = static_cast<const T*>(a.g) + kv1;
+  T* o = static_cast<T*>(a.o) + ((size_t)b * a.T * a.Hq + hq0) * D;
+  const bool gs1 = a.gate_scale == 1.0f;
+  const Lanes ln = make_lanes(tid & 63);
+
+  float nk = 0.f, ng = 0.f, nv, nq;
+  auto fetch = [&](int t) {
+    if (tid < D) {
+      nk = ldf(k + t * kvs + tid);
+      ng = ldf(g + t * kvs + tid);
+    }
+    nv = ldf(v + t * kvs + col);
+    nq = part < a.heads ? ldf(q + t * qs + tid) : 0.f;
+  };
+  fetch(0);
+  const float* S0 = a.S0 ? a.S0 + (size_t)bh * D * D : nullptr;
+  double S[RPT], z = 0.0;
+#pragma unroll
+  for (int r = 0; r < RPT; ++r) S[r] = S0 ? S0[(size_t)(part * RPT + r) * D + col] : 0.f;
+  if (tid < D && a.z0) z = a.z0[(size_t)bh * D + tid];
+  for (int t = 0; t < a.T; ++t) {
+    if (tid < D) {
+      const float al = gs1 ? 1.f / (1.f + expf(-ng)) : expf(a.gate_scale * log_sigmoid(ng));
+      z = fma((double)al, z, (double)nk);
+      sh_a[tid] = al;
+      sh_k[tid] = nk;
+      sh_z[t & 1][tid] = z;      // (the token before may still be read)
+    }
+    const float vv = nv, qq = nq;
+    __syncthreads();
+    if (t + 1 < a.T) fetch(t + 1);
+#pragma unroll
+    for (int r = 0; r < RPT; ++r) S[r] = fma((double)sh_a[part * RPT + r], S[r], (double)sh_k[part * RPT + r] * (double)vv);
+    for (int h0 = 0; h0 < a.heads; h0 += HT) {
+      const int nh = min(HT, a.heads - h0);
+      if (h0 > 0) __syncthreads();      // the pass before is done with sh_q / sh_part
+      if (part < nh) sh_q[part][col] = h0 == 0 ? qq : ldf(q + t * qs + (size_t)h0 * D + tid);
+      __syncthreads();
+#pragma unroll
+      for (int hh = 0; hh < HT; ++hh) {
+        if (hh >= nh) break;
+        Acc pn[2] = {0, 0};
+#pragma unroll
+        for (int r = 0; r < RPT; ++r) pn[r & 1] = fma((Acc)sh_q[hh][part * RPT + r], (Acc)S[r], pn[r & 1]);
+        sh_part[hh][part][col] = pn[0] + pn[1];
+      }
+      if (part < nh) {                  // a wave: 64 channels of q . z of its head
+        Acc d = row16_sum((Acc)sh_q[part][col] * (Acc)sh_z[t & 1][col]);
+        d += lane_get(ln.x1, d);
+        d += lane_get(ln.x2, d);
+        if ((tid & 63) == 0) sh_den[part][col / 64] = d;
+      }
+      __syncthreads();
+      if (part < nh) {
+        Acc num = 0, den = a.eps;
+#pragma unroll
+        for (int pp = 0; pp < NPART; ++pp) num += sh_part[part][pp][col];
+#pragma unroll
+        for (int i = 0; i < NWD; ++i) den += sh_den[part][i];
+        stf(o + t * qs + (size_t)(h0 + part) * D + col, (float)num / (float)den);
+        if (a.den_out != nullptr && col == 0) a.den_out[((size_t)b * a.T + t) * a.Hq + hq0 + h0 + part] = (float)den;
+      }
+    }
+  }
+  if (blockIdx.y != 0) return;
+  if (tid < D) a.z_out[(size_t)bh * D + tid] = (float)z;
+#pragma unroll
+  for (int r = 0; r < RPT; ++r) a.S_out[((size_t)bh * D + part * RPT + r) * D + col] = (float)S[r];
+}
+
 template <typename T, int D>
 hipError_t launch_step_d(const RecurrentParams& p, hipStream_t stream) {
   hipLaunchKernelGGL((gla_step_kernel<T, D>), dim3(p.B * p.Hkv), dim3(256), 0, stream, (const T*)p.q, (const T*)p.k,
@@ -429,7 +517,20 @@ hipError_t launch_walk(const RecurrentParams& p, bool in_place, hipStream_t stre
   // eight at 128): the walk is serial, and the state's update, which every one of them repeats, is the smaller part of it.
   // fp32, 256 tokens, 32 query heads on 8 kv heads, head dim 64 / 128: 68 / 137 us, where one workgroup for the four heads of a
   // group takes 147 / 344.  (Not in place: they would read a state that part 0 replaces.)
-  if (!in_place && (long long)p.B * p.Hq <= (D == 64 ? 512 : 256)) a.heads = 1;
+  const bool spread = !in_place && (long long)p.B * p.Hq <= (D == 64 ? 512 : 256);
+  // A few tokens go one after the other, where the walk pays for a chunk of 16 and, in one workgroup, for one batch of query heads
+  // after the other.  us at 1, 3 (in place) or 4 tokens, few / walk: in place, 8 kv heads, one query head each, 8 sequences, head dim
+  // 64, bf16 5.0 / 6.4, -, 8.5 / 6.4; four each, one sequence 5.0 / 9.0, 7.7 / 9.1, 9.1 / 9.1, 64 sequences, fp32 7.1 / 18.5, 10.8 / 18.1,
+  // 12.8 / 18.1.  Prefill, fp32, 64 sequences: one query head on each of 8 of dim 64 6.4 / 11.3, -, 11.7 / 11.4; eight on each of 4
+  // of dim 128 12.3 / 45.9, 6 tokens 39.1 / 46.7, 8 48.8 / 46.6; sixteen on one of dim 128 7.4 / 79.4, 12 tokens 36.8 / 80.6.  Out of
+  // place up to 512 workgroups take four query heads each (16 on one of dim 128, one token: 6.3 us, in one workgroup 14.9).
+  const int most = in_place ? std::min(4, a.group) : std::max(3, spread ? 0 : 3 * a.group / 4);
+  if (p.T <= most) {
+    if (!in_place && a.group % 4 == 0 && (long long)heads * (a.group / 4) <= 512) a.heads = 4;
+    hipLaunchKernelGGL((gla_few_kernel<T, D>), dim3(heads, a.group / a.heads), dim3(4 * D), 0, stream, a);
+    return hipGetLastError();
+  }
+  if (spread) a.heads = 1;
   // four query heads at a time; two where fp64 sums at head dim 128 would not leave registers for four (256, and 44 spilled)
   if constexpr (sizeof(T) == 2 || D == 64)
     if (a.heads % 4 == 0) return launch_sized<T, D, 4>(a, heads, stream);
