@@ -49,13 +49,15 @@ hipError_t launch_gla_chunk(const ChunkParams& p, hipStream_t stream) {
   a.B = p.B; a.T = p.T; a.Hq = p.Hq; a.Hkv = p.Hkv; a.W = p.W;
   a.seg_len = p.plan.seg_len; a.nseg = p.plan.nseg;
   // With few segments the output pass folds its predecessors' contributions itself instead of waiting for a scan: a launch less,
-  // against about 0.6 us per predecessor at head dim 64 and 1.3 at 128 (four times the state).  Scan / fold, us a call, 8 kv
-  // heads: d 64, 4 segments 22.2 / 18.2, 9: 22.7 / 21.8, 16: 24.2 / 29.4; d 128, 4: 29.6 / 27.7, 5: 30.9 / 32.8.  With many heads
-  // the scan is traffic: 64 heads, d 64, 5 segments 39.2 / 26.9; d 128, 5: 62.9 / 43.3.
-  const int nseg = p.plan.nseg, heads = p.B * p.Hkv;
-  a.fold = nseg > 1 && (p.d == 64 ? nseg <= 9 : (nseg <= 4 || (nseg <= 8 && heads >= 64)));
+  // and, with many heads, less traffic, against a walk over the predecessors' slots in each of the output pass's launches (one per
+  // four query heads of a group).  Scan / fold, us a call, at 2, 4 and 9 segments: 8 heads of 64, one launch 20.6 / 17.4, 21.1 / 18.9,
+  // 22.1 / 22.6, two 32.6 / 29.7, 32.9 / 32.0, 34.2 / 38.4, four 56.4 / 54.3, 56.7 / 58.4, 58.2 / 69.9; 64 heads, one 30.5 / 18.3, 36.0 /
+  // 22.7, 48.2 / 34.4, eight 125 / 116, 135 / 135, 235 / 226; 8 heads of 128, one 28.4 / 25.8, 29.4 / 30.0, 32.7 / 42.1, two 45.7 / 44.3,
+  // 47.0 / 51.8, 50.9 / 74.3.
+  const int nseg = p.plan.nseg, heads = p.B * p.Hkv, group = p.Hq / p.Hkv;
+  const int passes = group / 4 + (group % 4 + 1) / 2;
+  a.fold = nseg > 1 && nseg <= 9 && 5 * nseg * passes * (p.d / 64) <= 30 + 2 * heads;
   a.gate_scale = p.gate_scale; a.eps = p.eps;
-  const int group = p.Hq / p.Hkv;
   const int mode = !p.fuse_conv ? chunk::kPlain : (p.phi == 1 ? chunk::kConvElu : chunk::kConvId);
   const chunk::TraceEvents ev{p.ev_start, p.ev_stop};
   return p.d == 64 ? chunk::launch_d64(a, group, mode, stream, ev) : chunk::launch_d128(a, group, mode, stream, ev);

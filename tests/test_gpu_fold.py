@@ -24,3 +24,21 @@ def test_start_states(oracle, d, B, Hkv, nseg, shut):
                                x["q_halo"], x["k_halo"])
     for n in ("o", "den", "S", "z"):
         H.assert_close(got[n], ref[n], wl, n)
+
+
+# a group of more than four query heads takes several launches of the output pass, each of which folds
+@pytest.mark.parametrize("shut", [(), (1,)])
+@pytest.mark.parametrize("d,B,Hkv,group,nseg", [(64, 1, 2, 4, 6), (64, 1, 2, 4, 7), (64, 1, 1, 8, 3), (64, 1, 1, 8, 4), (64, 1, 1, 7, 2), (64, 4, 4, 16, 3), (64, 4, 4, 16, 4), (128, 1, 2, 2, 3), (128, 1, 2, 2, 4),
+                                                (128, 4, 4, 8, 3), (128, 4, 4, 8, 4), (128, 4, 16, 4, 9), (128, 4, 16, 4, 10)])
+def test_start_states_of_several_output_launches(oracle, d, B, Hkv, group, nseg, shut):
+    wl = Workload("fold", B, 64 * nseg - 11, Hkv * group, Hkv, d, 4, "bf16")
+    x = make_inputs(wl, seed=62, halo=True, state=True)
+    for s in shut:
+        at = 64 * (s * (nseg - 2))
+        x["G"][:, at:at + 64] = -30.0
+    print("segment start states", wl, shut, flush=True)
+    got = H.run_layer_prefill(wl, x, segment=64, gate_scale=0.25)
+    ref = oracle.layer_prefill(x["Q"], x["K"], x["V"], x["G"], x["wq"], x["wk"], 1, 0.25, 0.0, x["S0"], x["z0"], x["q_halo"], x["k_halo"])
+    for n in ("o", "den", "S", "z"):
+        # closed gates leave an output of one product of a value with a weight that is rounded to bf16
+        H.assert_close(got[n], ref[n], wl, n, 1 if shut and n == "o" else 0)
