@@ -5,7 +5,7 @@
 // u is recomputed from x (one more pass of W multiply-adds beats reading a stored copy).  Streaming: a thread owns
 // four adjacent channels and walks a run of tokens (plus the W - 1 tokens after it, whose du the run's last dx need)
 // with x and du of the last W tokens in registers, rows of x and dy travelling four at a time, one group ahead of the
-// arithmetic; 6 bytes per element moved in bf16 storage.  A strip of 64 tokens is cut into 4 or 16 runs, walked by as many
+// arithmetic; 6 bytes per element moved in bf16 storage.  A strip of 64 tokens is cut into 1, 4 or 16 runs, walked by as many
 // threads of the same workgroup.  dw: every (batch, strip) writes its partial sums to the workspace (those of its runs
 // added through LDS, in order), a second kernel adds them, each thread a share and the shares in order (no atomics:
 // repeated calls agree bit for bit).
@@ -170,6 +170,17 @@ __global__ void __launch_bounds__(256) conv_bwd_kernel(const T* __restrict__ x, 
     }
   }
   float* out = partial + ((size_t)b * gridDim.y + strip) * row * W;
+  if constexpr (NSUB == 1) {      // a thread's own 4 W sums are contiguous
+    if (!active) return;
+#pragma unroll
+    for (int v = 0; v < W; ++v) {
+      f4 t;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) t.v[i] = dw[(4 * v + i) / W][(4 * v + i) % W];
+      st4(out + (size_t)e0 * W + 4 * v, t);
+    }
+    return;
+  }
   // the strip's runs, in order
   __shared__ float sums[256 * 4 * W];
 #pragma unroll
@@ -217,6 +228,22 @@ __global__ void __launch_bounds__(256) conv_bwd_reduce_kernel(const float* __res
   }
 }
 
+// The same for up to 16 partial sums: four elements per thread, all loads at once (8 sequences of up to 4 tokens, 2 heads of 64: the
+// call 6.0 us with the shares).
+constexpr int kFewPartials = 16;
+__global__ void __launch_bounds__(64) conv_bwd_sum_kernel(const float* __restrict__ partial, float* __restrict__ dw, int n_partial, int n) {
+  const int e0 = (blockIdx.x * 64 + threadIdx.x) * 4;
+  if (e0 >= n) return;
+  float4 t[kFewPartials];
+#pragma unroll
+  for (int p = 0; p < kFewPartials; ++p)
+    t[p] = p < n_partial ? *reinterpret_cast<const float4*>(partial + (size_t)p * n + e0) : make_float4(0.f, 0.f, 0.f, 0.f);
+  float4 acc = t[0];
+#pragma unroll
+  for (int p = 1; p < kFewPartials; ++p) { acc.x += t[p].x; acc.y += t[p].y; acc.z += t[p].z; acc.w += t[p].w; }
+  *reinterpret_cast<float4*>(dw + e0) = acc;
+}
+
 template <typename T, int W, int PHI, int NSUB>
 void launch_kernel(const ConvBackwardParams& p, float* partial, int row, int strips, hipStream_t stream) {
   const int cols = 256 / NSUB;
@@ -230,13 +257,19 @@ hipError_t launch_phi(const ConvBackwardParams& p, hipStream_t stream) {
   const int strips = (p.T + kStrip - 1) / kStrip, n_partial = p.B * strips, n = row * W;
   float* partial = n_partial == 1 ? p.dw : static_cast<float*>(p.workspace);   // a single strip: its sums are the result
   // Runs of 16 tokens (4 of the strip's threads per four channels), or of 4 where those would leave most of the chip idle: the
-  // W - 1 tokens that a run reads and works out a second time cost more than the latency they hide at 256 strips x 1024
-  // channels and above (28.7 us in runs of 16, 37.9 in runs of 4), less at 128 and below (15.2 and 13.9).
-  const long long wide = (long long)((row + 1023) / 1024) * n_partial;
-  if (wide >= 192) launch_kernel<T, W, PHI, 4>(p, partial, row, strips, stream);
+  // W - 1 tokens that a run reads and works out a second time cost more than the latency they hide at 128K channels x strips and
+  // above (bf16, runs of 4 / 16, 2048 channels of 64 sequences of 64 tokens 21.5 / 17.5 us, of 8 of 200 12.3 / 14.1).  A thread
+  // walks a strip of up to 4 tokens alone (64 sequences of one token: 7.3 us, 9.4 in runs of 4), and a longer one, shorter than a
+  // whole strip, where that fills the chip: short sequences leave most runs empty (256 sequences, 2048 channels, bf16, 17 and 32
+  // tokens 19.6 and 30.2 us, in runs of 16 26.1 and 33.4; from 64 on the same).
+  const long long work = (long long)row * n_partial;
+  if (p.T <= 4 || (p.T < kStrip && work * (int)sizeof(T) >= 1 << 20)) launch_kernel<T, W, PHI, 1>(p, partial, row, strips, stream);
+  else if (work >= 96 * 1024) launch_kernel<T, W, PHI, 4>(p, partial, row, strips, stream);
   else launch_kernel<T, W, PHI, 16>(p, partial, row, strips, stream);
-  if (n_partial > 1)
+  if (n_partial > kFewPartials)
     hipLaunchKernelGGL(conv_bwd_reduce_kernel, dim3(n / 32), dim3(256), 0, stream, partial, p.dw, n_partial, n);
+  else if (n_partial > 1)
+    hipLaunchKernelGGL(conv_bwd_sum_kernel, dim3((n / 4 + 63) / 64), dim3(64), 0, stream, partial, p.dw, n_partial, n);
   return hipGetLastError();
 }
 
