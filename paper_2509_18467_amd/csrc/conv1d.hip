@@ -211,11 +211,12 @@ hipError_t launch_typed(const ConvParams& p, hipStream_t stream) {
     return hipGetLastError();
   };
   // The longest of 64, 32 and 16 tokens per strip that leaves two workgroups for every compute unit; strips of 4, with nothing to
-  // wait for but one group of rows, where none does: the three rows that a strip reads again cost less there than a walk in
-  // dependent groups (32 heads of 64, bf16, one sequence of 256 tokens: 4.5 us and 9.3; 4096: 9.0 and 11.5), and more above
-  // (8192: 17.0 and 14.8)
+  // wait for but one group of rows, for less than that: the three rows that a strip reads again cost less there than a walk in
+  // dependent groups, and more above.  32 heads of 64, bf16, one sequence, strips of 4 / 16: four taps, 4096 tokens 8.9 / 11.8 us,
+  // 5328 in 16 sequences 13.5 / 12.9, 8100 16.9 / 15.0; two, whose taps are read one by one, 2000 tokens 8.9 / 11.3, 4096 14.4 / 12.6.
   constexpr long long kWant = 512 * 256;
-  if (p.T <= 4 || threads(16) < kWant) return launch(conv1d_causal_kernel<T, 4>, 4, 64);
+  const long long few = (p.W == 2 || p.W == 3) ? 50000 : 80000;
+  if (p.T <= 4 || threads(16) < few) return launch(conv1d_causal_kernel<T, 4>, 4, 64);
   if (threads(64) >= kWant) return launch(conv1d_causal_kernel<T, 64>, 64, 256);
   if (threads(32) >= kWant) return launch(conv1d_causal_kernel<T, 32>, 32, 256);
   return launch(conv1d_causal_kernel<T, 16>, 16, 256);
