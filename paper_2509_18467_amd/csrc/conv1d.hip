@@ -68,7 +68,8 @@ __device__ inline float apply_phi(float x, int phi) {
 }
 
 // kStrip: tokens per thread (see launch_typed).  The thread of a sequence's last strip also writes the conv cache for a
-// continuation, whose rows it requests before anything else: one launch instead of two (a decode step's conv, 32 heads of 64:
+// continuation, whose rows it requests before anything else where a strip is one group (in a longer one they would take registers
+// from a wave in four: 32 heads of 128, bf16, 8100 tokens 26.4 us, requested at the end 24.3): one launch instead of two (a decode step's conv, 32 heads of 64:
 // 6.2 -> 4.2 us; 256 sequences, 32 heads of 128: 14.4 -> 6.2).
 template <typename T, int kStrip>
 __global__ void __launch_bounds__(256) conv1d_causal_kernel(const T* __restrict__ x, const T* __restrict__ w,
@@ -112,7 +113,7 @@ __global__ void __launch_bounds__(256) conv1d_causal_kernel(const T* __restrict_
   typedef typename Io<T>::Raw Raw;
   Raw last[3];         // the conv cache for a continuation: the last W - 1 rows of [halo ; x], as they are
   const bool ends = tail != nullptr && s == nstrips - 1;
-  if (ends) {
+  auto fetch_last = [&] {
 #pragma unroll
     for (int r = 0; r < 3; ++r) {
       last[r] = Io<T>::zero_raw();
@@ -121,7 +122,8 @@ __global__ void __launch_bounds__(256) conv1d_causal_kernel(const T* __restrict_
       if (src >= 0) last[r] = Io<T>::load_raw(x + ((size_t)b * Tn + src) * rowlen + e0);
       else if (halo != nullptr) last[r] = Io<T>::load_raw(halo + ((size_t)b * (W - 1) + (W - 1 + src)) * rowlen + e0);
     }
-  }
+  };
+  if (kStrip == kGroup && ends) fetch_last();
   float win[3][VEC];  // win[j] = row t-1-j
 #pragma unroll
   for (int j = 0; j < 3; ++j) {
@@ -176,6 +178,7 @@ __global__ void __launch_bounds__(256) conv1d_causal_kernel(const T* __restrict_
     }
   }
   if (ends) {
+    if (kStrip > kGroup) fetch_last();
 #pragma unroll
     for (int r = 0; r < 3; ++r)
       if (r < W - 1) *reinterpret_cast<Raw*>(tail + ((size_t)b * (W - 1) + r) * rowlen + e0) = last[r];
