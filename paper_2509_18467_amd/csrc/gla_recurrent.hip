@@ -182,8 +182,13 @@ __global__ void __launch_bounds__(4 * D, 2) gla_walk_kernel(const WalkArgs a) {
       const double before = ((g & 1) ? x1 : 1.0) * ((g & 2) ? x23 : 1.0), after = ((g & 1) ? 1.0 : x1) * ((g & 2) ? 1.0 : x23);
       const int r = lo & 3;
       const float first = lane_get(ln.n4 + ((lo >> 2) << 6), r == 0 ? d.al[0] : r == 1 ? d.al[1] : r == 2 ? d.al[2] : d.al[3]);
-      const double F = (tot * x1) * x23 * (double)first;
-      E[0] = (float)(before * e[0]); E[1] = (float)(before * p1); E[2] = (float)(before * p1 * e[2]); E[3] = (float)(before * tot);
+      const double last = (tot * x1) * x23, F = last * (double)first;
+      // of E and of the first token's alpha: in channels that nearly close, queries keep their bits down to 2^-94 (not 2^-62) and
+      // up to 2^95
+      const Center c = center_of((float)last);
+      const float firstc = first * c.down;
+      E[0] = (float)(before * e[0]) * c.up; E[1] = (float)(before * p1) * c.up;
+      E[2] = (float)(before * p1 * e[2]) * c.up; E[3] = (float)(before * tot) * c.up;
       const double Dc[4] = {after * s1 * e[1], after * s1, after * e[3], after};
       float kp[4];
       double s = 0.0;
@@ -198,10 +203,10 @@ __global__ void __launch_bounds__(4 * D, 2) gla_walk_kernel(const WalkArgs a) {
       f32_to_lds<D>(sm, g, n, 16 * w, kp);
       s += lane_get(ln.x1, s);
       s += lane_get(ln.x2, s);
-      zt = (float)z * first;
+      zt = (float)z * firstc;
       z = fma(z, F, s);
       if (g == 0) {
-        *reinterpret_cast<float*>(sm + L::oF + (16 * w + n) * 16) = first;
+        *reinterpret_cast<float*>(sm + L::oF + (16 * w + n) * 16) = firstc;
         *reinterpret_cast<double*>(sm + L::oF + (16 * w + n) * 16 + 8) = F;
       }
       __builtin_amdgcn_wave_barrier();   // LDS serves one wave's requests in order: its rows are complete below
