@@ -10,39 +10,47 @@
 //                  alpha_t once, in the query's gradient and not in the key's)
 //   dg_t = dlog alpha_t * gate_scale * (1 - sigmoid(g_t))
 //
-// Chunked form, in fp32 accuracy (chunk_f32.h).  Within a block of up to 16 tokens, with E_t the decay from the
-// block's first token on, Q' = q (.) E, K' = k / E, S~ the state decayed up to and including the first token and
-// R~ = E_last (.) (the gradient that flows into the block's end):
+// Chunked form, in fp32 accuracy (chunk_f32.h).  Within a chunk of up to 16 tokens, with E_t the decay from the
+// chunk's first token on, Q' = q (.) E, K' = k / E, S~ the state decayed up to and including the first token and
+// R~ = E_last (.) (the gradient that flows into the chunk's end):
 //   dq_t = [ E_t (.) ( S~ dO_t + sum_{i<=t} (dO_t . v_i) K'_i ) ] / den_t + z_t dden_t,   z_t = E_t (.) ( z~ + sum_{i<=t} K'_i )
-//   S~ <- S~ + K'^T V   (times E_last and the next alpha when the next block begins)
+//   S~ <- S~ + K'^T V   (times E_last and the next alpha when the next chunk begins)
 //   dk_i = [ R~ v_i + R~z + sum_{h, s>=i} Q'_s ( (dO_s . v_i) / den_s + dden_s ) ] / E_i
 //   dv_i = K'_i R~ + sum_{h, s>=i} (Q'_s . K'_i / den_s) dO_s
-//   R~ <- R~ + sum_h Q'^T d^   (times alpha of the block's first token when the block before it begins)
-// A token whose operands or denominator are not finite may spoil only what the equations say: the sums above run over
-// masked matrices, where a zero weight times an infinity is a NaN.  So a chunk with such a token (or with a key too large
-// to be divided by E) is walked in blocks of one token, and what a block reads of other tokens is cleared.
-// Five launches (three where there are few segments, whose contributions the sweeps fold themselves): the segments' contributions to the state (walked backwards, so that the walk stops once nothing
-// earlier can reach the segment's end), their scan, the forward sweep (dq, dden, and the segments' contributions to
-// the gradient that flows backwards), its scan, the reverse sweep (dk, dv, dg).  The gate's sum over all later tokens
-// is split at segment ends, where it equals sum_j S^[c, j] Gr[c, j], the states on the two sides of the boundary: no
-// pass over the sequence is needed for it.
+//   R~ <- R~ + sum_h Q'^T d^   (times alpha of the chunk's first token when the chunk before it begins)
+// Where a channel decays too fast for the quotients k / E, the forward sweep takes the chunk token by token on the vector ALUs,
+// S_t and z_t in registers.  So does the reverse sweep, for all chunks of the segment: one loop with both forms in it took registers
+// from the ordinary one (fp32 storage, 32768 tokens, 1520 us where two loops take 1063).  And a token whose operands or denominator
+// are not finite may spoil only what the equations say: the sums above run over masked matrices, where a zero weight times an
+// infinity is a NaN.  The forward sweep flags a segment with such a token, and the reverse sweep goes token by token there.
+// bf16 / fp32 storage, 32768 tokens, 32 / 8 heads of 64, us a call: ordinary gates 412 / 1063, one channel's logits at -30 1290 /
+// 1830, in blocks of one token with the matrices 3000 / 9450; 2 tokens of 100 closed in all channels 995 / 1615 (in blocks 666 / 1925).
+// Launches: with one segment, the forward sweep (dq, dden, and the segments' contributions to the gradient that flows backwards) and
+// the reverse sweep (dk, dv, dg).  With more, the segments' contributions to the state come first (walked backwards, so that the walk
+// stops once nothing earlier can reach the segment's end); beyond a few, a scan follows them, and another one the forward sweep.
+// The gate's sum over all later tokens is split at segment ends, where it equals sum_j S^[c, j] Gr[c, j], the states on the two
+// sides of the boundary: no pass over the sequence is needed for it.
 //
-// What it measures (32768 tokens, 32 query heads on 8 kv heads, d = 64, bf16): state 34 us, forward sweep 236, reverse
-// sweep 242, scans 5 each, 525 us in all; the token-by-token form on the vector ALUs that this replaces took 1421 us.  The
-// two sweeps move 0.57 and 0.54 GB (q, dO, k, v, g once each, the gate term in fp32, the gradients), 105 us each at the
-// rate of a large copy; what they spend beyond that is vector-ALU issue (splits, gates, the reduction of q . u over the
-// channels) and the waits of two waves per SIMD: their registers (230 and 220) leave room for no third, and a limit of
-// 168 spills (forward 636 us, reverse 423).
+// What it measures (32768 tokens, 32 query heads on 8 kv heads, d = 64, bf16), a call back to back with itself: 412 us.  Kernel by
+// kernel under a profiler, at their quickest: state 17, scans 4 each, forward sweep 198, reverse sweep 225.  The two sweeps move
+// 0.57 and 0.54 GB (q, dO, k, v, g once each, the gate term in fp32, the gradients), 105 us each at the rate of a large copy; what
+// they spend beyond that is vector-ALU issue (splits, gates, the reduction of q . u over the channels) and the waits of two waves
+// per SIMD: their registers (232 and 225) leave room for no third, and a limit of 168 spilled (forward 636 us, reverse 423).
 //
 // fp32 storage: the sums of every contraction are fp64 MFMAs and decays are multiplied up in 64 bits, rounded per chunk, because
-// chains of fp32 MFMAs alone were up to 2.4 times further from 64-bit arithmetic than sums token by token.  2-norm errors, 300
-// tokens, 4 query heads on 2, token by token / fp32 MFMAs / as it is: dq 4.2e-7 / 4.6e-7 / 3.7e-7, dk 1.6e-7 / 2.0e-7 / 1.1e-7,
-// dv 6.1e-8 / 1.5e-7 / 6.5e-8, dg 3.9e-6 / 1.3e-6 / 0.9e-6, dz0 9.2e-8 / 1.9e-7 / 9.0e-8.  256 tokens of 2 heads: 124 / 40 / 58 us.
+// chains of fp32 MFMAs alone were up to 2.4 times further from 64-bit arithmetic than sums token by token.  2-norm errors of
+// gradients, 20 tokens of 2 heads, 256 sequences, all sums token by token in fp32 / as it is: dq 3.7e-7 / 2.9e-7, dk 1.6e-7 / 9.5e-8,
+// dv 6.1e-8 / 4.6e-8, dS0 8.2e-8 / 8.0e-8, dz0 1.1e-7 / 9.5e-8; logits ~ N(0, 5^2), where chunks go token by token, 40 tokens, 8 heads
+// on 2: dq 2.2e-7 / 1.9e-7, dk 1.7e-7 / 1.4e-7, dv 6.1e-8 / 5.0e-8, dg 2.7e-6 / 2.1e-6.  256 tokens of 2 heads: 124 / 55 us.
 #include "chunk_f32.h"
 
 namespace lawcat {
 namespace {
 using namespace f32c;
+
+// A chunk in which a channel decays by more than this from its first token on goes token by token: centred (chunk_f32.h), the
+// operands of its products stand within 2^40 of unscaled values.
+constexpr float kWhole = 8.271806125530277e-25f;   // 2^-80
 
 template <typename T> using Wide = std::conditional_t<sizeof(T) == 4, double, float>;
 template <typename T> __device__ inline float inverse(float x) { return sizeof(T) == 4 ? 1.f / x : __builtin_amdgcn_rcpf(x); }
@@ -56,11 +64,11 @@ struct BwdArgs {
   float* dden;       // [heads][tokens][group], a chunk's as [group][its tokens]
   float* qdq;        // sum_h q (.) dq: [heads][tokens][D], a chunk's in the patch layout ([D / 16][64 lanes][4 tokens]), or, of
                      // fewer than 16 tokens, as [D][its tokens]
-  uint8_t* blocks;   // [heads][chunks]: into how many blocks the reverse sweep cuts the chunk
+  uint8_t* serial;   // [heads][segments]: whether the reverse sweep goes token by token
   float* slots_f;    // [heads][nseg - 1][D*D + 2D]: forward contributions, then the states after the segments
   float* slots_r;    // the same for Gr, segments in reverse order
   int *live_f, *live_r;   // [heads][nseg]: 0 = the segment's total decay is exactly zero in every channel
-  int B, T, Hq, Hkv, group, seg_len, nseg, chunks;
+  int B, T, Hq, Hkv, group, seg_len, nseg;
   int fold;          // few segments: the sweeps fold their predecessors' contributions, there are no scans
   float gate_scale;
 };
@@ -199,9 +207,10 @@ struct Sweep {
   // every wave forms all of it (32768 tokens of 32 / 8 heads: 1077 us and 1256); at 128 the tiles would not fit
   static constexpr bool kParts = sizeof(T) == 4 && D == 64;
   static constexpr int kTile = 2048;
-  // forward: partial q . u of every wave | parts of dO . v
+  // forward: partial q . u of every wave | parts of dO . v | the state before a chunk that goes token by token
   static constexpr int oDa = oEnd + NW * HB * kC * 4;
-  static constexpr int kForward = oDa + (kParts ? NW * HB * kTile : 0);
+  static constexpr int oX = oDa + (kParts ? NW * HB * kTile : 0);
+  static constexpr int kForward = oX + D * D * 4;
   // reverse: K' rows | R~ [channel][value column], later Q' rows of HB heads | scores
   static constexpr int oK = oEnd;
   static constexpr int oU = oK + kC * f32_row_bytes<D>();
@@ -238,7 +247,7 @@ __global__ void __launch_bounds__(4 * D, 2) bwd_forward_kernel(const BwdArgs a) 
   const unsigned offk = St::offset(K, g, n, 16 * w), offq = St::offset(Q, g, n, 16 * w);
   const int c = 16 * w + n;
 
-  // state before the next block's first token (to be decayed by f), normalizer; gradient contribution
+  // state before the next chunk's first token (to be decayed by f), normalizer; gradient contribution
   floatx4 X[D / 16], R[D / 16];
   float z = 0.f;
   double Rz = 0.0;       // a long sum of signed terms: 64 bits
@@ -246,11 +255,11 @@ __global__ void __launch_bounds__(4 * D, 2) bwd_forward_kernel(const BwdArgs a) 
                  a.S0 ? a.S0 + (size_t)bh * D * D : nullptr, a.z0 ? a.z0 + (size_t)bh * D : nullptr, c, g, X, z);
 #pragma unroll
   for (int jt = 0; jt < D / 16; ++jt) R[jt] = floatx4{0.f, 0.f, 0.f, 0.f};
-  float pend = 1.f;      // E_last of the block before
-  float P = 1.f;         // decay from the segment's start up to the block before
+  float pend = 1.f;      // E_last of the chunk before
+  float P = 1.f;         // decay from the segment's start up to the chunk before
   float qdq[4] = {0.f, 0.f, 0.f, 0.f};
 
-  // inputs of the next item, in registers.  Item = (chunk, block of the chunk, HB query heads).
+  // inputs of the next item, in registers.  Item = (chunk, HB query heads).
   typename St::Raw rq[HB], ro[HB], rk, rv, rg;
   float rden = 1.f;
   auto fetch = [&](int ci, int hb) {
@@ -273,38 +282,20 @@ __global__ void __launch_bounds__(4 * D, 2) bwd_forward_kernel(const BwdArgs a) 
   };
 
   const int nchunk = (rows + kC - 1) / kC;
-  int ci = 0, blk = 0, hb = 0, nblk = 1, cut = 1, lo = 0, hi = kC;
-  constexpr int kBad = 256;
+  int ci = 0, hb = 0;
+  constexpr int kSharp = 1, kBad = 2;
+  bool sharp = false, serial = false;   // a wave's channels decay too fast for products over the chunk; any wave's: token by token
+  bool any_serial = false;
   bool bad = false;      // a token of the chunk has a query too large, or operands or a denominator that are not finite
   Decay d;
   float kk[4], kp[4], zt[4], wf = 0.f;
   if (nchunk > 0) fetch(0, 0);
   while (ci < nchunk) {
     const int row0 = ci * kC;
-    const size_t chunk = (size_t)bh * a.chunks + (s0 + row0) / kC, token = (size_t)bh * a.T + s0 + row0;
+    const size_t token = (size_t)bh * a.T + s0 + row0;
     const int len = min(kC, rows - row0);        // the chunk's tokens
-    // ---- rows to LDS (the block's tokens), gates
-    auto rows_to_lds = [&] {
-      const bool part = hi - lo < kC;
-      if (hb == 0) St::template to_lds<D>(sm + L::oV, g, n, 16 * w, part ? St::keep(rv, g, n, lo, hi) : rv);
-#pragma unroll
-      for (int h = 0; h < HB; ++h) St::template to_lds<D>(sm + h * L::kSet, g, n, 16 * w, part ? St::keep(ro[h], g, n, lo, hi) : ro[h]);
-      if constexpr (L::kParts) {
-        __builtin_amdgcn_wave_barrier();   // LDS serves one wave's requests in order: its rows are complete below
-#pragma unroll
-        for (int h = 0; h < HB; ++h) dot_part64<D>(sm + L::oV, sm + h * L::kSet, w, g, n, sm + L::oDa + (w * HB + h) * L::kTile);
-      }
-      if (tid < HB * kC) {
-        const bool in = (tid & 15) >= lo && (tid & 15) < hi;
-        float* den = reinterpret_cast<float*>(sm + L::oDen);
-        den[tid] = in ? 1.f / rden : 0.f;
-        den[HB * kC + tid] = in ? rden : 1.f;
-      }
-    };
-    const bool fresh = hb == 0 && blk == 0;      // the chunk's first block is not known yet
-    lo = fresh ? 0 : blk * (kC / nblk);
-    hi = fresh ? kC : lo + kC / nblk;
-    if (fresh) {
+    // ---- rows to LDS, gates
+    if (hb == 0) {
       float gl[4];
       St::patch(qd, rg, gl);
       St::patch(qd, rk, kk);
@@ -314,11 +305,23 @@ __global__ void __launch_bounds__(4 * D, 2) bwd_forward_kernel(const BwdArgs a) 
         d.al[i] = row0 + 4 * g + i < rows ? alpha_of(gl[i], a.gate_scale) : 1.f;
         tame = tame && fabsf(kk[i]) < kTame;
       }
-      cut = whole_chunk<Wide<T>>(d, ln, g);
-      if (__builtin_amdgcn_ballot_w64(!tame) != 0) cut = kC;
+      whole_chunk<Wide<T>>(d, ln, g);
+      sharp = __builtin_amdgcn_ballot_w64(!tame || !(d.last >= kWhole)) != 0;
       bad = false;
+      St::template to_lds<D>(sm + L::oV, g, n, 16 * w, rv);
     }
-    rows_to_lds();
+#pragma unroll
+    for (int h = 0; h < HB; ++h) St::template to_lds<D>(sm + h * L::kSet, g, n, 16 * w, ro[h]);
+    if constexpr (L::kParts) {
+      __builtin_amdgcn_wave_barrier();   // LDS serves one wave's requests in order: its rows are complete below
+#pragma unroll
+      for (int h = 0; h < HB; ++h) dot_part64<D>(sm + L::oV, sm + h * L::kSet, w, g, n, sm + L::oDa + (w * HB + h) * L::kTile);
+    }
+    if (tid < HB * kC) {
+      float* den = reinterpret_cast<float*>(sm + L::oDen);
+      den[tid] = 1.f / rden;
+      den[HB * kC + tid] = rden;
+    }
     float qq[HB][4];
 #pragma unroll
     for (int h = 0; h < HB; ++h) St::patch(qd, rq[h], qq[h]);
@@ -328,27 +331,29 @@ __global__ void __launch_bounds__(4 * D, 2) bwd_forward_kernel(const BwdArgs a) 
 #pragma unroll
       for (int i = 0; i < 4; ++i) top = fmaxf(top, fabsf(qq[h][i]));
     bad = bad || __builtin_amdgcn_ballot_w64(!(top < kTame)) != 0;
-    int* flags = reinterpret_cast<int*>(sm + L::oFlag);      // per wave: the cut of its channels, and whether its part is bad
-    if (l == 0) flags[w] = cut | (bad ? kBad : 0);
+    int* flags = reinterpret_cast<int*>(sm + L::oFlag);
+    if (l == 0) flags[w] = (sharp ? kSharp : 0) | (bad ? kBad : 0);
     __syncthreads();
-    if (fresh) {
-      int m = 1;
+    if (hb == 0) {
+      int any = 0;
 #pragma unroll
-      for (int j = 0; j < NW; ++j) m = max(m, flags[j] & (kBad - 1));
-      nblk = __builtin_amdgcn_readfirstlane(m);
-      if (nblk > 1) {
-        hi = kC / nblk;
-        rows_to_lds();
-        __syncthreads();
-      }
+      for (int j = 0; j < NW; ++j) any |= flags[j];
+      serial = __builtin_amdgcn_readfirstlane(any & kSharp) != 0;
     }
     const int hb1 = hb + 1 < nb ? hb + 1 : 0;
-    const int blk1 = hb1 ? blk : (blk + 1 < nblk ? blk + 1 : 0);
-    const int ci1 = (hb1 || blk1) ? ci : ci + 1;
-    if (ci1 < nchunk) fetch(ci1, hb1);
-    // ---- once per block: decays, K', the state decayed up to the first token, z_t
-    if (hb == 0) {
-      if (nblk > 1) block_of_chunk<Wide<T>>(d, ln, g, lo, hi);
+    const int ci1 = hb1 ? ci : ci + 1;
+    if (!serial && ci1 < nchunk) fetch(ci1, hb1);
+    // ---- once per chunk: decays, K', the state decayed up to the first token, z_t
+    if (hb == 0 && serial) {
+#pragma unroll
+      for (int jt = 0; jt < D / 16; ++jt)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) X[jt][i] *= pend;
+      z *= pend;
+      wf = P * d.first;
+      P *= d.first * d.last;
+      pend = 1.f;
+    } else if (hb == 0) {
       center(d);
       const float f = d.first * pend;
 #pragma unroll
@@ -359,44 +364,99 @@ __global__ void __launch_bounds__(4 * D, 2) bwd_forward_kernel(const BwdArgs a) 
       float ones[4];
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const int t = 4 * g + i;
-        kp[i] = (t >= lo && t < hi) ? kk[i] * inverse<T>(d.E[i]) : 0.f;
+        kp[i] = kk[i] * inverse<T>(d.E[i]);
         // running sums over the tokens: a lower triangle of ones against K'
-        ones[i] = t <= row ? 1.f : 0.f;
+        ones[i] = 4 * g + i <= row ? 1.f : 0.f;
       }
       const floatx4 pz = token_steps<kWide>(ones, kp, floatx4{z, z, z, z});
 #pragma unroll
       for (int i = 0; i < 4; ++i) zt[i] = d.E[i] * pz[i];
-      z = lane_get(ln.n4 + 192, pz[3]);      // all of the block's tokens
+      z = lane_get(ln.n4 + 192, pz[3]);      // all of the chunk's tokens
       wf = P * d.first;
       P *= d.first * d.last;
       pend = d.last;
     }
-    // ---- u_t = E_t ( S~ dO_t + sum_{i <= t} (dO_t . v_i) K'_i )
+    const bool last_head = hb + 1 == nb;
     floatx4 u[HB];
+    if (serial) {
+      // ---- token by token: S_t, z_t, u_t = S_t dO_t
+      int lane = l;                                   // not known to be l: nothing of this loop is formed before it
+      asm volatile("" : "+v"(lane));
+      const int gs = lane >> 4, ns = lane & 15;
+      const Lanes lns = make_lanes(lane);
+      floatx4* before = reinterpret_cast<floatx4*>(sm + L::oX) + tid;
+      const float z0 = z;
+      if (!last_head) {
 #pragma unroll
-    for (int h = 0; h < HB; ++h) u[h] = floatx4{0.f, 0.f, 0.f, 0.f};
-    contract<T, D, HB>(X, sm, g, n, u);
+        for (int jt = 0; jt < D / 16; ++jt) before[4 * D * jt] = X[jt];
+      }
+#pragma unroll 1
+      for (int tg = 0; tg < 4; ++tg) {
+        const int from = ((tg << 4) + ns) << 2;       // the lane that holds tokens 4 tg .. of this channel
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const unsigned char* col = sm + (4 * tg + i) * L::kRow + 4 * gs * St::kBytes;
+          const float al = lane_get(from, d.al[i]), kt = lane_get(from, kk[i]);
+          z = fmaf(al, z, kt);
+          if (gs == tg) zt[i] = z;
+          constexpr int NP = kWide ? 4 : 1;            // partial sums
+          float part[HB][NP] = {};
+#pragma unroll
+          for (int jt = 0; jt < D / 16; ++jt) {
+            const floatx4 v4 = St::four(col + L::oV + 16 * jt * St::kBytes);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) X[jt][e] = fmaf(al, X[jt][e], kt * v4[e]);
+#pragma unroll
+            for (int h = 0; h < HB; ++h) {
+              const floatx4 o4 = St::four(col + h * L::kSet + 16 * jt * St::kBytes);
+#pragma unroll
+              for (int e = 0; e < 4; ++e) part[h][e % NP] = fmaf(X[jt][e], o4[e], part[h][e % NP]);
+            }
+          }
+#pragma unroll
+          for (int h = 0; h < HB; ++h) {
+            float sum = kWide ? (part[h][0] + part[h][1 % NP]) + (part[h][2 % NP] + part[h][3 % NP]) : part[h][0];
+            sum += lane_get(lns.x1, sum);
+            sum += lane_get(lns.x2, sum);
+            u[h][i] = gs == tg ? sum : (tg == 0 ? 0.f : u[h][i]);
+          }
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+      if (ci1 < nchunk) fetch(ci1, hb1);     // not before: its registers are the loop's
+      if (!last_head) {
+        z = z0;
+#pragma unroll
+        for (int jt = 0; jt < D / 16; ++jt) X[jt] = before[4 * D * jt];
+      }
+    } else {
+      // ---- u_t = E_t ( S~ dO_t + sum_{i <= t} (dO_t . v_i) K'_i )
+#pragma unroll
+      for (int h = 0; h < HB; ++h) u[h] = floatx4{0.f, 0.f, 0.f, 0.f};
+      contract<T, D, HB>(X, sm, g, n, u);
+#pragma unroll
+      for (int h = 0; h < HB; ++h) {
+        floatx4 da;    // [token i of v][token `row` of dO]
+        if constexpr (L::kParts) da = add64(floatx4{0.f, 0.f, 0.f, 0.f}, sum_parts64<NW>(sm + L::oDa + h * L::kTile, HB * L::kTile, g, n));
+        else da = dot_rows<T, D, kWide>(sm + L::oV, sm + h * L::kSet, g, n);
+        float am[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) am[i] = 4 * g + i <= row ? da[i] : 0.f;
+        const floatx4 s = token_steps<kWide>(am, kp, floatx4{0.f, 0.f, 0.f, 0.f});
+#pragma unroll
+        for (int i = 0; i < 4; ++i) u[h][i] = (u[h][i] + s[i]) * d.E[i];
+      }
+    }
     float* part = reinterpret_cast<float*>(sm + L::oEnd);
 #pragma unroll
     for (int h = 0; h < HB; ++h) {
-      floatx4 da;    // [token i of v][token `row` of dO]
-      if constexpr (L::kParts) da = add64(floatx4{0.f, 0.f, 0.f, 0.f}, sum_parts64<NW>(sm + L::oDa + h * L::kTile, HB * L::kTile, g, n));
-      else da = dot_rows<T, D, kWide>(sm + L::oV, sm + h * L::kSet, g, n);
-      float am[4];
+      floatx4 s;
 #pragma unroll
-      for (int i = 0; i < 4; ++i) am[i] = 4 * g + i <= row ? da[i] : 0.f;
-      floatx4 s = token_steps<kWide>(am, kp, floatx4{0.f, 0.f, 0.f, 0.f});
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        u[h][i] = (u[h][i] + s[i]) * d.E[i];
-        s[i] = row16_sum(qq[h][i] * u[h][i]);
-      }
+      for (int i = 0; i < 4; ++i) s[i] = row16_sum(qq[h][i] * u[h][i]);
       if (n == 0) *reinterpret_cast<floatx4*>(part + (w * HB + h) * kC + 4 * g) = s;
     }
     __syncthreads();
     // ---- dden = -(q . u) / den^2, dq = u / den + z dden
-    const bool last_head = hb + 1 == nb;
     const bool carries = __builtin_amdgcn_ballot_w64(wf != 0.f) != 0;   // this wave's channels still reach the segment's start
     float qw[HB][4];
     Wide<T> rz = 0;
@@ -411,7 +471,7 @@ __global__ void __launch_bounds__(4 * D, 2) bwd_forward_kernel(const BwdArgs a) 
       const float* den = reinterpret_cast<const float*>(sm + L::oDen);
       const double r = den[at], rr = r + r * (1.0 - (double)den[HB * kC + at] * r);
       mine = (float)(-(s * rr) * rr);
-      if (w == 0 && n < 4 * HB && t >= lo && t < min(hi, len)) a.dden[token * a.group + (hb * HB + h) * len + t] = mine;
+      if (w == 0 && n < 4 * HB && t < len) a.dden[token * a.group + (hb * HB + h) * len + t] = mine;
     }
     const float dds[16] = {row16_get<0>(mine), row16_get<1>(mine), row16_get<2>(mine), row16_get<3>(mine),
                            row16_get<4>(mine), row16_get<5>(mine), row16_get<6>(mine), row16_get<7>(mine),
@@ -424,16 +484,14 @@ __global__ void __launch_bounds__(4 * D, 2) bwd_forward_kernel(const BwdArgs a) 
       floatx4 dd;
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const int t = 4 * g + i;
-        const bool in = t >= lo && t < hi;
         dd[i] = dds[4 * h + i];
         dq[i] = fmaf(zt[i], dd[i], u[h][i] * rd[i]);
-        if (in) qdq[i] = fmaf(qq[h][i], dq[i], qdq[i]);
-        const float qe = in ? wf * d.E[i] * qq[h][i] : 0.f;
+        qdq[i] = fmaf(qq[h][i], dq[i], qdq[i]);
+        const float qe = wf * d.E[i] * qq[h][i];
         rz = fma((Wide<T>)qe, (Wide<T>)dd[i], rz);
         qw[h][i] = qe * rd[i];
       }
-      St::store(dQ, qd, offq + (unsigned)(hb * HB + h) * D * St::kBytes, row0, g, n, lo, hi, dq);
+      St::store(dQ, qd, offq + (unsigned)(hb * HB + h) * D * St::kBytes, row0, g, n, 0, kC, dq);
     }
     Rz += rz;
     // q and dO reach rz through dden, and a denominator of zero does: what is not finite in any of them shows here
@@ -441,29 +499,28 @@ __global__ void __launch_bounds__(4 * D, 2) bwd_forward_kernel(const BwdArgs a) 
     if (seg > 0 && carries) accumulate<T, D, HB>(R, sm, g, n, qw);
     if (last_head) {
       float kp1[1][4] = {{kp[0], kp[1], kp[2], kp[3]}};
-      accumulate<T, D, 1>(X, sm + L::oV, g, n, kp1);
-      if (blk + 1 == nblk) {
-        float* out = a.qdq + token * D;
-        if (len == kC) {
-          *reinterpret_cast<floatx4*>(out + (w * 64 + l) * 4) = floatx4{qdq[0], qdq[1], qdq[2], qdq[3]};
-        } else {
+      if (!serial) accumulate<T, D, 1>(X, sm + L::oV, g, n, kp1);
+      float* out = a.qdq + token * D;
+      if (len == kC) {
+        *reinterpret_cast<floatx4*>(out + (w * 64 + l) * 4) = floatx4{qdq[0], qdq[1], qdq[2], qdq[3]};
+      } else {
 #pragma unroll
-          for (int i = 0; i < 4; ++i)
-            if (4 * g + i < len) out[c * len + 4 * g + i] = qdq[i];
-        }
-        if (tid == 0) {
-          int any = bad ? kBad : 0;
-#pragma unroll
-          for (int j = 0; j < NW; ++j) any |= flags[j];
-          a.blocks[chunk] = (uint8_t)((any & kBad) ? kC : nblk);
-        }
-#pragma unroll
-        for (int i = 0; i < 4; ++i) qdq[i] = 0.f;
+        for (int i = 0; i < 4; ++i)
+          if (4 * g + i < len) out[c * len + 4 * g + i] = qdq[i];
       }
+      if (tid == 0) {
+        int any = bad;
+#pragma unroll
+        for (int j = 0; j < NW; ++j) any |= flags[j];
+        any_serial = any_serial || any != 0;
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i) qdq[i] = 0.f;
     }
     __syncthreads();
-    ci = ci1; blk = blk1; hb = hb1;
+    ci = ci1; hb = hb1;
   }
+  if (tid == 0) a.serial[(size_t)bh * a.nseg + seg] = any_serial;
   if (seg > 0) {
     float* slot = a.slots_r + ((size_t)bh * (a.nseg - 1) + (a.nseg - 1 - seg)) * slot_floats<D>();
 #pragma unroll
@@ -480,8 +537,9 @@ __global__ void __launch_bounds__(4 * D, 2) bwd_forward_kernel(const BwdArgs a) 
 }
 
 // ---- reverse sweep: dk, dv, dg, and the start state's gradient.  grid (nseg, heads), 4 D threads.
-template <typename T, int D, int HB>
-__global__ void __launch_bounds__(4 * D, 2) bwd_reverse_kernel(const BwdArgs a) {
+// kTokens: every chunk of the segment token by token.
+template <typename T, int D, int HB, bool kTokens>
+__device__ __forceinline__ void reverse_sweep(const BwdArgs& a) {
   typedef Store<T> St;
   typedef Sweep<T, D, HB> L;
   constexpr int NW = L::NW;
@@ -526,7 +584,7 @@ __global__ void __launch_bounds__(4 * D, 2) bwd_reverse_kernel(const BwdArgs a) 
     later = fmaf(Rz0, zend, later);
   }
   double Rz = Rz0;
-  float pend = 1.f;      // alpha of the first token of the block after
+  float pend = 1.f;      // alpha of the first token of the chunk after
 
   typename St::Raw rq[HB], ro[HB], rk, rv, rg;
   floatx4 rqdq = {0.f, 0.f, 0.f, 0.f};
@@ -561,55 +619,58 @@ __global__ void __launch_bounds__(4 * D, 2) bwd_reverse_kernel(const BwdArgs a) 
   };
 
   const int nchunk = (rows + kC - 1) / kC;
-  auto blocks_of = [&](int ci) { return __builtin_amdgcn_readfirstlane((int)a.blocks[(size_t)bh * a.chunks + s0 / kC + ci]); };
-  int ci = nchunk - 1, hb = 0, nblk = ci >= 0 ? blocks_of(ci) : 1, blk = nblk - 1, lo = 0, hi = kC;
+  int ci = nchunk - 1, hb = 0;
   Decay d;
   float kk[4], kp[4], rE[4], sig[4], qdq[4];
-  floatx4 dk0, dk, dv0, dv;     // from after the block (state products), within it
+  floatx4 dk0, dk, dv0, dv;     // from after the chunk (state products), within it
   doublex4 dvw;                 // fp32 storage: dv0 + dv
   if (ci >= 0) fetch(ci, 0);
   while (ci >= 0) {
     const int row0 = ci * kC;
-    // ---- once per block: decays, K', R~; rows to LDS
+    // ---- once per chunk: decays, K', R~; rows to LDS
     if (hb == 0) {
-      if (blk == nblk - 1) {
-        float gl[4];
-        St::patch(qd, rg, gl);
-        St::patch(qd, rk, kk);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          d.al[i] = row0 + 4 * g + i < rows ? alpha_of(gl[i], a.gate_scale) : 1.f;
-          sig[i] = __builtin_amdgcn_rcpf(1.f + __expf(gl[i]));       // 1 - sigmoid(g)
-          qdq[i] = rqdq[i];
-        }
-        whole_chunk<Wide<T>>(d, ln, g);
-      }
-      lo = blk * (kC / nblk);
-      hi = lo + kC / nblk;
-      if (nblk > 1) block_of_chunk<Wide<T>>(d, ln, g, lo, hi);
-      center(d);
-      const float f = d.last * pend;
-      pend = d.first;
-      Rz *= f;
+      float gl[4];
+      St::patch(qd, rg, gl);
+      St::patch(qd, rk, kk);
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const int t = 4 * g + i;
-        rE[i] = inverse<T>(d.E[i]);
-        kp[i] = (t >= lo && t < hi) ? kk[i] * rE[i] : 0.f;
+        d.al[i] = row0 + 4 * g + i < rows ? alpha_of(gl[i], a.gate_scale) : 1.f;
+        sig[i] = __builtin_amdgcn_rcpf(1.f + __expf(gl[i]));       // 1 - sigmoid(g)
+        qdq[i] = rqdq[i];
       }
-      f32_to_lds<D>(sm + L::oK, g, n, 16 * w, kp);
+      whole_chunk<Wide<T>>(d, ln, g);
+      if constexpr (kTokens) {
+        Rz *= pend;
 #pragma unroll
-      for (int jt = 0; jt < D / 16; ++jt) {
+        for (int i = 0; i < 4; ++i) d.E[i] = rE[i] = 1.f;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) R[jt][i] *= f;
-        *reinterpret_cast<floatx4*>(sm + L::oU + c * f32_row_bytes<D>() + (16 * jt + 4 * g) * 4) = R[jt];
+        for (int jt = 0; jt < D / 16; ++jt)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) R[jt][i] *= pend;
+        dk0 = dk = dv0 = dv = floatx4{0.f, 0.f, 0.f, 0.f};
+        dvw = kZero64;
+      } else {
+        center(d);
+        const float f = d.last * pend;
+        Rz *= f;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          rE[i] = inverse<T>(d.E[i]);
+          kp[i] = kk[i] * rE[i];
+        }
+        f32_to_lds<D>(sm + L::oK, g, n, 16 * w, kp);
+#pragma unroll
+        for (int jt = 0; jt < D / 16; ++jt) {
+#pragma unroll
+          for (int i = 0; i < 4; ++i) R[jt][i] *= f;
+          *reinterpret_cast<floatx4*>(sm + L::oU + c * f32_row_bytes<D>() + (16 * jt + 4 * g) * 4) = R[jt];
+        }
       }
+      pend = d.first;
       St::template to_lds<D>(sm + L::oV, g, n, 16 * w, rv);
     }
-    // the block's tokens only (v: every token's row stays its own)
-    const bool part = hi - lo < kC;
 #pragma unroll
-    for (int h = 0; h < HB; ++h) St::template to_lds<D>(sm + h * L::kSet, g, n, 16 * w, part ? St::keep(ro[h], g, n, lo, hi) : ro[h]);
+    for (int h = 0; h < HB; ++h) St::template to_lds<D>(sm + h * L::kSet, g, n, 16 * w, ro[h]);
     unsigned char* das = sm + L::oSc + NW * HB * L::kTile;     // parts of dO . v
     if constexpr (L::kParts) {
       __builtin_amdgcn_wave_barrier();
@@ -618,28 +679,90 @@ __global__ void __launch_bounds__(4 * D, 2) bwd_reverse_kernel(const BwdArgs a) 
     }
     float* den = reinterpret_cast<float*>(sm + L::oDen);
     if (tid < HB * kC) {
-      const bool in = (tid & 15) >= lo && (tid & 15) < hi;
-      den[tid] = in ? 1.f / rden : 0.f;
-      den[HB * kC + tid] = in ? rdd : 0.f;
+      den[tid] = 1.f / rden;
+      den[HB * kC + tid] = rdd;
     }
     float qp[HB][4];
 #pragma unroll
     for (int h = 0; h < HB; ++h) {
       St::patch(qd, rq[h], qp[h]);
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int t = 4 * g + i;
-        qp[h][i] = (t >= lo && t < hi) ? qp[h][i] * d.E[i] : 0.f;
-      }
+      for (int i = 0; i < 4; ++i) qp[h][i] *= d.E[i];
     }
     __syncthreads();
     const int hb1 = hb + 1 < nb ? hb + 1 : 0;
-    const int blk1 = hb1 ? blk : blk - 1;
-    const int ci1 = blk1 >= 0 ? ci : ci - 1;
-    const int nblk1 = ci1 == ci ? nblk : (ci1 >= 0 ? blocks_of(ci1) : 1);
-    if (ci1 >= 0) fetch(ci1, hb1);
+    const int ci1 = hb1 ? ci : ci - 1;
+    if (!kTokens && ci1 >= 0) fetch(ci1, hb1);
+    if constexpr (kTokens) {
+      // ---- token by token, these query heads' part: Gr_t, dk_t = Gr_t v^_t, dv_t = k_t Gr_t (over the channels through LDS)
+      int lane = l;                                   // not known to be l: nothing of this loop is formed before it
+      asm volatile("" : "+v"(lane));
+      const int gs = lane >> 4, ns = lane & 15;
+      const Lanes lns = make_lanes(lane);
+      floatx4 Y[D / 16];
+      double y = hb == 0 ? Rz : 0.0;
+#pragma unroll
+      for (int jt = 0; jt < D / 16; ++jt) Y[jt] = hb == 0 ? R[jt] : floatx4{0.f, 0.f, 0.f, 0.f};
+      float* dvp = reinterpret_cast<float*>(sm + L::oU);
+      float aln = 1.f;       // alpha of the token after
+#pragma unroll 1
+      for (int tg = 3; tg >= 0; --tg) {
+        const int from = ((tg << 4) + ns) << 2;
+#pragma unroll
+        for (int i = 3; i >= 0; --i) {
+          const unsigned char* col = sm + (4 * tg + i) * L::kRow + 4 * gs * St::kBytes;
+          const float kt = lane_get(from, kk[i]);
+          float wt[HB];
+          y *= aln;
+#pragma unroll
+          for (int h = 0; h < HB; ++h) {
+            const float qv = lane_get(from, qp[h][i]);
+            wt[h] = qv * den[h * kC + 4 * tg + i];
+            y = fma((double)qv, (double)den[(HB + h) * kC + 4 * tg + i], y);
+          }
+          float part[4] = {};
+#pragma unroll
+          for (int jt = 0; jt < D / 16; ++jt) {
+            floatx4 x = Y[jt] * aln;
+#pragma unroll
+            for (int h = 0; h < HB; ++h) {
+              const floatx4 o4 = St::four(col + h * L::kSet + 16 * jt * St::kBytes);
+#pragma unroll
+              for (int e = 0; e < 4; ++e) x[e] = fmaf(wt[h], o4[e], x[e]);
+            }
+            Y[jt] = x;
+            const floatx4 v4 = St::four(col + L::oV + 16 * jt * St::kBytes);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+              part[e] = fmaf(x[e], v4[e], part[e]);
+              x[e] = row16_sum(kt * x[e]);
+            }
+            if (ns == 0) *reinterpret_cast<floatx4*>(dvp + (w * kC + 4 * tg + i) * D + 16 * jt + 4 * gs) = x;
+          }
+          float acc = (part[0] + part[1]) + (part[2] + part[3]);
+          acc += lane_get(lns.x1, acc);
+          acc += lane_get(lns.x2, acc);
+          if (gs == tg) dk[i] += acc + (float)y;
+          aln = lane_get(from, d.al[i]);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+      Rz = hb == 0 ? y : Rz + y;
+#pragma unroll
+      for (int jt = 0; jt < D / 16; ++jt) R[jt] = hb == 0 ? Y[jt] : R[jt] + Y[jt];
+      if (ci1 >= 0) fetch(ci1, hb1);         // not before: its registers are the loop's
+      __syncthreads();
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        Wide<T> s = 0;
+#pragma unroll
+        for (int j = 0; j < NW; ++j) s += dvp[(j * kC + 4 * g + i) * D + c];
+        if (kWide) dvw[i] += s;
+        else dv[i] += s;
+      }
+    } else {
     if (hb == 0) {
-      // ---- what flows in from after the block: dk gets R~ v^, dv gets K' R~
+      // ---- what flows in from after the chunk: dk gets R~ v^, dv gets K' R~
       floatx4 acc[1] = {floatx4{(float)Rz, (float)Rz, (float)Rz, (float)Rz}};
       contract<T, D, 1>(R, sm + L::oV, g, n, acc);
       dk0 = acc[0];
@@ -690,7 +813,7 @@ __global__ void __launch_bounds__(4 * D, 2) bwd_reverse_kernel(const BwdArgs a) 
         *reinterpret_cast<doublex4*>(p + l * 32) = sc;
       }
     }
-    // ---- dk within the block, and what the block adds to the gradient flowing on
+    // ---- dk within the chunk, and what the chunk adds to the gradient flowing on
     float qw[HB][4];
     Wide<T> rzt[4] = {0, 0, 0, 0};
 #pragma unroll
@@ -717,7 +840,7 @@ __global__ void __launch_bounds__(4 * D, 2) bwd_reverse_kernel(const BwdArgs a) 
     rz += lane_get(ln.x2, rz);
     Rz += rz;
     if constexpr (!L::kParts) __syncthreads();
-    // ---- dv within the block: this wave's 16 value columns
+    // ---- dv within the chunk: this wave's 16 value columns
     if constexpr (sizeof(T) == 2) {
       if constexpr (HB == 1) {
         const unsigned char* p = sm + L::oSc + l * 8;
@@ -751,17 +874,17 @@ __global__ void __launch_bounds__(4 * D, 2) bwd_reverse_kernel(const BwdArgs a) 
         for (int i = 0; i < 4; ++i) dvw = mfma_f64(sc[i], f[i], dvw);
       }
     }
+    }
     if (hb + 1 == nb) {
-      // ---- outputs of the block; the gate's sum over this token and all later ones (by additions: no later token's sum
+      // ---- outputs; the gate's sum over this token and all later ones (by additions: no later token's sum
       // holds an earlier token's term, finite or not)
       float dkv[4], dvv[4], dgv[4];
       Wide<T> x[4];
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const int t = 4 * g + i;
         dkv[i] = (dk0[i] + dk[i]) * rE[i];
         dvv[i] = kWide ? (float)dvw[i] : dv0[i] + dv[i];
-        x[i] = (t >= lo && t < hi) ? fmaf(-kk[i], dkv[i], qdq[i]) : 0.f;
+        x[i] = fmaf(-kk[i], dkv[i], qdq[i]);
       }
 #pragma unroll
       for (int i = 2; i >= 0; --i) x[i] += x[i + 1];
@@ -771,13 +894,12 @@ __global__ void __launch_bounds__(4 * D, 2) bwd_reverse_kernel(const BwdArgs a) 
 #pragma unroll
       for (int i = 0; i < 4; ++i) dgv[i] = (float)(x[i] + rest) * a.gate_scale * sig[i];
       later = lane_get(ln.n4, (float)(x[0] + rest));
-      St::store(dK, qd, offk, row0, g, n, lo, hi, dkv);
-      St::store(dV, qd, offk, row0, g, n, lo, hi, dvv);
-      St::store(dG, qd, offk, row0, g, n, lo, hi, dgv);
+      St::store(dK, qd, offk, row0, g, n, 0, kC, dkv);
+      St::store(dV, qd, offk, row0, g, n, 0, kC, dvv);
+      St::store(dG, qd, offk, row0, g, n, 0, kC, dgv);
     }
     __syncthreads();
-    ci = ci1; hb = hb1; nblk = nblk1;
-    blk = blk1 >= 0 ? blk1 : nblk1 - 1;
+    ci = ci1; hb = hb1;
   }
   if (seg == 0) {
     if (a.dS0 != nullptr) {
@@ -790,6 +912,12 @@ __global__ void __launch_bounds__(4 * D, 2) bwd_reverse_kernel(const BwdArgs a) 
     }
     if (a.dz0 != nullptr && g == 0) a.dz0[(size_t)bh * D + c] = (float)(pend * Rz);
   }
+}
+
+template <typename T, int D, int HB>
+__global__ void __launch_bounds__(4 * D, 2) bwd_reverse_kernel(const BwdArgs a) {
+  if (a.serial[(size_t)blockIdx.y * a.nseg + blockIdx.x] != 0) reverse_sweep<T, D, HB, true>(a);
+  else reverse_sweep<T, D, HB, false>(a);
 }
 
 template <int D>
@@ -828,19 +956,19 @@ hipError_t launch_typed(const BwdArgs& a, hipStream_t stream) {
 }
 
 struct Sizes {
-  size_t qdq, slots, blocks, live, dden, total;   // floats / words, and bytes in all
+  size_t qdq, slots, serial, live, dden, total;   // floats / words, and bytes in all
 };
 Sizes workspace_sizes(int B, int T, int Hq, int Hkv, int d, int nseg) {
-  const size_t heads = (size_t)B * Hkv, chunks = ((size_t)T + kC - 1) / kC;
+  const size_t heads = (size_t)B * Hkv;
   Sizes s;
   s.qdq = heads * T * d;
   s.slots = heads * (nseg - 1) * (d * d + 2 * d);
-  s.blocks = (heads * chunks + 15) / 16 * 4;
+  s.serial = (heads * nseg + 15) / 16 * 4;
   s.live = heads * nseg;
   s.dden = (size_t)B * T * Hq;
   // the size is two states and a row per segment beside both tensors, as callers may have kept it; what is used is less (but
   // for sequences of millions of tokens)
-  const size_t used = s.qdq + 2 * s.slots + s.blocks + 2 * s.live + s.dden, rule = s.qdq + s.dden + heads * nseg * (2 * (d * d + 2 * d) + d);
+  const size_t used = s.qdq + 2 * s.slots + s.serial + 2 * s.live + s.dden, rule = s.qdq + s.dden + heads * nseg * (2 * (d * d + 2 * d) + d);
   s.total = (used > rule ? used : rule) * 4 + 256;
   return s;
 }
@@ -850,9 +978,11 @@ Sizes workspace_sizes(int B, int T, int Hq, int Hkv, int d, int nseg) {
 bool gla_backward_supports(int d, int group) { return group * d <= 2048 && group <= d; }
 
 // Segments of the sequence, a multiple of 64 tokens: as many as make one round of the workgroups that the chip holds over all
-// (batch, kv head) pairs, which is what the sweeps' registers allow: at head dim 64 two per compute unit (of four waves), three
-// with one query head per pass in bf16 storage, at 128 one (of eight).  bf16, 32 / 8 heads, 32768 tokens of 64 430 us, 16384 of
-// 128 617; in two rounds, with twice the contributions and start states, 470 and 663.  Two rounds where one would leave many
+// (batch, kv head) pairs, which is what the sweeps' registers allow: at head dim 64 two per compute unit (of four waves), with one query
+// head per pass in bf16 storage three in the reverse sweep (a limit of registers for three in the forward one too spilled: 96.7 us
+// and 101.1 for 8192 tokens of 8 heads), at 128 one (of eight).  bf16, 32 / 8 heads, 32768 tokens of 64 or 16384 of 128: two rounds,
+// with twice the contributions and start states, take a tenth longer (430 us and 470, 617 and 663, of sweeps a little slower than
+// these).  Two rounds where one would leave many
 // places empty (300 pairs: two rounds of a third of the sequence, not one of all of it).  A segment's rows are addressed with
 // 32-bit offsets from its first row.
 void gla_backward_plan(int B, int T, int Hq, int Hkv, int d, int bf16, int* seg_len, int* nseg) {
@@ -880,7 +1010,6 @@ hipError_t launch_gla_backward(const GlaBackwardParams& p, hipStream_t stream) {
   a.dq = p.dq; a.dk = p.dk; a.dv = p.dv; a.dg = p.dg; a.dS0 = p.dS0; a.dz0 = p.dz0;
   a.B = p.B; a.T = p.T; a.Hq = p.Hq; a.Hkv = p.Hkv; a.group = p.Hq / p.Hkv;
   a.gate_scale = p.gate_scale;
-  a.chunks = (p.T + kC - 1) / kC;
   gla_backward_plan(p.B, p.T, p.Hq, p.Hkv, p.d, p.bf16, &a.seg_len, &a.nseg);
   if (!gla_backward_supports(p.d, a.group)) return hipErrorInvalidValue;
   // Fold / scan, us a call: head dim 64, fp32, 2 heads, 4 segments 40.0 / 45.3, 8 segments 44.0 / 46.0, bf16, 8 kv heads, 16
@@ -891,7 +1020,7 @@ hipError_t launch_gla_backward(const GlaBackwardParams& p, hipStream_t stream) {
   a.qdq = w; w += s.qdq;
   a.slots_f = w; w += s.slots;
   a.slots_r = w; w += s.slots;
-  a.blocks = reinterpret_cast<uint8_t*>(w); w += s.blocks;
+  a.serial = reinterpret_cast<uint8_t*>(w); w += s.serial;
   a.live_f = reinterpret_cast<int*>(w); w += s.live;
   a.live_r = reinterpret_cast<int*>(w); w += s.live;
   a.dden = w;

@@ -105,14 +105,15 @@ def test_a_key_too_large_to_be_divided_by_a_decay(oracle, shape):
 
 @pytest.mark.parametrize("which", ["q", "k", "v", "dO"])
 @pytest.mark.parametrize("sign", [1, -1])
+@pytest.mark.parametrize("level", [-2.6875, -3.5])
 @pytest.mark.parametrize("shape", [SHAPES[0], SHAPES[2], SHAPES[4]], ids=str)
-def test_tiny_and_huge_values_in_channels_that_nearly_close(oracle, shape, which, sign):
-    """Chunks that decay by nearly 2^-64, and operands scaled by a power of two: the gradients scale by powers of two as the
+def test_tiny_and_huge_values_in_channels_that_nearly_close(oracle, shape, level, which, sign):
+    """Chunks that decay by nearly 2^-60 and 2^-77, and operands scaled by a power of two: the gradients scale by powers of two as the
     equations say (eps = 0).  2^80 in fp32 storage; 2^64 in bf16 storage, whose products need 16 bits below an fp32 value."""
     power = sign * (80 if shape[3] == "fp32" else 64)
     wl, (q, k, v, g, dO), _ = _inputs(*shape[:5], False)
-    g[:, :, 0] = H.host(torch.tensor(-2.6875))
-    print("backward, scaled operand", wl, which, power, flush=True)
+    g[:, :, 0] = level
+    print("backward, scaled operand", wl, level, which, power, flush=True)
     den = oracle.gla_prefill(q, k, v, g, 1.0, 0.0)["den"].astype(np.float32)
     ref = _run(wl, q, k, v, g, dO, den, None, None)
     f = np.float32(2.0) ** np.float32(power)
