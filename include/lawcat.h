@@ -155,9 +155,9 @@ LAWCAT_API int lawcat_gla_prefill(const lawcat_desc* desc, const void* q, const 
  *   q, k, v, gate_logits, S0, z0 as lawcat_gla_prefill took them; den [B,T,Hq] as it returned it (den_out; the
  *   output O itself is not needed);  dO [B,T,Hq,dv];  dq, dk, dv, dgate_logits: shapes and type of q, k, v,
  *   gate_logits;  dS0 [B,Hkv,dk,dv], dz0 [B,Hkv,dk]: nullable.  Workspace: LAWCAT_CALL_GLA_BACKWARD.
- * fp32 arithmetic throughout (both storage types; on the matrix cores), chunked, parallel over (batch, kv head) and
- * segments of the sequence.  Query heads per kv head x head dim above 2048, or above the head dim, is
- * LAWCAT_E_UNSUPPORTED.
+ * fp32 arithmetic throughout (both storage types; on the matrix cores, fp32 storage with 64-bit sums), chunked,
+ * parallel over (batch, kv head) and segments of the sequence; segments in which a gate all but closes take their
+ * tokens one by one.  Query heads per kv head x head dim above 2048 is LAWCAT_E_UNSUPPORTED.
  */
 LAWCAT_API int lawcat_gla_backward(const lawcat_desc* desc, const void* q, const void* k, const void* v,
                         const void* gate_logits, const float* den, const void* dO,
@@ -189,9 +189,9 @@ LAWCAT_API int lawcat_gla_step(const lawcat_desc* desc, const void* q, const voi
                     const void* gate_logits, float* S, float* z, void* o, void* stream);
 
 /*
- * Section 4.2, n = desc->T consecutive recurrent (decode) steps per sequence in ONE launch: the same fp32
- * token-by-token arithmetic as n calls of lawcat_gla_step, with the state held on chip between the steps, so
- * the state's 2 * Hkv * dk * dv * 4 bytes cross HBM once per call instead of once per token (streaming
+ * Section 4.2, n = desc->T consecutive recurrent (decode) steps per sequence in ONE launch: the results of n
+ * calls of lawcat_gla_step to fp32 rounding (16 tokens at a time, sums in fp32 or wider), with the state held on
+ * chip between the steps, so the state's 2 * Hkv * dk * dv * 4 bytes cross HBM once per call instead of once per token (streaming
  * inference in blocks of tokens, speculative or chunked decoding).
  *   q [B,n,Hq,dk]  k, gate_logits [B,n,Hkv,dk]  v [B,n,Hkv,dv]  o [B,n,Hq,dv]
  *   S [B,Hkv,dk,dv], z [B,Hkv,dk]: read, updated in place to the state after the n-th token.

@@ -105,9 +105,9 @@ __device__ inline void conv_tile(const T* __restrict__ x, const T* __restrict__ 
 
 // bf16 storage, matrix cores.  One workgroup (4 waves) walks `tiles_per_block` consecutive tiles of one
 // (batch, head group): a tile is TT tokens x GH adjacent heads that share one matrix, ROWS = TT * GH rows of D
-// channels (256 rows at D = 64, 128 at D = 128).
-//   load  : thread = 8 adjacent channels (16 bytes) x a run of 8 tokens; 11 raw rows in registers (the run and
-//           the three before it), read through a buffer descriptor over the workgroup's own token range, so
+// channels (at D = 64 256 rows of four heads or 128 of one, at D = 128 64).
+//   load  : thread = 8 adjacent channels (16 bytes) x a run of 8 tokens (256 rows) or 4; the run's raw rows and the
+//           three before it in registers, read through a buffer descriptor over the workgroup's own token range, so
 //           that rows before the first token and past the last read as zero without a branch; the next tile's
 //           rows are requested before the current tile's products start
 //   conv  : in registers, fp32; rounded to bf16 into LDS, row = token * GH + head (the order in memory)
@@ -343,7 +343,7 @@ hipError_t launch_mfma(const ConvParams& p, const void* wf, int group, hipStream
   const int ntiles = (p.T + TT - 1) / TT;
   const int nbh = p.B * (p.H / GH);
   // one round of workgroups: as many per (batch, head group) as the chip holds at once, each walking a
-  // contiguous run of tiles (the matrix is transposed into LDS once per workgroup)
+  // contiguous run of tiles (the matrix goes into LDS once per workgroup)
   const int per_bh = kComputeUnits * kResident / nbh > 0 ? kComputeUnits * kResident / nbh : 1;
   const int tpb = (ntiles + per_bh - 1) / per_bh;
   // a workgroup addresses its own token range with 32-bit byte offsets

@@ -975,7 +975,7 @@ Sizes workspace_sizes(int B, int T, int Hq, int Hkv, int d, int nseg) {
 
 }  // namespace
 
-bool gla_backward_supports(int d, int group) { return group * d <= 2048 && group <= d; }
+bool gla_backward_supports(int d, int group) { return group * d <= 2048; }
 
 // Segments of the sequence, a multiple of 64 tokens: as many as make one round of the workgroups that the chip holds over all
 // (batch, kv head) pairs, which is what the sweeps' registers allow: at head dim 64 two per compute unit (of four waves), with one query

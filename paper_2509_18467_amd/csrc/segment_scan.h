@@ -14,15 +14,16 @@ namespace {   // one copy per translation unit: the kernels are registered by ad
 // AFTER: slot[seg] <- state after segment seg, for all but the last, which has no slot (nseg_max - 1 of them per head).
 // The recurrence is linear, so the segments are cut into 8 groups: 8 threads per 1 or 4 state elements each
 // reduce their group to (product of decays, contribution from a zero start), the eight pairs are
-// combined through LDS, and each thread replays its group from its true start, out of registers where a group has at
-// most U segments.  All loads of a group are independent of the running state and issued together.
+// combined through LDS, and each thread replays its group from its true start.  All loads of a group are independent of the running state and issued together.
 //
 // What bounds it: latency, two rounds of dependent loads in a launch of microseconds.  8 heads, every segment passed on: 64
 // segments at head dim 64 6.3 us, 9 segments 4.6, 27 segments at head dim 128 7.4 (one element per thread and a second
 // read of the slots: 6.5, 5.6, 13.2).  U and the elements per thread go together: eight segments of four elements at 128 take
 // registers that cost more than the second read (9.7).  Loads past a short group's end repeat its last segment: a branch
 // between them cost 2 us.
-// adjacent state elements of a thread: one where a head has up to 64 segments (head dim 64), four where it has up to 32
+// A thread keeps its group in registers up to 8 U contributions per head, 64 at head dim 64 and 32 at 128; beyond that it reads the
+// slots a second time.
+// adjacent state elements of a thread: one at head dim 64, four at 128
 template <int D> constexpr int kScanVec = D == 64 ? 1 : 4;
 template <int D, bool AFTER = false>
 __global__ void __launch_bounds__(256) segment_scan_kernel(float* __restrict__ ws, const int* __restrict__ seg_live,
