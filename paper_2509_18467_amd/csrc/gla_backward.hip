@@ -947,8 +947,8 @@ hipError_t launch_sized(const BwdArgs& a, hipStream_t stream) {
 
 template <typename T, int D>
 hipError_t launch_typed(const BwdArgs& a, hipStream_t stream) {
-  // query heads per pass: four, in fp32 storage two, whose 64-bit sums would spill with four (head dim 64, 500 tokens, 2 x 8 heads on
-  // 2: 117.7 us and 130.6; 128, 512 tokens, 8 heads on 2: 324 and 334, with one head 340)
+  // query heads per pass: four, in fp32 storage two, whose 64-bit sums would spill with four.  us with one, two and four: head dim
+  // 64, 500 tokens, 2 x 8 heads on 2, 122.5, 109.8, 136.5; 128, 512 tokens, 8 heads on 2, 323, 291, 305
   if constexpr (sizeof(T) == 2)
     if (a.group % 4 == 0) return launch_sized<T, D, 4>(a, stream);
   if (a.group % 2 == 0) return launch_sized<T, D, 2>(a, stream);
@@ -981,8 +981,7 @@ bool gla_backward_supports(int d, int group) { return group * d <= 2048; }
 // (batch, kv head) pairs, which is what the sweeps' registers allow: at head dim 64 two per compute unit (of four waves), with one query
 // head per pass in bf16 storage three in the reverse sweep (a limit of registers for three in the forward one too spilled: 96.7 us
 // and 101.1 for 8192 tokens of 8 heads), at 128 one (of eight).  bf16, 32 / 8 heads, 32768 tokens of 64 or 16384 of 128: two rounds,
-// with twice the contributions and start states, take a tenth longer (430 us and 470, 617 and 663, of sweeps a little slower than
-// these).  Two rounds where one would leave many
+// with twice the contributions and start states, take 447 and 627 us, one 409 and 582.  Two rounds where one would leave many
 // places empty (300 pairs: two rounds of a third of the sequence, not one of all of it).  A segment's rows are addressed with
 // 32-bit offsets from its first row.
 void gla_backward_plan(int B, int T, int Hq, int Hkv, int d, int bf16, int* seg_len, int* nseg) {
@@ -1012,8 +1011,9 @@ hipError_t launch_gla_backward(const GlaBackwardParams& p, hipStream_t stream) {
   a.gate_scale = p.gate_scale;
   gla_backward_plan(p.B, p.T, p.Hq, p.Hkv, p.d, p.bf16, &a.seg_len, &a.nseg);
   if (!gla_backward_supports(p.d, a.group)) return hipErrorInvalidValue;
-  // Fold / scan, us a call: head dim 64, fp32, 2 heads, 4 segments 40.0 / 45.3, 8 segments 44.0 / 46.0, bf16, 8 kv heads, 16
-  // segments 72.4 / 67.1; head dim 128, 5 segments 106.2 / 107.0, 8 segments 119.4 / 110.6
+  // Fold / scan, us a call: head dim 64, fp32, 2 heads, 4 segments 54.8 / 58.3, 8 segments 59.0 / 59.2, bf16, 8 kv heads, 16
+  // segments 69.1 / 61.1; head dim 128, fp32, 8 heads on 2, 5 segments 294 / 290, 8 segments 306 / 291 (with fewer heads, whose
+  // calls are shorter, 5 are about equal)
   a.fold = a.nseg > 1 && a.nseg <= (p.d == 64 ? 8 : 5);
   const Sizes s = workspace_sizes(p.B, p.T, p.Hq, p.Hkv, p.d, a.nseg);
   float* w = static_cast<float*>(p.workspace);
