@@ -462,9 +462,8 @@ __global__ void __launch_bounds__(D * 4, D == 64 ? 2 : 1)
   // grid rows past a short sequence's last segment (packed batches) have nothing to do; the whole team leaves
   // before the first barrier
   if (seg >= nseg_pass) return;
-  constexpr bool active = true;
   const int s0 = seg * a.seg_len;
-  const int s1 = active ? min(T, s0 + a.seg_len) : s0;
+  const int s1 = min(T, s0 + a.seg_len);
 
   // load-stage patch of this thread: 8 tokens x 2 channels
   const int cp = l & 31, th = l >> 5;
@@ -474,25 +473,37 @@ __global__ void __launch_bounds__(D * 4, D == 64 ? 2 : 1)
 
   // Output pass: did the scan run for this head?  It leaves the workspace untouched when no segment of the head
   // passes anything on (every total decay exactly zero): then a segment starts from its predecessor's
-  // contribution as the state pass wrote it, the first from S0, z0.  The loads are issued here and reduced after
-  // the conv weights below, so that the two latencies overlap.
+  // contribution as the state pass wrote it, the first from S0, z0.  With few segments (fold): lane j, whether segment j, before
+  // this one, passes anything on.  The prologue's loads are issued in the order in which they are waited for: these, the conv
+  // weights, the first granule's rows, the start state.
   int live_any = 0;
-  if (OUTPUT && nseg > 1 && !a.fold)
-    for (int j = tid; j < nseg - 1; j += G::TEAM) live_any |= a.seg_live[(size_t)bh * a.nseg + j];
+  if (OUTPUT) {
+    if (a.fold) live_any = l >= seg || a.seg_live[(size_t)bh * a.nseg + l] != 0;
+    else
+      for (int j = tid; j < nseg - 1; j += G::TEAM) live_any |= a.seg_live[(size_t)bh * a.nseg + j];
+  }
 
   float* wl = reinterpret_cast<float*>(smem + G::kWl);
+  // conv weights as fp32 [head][channel][4 taps], taps beyond W zero; row GR is the key head.  All of a thread's loads are issued
+  // here (a channel's four taps in one) and used below, after the granule's and the state's.
+  constexpr int kRows = OUTPUT ? GR + 1 : 1, kWeights = (kRows * D + G::TEAM - 1) / G::TEAM;   // channels per thread
+  uint2 wraw[kWeights];
   if (CONV) {
-    // conv weights as fp32 [head][channel][4 taps], taps beyond W zero; row GR is the key head
-    const float wscale = MODE == kConvElu ? kLog2e : 1.f;
-    for (int e = tid; e < (GR + 1) * D * 4; e += G::TEAM) {
-      const int dl = e & 3, c = (e >> 2) % D, hh = e / (4 * D);
-      float val = 0.f;
-      if (dl < a.W && (OUTPUT || hh == GR)) {
-        const bf16_t* src = hh < GR ? a.wq + ((size_t)(hk * a.group + a.qh0 + hh) * D + c) * a.W + dl
-                                    : a.wk + ((size_t)hk * D + c) * a.W + dl;
-        val = __uint_as_float((uint32_t)(*src) << 16) * wscale;
+#pragma unroll
+    for (int j = 0; j < kWeights; ++j) {
+      const int e = tid + j * G::TEAM, c = e % D, hh = OUTPUT ? e / D : GR;
+      wraw[j] = make_uint2(0, 0);
+      if (e < kRows * D) {
+        const bf16_t* src = hh < GR ? a.wq + ((size_t)(hk * a.group + a.qh0 + hh) * D + c) * a.W
+                                    : a.wk + ((size_t)hk * D + c) * a.W;
+        if (a.W == 4) {
+          wraw[j] = *reinterpret_cast<const uint2*>(src);
+        } else {
+          wraw[j].x = src[0];
+          if (a.W > 1) wraw[j].x |= (uint32_t)src[1] << 16;
+          if (a.W > 2) wraw[j].y = src[2];
+        }
       }
-      wl[e] = val;
     }
   }
 
@@ -514,18 +525,23 @@ __global__ void __launch_bounds__(D * 4, D == 64 ? 2 : 1)
   // whole prefetch.)
   const unsigned lrow = (unsigned)n * G::QRS + (unsigned)g4 * 8;
 
+  // the output pass walks its segment forwards, the state pass backwards (see compute_state)
+  const int nseg_gran = (s1 - s0 + G::NTG - 1) / G::NTG;
+  const int tfirst = OUTPUT ? s0 : s0 + (nseg_gran - 1) * G::NTG;
+  const int tstep = OUTPUT ? G::NTG : -G::NTG;
+  Raw<KK::NQ> raw;
+  KK::fetch(raw, srcK, srcG, srcV, tfirst, tl0, coff, a.W);
   // ---- state in accumulators: Sacc[rt][ct][i] = S[16 rt + 4 g4 + i][16 tile(ct) + n]; ct == CT holds z replicated
   floatx4 Sacc[G::RT][G::NT];
   {
     const float* Sin = nullptr;
     const float* zin = nullptr;
     int first = seg;   // fold: first segment whose contribution is still to be added
-    if (OUTPUT && active) {
+    if (OUTPUT) {
       bool scanned = false;
       if (a.fold) {
         // after the last of the predecessors whose total decay is exactly zero nothing earlier counts
-        const bool shut = l < seg && a.seg_live[(size_t)bh * a.nseg + l] == 0;
-        const unsigned long long m = __builtin_amdgcn_ballot_w64(shut);
+        const unsigned long long m = __builtin_amdgcn_ballot_w64(live_any == 0);
         first = m ? 64 - __builtin_clzll(m) : 0;
       } else if (nseg > 1) {
         // team-wide OR through the per-wave flag words (free until the granule loop; the barrier that ends the
@@ -563,22 +579,56 @@ __global__ void __launch_bounds__(D * 4, D == 64 ? 2 : 1)
         }
       }
     }
+    if (CONV) {
+      const float wscale = MODE == kConvElu ? kLog2e : 1.f;
+  #pragma unroll
+      for (int j = 0; j < kWeights; ++j) {
+        const int e = tid + j * G::TEAM;
+        if (e < kRows * D)
+          *reinterpret_cast<floatx4*>(wl + ((size_t)(OUTPUT ? e : e + GR * D)) * 4) =
+              floatx4{bf_lo(wraw[j].x) * wscale, bf_hi(wraw[j].x) * wscale, bf_lo(wraw[j].y) * wscale, bf_hi(wraw[j].y) * wscale};
+      }
+    }
     if (OUTPUT && a.fold) {
-      // state <- decay (.) state + contribution, segment by segment (in the scan's order)
-#pragma unroll 1
-      for (int j = first; j < seg; ++j) {
+      // state <- decay (.) state + contribution, segment by segment (in the scan's order); at head dim 64 the next segment's
+      // slot travels meanwhile (at 128 there are no registers for it)
+      struct Slot { float s[G::RT][4]; floatx4 z[G::RT], dec[G::RT]; };
+      auto load_slot = [&](int j, Slot& o) {
         const float* slot = a.ws + ((size_t)bh * a.nseg + j) * G::kSlot;
 #pragma unroll
         for (int rt = 0; rt < G::RT; ++rt) {
           const int c = 16 * rt + 4 * g4;
-          const floatx4 dz = *reinterpret_cast<const floatx4*>(slot + D * D + c);
-          const floatx4 dec = *reinterpret_cast<const floatx4*>(slot + D * D + D + c);
+          o.z[rt] = *reinterpret_cast<const floatx4*>(slot + D * D + c);
+          o.dec[rt] = *reinterpret_cast<const floatx4*>(slot + D * D + D + c);
+#pragma unroll
+          for (int i = 0; i < 4; ++i) o.s[rt][i] = slot[(size_t)(c + i) * D + 16 * w + n];
+        }
+      };
+      auto add_slot = [&](const Slot& o) {
+#pragma unroll
+        for (int rt = 0; rt < G::RT; ++rt)
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
-            const float ds = slot[(size_t)(c + i) * D + 16 * w + n];
-            Sacc[rt][0][i] = fmaf(dec[i], Sacc[rt][0][i], ds);
-            Sacc[rt][G::CT][i] = fmaf(dec[i], Sacc[rt][G::CT][i], dz[i]);
+            Sacc[rt][0][i] = fmaf(o.dec[rt][i], Sacc[rt][0][i], o.s[rt][i]);
+            Sacc[rt][G::CT][i] = fmaf(o.dec[rt][i], Sacc[rt][G::CT][i], o.z[rt][i]);
           }
+      };
+      Slot x, y;
+      if constexpr (D == 64) {
+        if (first < seg) load_slot(first, x);
+#pragma unroll 1
+        for (int j = first; j < seg; j += 2) {
+          load_slot(min(j + 1, seg - 1), y);
+          add_slot(x);
+          if (j + 1 >= seg) break;
+          load_slot(min(j + 2, seg - 1), x);
+          add_slot(y);
+        }
+      } else {
+#pragma unroll 1
+        for (int j = first; j < seg; ++j) {
+          load_slot(j, x);
+          add_slot(x);
         }
       }
     }
@@ -586,12 +636,6 @@ __global__ void __launch_bounds__(D * 4, D == 64 ? 2 : 1)
   float rgran[2] = {1.f, 1.f};  // state pass: decay of everything after the current granule, this lane's 2 channels
 
   const bool gs1 = a.gate_scale == 1.0f;
-  Raw<KK::NQ> raw;
-  // the output pass walks its segment forwards, the state pass backwards (see compute_state)
-  const int nseg_gran = (s1 - s0 + G::NTG - 1) / G::NTG;
-  const int tfirst = OUTPUT ? s0 : s0 + (nseg_gran - 1) * G::NTG;
-  const int tstep = OUTPUT ? G::NTG : -G::NTG;
-  if (s0 < s1) KK::fetch(raw, srcK, srcG, srcV, tfirst, tl0, coff, a.W);
   __syncthreads();  // conv weights are in LDS
 
   // Per granule: compute stage, barrier, MFMA stage, barrier.
@@ -836,8 +880,7 @@ __global__ void __launch_bounds__(D * 4, D == 64 ? 2 : 1)
   float* Sdst = nullptr;
   float* zdst = nullptr;
   float* ddst = nullptr;
-  if (!active) {
-  } else if (!OUTPUT) {
+  if (!OUTPUT) {
     Sdst = a.ws + ((size_t)bh * a.nseg + seg) * G::kSlot;
     zdst = Sdst + D * D;
     ddst = zdst + D;
