@@ -76,7 +76,7 @@ inline Path prefill_path(const lawcat_desc* d) {
 }
 
 ChunkPlan plan_for(const lawcat_desc* d) {
-  return make_chunk_plan(d->B, d->T, d->Hkv, d->dk, d->carry_mode, d->segment);
+  return make_chunk_plan(d->B, d->T, d->Hq, d->Hkv, d->dk, d->carry_mode, d->segment);
 }
 
 size_t workspace_bytes_checked(const lawcat_desc* d, int which) {
@@ -115,7 +115,7 @@ ChunkPlan varlen_plan(const lawcat_desc* d, const int32_t* seq_start) {
   const long long total = seq_start[d->B];
   int longest = 1;
   for (int i = 0; i < d->B; ++i) longest = std::max(longest, (int)(seq_start[i + 1] - seq_start[i]));
-  ChunkPlan one = make_chunk_plan(1, (int)std::min<long long>(total, 0x7fffffc0LL), d->Hkv, d->dk, d->carry_mode, d->segment);
+  ChunkPlan one = make_chunk_plan(1, (int)std::min<long long>(total, 0x7fffffc0LL), d->Hq, d->Hkv, d->dk, d->carry_mode, d->segment);
   ChunkPlan p;
   const int whole = (longest + 63) / 64 * 64;
   p.seg_len = std::min(one.seg_len, whole);

@@ -10,7 +10,7 @@ hipError_t launch_d128(const ChunkArgs& a, int group, int mode, hipStream_t stre
 
 bool chunk_path_supports(int group) { return group >= 1 && group <= 64; }
 
-ChunkPlan make_chunk_plan(int B, int T, int Hkv, int d, int carry_mode, int segment) {
+ChunkPlan make_chunk_plan(int B, int T, int Hq, int Hkv, int d, int carry_mode, int segment) {
   ChunkPlan p;
   const int heads = B * Hkv;
   int seg_len;
@@ -19,15 +19,21 @@ ChunkPlan make_chunk_plan(int B, int T, int Hkv, int d, int carry_mode, int segm
   } else if (segment > 0) {
     seg_len = segment;
   } else {
-    // enough workgroups to fill 256 compute units once (two 4-wave teams per unit at head dim 64, one
-    // 8-wave team at 128).  Segments of two granules (128 tokens) at least, except where even those would leave
+    // enough workgroups (of up to four query heads each) to fill 256 compute units once (two 4-wave teams per unit at head dim
+    // 64, one 8-wave team at 128).  Segments of two granules (128 tokens) at least, except where even those would leave
     // more than half of the chip without a workgroup: short sequences are bound by the serial work of one
     // workgroup, and one-granule segments halve it (T = 1K .. 2K: 31 -> 23 us at head dim 64, 51 -> 41 at 128)
     const int slots = d == 64 ? 512 : 256;
-    const int want = (slots + heads - 1) / heads;
+    const long long groups = (long long)heads * std::max(1, Hq / Hkv / 4);   // workgroups per segment
+    const int want = (int)((slots + groups - 1) / groups);
     seg_len = (T + want - 1) / want;
     seg_len = (seg_len + 63) / 64 * 64;
-    if (seg_len < 128) seg_len = (long long)((T + 127) / 128) * heads * 2 <= slots ? 64 : 128;
+    if (seg_len < 128) {
+      // (not where segments of 128 leave few contributions per head, which the output pass folds, and keep half of the compute
+      // units busy: one granule / two, 4 x 1000 tokens, 32 query heads on 8 of 64, 36 / 34 us, 4 x 500, of 128, 47 / 43)
+      const int n = (T + 127) / 128;
+      seg_len = n * groups * 2 <= slots && (n > 8 || n * heads <= (d == 64 ? 160 : 112)) ? 64 : 128;
+    }
   }
   p.seg_len = seg_len;
   p.nseg = (T + seg_len - 1) / seg_len;
@@ -48,15 +54,23 @@ hipError_t launch_gla_chunk(const ChunkParams& p, hipStream_t stream) {
   a.seg_live = reinterpret_cast<int*>(a.ws + (size_t)p.B * p.Hkv * p.plan.nseg * (p.d * p.d + 2 * p.d));
   a.B = p.B; a.T = p.T; a.Hq = p.Hq; a.Hkv = p.Hkv; a.W = p.W;
   a.seg_len = p.plan.seg_len; a.nseg = p.plan.nseg;
-  // With few segments the output pass folds its predecessors' contributions itself instead of waiting for a scan: a launch less,
-  // and, with many heads, less traffic, against a walk over the predecessors' slots in each of the output pass's launches (one per
-  // four query heads of a group).  Scan / fold, us a call, at 2, 4 and 9 segments: 8 heads of 64, one launch 20.6 / 17.4, 21.1 / 18.9,
-  // 22.1 / 22.6, two 32.6 / 29.7, 32.9 / 32.0, 34.2 / 38.4, four 56.4 / 54.3, 56.7 / 58.4, 58.2 / 69.9; 64 heads, one 30.5 / 18.3, 36.0 /
-  // 22.7, 48.2 / 34.4, eight 125 / 116, 135 / 135, 235 / 226; 8 heads of 128, one 28.4 / 25.8, 29.4 / 30.0, 32.7 / 42.1, two 45.7 / 44.3,
-  // 47.0 / 51.8, 50.9 / 74.3.
+  // A workgroup of the output pass takes four query heads of a group, or two or one where that still gives no more workgroups than
+  // compute units: each is a serial walk, and those for two heads or one are shorter, at the price of forming the keys' side again.
+  // us a call with four / two / one, 8 kv heads: of 64, 32 query heads, 64 tokens 13.7 / 11.9 / 10.7, 517 20.4 / 19.1 / -; 1500, where
+  // two would be 384 workgroups, 21.8 / 22.6 / 27 (on 4 kv heads); of 128, 64 tokens 19.2 / 16.6 / 14.2, 1000 36.6 / 33.9 / 41.9 (512).
+  // (Not in place: a workgroup would read a start state that another one replaces.)
   const int nseg = p.plan.nseg, heads = p.B * p.Hkv, group = p.Hq / p.Hkv;
-  const int passes = group / 4 + (group % 4 + 1) / 2;
-  a.fold = nseg > 1 && nseg <= 9 && 5 * nseg * passes * (p.d / 64) <= 30 + 2 * heads;
+  const long long walks = (long long)nseg * heads;
+  a.most = 4;
+  if (!(p.S0 == p.S_out || p.z0 == p.z_out)) a.most = walks * group <= 256 ? 1 : walks * ((group + 1) / 2) <= 256 ? 2 : 4;
+  // With few segments the output pass folds its predecessors' contributions itself instead of waiting for a scan: a launch less,
+  // and, with many heads, less traffic, against a walk over the predecessors' slots in each of the output pass's launches (more than
+  // one for groups that are no multiple of 4).  Scan / fold, us a call, query heads on kv heads x sequences: of 64, 32 on 4 8 segments
+  // 19.2 / 18.7, 10 20.6 / 21.2; 32 on 8 3 segments 18.0 / 14.9, 8 20.5 / 19.5, 10 21.6 / 21.9; x 4 4 segments 26.4 / 20.3, 10
+  // 35.2 / 32.0, 12 44.6 / 41.3, 16 36.1 / 38.2; x 16 8 segments 76 / 59.  Of 128, 8 heads, 3 segments 23.6 / 22.1, 4 26.2 / 27.5; x 4
+  // 4 segments 40.1 / 33.6, 8 46.6 / 46.5; 32 on 4 x 16 4 segments 74 / 64, 8 121 / 149.
+  const int passes = group % 4 == 0 || a.most == 1 ? 1 : group / 4 + (group % 4 + 1) / 2;
+  a.fold = nseg > 1 && nseg * passes <= (p.d == 64 ? std::min(12, 8 + heads / 8) : std::min(7, 3 + heads / 16));
   a.gate_scale = p.gate_scale; a.eps = p.eps;
   const int mode = !p.fuse_conv ? chunk::kPlain : (p.phi == 1 ? chunk::kConvElu : chunk::kConvId);
   const chunk::TraceEvents ev{p.ev_start, p.ev_stop};

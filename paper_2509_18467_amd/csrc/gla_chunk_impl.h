@@ -75,7 +75,8 @@ struct ChunkArgs {
   const int* seq_start;
   int B, T, Hq, Hkv, W;
   int group;   // query heads per kv head (Hq / Hkv)
-  int qh0;     // first query head, within its group, that this launch of the output pass covers
+  int qh0;     // first query head, within its group, that this launch of the output pass covers (its z index: GR heads each)
+  int most;    // most query heads that a workgroup of the output pass takes: 4, 2 or 1
   int seg_len, nseg;
   int fold;    // few segments: the output pass folds its predecessors' contributions itself, there is no scan
   float gate_scale, eps;
@@ -450,6 +451,8 @@ __global__ void __launch_bounds__(D * 4, D == 64 ? 2 : 1)
   const int seg = blockIdx.x;
   const int bh = blockIdx.y;
   const int b = bh / a.Hkv, hk = bh % a.Hkv;
+  const int qh0 = OUTPUT ? a.qh0 + (int)blockIdx.z * GR : 0;   // first query head, within its group, of this workgroup
+  const bool keeps = qh0 == 0;   // of the workgroups of a group: the one that stores the final state and the keys' cache
   // this sequence: first row in the packed tensors, length, segments (token indices below are relative to row0)
   size_t row0 = (size_t)b * a.T;
   int T = a.T, nseg = a.nseg;
@@ -494,7 +497,7 @@ __global__ void __launch_bounds__(D * 4, D == 64 ? 2 : 1)
       const int e = tid + j * G::TEAM, c = e % D, hh = OUTPUT ? e / D : GR;
       wraw[j] = make_uint2(0, 0);
       if (e < kRows * D) {
-        const bf16_t* src = hh < GR ? a.wq + ((size_t)(hk * a.group + a.qh0 + hh) * D + c) * a.W
+        const bf16_t* src = hh < GR ? a.wq + ((size_t)(hk * a.group + qh0 + hh) * D + c) * a.W
                                     : a.wk + ((size_t)hk * D + c) * a.W;
         if (a.W == 4) {
           wraw[j] = *reinterpret_cast<const uint2*>(src);
@@ -515,8 +518,8 @@ __global__ void __launch_bounds__(D * 4, D == 64 ? 2 : 1)
   const RowSrc srcG = make_row_src((const char*)a.g + (row0 * a.Hkv + hk) * D * 2, nullptr, kvstride, T, D * 2);
   const RowSrc srcV = make_row_src((const char*)a.v + (row0 * a.Hkv + hk) * D * 2, nullptr, kvstride, T, D * 2);
   const RowSrc srcQ = make_row_src(
-      (const char*)a.q + (row0 * a.Hq + hk * a.group + a.qh0) * D * 2,
-      (CONV && a.q_halo) ? (const char*)a.q_halo + ((size_t)b * (a.W - 1) * a.Hq + hk * a.group + a.qh0) * D * 2 : nullptr, qstride, T,
+      (const char*)a.q + (row0 * a.Hq + hk * a.group + qh0) * D * 2,
+      (CONV && a.q_halo) ? (const char*)a.q_halo + ((size_t)b * (a.W - 1) * a.Hq + hk * a.group + qh0) * D * 2 : nullptr, qstride, T,
       (GR > 0 ? GR : 1) * D * 2);
   const unsigned coff = (unsigned)c0 * 2;
   // This lane's part of the LDS address of a token-major row, formed once so that the chunk loop only adds a
@@ -813,7 +816,7 @@ __global__ void __launch_bounds__(D * 4, D == 64 ? 2 : 1)
               const int tok = tq + n;
               const float rden = fast_rcp(o.den);
               if (tok < s1) {
-                bf16_t* orow = a.o + ((row0 + tok) * a.Hq + hk * a.group + a.qh0 + hh) * D;
+                bf16_t* orow = a.o + ((row0 + tok) * a.Hq + hk * a.group + qh0 + hh) * D;
 #pragma unroll
                 for (int ct = 0; ct < G::CT; ++ct) {
                   const uint2 pk = make_uint2(pack2(oacc[ct][0] * rden, oacc[ct][1] * rden),
@@ -821,7 +824,7 @@ __global__ void __launch_bounds__(D * 4, D == 64 ? 2 : 1)
                   *reinterpret_cast<uint2*>(orow + 16 * (w * G::CT + ct) + 4 * g4) = pk;
                 }
                 if (a.den_out != nullptr && w == 0 && g4 == 0)
-                  a.den_out[(row0 + tok) * a.Hq + hk * a.group + a.qh0 + hh] = o.den;
+                  a.den_out[(row0 + tok) * a.Hq + hk * a.group + qh0 + hh] = o.den;
               }
             };
             HeadOps opA, opB;
@@ -884,7 +887,7 @@ __global__ void __launch_bounds__(D * 4, D == 64 ? 2 : 1)
     Sdst = a.ws + ((size_t)bh * a.nseg + seg) * G::kSlot;
     zdst = Sdst + D * D;
     ddst = zdst + D;
-  } else if (seg == nseg - 1) {
+  } else if (seg == nseg - 1 && keeps) {
     Sdst = a.S_out + (size_t)bh * D * D;
     zdst = a.z_out + (size_t)bh * D;
   }
@@ -905,12 +908,12 @@ __global__ void __launch_bounds__(D * 4, D == 64 ? 2 : 1)
   // ---- conv cache out: the last W-1 raw rows of [halo ; x] for this workgroup's heads
   if (OUTPUT && CONV && seg == nseg - 1 && a.W > 1) {
     const int Wm = a.W - 1;
-    for (int e = tid; e < (GR + 1) * Wm * D; e += G::TEAM) {
+    for (int e = tid; e < (GR + (keeps ? 1 : 0)) * Wm * D; e += G::TEAM) {
       const int c = e % D, r = (e / D) % Wm, hh = e / (D * Wm);
       const bool isq = hh < GR;
       bf16_t* dst = isq ? a.q_tail : a.k_tail;
       if (dst == nullptr) continue;
-      const int H = isq ? a.Hq : a.Hkv, head = isq ? hk * a.group + a.qh0 + hh : hk;
+      const int H = isq ? a.Hq : a.Hkv, head = isq ? hk * a.group + qh0 + hh : hk;
       const bf16_t* x = isq ? a.q : a.k;
       const bf16_t* halo = isq ? a.q_halo : a.k_halo;
       const int src = T - Wm + r;
@@ -923,7 +926,7 @@ __global__ void __launch_bounds__(D * 4, D == 64 ? 2 : 1)
 }
 
 template <int D, int GR, int MODE>
-hipError_t launch_all(const ChunkArgs& a, hipStream_t stream, bool with_state_pass, const TraceEvents& ev) {
+hipError_t launch_all(const ChunkArgs& a, int parts, hipStream_t stream, bool with_state_pass, const TraceEvents& ev) {
   using G = Geo<D, GR>;
   const int heads = a.B * a.Hkv;
   hipError_t e;
@@ -948,30 +951,29 @@ hipError_t launch_all(const ChunkArgs& a, hipStream_t stream, bool with_state_pa
   if (e != hipSuccess) return e;
   // measurement entry point: the two events take the kernel's own start and stop timestamps (no dispatch gaps)
   if (ev.start != nullptr && ev.stop != nullptr)
-    hipExtLaunchKernelGGL(k3, dim3(a.nseg, heads), dim3(G::TEAM), G::kBytes, stream, ev.start, ev.stop, 0, a);
+    hipExtLaunchKernelGGL(k3, dim3(a.nseg, heads, parts), dim3(G::TEAM), G::kBytes, stream, ev.start, ev.stop, 0, a);
   else
-    hipLaunchKernelGGL(k3, dim3(a.nseg, heads), dim3(G::TEAM), G::kBytes, stream, a);
+    hipLaunchKernelGGL(k3, dim3(a.nseg, heads, parts), dim3(G::TEAM), G::kBytes, stream, a);
   return hipGetLastError();
 }
 
-// A group of any size is covered by output-pass launches over 4, 2 or 1 of its query heads at a time; they
-// share one state pass and one scan (the key side does not depend on the query heads), and each writes the
-// same final state.
+// A group of any size is covered by output-pass launches whose workgroups take 4, 2 or 1 of its query heads each; they
+// share one state pass and one scan (the key side does not depend on the query heads).
 template <int D>
 hipError_t launch_d(const ChunkArgs& a0, int group, int mode, hipStream_t stream, const TraceEvents& ev0) {
   ChunkArgs a = a0;
   a.group = group;
   bool first = true;
   for (int qh0 = 0; qh0 < group;) {
-    const int left = group - qh0, gr = left >= 4 ? 4 : (left >= 2 ? 2 : 1);
+    const int left = group - qh0, gr = left >= a.most ? a.most : (left >= 2 ? 2 : 1), parts = left / gr;
     a.qh0 = qh0;
     const TraceEvents ev = first ? ev0 : TraceEvents{nullptr, nullptr};
     hipError_t e;
 #define LAWCAT_CASE(GRV)                                                                      \
   case GRV:                                                                                   \
-    e = mode == kPlain    ? launch_all<D, GRV, kPlain>(a, stream, first, ev)                  \
-        : mode == kConvId ? launch_all<D, GRV, kConvId>(a, stream, first, ev)                 \
-                          : launch_all<D, GRV, kConvElu>(a, stream, first, ev);               \
+    e = mode == kPlain    ? launch_all<D, GRV, kPlain>(a, parts, stream, first, ev)           \
+        : mode == kConvId ? launch_all<D, GRV, kConvId>(a, parts, stream, first, ev)          \
+                          : launch_all<D, GRV, kConvElu>(a, parts, stream, first, ev);        \
     break;
     switch (gr) {
       LAWCAT_CASE(1)
@@ -982,7 +984,7 @@ hipError_t launch_d(const ChunkArgs& a0, int group, int mode, hipStream_t stream
 #undef LAWCAT_CASE
     if (e != hipSuccess) return e;
     first = false;
-    qh0 += gr;
+    qh0 += gr * parts;
   }
   return hipSuccess;
 }

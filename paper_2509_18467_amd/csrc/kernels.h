@@ -95,7 +95,7 @@ struct ChunkPlan {
   int nseg;
   size_t workspace_bytes;
 };
-ChunkPlan make_chunk_plan(int B, int T, int Hkv, int d, int carry_mode, int segment);
+ChunkPlan make_chunk_plan(int B, int T, int Hq, int Hkv, int d, int carry_mode, int segment);
 bool chunk_path_supports(int group);  // query heads per kv head the kernel is built for
 
 struct ChunkParams {
