@@ -476,10 +476,14 @@ int lawcat_layer_prefill_fm(const lawcat_desc* desc, const void* Q, const void* 
   char* inner = static_cast<char*>(kd) + align_up(rows * desc->Hkv * desc->dk * elem_bytes(desc), 256);
   const size_t inner_bytes = workspace_bytes - (size_t)(inner - ws);
   // queries: each head with the matrix of the kv head whose state it reads
-  st = lawcat_conv1d_feature(desc, desc->Hq, Q, wq, wf, q_halo, qd, q_tail_out, stream);
-  if (st != LAWCAT_OK) return st;
-  st = lawcat_conv1d_feature(desc, desc->Hkv, K, wk, wf, k_halo, kd, k_tail_out, stream);
-  if (st != LAWCAT_OK) return st;
+  ConvParams c{};
+  c.B = desc->B; c.T = desc->T; c.d = desc->dk; c.W = desc->conv_width;
+  c.phi = desc->feature_map; c.bf16 = desc->dtype == LAWCAT_DTYPE_BF16;
+  const bool cached = desc->conv_width > 1;
+  ConvParams cq = c, ck = c;
+  cq.x = Q; cq.w = wq; cq.halo = cached ? q_halo : nullptr; cq.y = qd; cq.tail_out = cached ? q_tail_out : nullptr; cq.H = desc->Hq;
+  ck.x = K; ck.w = wk; ck.halo = cached ? k_halo : nullptr; ck.y = kd; ck.tail_out = cached ? k_tail_out : nullptr; ck.H = desc->Hkv;
+  if (launch_conv_feature_pair(cq, ck, wf, static_cast<hipStream_t>(stream)) != hipSuccess) return LAWCAT_E_HIP;
   // the attention on the transformed q-dot, k-dot
   return lawcat_gla_prefill(desc, qd, kd, V, gate_logits, S0, z0, O, den_out, S_out, z_out, inner, inner_bytes, stream);
 }

@@ -11,9 +11,7 @@
 // per workgroup, which walks a run of tiles.  5003 tokens, 32 / 8 heads of 128: 24.7 / 9.6 us with the rows kept for a
 // continuation (3.3 and 2.1 TB/s); 32.9 / 18.0 when the matrix was transposed into LDS two bytes at a time, the taps were
 // read one by one and a second launch copied those rows.
-#include <mutex>
-
-#include "kernels.h"
+#include "segment_scan.h"
 
 namespace lawcat {
 namespace {
@@ -116,12 +114,19 @@ __device__ inline void conv_tile(const T* __restrict__ x, const T* __restrict__ 
 //   store : the wave reads its 16 finished rows back 16 bytes per lane and stores whole 128/256-byte rows
 //           (buffer stores: rows past the last token are dropped)
 // WT: the conv width when it is the paper's 4 (no per-tap branches), 0 = any width up to 4, read from W.
+struct FeatureArgs {
+  const bf16_t *x, *w, *halo, *wf;
+  bf16_t *y, *tail;
+  int Tn, H, group, W, tiles_per_block;
+  int runs;                                  // workgroups per (batch, head group)
+};
 template <int D, int GH, int TT, bool ELU, int WT>
-__global__ void __launch_bounds__(256) conv_feature_mfma_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ w,
-                                                                const bf16_t* __restrict__ halo,
-                                                                const bf16_t* __restrict__ wf, bf16_t* __restrict__ y,
-                                                                bf16_t* __restrict__ tail, int Tn, int H, int group, int Wrt, int tiles_per_block) {
-  const int W = WT != 0 ? WT : Wrt;
+__device__ __forceinline__ void feature_tiles(const FeatureArgs& a, int block, unsigned char* smem) {
+  const bf16_t *__restrict__ x = a.x, *__restrict__ w = a.w, *__restrict__ halo = a.halo, *__restrict__ wf = a.wf;
+  bf16_t *__restrict__ y = a.y, *__restrict__ tail = a.tail;
+  const int Tn = a.Tn, H = a.H, group = a.group, tiles_per_block = a.tiles_per_block;
+  const int bx = block % a.runs, by = block / a.runs;
+  const int W = WT != 0 ? WT : a.W;
   constexpr int RS = D * 2 + 16;              // LDS row stride in bytes (16-byte reads of 16 rows hit distinct banks)
   constexpr int KS = D / 32, FT = D / 16;
   constexpr int ROWS = TT * GH;
@@ -130,11 +135,10 @@ __global__ void __launch_bounds__(256) conv_feature_mfma_kernel(const bf16_t* __
   constexpr int NTOK = ROWS * VPH / 256;      // tokens per thread
   constexpr int kRsrcFlags = 0x00020000;      // raw buffer, 32-bit data format of gfx9-family descriptors
   static_assert(ROWS * VPH == 256 * NTOK && 256 % VECS == 0, "tile must give every thread NTOK tokens of one vector");
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   unsigned char* wts = smem;                  // Wf: [c][f] bf16
   unsigned char* xs = smem + D * RS;          // the tile: [row][c] bf16
   const int hgroups = H / GH;
-  const int b = blockIdx.y / hgroups, h0 = (blockIdx.y % hgroups) * GH;
+  const int b = by / hgroups, h0 = (by % hgroups) * GH;
   const int tid = threadIdx.x, l = tid & 63, wv = tid >> 6;
   const int n = l & 15, g = l >> 4;
   const int v = tid % VECS, run = tid / VECS;
@@ -143,7 +147,7 @@ __global__ void __launch_bounds__(256) conv_feature_mfma_kernel(const bf16_t* __
   const unsigned coff = (unsigned)((h0 + hh) * D + c0) * 2;    // this thread's columns, in bytes
 
   const int ntiles = (Tn + TT - 1) / TT;
-  const int tile0 = blockIdx.x * tiles_per_block;
+  const int tile0 = bx * tiles_per_block;
   const int tile_end = min(ntiles, tile0 + tiles_per_block);
   // this workgroup's tokens [first, last) and the three rows before them; the host has checked that the range
   // stays far below 2^32 bytes, so that the wrapped offsets of rows -3 .. -1 fall outside the descriptor
@@ -274,6 +278,15 @@ __global__ void __launch_bounds__(256) conv_feature_mfma_kernel(const bf16_t* __
   }
 }
 
+// grid: the workgroups of one tensor, or of the queries and then of the keys (two shapes of tile, one launch: the keys' few bytes
+// travel beside the queries').  The whole layer, 5003 tokens, 32 / 8 heads of 128, gates included: 112.6 -> 106.2 us, 500 tokens 55.2 -> 47.5.
+template <int D, int GH, int TT, int GH2, int TT2, bool ELU, int WT>
+__global__ void __launch_bounds__(256) conv_feature_mfma_kernel(const FeatureArgs a, const FeatureArgs a2, int first) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  if ((int)blockIdx.x < first) feature_tiles<D, GH, TT, ELU, WT>(a, blockIdx.x, smem);
+  else if constexpr (GH2 > 0) feature_tiles<D, GH2, TT2, ELU, WT>(a2, blockIdx.x - first, smem);
+}
+
 // fp32 storage, plain FMAs.  Same grid.
 template <int D>
 __global__ void __launch_bounds__(256) conv_feature_f32_kernel(const float* __restrict__ x, const float* __restrict__ w,
@@ -308,52 +321,59 @@ namespace {
 
 constexpr int kComputeUnits = 256;   // MI355X
 
+constexpr int feature_lds(int d, int rows) { return (d + rows) * (d * 2 + 16); }
+// workgroups per compute unit (LDS, registers)
+constexpr int resident(int lds) { return (160 * 1024 / lds) < 3 ? (160 * 1024 / lds) : 3; }
+
+// Tiles of one tensor: `places` workgroups for all of its (batch, head group) pairs, each walking a contiguous run of tiles (the
+// matrix goes into LDS once per workgroup).
 template <int D, int GH, int TT>
-hipError_t launch_mfma(const ConvParams& p, const void* wf, int group, hipStream_t stream) {
-  constexpr int RS = D * 2 + 16;
-  constexpr int lds = (D + TT * GH) * RS;
-  constexpr int kResident = (160 * 1024 / lds) < 3 ? (160 * 1024 / lds) : 3;   // workgroups per compute unit (LDS, registers)
-  if (lds > 64 * 1024) {
-    // above the default limit: raise it once per device, for both instances
-    constexpr int kMaxDev = 64;
-    static std::once_flag once[kMaxDev];
-    static hipError_t status[kMaxDev];
-    int dev = 0;
-    hipError_t e = hipGetDevice(&dev);
-    if (e != hipSuccess) return e;
-    auto set = [&] {
-      const void* instances[4] = {reinterpret_cast<const void*>(conv_feature_mfma_kernel<D, GH, TT, true, 4>),
-                                  reinterpret_cast<const void*>(conv_feature_mfma_kernel<D, GH, TT, false, 4>),
-                                  reinterpret_cast<const void*>(conv_feature_mfma_kernel<D, GH, TT, true, 0>),
-                                  reinterpret_cast<const void*>(conv_feature_mfma_kernel<D, GH, TT, false, 0>)};
-      for (const void* k : instances) {
-        hipError_t r = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-        if (r != hipSuccess) return r;
-      }
-      return hipSuccess;
-    };
-    if (dev < 0 || dev >= kMaxDev) {
-      e = set();
-    } else {
-      std::call_once(once[dev], [&] { status[dev] = set(); });
-      e = status[dev];
-    }
-    if (e != hipSuccess) return e;
-  }
+bool feature_args(const ConvParams& p, const void* wf, int group, int places, FeatureArgs& a, int& blocks) {
   const int ntiles = (p.T + TT - 1) / TT;
-  const int nbh = p.B * (p.H / GH);
-  // one round of workgroups: as many per (batch, head group) as the chip holds at once, each walking a
-  // contiguous run of tiles (the matrix goes into LDS once per workgroup)
-  const int per_bh = kComputeUnits * kResident / nbh > 0 ? kComputeUnits * kResident / nbh : 1;
-  const int tpb = (ntiles + per_bh - 1) / per_bh;
+  const long long nbh = (long long)p.B * (p.H / GH);
+  const long long per_bh = places / nbh > 0 ? places / nbh : 1;
+  const int tpb = (int)((ntiles + per_bh - 1) / per_bh);
   // a workgroup addresses its own token range with 32-bit byte offsets
-  if (((unsigned long long)tpb * TT + 16) * p.H * D * 2 >= (1ull << 31) || nbh > 65535) return hipErrorInvalidValue;
-  const dim3 grid((ntiles + tpb - 1) / tpb, nbh);
-  auto kernel = p.W == 4 ? (p.phi == 1 ? conv_feature_mfma_kernel<D, GH, TT, true, 4> : conv_feature_mfma_kernel<D, GH, TT, false, 4>)
-                         : (p.phi == 1 ? conv_feature_mfma_kernel<D, GH, TT, true, 0> : conv_feature_mfma_kernel<D, GH, TT, false, 0>);
-  hipLaunchKernelGGL(kernel, grid, dim3(256), lds, stream, (const bf16_t*)p.x, (const bf16_t*)p.w, (const bf16_t*)p.halo,
-                     (const bf16_t*)wf, (bf16_t*)p.y, p.W > 1 ? (bf16_t*)p.tail_out : nullptr, p.T, p.H, group, p.W, tpb);
-  return hipGetLastError();
+  if (((unsigned long long)tpb * TT + 16) * p.H * D * 2 >= (1ull << 31) || nbh > 65535) return false;
+  a.x = (const bf16_t*)p.x; a.w = (const bf16_t*)p.w; a.halo = (const bf16_t*)p.halo; a.wf = (const bf16_t*)wf;
+  a.y = (bf16_t*)p.y; a.tail = p.W > 1 ? (bf16_t*)p.tail_out : nullptr;
+  a.Tn = p.T; a.H = p.H; a.group = group; a.W = p.W; a.tiles_per_block = tpb;
+  a.runs = (ntiles + tpb - 1) / tpb;
+  if ((unsigned long long)a.runs * nbh >= (1ull << 30)) return false;
+  blocks = (int)(a.runs * nbh);
+  return true;
+}
+
+// One tensor (k null), or queries and keys in one launch (GH2 > 0).
+template <int D, int GH, int TT, int GH2, int TT2>
+hipError_t launch_mfma(const ConvParams& p, const ConvParams* k, const void* wf, int group, hipStream_t stream) {
+  constexpr int rows = TT * GH > TT2 * GH2 ? TT * GH : TT2 * GH2, lds = feature_lds(D, rows);
+  constexpr int kPlaces = kComputeUnits * resident(lds);      // one round of workgroups
+  FeatureArgs a, a2{};
+  int first, second = 0;
+  // the two tensors' workgroups in proportion to their elements
+  const int mine = k ? (int)((long long)kPlaces * p.H / (p.H + k->H)) : kPlaces;
+  if (!feature_args<D, GH, TT>(p, wf, group, mine, a, first)) return hipErrorInvalidValue;
+  if constexpr (GH2 > 0)
+    if (!feature_args<D, GH2, TT2>(*k, wf, 1, kPlaces - mine, a2, second)) return hipErrorInvalidValue;
+  auto launch = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(first + second), dim3(256), lds, stream, a, a2, first);
+    return hipGetLastError();
+  };
+#define LAWCAT_KERNEL(ELU, WT) conv_feature_mfma_kernel<D, GH, TT, GH2, TT2, ELU, WT>
+#define LAWCAT_LAUNCH(ELU, WT)                                       \
+  {                                                                  \
+    const hipError_t e = set_lds<LAWCAT_KERNEL(ELU, WT)>(lds);       \
+    return e != hipSuccess ? e : launch(LAWCAT_KERNEL(ELU, WT));     \
+  }
+  if (p.W == 4) {
+    if (p.phi == 1) LAWCAT_LAUNCH(true, 4)
+    LAWCAT_LAUNCH(false, 4)
+  }
+  if (p.phi == 1) LAWCAT_LAUNCH(true, 0)
+  LAWCAT_LAUNCH(false, 0)
+#undef LAWCAT_LAUNCH
+#undef LAWCAT_KERNEL
 }
 
 }  // namespace
@@ -365,8 +385,8 @@ hipError_t launch_conv_feature(const ConvParams& p, const void* wf, int group, h
     // rows per tile: 256 (four heads) or 128 at d = 64; at d = 128 the matrix takes 34 KB of LDS, and 64-row tiles leave three
     // workgroups per compute unit instead of two.  Single heads, 5003 tokens, tiles twice as long and as taken: 7.4 / 6.3 us
     // at d = 64, 11.1 / 9.8 at 128
-    if (p.d == 64) return four ? launch_mfma<64, 4, 64>(p, wf, group, stream) : launch_mfma<64, 1, 128>(p, wf, group, stream);
-    return four ? launch_mfma<128, 4, 16>(p, wf, group, stream) : launch_mfma<128, 1, 64>(p, wf, group, stream);
+    if (p.d == 64) return four ? launch_mfma<64, 4, 64, 0, 0>(p, nullptr, wf, group, stream) : launch_mfma<64, 1, 128, 0, 0>(p, nullptr, wf, group, stream);
+    return four ? launch_mfma<128, 4, 16, 0, 0>(p, nullptr, wf, group, stream) : launch_mfma<128, 1, 64, 0, 0>(p, nullptr, wf, group, stream);
   }
   const dim3 grid((p.T + kTile * kTilesPerBlock - 1) / (kTile * kTilesPerBlock), p.B * p.H);
   if (p.d == 64) {
@@ -380,6 +400,17 @@ hipError_t launch_conv_feature(const ConvParams& p, const void* wf, int group, h
   }
   const hipError_t e = hipGetLastError();
   return e != hipSuccess ? e : launch_conv_tail(p, stream);
+}
+
+hipError_t launch_conv_feature_pair(const ConvParams& q, const ConvParams& k, const void* wf, hipStream_t stream) {
+  const int group = q.H / k.H;
+  if (q.bf16) {
+    const bool four = group % 4 == 0;
+    if (q.d == 64) return four ? launch_mfma<64, 4, 64, 1, 128>(q, &k, wf, group, stream) : launch_mfma<64, 1, 128, 1, 128>(q, &k, wf, group, stream);
+    return four ? launch_mfma<128, 4, 16, 1, 64>(q, &k, wf, group, stream) : launch_mfma<128, 1, 64, 1, 64>(q, &k, wf, group, stream);
+  }
+  const hipError_t e = launch_conv_feature(q, wf, group, stream);
+  return e != hipSuccess ? e : launch_conv_feature(k, wf, 1, stream);
 }
 
 }  // namespace lawcat

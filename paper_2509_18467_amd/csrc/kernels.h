@@ -65,6 +65,8 @@ struct GateProjectParams {
 hipError_t launch_gate_project(const GateProjectParams& p, hipStream_t stream);
 
 hipError_t launch_conv_feature(const ConvParams& p, const void* wf, int group, hipStream_t stream);
+// The same for the queries and the keys of one layer (of equal B, T, d, W): one launch where the storage is bf16.
+hipError_t launch_conv_feature_pair(const ConvParams& q, const ConvParams& k, const void* wf, hipStream_t stream);
 
 struct RecurrentParams {
   const void* q;  // [B,T,Hq,d]  (q-dot)
