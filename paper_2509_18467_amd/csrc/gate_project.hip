@@ -5,8 +5,8 @@
 // (26 flop/B at dm = 2048, N = 512), so the matrix cores are used for what they are, a dense contraction, and
 // the kernel is laid out around the reads of x.
 //   bf16 storage, rank 32: both products transposed so that no operand is ever shuffled,
-//     H^T = W1 x^T   (A = 16 rows of w1, read from L2 in fragment layout; B = 16 tokens of x, read from HBM as whole
-//                     row pieces and turned into fragment layout through the wave's own LDS rows),
+//     H^T = W1 x^T   (A = 16 rows of w1, B = 16 tokens of x, both read as whole row pieces and turned into fragment layout
+//                     through the wave's own LDS rows),
 //     G^T = W2 H^T   (the two accumulator tiles of H^T, rounded to bf16, ARE the B operand: k slot s < 4 is
 //                     rank 4g + s, slot s >= 4 rank 16 + 4g + s - 4; w2 rows are read with the same permutation),
 //     a lane then holds 4 adjacent channels of one token; they pass through the wave's own LDS rows and leave
@@ -25,7 +25,7 @@ typedef unsigned int u32x4 __attribute__((vector_size(16)));
 
 constexpr int kRsrcFlags = 0x00020000;  // raw buffer, 32-bit data format of gfx9-family descriptors
 constexpr int kRank = 32;               // what the matrix-core kernel is built for
-constexpr int kSlab = 128;              // channels of x per step of the first product
+constexpr int kSlab = 64;               // channels of x per step of the first product
 constexpr int kGroupCh = 128;           // output channels staged per store round
 
 __device__ inline uint32_t pack2(float a, float b) {
@@ -38,20 +38,24 @@ __device__ inline float bf_hi(uint32_t u) { return __uint_as_float(u & 0xffff000
 // grid (ceil(rows / (16 TT))), kWaves waves; rows = B * T tokens.  A workgroup owns 16 TT tokens (TT tiles of 16): its
 // waves split the channels of x for the first product (slab w, w + kWaves, ...), add their partial H^T
 // through LDS, and split the output channels for the second (group w, w + kWaves, ...): short dependent
-// chains and many waves per compute unit, which is what a streaming kernel needs to keep HBM busy.  With TT = 2
-// every fragment of w1 (which comes from L2, 8 KB per slab) serves two MFMAs: half the L2 traffic per token,
-// which measured 20 % of the kernel's time; TT = 1 where there are too few tokens to fill the chip otherwise.
-template <int TT, int kWaves>
+// chains and many waves per compute unit, which is what a streaming kernel needs to keep HBM busy.
+// What bounds it: w1 (256 KB at d_model 4096), which every workgroup reads from L2, twice as much as 16 tokens of x.  With w1 in
+// fragment layout straight from L2 (16 rows, one cache line each, per 16 lanes) 5003 tokens at d_model 4096 took 24.2 us, in whole
+// row pieces 18.6 for 16 tokens a workgroup and 16.5 for 32; without w2 on its way before the sums meet 1 more.  How many slabs are
+// on their way (1 to 4) makes no difference up to 10K tokens; two are 4 % better at 32K.
+template <int TT, int kWaves, int kDepth>
 __global__ void __launch_bounds__(64 * kWaves) gate_project_mfma_kernel(const bf16_t* __restrict__ x,
                                                                         const bf16_t* __restrict__ w1,
                                                                         const bf16_t* __restrict__ w2,
                                                                         const bf16_t* __restrict__ bias,
                                                                         bf16_t* __restrict__ g, long long rows, int dm, int N) {
-  constexpr int RS = kGroupCh * 2 + 16;   // LDS row stride (a 256-byte row piece plus padding), bytes
   constexpr int NR = 16 * TT;             // tokens of the workgroup
-  __shared__ __attribute__((aligned(16))) unsigned char stage[kWaves * NR * RS];
+  constexpr int SS = kSlab * 2 + 16;      // LDS row stride of a slab's rows of x and of w1, bytes
+  constexpr int RS = kGroupCh * 2 + 16;   // of staged logits (a 256-byte row piece plus padding)
+  constexpr int kMine = (NR + kRank) * SS > NR * RS ? (NR + kRank) * SS : NR * RS;
+  __shared__ __attribute__((aligned(16))) unsigned char stage[kWaves * kMine];
   __shared__ __attribute__((aligned(16))) float part[kWaves][TT][2][64][4];
-  const int l = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int l = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int n = l & 15, gq = l >> 4;
   const long long row0 = (long long)blockIdx.x * NR;   // first token of this workgroup
   const int nrows = (int)((rows - row0) < NR ? (rows - row0) : NR);
@@ -59,56 +63,70 @@ __global__ void __launch_bounds__(64 * kWaves) gate_project_mfma_kernel(const bf
   // not written
   const __amdgpu_buffer_rsrc_t xsrc = __builtin_amdgcn_make_buffer_rsrc(
       (void*)(reinterpret_cast<const char*>(x) + (size_t)row0 * dm * 2), 0, nrows * dm * 2, kRsrcFlags);
+  const __amdgpu_buffer_rsrc_t wsrc = __builtin_amdgcn_make_buffer_rsrc((void*)w1, 0, kRank * dm * 2, kRsrcFlags);
   const __amdgpu_buffer_rsrc_t gdst = __builtin_amdgcn_make_buffer_rsrc(
       (void*)(reinterpret_cast<char*>(g) + (size_t)row0 * N * 2), 0, nrows * N * 2, kRsrcFlags);
 
-  // ---- H^T[rank][token] = sum_c w1[rank][c] x[token][c], this wave's slabs
-  // x: the slab's NR rows x 256 bytes are read as whole row pieces (16 lanes per row, 4 rows per instruction --
-  // the order in which HBM likes to be asked), pass through this wave's own LDS rows and come back in fragment
-  // layout (lane (token n, group gq): 16 bytes at 64 j + 16 gq).  w1 comes from L2 and is read in fragment
-  // layout directly.
+  // ---- H^T[rank][token] = sum_c w1[rank][c] x[token][c], this wave's slabs of 64 channels
+  // The slab's rows of x and of w1 are read as whole row pieces (8 lanes per row, 8 rows per instruction: read in fragment layout,
+  // 16 lanes of a load touch 16 rows, and the cache serves a line at a time), kDepth slabs ahead, pass through this wave's own LDS
+  // rows and come back in fragment layout (lane (row n, group gq): 16 bytes at 64 j + 16 gq).
   floatx4 acc[TT][2];
 #pragma unroll
   for (int tt = 0; tt < TT; ++tt) { acc[tt][0] = floatx4{0.f, 0.f, 0.f, 0.f}; acc[tt][1] = floatx4{0.f, 0.f, 0.f, 0.f}; }
-  unsigned char* mine = stage + (size_t)wv * NR * RS;
-  const int lr = l >> 4, lp = l & 15;                                   // row within a group of 4, 16-byte piece
-  const unsigned xoff = (unsigned)lr * dm * 2 + lp * 16;
-  const bf16_t* wrow0 = w1 + (size_t)n * dm + gq * 8;                    // rank n, and rank 16 + n below
-  const bf16_t* wrow1 = wrow0 + (size_t)16 * dm;
-  u32x4 xb[4 * TT], wa[2][4];
-  auto fetch = [&](int k0) {
+  unsigned char* mine = stage + (size_t)wv * kMine;
+  const int lr = l >> 3, lp = l & 7;                                    // row within a group of 8, 16-byte piece
+  const unsigned off = (unsigned)lr * dm * 2 + lp * 16;
+  struct Slab { u32x4 x[2 * TT], w[kRank / 8]; };
+  auto fetch = [&](int k0, Slab& o) {
+    // (a slab past the last channel: offsets that no descriptor covers read as zero)
+    const unsigned at = k0 < dm ? off + (unsigned)k0 * 2 : 0xF0000000u, step = k0 < dm ? (unsigned)dm * 16 : 0u;
 #pragma unroll
-    for (int it = 0; it < 4 * TT; ++it)
-      xb[it] = __builtin_amdgcn_raw_buffer_load_b128(xsrc, (int)(xoff + (unsigned)(4 * it) * dm * 2 + k0 * 2), 0, 0);
+    for (int it = 0; it < 2 * TT; ++it) o.x[it] = __builtin_amdgcn_raw_buffer_load_b128(xsrc, (int)(at + it * step), 0, 0);
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      wa[0][j] = *reinterpret_cast<const u32x4*>(wrow0 + k0 + 32 * j);
-      wa[1][j] = *reinterpret_cast<const u32x4*>(wrow1 + k0 + 32 * j);
-    }
+    for (int it = 0; it < kRank / 8; ++it) o.w[it] = __builtin_amdgcn_raw_buffer_load_b128(wsrc, (int)(at + it * step), 0, 0);
   };
   constexpr int kStep = kSlab * kWaves;
-  if (wv * kSlab < dm) fetch(wv * kSlab);
+  Slab buf[kDepth];
+#pragma unroll
+  for (int d = 0; d < kDepth; ++d) fetch(wv * kSlab + d * kStep, buf[d]);
 #pragma unroll 1
-  for (int k0 = wv * kSlab; k0 < dm; k0 += kStep) {
-    // this slab's rows into LDS (the previous slab's fragment reads were issued before these writes, and LDS
-    // serves one wave's requests in order)
+  for (int k0 = wv * kSlab; k0 < dm; k0 += kStep * kDepth) {
 #pragma unroll
-    for (int it = 0; it < 4 * TT; ++it) *reinterpret_cast<u32x4*>(mine + (4 * it + lr) * RS + lp * 16) = xb[it];
-    u32x4 wc[2][4];
+    for (int d = 0; d < kDepth; ++d) {
+      // this slab's rows into LDS (the previous slab's fragment reads were issued before these writes, and LDS
+      // serves one wave's requests in order)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) { wc[0][j] = wa[0][j]; wc[1][j] = wa[1][j]; }
-    __builtin_amdgcn_wave_barrier();
-    if (k0 + kStep < dm) fetch(k0 + kStep);
+      for (int it = 0; it < 2 * TT; ++it) *reinterpret_cast<u32x4*>(mine + (8 * it + lr) * SS + lp * 16) = buf[d].x[it];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
+      for (int it = 0; it < kRank / 8; ++it) *reinterpret_cast<u32x4*>(mine + (NR + 8 * it + lr) * SS + lp * 16) = buf[d].w[it];
+      __builtin_amdgcn_wave_barrier();
+      fetch(k0 + (d + kDepth) * kStep, buf[d]);
 #pragma unroll
-      for (int tt = 0; tt < TT; ++tt) {
-        const bf16x8 b = *reinterpret_cast<const bf16x8*>(mine + (16 * tt + n) * RS + 64 * j + 16 * gq);
-        acc[tt][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, wc[0][j]), b, acc[tt][0], 0, 0, 0);
-        acc[tt][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, wc[1][j]), b, acc[tt][1], 0, 0, 0);
+      for (int j = 0; j < kSlab / 32; ++j) {
+        const unsigned char* p = mine + n * SS + 64 * j + 16 * gq;
+        const bf16x8 a0 = *reinterpret_cast<const bf16x8*>(p + NR * SS), a1 = *reinterpret_cast<const bf16x8*>(p + (NR + 16) * SS);
+#pragma unroll
+        for (int tt = 0; tt < TT; ++tt) {
+          const bf16x8 b = *reinterpret_cast<const bf16x8*>(p + 16 * tt * SS);
+          acc[tt][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a0, b, acc[tt][0], 0, 0, 0);
+          acc[tt][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a1, b, acc[tt][1], 0, 0, 0);
+        }
       }
+      __builtin_amdgcn_wave_barrier();
     }
   }
+  // this wave's first group of w2's rows, on the way while the sums meet
+  uint2 w2lo[kGroupCh / 16], w2hi[kGroupCh / 16];
+  auto fetch2 = [&](int c0) {
+#pragma unroll
+    for (int ct = 0; ct < kGroupCh / 16; ++ct) {
+      const bf16_t* wr = w2 + (size_t)(c0 + 16 * ct + n) * kRank;      // row of w2 = 32 ranks = 64 bytes
+      w2lo[ct] = *reinterpret_cast<const uint2*>(wr + 4 * gq);
+      w2hi[ct] = *reinterpret_cast<const uint2*>(wr + 16 + 4 * gq);
+    }
+  };
+  if (wv * kGroupCh < N) fetch2(wv * kGroupCh);
   // the waves' partial sums meet in LDS; every wave adds them up in the same order
 #pragma unroll
   for (int tt = 0; tt < TT; ++tt) {
@@ -141,10 +159,7 @@ __global__ void __launch_bounds__(64 * kWaves) gate_project_mfma_kernel(const bf
   for (int c0 = wv * kGroupCh; c0 < N; c0 += kGroupCh * kWaves) {
 #pragma unroll
     for (int ct = 0; ct < kGroupCh / 16; ++ct) {
-      const bf16_t* wr = w2 + (size_t)(c0 + 16 * ct + n) * kRank;      // row of w2 = 32 ranks = 64 bytes
-      const uint2 lo = *reinterpret_cast<const uint2*>(wr + 4 * gq);
-      const uint2 hi = *reinterpret_cast<const uint2*>(wr + 16 + 4 * gq);
-      const u32x4 abits = {lo.x, lo.y, hi.x, hi.y};
+      const u32x4 abits = {w2lo[ct].x, w2lo[ct].y, w2hi[ct].x, w2hi[ct].y};
       float bv[4] = {0.f, 0.f, 0.f, 0.f};
       if (bias != nullptr) {
         const uint2 bb = *reinterpret_cast<const uint2*>(bias + c0 + 16 * ct + 4 * gq);
@@ -159,6 +174,7 @@ __global__ void __launch_bounds__(64 * kWaves) gate_project_mfma_kernel(const bf
             make_uint2(pack2(out[0], out[1]), pack2(out[2], out[3]));
       }
     }
+    if (c0 + kGroupCh * kWaves < N) fetch2(c0 + kGroupCh * kWaves);
     __builtin_amdgcn_wave_barrier();   // LDS serves one wave's requests in order: the rows are complete below
 #pragma unroll
     for (int it = 0; it < NR * (kGroupCh / 8) / 64; ++it) {
@@ -209,21 +225,20 @@ __global__ void __launch_bounds__(256) gate_project_generic_kernel(const T* __re
 hipError_t launch_gate_project(const GateProjectParams& p, hipStream_t stream) {
   const long long rows = (long long)p.B * p.T;
   if (rows > 0x7fffffffLL) return hipErrorInvalidValue;
-  if (p.bf16 && p.rank == kRank && p.dm % kSlab == 0 && p.N % kGroupCh == 0 && (long long)32 * p.dm * 2 < (1ll << 31) &&
+  if (p.bf16 && p.rank == kRank && p.dm % 128 == 0 && p.N % kGroupCh == 0 && (long long)32 * p.dm * 2 < (1ll << 31) &&
       (long long)32 * p.N * 2 < (1ll << 31)) {
-    // 32 tokens per workgroup where that still leaves two workgroups for every compute unit, else 16; with eight waves instead of
-    // four while there are two workgroups per compute unit at most (d_model 4096, 1024 outputs: 2000 tokens 17.7 -> 14.5 us,
-    // 8192 27.0 -> 25.9; d_model 2048, 512 outputs: the same up to there, 10006 tokens 19.9 and 21.7).  A second slab in flight
-    // per wave costs a third of the waves: 27.7 us at 5003 tokens, d_model 4096, where this takes 24.4.
-    if ((rows + 31) / 32 >= 512)
-      hipLaunchKernelGGL((gate_project_mfma_kernel<2, 4>), dim3((unsigned)((rows + 31) / 32)), dim3(256), 0, stream,
-                         (const bf16_t*)p.x, (const bf16_t*)p.w1, (const bf16_t*)p.w2, (const bf16_t*)p.bias, (bf16_t*)p.g, rows, p.dm, p.N);
-    else if ((rows + 15) / 16 <= 512)
-      hipLaunchKernelGGL((gate_project_mfma_kernel<1, 8>), dim3((unsigned)((rows + 15) / 16)), dim3(512), 0, stream,
-                         (const bf16_t*)p.x, (const bf16_t*)p.w1, (const bf16_t*)p.w2, (const bf16_t*)p.bias, (bf16_t*)p.g, rows, p.dm, p.N);
-    else
-      hipLaunchKernelGGL((gate_project_mfma_kernel<1, 4>), dim3((unsigned)((rows + 15) / 16)), dim3(256), 0, stream,
-                         (const bf16_t*)p.x, (const bf16_t*)p.w1, (const bf16_t*)p.w2, (const bf16_t*)p.bias, (bf16_t*)p.g, rows, p.dm, p.N);
+    // Few tokens: eight waves share 16, or 32 once 16 would be more workgroups than compute units (each reads all of w1); many:
+    // four waves, and 32 tokens once that leaves two workgroups for every compute unit.  us, d_model 4096 with 1024 outputs / 2048 with
+    // 512: 4096 tokens, 16 to eight waves 12.7 / 8.4; 5003, 16 / 32 18.6, 12.1 / 16.3, 10.0; 10006, 16 to four waves / 32 29.9, 17.2 /
+    // 32.4, 16.2 (32 to eight waves 34.1, 18.9); 16384, 32 to four / to eight 39.0, 18.8 / 41.9, 23.2.
+    auto launch = [&](auto kernel, int tokens, int waves) {
+      hipLaunchKernelGGL(kernel, dim3((unsigned)((rows + tokens - 1) / tokens)), dim3(64 * waves), 0, stream, (const bf16_t*)p.x,
+                         (const bf16_t*)p.w1, (const bf16_t*)p.w2, (const bf16_t*)p.bias, (bf16_t*)p.g, rows, p.dm, p.N);
+    };
+    if (rows <= 16 * 256) launch(gate_project_mfma_kernel<1, 8, 1>, 16, 8);
+    else if (rows <= 32 * 256) launch(gate_project_mfma_kernel<2, 8, 1>, 32, 8);
+    else if ((rows + 31) / 32 < 512) launch(gate_project_mfma_kernel<1, 4, 1>, 16, 4);
+    else launch(gate_project_mfma_kernel<2, 4, 2>, 32, 4);
     return hipGetLastError();
   }
   const size_t lds = (size_t)(p.dm + p.rank) * sizeof(float);
