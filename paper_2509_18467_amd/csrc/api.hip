@@ -7,7 +7,7 @@
 #include <cmath>
 #include <mutex>
 
-#include "kernels.h"
+#include "segment_scan.h"
 
 using namespace lawcat;
 
@@ -116,7 +116,7 @@ ChunkPlan varlen_plan(const lawcat_desc* d, const int32_t* seq_start) {
   int longest = 1;
   for (int i = 0; i < d->B; ++i) longest = std::max(longest, (int)(seq_start[i + 1] - seq_start[i]));
   ChunkPlan one = make_chunk_plan(1, (int)std::min<long long>(total, 0x7fffffc0LL), d->Hq, d->Hkv, d->dk, d->carry_mode, d->segment);
-  ChunkPlan p;
+  ChunkPlan p{};
   const int whole = (longest + 63) / 64 * 64;
   p.seg_len = std::min(one.seg_len, whole);
   if (d->carry_mode == LAWCAT_CARRY_SEQUENTIAL) p.seg_len = whole;
@@ -127,11 +127,12 @@ ChunkPlan varlen_plan(const lawcat_desc* d, const int32_t* seq_start) {
     auto groups = [&](int seg_len) {
       long long n = 0;
       for (int i = 0; i < d->B; ++i) n += (seq_start[i + 1] - seq_start[i] + seg_len - 1) / seg_len;
-      return n * d->Hkv;
+      return n * d->Hkv * std::max(1, d->Hq / d->Hkv / 4);     // workgroups take up to four query heads
     };
     while (p.seg_len < whole && groups(p.seg_len) > slots) p.seg_len += 64;
   }
-  p.nseg = (longest + p.seg_len - 1) / p.seg_len;
+  p.nseg = cut_sequence(longest, p.seg_len).nseg;
+  p.per_head = (int)((total + p.seg_len - 1) / p.seg_len) + d->B - 1;
   p.workspace_bytes = p.nseg > 1 ? (size_t)d->B * d->Hkv * p.nseg * ((d->dk * d->dk + 2 * d->dk) * sizeof(float) + sizeof(int)) : 0;
   return p;
 }

@@ -11,7 +11,7 @@ hipError_t launch_d128(const ChunkArgs& a, int group, int mode, hipStream_t stre
 bool chunk_path_supports(int group) { return group >= 1 && group <= 64; }
 
 ChunkPlan make_chunk_plan(int B, int T, int Hq, int Hkv, int d, int carry_mode, int segment) {
-  ChunkPlan p;
+  ChunkPlan p{};
   const int heads = B * Hkv;
   int seg_len;
   if (carry_mode == 1) {
@@ -51,6 +51,7 @@ hipError_t launch_gla_chunk(const ChunkParams& p, hipStream_t stream) {
   a.q_tail = (bf16_t*)p.q_tail; a.k_tail = (bf16_t*)p.k_tail;
   a.ws = (float*)p.workspace;
   a.seq_start = p.seq_start;
+  a.per_head = p.plan.per_head; a.inv_len = 1.0 / p.plan.seg_len;
   a.seg_live = reinterpret_cast<int*>(a.ws + (size_t)p.B * p.Hkv * p.plan.nseg * (p.d * p.d + 2 * p.d));
   a.B = p.B; a.T = p.T; a.Hq = p.Hq; a.Hkv = p.Hkv; a.W = p.W;
   a.seg_len = p.plan.seg_len; a.nseg = p.plan.nseg;
@@ -60,7 +61,7 @@ hipError_t launch_gla_chunk(const ChunkParams& p, hipStream_t stream) {
   // two would be 384 workgroups, 21.8 / 22.6 / 27 (on 4 kv heads); of 128, 64 tokens 19.2 / 16.6 / 14.2, 1000 36.6 / 33.9 / 41.9 (512).
   // (Not in place: a workgroup would read a start state that another one replaces.)
   const int nseg = p.plan.nseg, heads = p.B * p.Hkv, group = p.Hq / p.Hkv;
-  const long long walks = (long long)nseg * heads;
+  const long long walks = p.seq_start ? (long long)p.Hkv * p.plan.per_head : (long long)nseg * heads;
   a.most = 4;
   if (!(p.S0 == p.S_out || p.z0 == p.z_out)) a.most = walks * group <= 256 ? 1 : walks * ((group + 1) / 2) <= 256 ? 2 : 4;
   // With few segments the output pass folds its predecessors' contributions itself instead of waiting for a scan: a launch less,
@@ -69,6 +70,11 @@ hipError_t launch_gla_chunk(const ChunkParams& p, hipStream_t stream) {
   // 19.2 / 18.7, 10 20.6 / 21.2; 32 on 8 3 segments 18.0 / 14.9, 8 20.5 / 19.5, 10 21.6 / 21.9; x 4 4 segments 26.4 / 20.3, 10
   // 35.2 / 32.0, 12 44.6 / 41.3, 16 36.1 / 38.2; x 16 8 segments 76 / 59.  Of 128, 8 heads, 3 segments 23.6 / 22.1, 4 26.2 / 27.5; x 4
   // 4 segments 40.1 / 33.6, 8 46.6 / 46.5; 32 on 4 x 16 4 segments 74 / 64, 8 121 / 149.
+  // Packed batches: by the length of the segments where there are more workgroups than compute units and they run long enough to repay
+  // finding out (0.7 us a pass).  us a call in order / by length, 32 query heads on 8 kv heads: of 64, 24 sequences, 25947 tokens 142 / 109,
+  // 8 sequences, 29399 tokens 112.5 / 106.6, 12 sequences, 2064 tokens 28.2 / 30.4; of 128, 16 sequences, 16917 tokens 235 / 175, 12, 2064
+  // 50.6 / 52.7.
+  a.ordered = p.seq_start && p.B <= 64 && walks * std::max(1, group / 4) > 256 && a.seg_len > 128;
   const int passes = group % 4 == 0 || a.most == 1 ? 1 : group / 4 + (group % 4 + 1) / 2;
   a.fold = nseg > 1 && nseg * passes <= (p.d == 64 ? std::min(12, 8 + heads / 8) : std::min(7, 3 + heads / 16));
   a.gate_scale = p.gate_scale; a.eps = p.eps;

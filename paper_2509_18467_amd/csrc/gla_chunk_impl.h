@@ -68,16 +68,20 @@ struct ChunkArgs {
   float* z_out;
   bf16_t *q_tail, *k_tail;
   float* ws;
-  int* seg_live;   // [B*Hkv][nseg]: written by the state pass, 0 = the segment's total decay is exactly zero in every channel
+  int* seg_live;   // one per workspace slot: written by the state pass, 0 = the segment's total decay is exactly zero in every channel
   // Sequences of different lengths packed along the token axis: device array of B + 1 row offsets, or null for B
-  // sequences of T tokens each.  With it, T is the longest length and nseg the segment count of that length;
-  // a shorter sequence uses the first ceil(length / seg_len) of its nseg workspace slots.
+  // sequences of T tokens each (nseg segments of seg_len, grid (nseg, B * Hkv)).  With it, T is the longest length and nseg the segment
+  // count of that length: every sequence has nseg workspace slots, is cut by cut_sequence(), and find_place() says which workgroup
+  // takes which segment.
   const int* seq_start;
   int B, T, Hq, Hkv, W;
   int group;   // query heads per kv head (Hq / Hkv)
   int qh0;     // first query head, within its group, that this launch of the output pass covers (its z index: GR heads each)
   int most;    // most query heads that a workgroup of the output pass takes: 4, 2 or 1
   int seg_len, nseg;
+  int per_head;     // packed batches: bound of the segments per kv head, whatever the lengths
+  double inv_len;   // 1 / seg_len
+  int ordered;      // packed batches: workgroups by the length of their segments
   int fold;    // few segments: the output pass folds its predecessors' contributions itself, there is no scan
   float gate_scale, eps;
 };
@@ -432,6 +436,73 @@ struct Kernel {
   }
 };
 
+// x / most for 0 <= x < 2^31, most >= 64: the quotient is off by less than 2^-20, and x + 1/2 lies 1 / (2 most) from the next whole multiple
+__device__ inline int over(int x, double inv_most) { return (int)(((double)x + 0.5) * inv_most); }
+
+// What workgroup (x, hk) of a packed batch works on (uniform): sequence and segment; seg < 0: nothing.  64 lanes look at 64 sequences at a
+// time.
+//   in order (few workgroups): sequence b has those from first row / seg_len + b on (no more tokens lie before it than first row / seg_len
+//     segments hold, and each of the b sequences rounds up once, so these ranges do not overlap, whatever the lengths; a few at
+//     their ends have nothing to do).
+//   by length (`ordered`, up to 64 sequences, one per lane): the longest segments first (workgroups are placed in order, and those
+//     past what the chip holds at once should be the shortest ones), a kv head's after the other's, an odd number each, so that the
+//     segments of all heads spread alike over the eight dies, and no workgroup without work among them: one that leaves at
+//     once still takes a place in turn, and those behind it wait for that place (24 sequences, 26K tokens: the last began 57 us late).
+struct Place { int hk, b, seg, T, nseg, len; size_t row0; };
+__device__ inline Place find_place(const ChunkArgs& a, int l) {
+  const int* seq_start = a.seq_start;
+  int row = 0, end = 0, at, lane;
+  Place p{(int)blockIdx.y, 0, -1, 0, 0, 0, 0};
+  if (a.ordered) {
+    int n = 0;
+    float len = 0.f;       // about how long its segments are
+    if (l < a.B) {
+      row = seq_start[l];
+      end = seq_start[l + 1];
+      n = over(end - row + a.seg_len - 1, a.inv_len);
+      len = (float)(end - row) * __builtin_amdgcn_rcpf((float)n);
+    }
+    int first = 0, all = 0;
+#pragma unroll 1
+    for (int j = 0; j < a.B; ++j) {
+      const float lj = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(len), j));
+      const int nj = __builtin_amdgcn_readlane(n, j);
+      first += (lj > len || (lj == len && j < l)) ? nj : 0;
+      all += nj;
+    }
+    const unsigned odd = all | 1;
+    p.hk = blockIdx.x / odd;
+    const int e = blockIdx.x - p.hk * odd;
+    if (p.hk >= a.Hkv || e >= all) return p;
+    lane = __builtin_ctzll(__builtin_amdgcn_ballot_w64(first <= e && e < first + n));
+    p.seg = e - __builtin_amdgcn_readlane(first, lane);
+    p.b = lane;
+  } else {
+    const int e = blockIdx.x;
+    int lo = 0, n = a.B, cnt;
+    do {
+      const int stride = (n + 63) / 64, i = lo + l * stride;
+      const bool in = l * stride < n;
+      if (in) { row = seq_start[i]; end = seq_start[i + 1]; }
+      at = over(row, a.inv_len) + i;
+      cnt = __builtin_popcountll(__builtin_amdgcn_ballot_w64(in && at <= e));
+      lo += (cnt - 1) * stride;
+      n = min(stride, a.B - lo);
+    } while (n > 1);
+    lane = cnt - 1;
+    p.b = lo;
+    p.seg = e - __builtin_amdgcn_readlane(at, lane);
+  }
+  const int row0 = __builtin_amdgcn_readlane(row, lane);
+  p.row0 = (size_t)row0;
+  p.T = __builtin_amdgcn_readlane(end, lane) - row0;
+  // cut_sequence(), with a division only where it matters
+  p.nseg = over(p.T + a.seg_len - 1, a.inv_len);
+  p.len = a.seg_len;
+  if (p.nseg > 1 && a.seg_len > 64) p.len = cut_sequence(p.T, a.seg_len).len;
+  return p;
+}
+
 // One workgroup = one team of d/16 waves.  At head dim 64 two workgroups share a compute unit (256 VGPRs each).
 template <int D, int GR, int MODE, bool OUTPUT>
 __global__ void __launch_bounds__(D * 4, D == 64 ? 2 : 1)
@@ -448,25 +519,27 @@ __global__ void __launch_bounds__(D * 4, D == 64 ? 2 : 1)
   const int l = tid & 63;   // lane
   const int g4 = l >> 4;    // MFMA lane group
   const int n = l & 15;     // MFMA row/column within a tile
-  const int seg = blockIdx.x;
-  const int bh = blockIdx.y;
-  const int b = bh / a.Hkv, hk = bh % a.Hkv;
+  // this workgroup's sequence (first row in the packed tensors, length, segments; token indices below are relative to row0), kv head
+  // and segment
+  int seg = blockIdx.x, b, hk, T = a.T, nseg = a.nseg, seg_len = a.seg_len;
+  size_t row0;
+  if (a.seq_start == nullptr) {
+    b = blockIdx.y / a.Hkv; hk = blockIdx.y % a.Hkv;
+    row0 = (size_t)b * a.T;
+  } else {
+    const Place p = find_place(a, l);
+    if (p.seg < 0) return;      // (the whole team, before the first barrier)
+    hk = p.hk; b = p.b; seg = p.seg; T = p.T; nseg = p.nseg; seg_len = p.len; row0 = p.row0;
+  }
+  const int bh = b * a.Hkv + hk;
+  const size_t slot0 = (size_t)bh * a.nseg;      // workspace slot of this head's first segment
   const int qh0 = OUTPUT ? a.qh0 + (int)blockIdx.z * GR : 0;   // first query head, within its group, of this workgroup
   const bool keeps = qh0 == 0;   // of the workgroups of a group: the one that stores the final state and the keys' cache
-  // this sequence: first row in the packed tensors, length, segments (token indices below are relative to row0)
-  size_t row0 = (size_t)b * a.T;
-  int T = a.T, nseg = a.nseg;
-  if (a.seq_start != nullptr) {
-    row0 = (size_t)a.seq_start[b];
-    T = a.seq_start[b + 1] - a.seq_start[b];
-    nseg = (T + a.seg_len - 1) / a.seg_len;
-  }
   const int nseg_pass = OUTPUT ? nseg : nseg - 1;  // the first pass skips the last segment
-  // grid rows past a short sequence's last segment (packed batches) have nothing to do; the whole team leaves
-  // before the first barrier
+  // workgroups past a sequence's last segment (packed batches) have nothing to do either
   if (seg >= nseg_pass) return;
-  const int s0 = seg * a.seg_len;
-  const int s1 = min(T, s0 + a.seg_len);
+  const int s0 = seg * seg_len;
+  const int s1 = min(T, s0 + seg_len);
 
   // load-stage patch of this thread: 8 tokens x 2 channels
   const int cp = l & 31, th = l >> 5;
@@ -481,9 +554,9 @@ __global__ void __launch_bounds__(D * 4, D == 64 ? 2 : 1)
   // weights, the first granule's rows, the start state.
   int live_any = 0;
   if (OUTPUT) {
-    if (a.fold) live_any = l >= seg || a.seg_live[(size_t)bh * a.nseg + l] != 0;
+    if (a.fold) live_any = l >= seg || a.seg_live[slot0 + l] != 0;
     else
-      for (int j = tid; j < nseg - 1; j += G::TEAM) live_any |= a.seg_live[(size_t)bh * a.nseg + j];
+      for (int j = tid; j < nseg - 1; j += G::TEAM) live_any |= a.seg_live[slot0 + j];
   }
 
   float* wl = reinterpret_cast<float*>(smem + G::kWl);
@@ -558,7 +631,7 @@ __global__ void __launch_bounds__(D * 4, D == 64 ? 2 : 1)
         scanned = __builtin_amdgcn_readfirstlane(any) != 0;
       }
       if (a.fold ? first > 0 : scanned || (nseg > 1 && seg > 0)) {
-        Sin = a.ws + ((size_t)bh * a.nseg + (a.fold ? first - 1 : scanned ? seg : seg - 1)) * G::kSlot;
+        Sin = a.ws + (slot0 + (a.fold ? first - 1 : scanned ? seg : seg - 1)) * G::kSlot;
         zin = Sin + D * D;
       } else {
         if (a.S0 != nullptr) Sin = a.S0 + (size_t)bh * D * D;
@@ -597,7 +670,7 @@ __global__ void __launch_bounds__(D * 4, D == 64 ? 2 : 1)
       // slot travels meanwhile (at 128 there are no registers for it)
       struct Slot { float s[G::RT][4]; floatx4 z[G::RT], dec[G::RT]; };
       auto load_slot = [&](int j, Slot& o) {
-        const float* slot = a.ws + ((size_t)bh * a.nseg + j) * G::kSlot;
+        const float* slot = a.ws + (slot0 + j) * G::kSlot;
 #pragma unroll
         for (int rt = 0; rt < G::RT; ++rt) {
           const int c = 16 * rt + 4 * g4;
@@ -884,7 +957,7 @@ __global__ void __launch_bounds__(D * 4, D == 64 ? 2 : 1)
   float* zdst = nullptr;
   float* ddst = nullptr;
   if (!OUTPUT) {
-    Sdst = a.ws + ((size_t)bh * a.nseg + seg) * G::kSlot;
+    Sdst = a.ws + (slot0 + seg) * G::kSlot;
     zdst = Sdst + D * D;
     ddst = zdst + D;
   } else if (seg == nseg - 1 && keeps) {
@@ -903,7 +976,7 @@ __global__ void __launch_bounds__(D * 4, D == 64 ? 2 : 1)
       }
     // total decay of the segment: the waves that loaded chunk 0 hold it for their two channels
     if (ddst != nullptr && mcw == 0 && th == 0) *reinterpret_cast<float2*>(ddst + c0) = make_float2(rgran[0], rgran[1]);
-    if (!OUTPUT && tid == 0) a.seg_live[(size_t)bh * a.nseg + seg] = dead ? 0 : 1;
+    if (!OUTPUT && tid == 0) a.seg_live[slot0 + seg] = dead ? 0 : 1;
   }
   // ---- conv cache out: the last W-1 raw rows of [halo ; x] for this workgroup's heads
   if (OUTPUT && CONV && seg == nseg - 1 && a.W > 1) {
@@ -929,6 +1002,7 @@ template <int D, int GR, int MODE>
 hipError_t launch_all(const ChunkArgs& a, int parts, hipStream_t stream, bool with_state_pass, const TraceEvents& ev) {
   using G = Geo<D, GR>;
   const int heads = a.B * a.Hkv;
+  const int x = !a.seq_start ? a.nseg : a.ordered ? (a.per_head | 1) * a.Hkv : a.per_head | 1, y = !a.seq_start ? heads : a.ordered ? 1 : a.Hkv;
   hipError_t e;
   if (a.nseg > 1 && with_state_pass) {
     // GR = 0: key side only
@@ -936,7 +1010,7 @@ hipError_t launch_all(const ChunkArgs& a, int parts, hipStream_t stream, bool wi
     constexpr int lds1 = Geo<D, 0>::kBytes;
     e = set_lds<gla_chunk_kernel<D, 0, MODE, false>>(lds1);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k1, dim3(a.nseg - 1, heads), dim3(G::TEAM), lds1, stream, a);
+    hipLaunchKernelGGL(k1, dim3(a.seq_start ? x : x - 1, y), dim3(G::TEAM), lds1, stream, a);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
     if (!a.fold) {
@@ -951,9 +1025,9 @@ hipError_t launch_all(const ChunkArgs& a, int parts, hipStream_t stream, bool wi
   if (e != hipSuccess) return e;
   // measurement entry point: the two events take the kernel's own start and stop timestamps (no dispatch gaps)
   if (ev.start != nullptr && ev.stop != nullptr)
-    hipExtLaunchKernelGGL(k3, dim3(a.nseg, heads, parts), dim3(G::TEAM), G::kBytes, stream, ev.start, ev.stop, 0, a);
+    hipExtLaunchKernelGGL(k3, dim3(x, y, parts), dim3(G::TEAM), G::kBytes, stream, ev.start, ev.stop, 0, a);
   else
-    hipLaunchKernelGGL(k3, dim3(a.nseg, heads, parts), dim3(G::TEAM), G::kBytes, stream, a);
+    hipLaunchKernelGGL(k3, dim3(x, y, parts), dim3(G::TEAM), G::kBytes, stream, a);
   return hipGetLastError();
 }
 

@@ -9,6 +9,14 @@
 namespace lawcat {
 namespace {   // one copy per translation unit: the kernels are registered by address
 
+// Segments of one sequence of a packed batch: as few as segments of up to `most` tokens give, equally long up to a granule of 64
+// (n = ceil(T / most) segments of ceil(T / n), rounded up to 64, are n: `most` is a multiple of 64 and not below that).
+struct Cut { int nseg, len; };
+__host__ __device__ inline Cut cut_sequence(int T, int most) {
+  const unsigned n = ((unsigned)T + most - 1) / (unsigned)most;
+  return {(int)n, (int)(((unsigned)(T + 63) / 64 + n - 1) / n * 64)};
+}
+
 // Turns per-segment contributions into segment start states, in place:
 //   slot[seg] <- state before segment seg;  state <- decay[seg] (.) state + contribution[seg].
 // AFTER: slot[seg] <- state after segment seg, for all but the last, which has no slot (nseg_max - 1 of them per head).
@@ -40,7 +48,7 @@ __global__ void __launch_bounds__(256) segment_scan_kernel(float* __restrict__ w
   int nseg = nseg_max;
   if (seq_start != nullptr) {
     const int b = bh / Hkv;
-    nseg = (seq_start[b + 1] - seq_start[b] + seg_len - 1) / seg_len;
+    nseg = cut_sequence(seq_start[b + 1] - seq_start[b], seg_len).nseg;
   }
   if (nseg < 2) return;
   {
