@@ -139,6 +139,8 @@ LAWCAT_API int lawcat_gate_project(const lawcat_desc* desc, int d_model, int ran
  *   q [B,T,Hq,dk]  k, gate_logits [B,T,Hkv,dk]  v [B,T,Hkv,dv]  o [B,T,Hq,dv]
  *   den_out (nullable) [B,T,Hq] fp32 = q_t . z_t + eps
  *   S_out [B,Hkv,dk,dv], z_out [B,Hkv,dk]: the state after token T (required).
+ * fp32 storage: the workspace may be smaller or NULL; with lawcat_workspace_bytes of it (and buffers of their own for the state
+ * in and out) a sequence is cut into segments that run side by side, the same sums in another order.
  */
 LAWCAT_API int lawcat_gla_prefill(const lawcat_desc* desc, const void* q, const void* k, const void* v,
                        const void* gate_logits, const float* S0, const float* z0, void* o,

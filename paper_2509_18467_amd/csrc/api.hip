@@ -85,7 +85,8 @@ size_t workspace_bytes_checked(const lawcat_desc* d, int which) {
     case LAWCAT_CALL_GLA_STEP:
       return 0;
     case LAWCAT_CALL_GLA_PREFILL:
-      return prefill_path(d) == Path::kChunkBf16 ? plan_for(d).workspace_bytes : 0;
+      if (prefill_path(d) == Path::kChunkBf16) return plan_for(d).workspace_bytes;
+      return d->dtype == LAWCAT_DTYPE_F32 && d->carry_mode != LAWCAT_CARRY_SEQUENTIAL ? gla_recurrent_workspace_bytes(d->B, d->T, d->Hq, d->Hkv, d->dk) : 0;
     case LAWCAT_CALL_LAYER_PREFILL: {
       if (prefill_path(d) == Path::kChunkBf16) return plan_for(d).workspace_bytes;
       // unfused: q-dot and k-dot staged in the storage type
@@ -252,10 +253,10 @@ int lawcat_gla_prefill(const lawcat_desc* desc, const void* q, const void* k, co
       !aligned16(z0) || !aligned16(o) || !aligned16(den_out) || !aligned16(S_out) || !aligned16(z_out) ||
       !aligned16(workspace))
     return LAWCAT_E_ALIGN;
-  const size_t need = workspace_bytes_checked(desc, LAWCAT_CALL_GLA_PREFILL);
-  if (need > 0 && (workspace == nullptr || workspace_bytes < need)) return LAWCAT_E_WORKSPACE;
   hipStream_t hs = static_cast<hipStream_t>(stream);
   if (prefill_path(desc) == Path::kChunkBf16) {
+    const size_t need = workspace_bytes_checked(desc, LAWCAT_CALL_GLA_PREFILL);
+    if (need > 0 && (workspace == nullptr || workspace_bytes < need)) return LAWCAT_E_WORKSPACE;
     ChunkParams c{};
     c.q = q; c.k = k; c.v = v; c.g = gate_logits; c.S0 = S0; c.z0 = z0; c.o = o; c.den_out = den_out;
     c.S_out = S_out; c.z_out = z_out; c.workspace = workspace;
@@ -269,6 +270,8 @@ int lawcat_gla_prefill(const lawcat_desc* desc, const void* q, const void* k, co
   r.S_out = S_out; r.z_out = z_out; r.B = desc->B; r.T = desc->T; r.Hq = desc->Hq; r.Hkv = desc->Hkv;
   r.d = desc->dk; r.gate_scale = desc->gate_scale; r.eps = desc->eps;
   r.bf16 = desc->dtype == LAWCAT_DTYPE_BF16;
+  if (desc->carry_mode != LAWCAT_CARRY_SEQUENTIAL) r.workspace = workspace;
+  r.workspace_bytes = workspace_bytes;
   return hip_status(launch_gla_recurrent(r, hs));
 }
 

@@ -1,9 +1,10 @@
 // Normalized gated linear attention (paper section 4.2) in fp32 accuracy:
 //   S_t = diag(alpha_t) S_{t-1} + k_t^T v_t,  z_t = alpha_t (.) z_{t-1} + k_t,
 //   o_t = q_t S_t / (q_t . z_t + eps)
-// Three kernels: gla_walk_kernel walks a whole sequence (prefill with fp32 storage, where bf16 matrix-core operands would not
-// meet the fp32 error bound, and blocks of decode steps), gla_few_kernel takes a few tokens one after the other (the same
-// calls), gla_step_kernel is the decode step (lawcat_gla_step, one token, state updated in place).
+// Three kernels: gla_walk_kernel walks a whole sequence or a segment of it (prefill with fp32 storage, where bf16 matrix-core operands
+// would not meet the fp32 error bound, and blocks of decode steps; gla_span_kernel forms what segments add to the state),
+// gla_few_kernel takes a few tokens one after the other (the same calls), gla_step_kernel is the decode step (lawcat_gla_step, one
+// token, state updated in place).
 //
 // gla_walk_kernel: 16 tokens at a time on the matrix cores.  Within a block of up to 16 tokens, with E_t the decay after the
 // block's first token up to t, Q' = q (.) E, K' = k / E and S~, z~ the state decayed by the first token's alpha:
@@ -48,7 +49,14 @@ struct WalkArgs {
   int T, Hq, Hkv, group;
   int heads;             // query heads that one workgroup takes
   float gate_scale, eps;
+  double* slots;         // [B * Hkv][nseg - 1]: what each segment adds to the state
+  int seg_len, nseg;     // segments of seg_len tokens, a multiple of kSpan; one: all of the sequence
 };
+
+// A segment's contribution in the workspace, in 64 bits (rounded there, S after 100 slowly decaying tokens was 2 % further from 64-bit
+// arithmetic than the walk in one piece): S [key channel][value column], z, the decay over the segment.
+template <int D> constexpr int slot_doubles() { return D * D + 2 * D; }
+constexpr int kSpan = 32;     // tokens at a time of the pass that forms them
 
 // One tensor's rows of a sequence at this workgroup's head; a descriptor covers one chunk (any length of sequence).
 struct Source {
@@ -80,8 +88,8 @@ __device__ inline float load_one(const Rows& r, unsigned off) {
   else return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r.rsrc, (int)off, 0, 0));
 }
 
-// grid (B * Hkv, parts), 4 D threads; a part takes `heads` of the group's query heads, a multiple of HB, and part 0 stores the
-// state.  With one part S_out, z_out may be S0, z0: a wave reads and writes the same elements of both.
+// grid (B * Hkv, parts, segments), 4 D threads; a part takes `heads` of the group's query heads, a multiple of HB, and part 0 of the last
+// segment stores the state.  With one part and one segment S_out, z_out may be S0, z0: a wave reads and writes the same elements of both.
 // Layouts of a 16 x 16 tile in a lane (g, n): "patch" = rows 4 g + i, column n (an fp32 accumulator; rows are tokens, columns
 // the wave's channels); "strided" = rows 4 i + g (an fp64 accumulator, and the tokens of step i of a contraction over them).
 template <typename T, int D, int HB>
@@ -96,28 +104,29 @@ __global__ void __launch_bounds__(4 * D, 2) gla_walk_kernel(const WalkArgs a) {
   const Lanes ln = make_lanes(l);
   const Quad qd = make_quad(l);
   const int bh = blockIdx.x, b = bh / a.Hkv, hk = bh % a.Hkv;
-  const int nb = a.heads / HB, nchunk = (a.T + kC - 1) / kC;
+  const int s0 = kWide ? blockIdx.z * a.seg_len : 0, rows = kWide ? min(a.T - s0, a.seg_len) : a.T;      // this segment's tokens
+  const int nb = a.heads / HB, nchunk = (rows + kC - 1) / kC;
   const int hq0 = hk * a.group + blockIdx.y * a.heads;      // first query head
   const unsigned kvs = (unsigned)a.Hkv * D * St::kBytes, qs = (unsigned)a.Hq * D * St::kBytes;
-  const size_t kv1 = ((size_t)b * a.T * a.Hkv + hk) * D * St::kBytes;
-  const size_t q1 = ((size_t)b * a.T * a.Hq + hq0) * D * St::kBytes;
+  const size_t kv1 = (((size_t)b * a.T + s0) * a.Hkv + hk) * D * St::kBytes;
+  const size_t q1 = (((size_t)b * a.T + s0) * a.Hq + hq0) * D * St::kBytes;
   const Source K{(const char*)a.k + kv1, kvs, D * St::kBytes}, V{(const char*)a.v + kv1, kvs, D * St::kBytes},
       Gt{(const char*)a.g + kv1, kvs, D * St::kBytes}, Q{(const char*)a.q + q1, qs, (unsigned)a.heads * D * St::kBytes},
       O{(const char*)a.o + q1, qs, (unsigned)a.heads * D * St::kBytes};
-  const unsigned offk = St::offset(chunk_rows(K, 0, a.T), g, n, 16 * w), offq = St::offset(chunk_rows(Q, 0, a.T), g, n, 16 * w);
+  const unsigned offk = St::offset(chunk_rows(K, 0, rows), g, n, 16 * w), offq = St::offset(chunk_rows(Q, 0, rows), g, n, 16 * w);
   const unsigned own = (unsigned)(16 * w + n) * St::kBytes;
 
   typename St::Raw rq[HB], rk, rg;
   float rv[4];
   auto fetch = [&](int ci, int hb) {
     if (hb == 0) {
-      rg = St::load(chunk_rows(Gt, ci * kC, a.T), offk, 0);
-      rk = St::load(chunk_rows(K, ci * kC, a.T), offk, 0);
-      const Rows v = chunk_rows(V, ci * kC, a.T);
+      rg = St::load(chunk_rows(Gt, ci * kC, rows), offk, 0);
+      rk = St::load(chunk_rows(K, ci * kC, rows), offk, 0);
+      const Rows v = chunk_rows(V, ci * kC, rows);
 #pragma unroll
       for (int i = 0; i < 4; ++i) rv[i] = load_one<T>(v, (unsigned)(4 * i + g) * kvs + own);
     }
-    const Rows q = chunk_rows(Q, ci * kC, a.T);
+    const Rows q = chunk_rows(Q, ci * kC, rows);
 #pragma unroll
     for (int h = 0; h < HB; ++h) rq[h] = St::load(q, offq + (unsigned)(hb * HB + h) * D * St::kBytes, 0);
   };
@@ -134,6 +143,58 @@ __global__ void __launch_bounds__(4 * D, 2) gla_walk_kernel(const WalkArgs a) {
     for (int i = 0; i < 4; ++i)
       X[rt][i] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(Sin.rsrc, (int)soff, (16 * rt + i) * D * 4, 0));
   double z = a.z0 ? a.z0[(size_t)bh * D + 16 * w + n] : 0.f;
+  if (kWide && blockIdx.z > 0) {
+    // ... then the segments before this one, in 64 bits, rounded once
+    double Y[RT][4];
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) Y[rt][i] = (double)X[rt][i];
+    struct Part { double s[RT][4], dec[RT][4], z, zdec; };
+    auto load_part = [&](int j, Part& o) {
+      const double *slot = a.slots + ((size_t)bh * (a.nseg - 1) + j) * slot_doubles<D>(), *zd = slot + D * D;
+#pragma unroll
+      for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int c = 16 * rt + 4 * g + i;
+          o.s[rt][i] = slot[c * D + 16 * w + n];
+          o.dec[rt][i] = zd[D + c];
+        }
+      o.z = zd[16 * w + n];
+      o.zdec = zd[D + 16 * w + n];
+    };
+    auto add_part = [&](const Part& o) {
+#pragma unroll
+      for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) Y[rt][i] = fma(o.dec[rt][i], Y[rt][i], o.s[rt][i]);
+      z = fma(o.zdec, z, o.z);
+    };
+    const int before = blockIdx.z;
+    Part x, y;
+    if constexpr (D == 64) {       // the next one travels meanwhile (at 128 there are no registers for it)
+      load_part(0, x);
+#pragma unroll 1
+      for (int j = 0; j < before; j += 2) {
+        load_part(min(j + 1, before - 1), y);
+        add_part(x);
+        if (j + 1 >= before) break;
+        load_part(min(j + 2, before - 1), x);
+        add_part(y);
+      }
+    } else {
+#pragma unroll 1
+      for (int j = 0; j < before; ++j) {
+        load_part(j, x);
+        add_part(x);
+      }
+    }
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) X[rt][i] = (float)Y[rt][i];
+  }
 
   int* flags = reinterpret_cast<int*>(sm + L::oFlag);
   Decay d;
@@ -150,7 +211,7 @@ __global__ void __launch_bounds__(4 * D, 2) gla_walk_kernel(const WalkArgs a) {
     for (int i = 0; i < 4; ++i) {
       // alpha = sigmoid(g)^gate_scale; at gate_scale 1 directly 1 / (1 + e^-g)
       const float al = gs1 ? 1.f / (1.f + expf(-gl[i])) : expf(a.gate_scale * log_sigmoid(gl[i]));
-      d.al[i] = row0 + 4 * g + i < a.T ? al : 1.f;
+      d.al[i] = row0 + 4 * g + i < rows ? al : 1.f;
       vv[i] = rv[i];
       tame = tame && fabsf(kk[i]) < kTame && fabsf(vv[i]) < kTame;
     }
@@ -241,14 +302,14 @@ __global__ void __launch_bounds__(4 * D, 2) gla_walk_kernel(const WalkArgs a) {
     }
     __syncthreads();
     // ---- own 16 value columns
-    const Rows orow = chunk_rows(O, row0, a.T);
+    const Rows orow = chunk_rows(O, row0, rows);
     float vm[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) vm[i] = (4 * i + g >= lo && 4 * i + g < hi) ? vv[i] : 0.f;
     auto first_alpha = [&](int rt, int i) { return *reinterpret_cast<const float*>(sm + L::oF + (16 * rt + 4 * g + i) * 16); };
     auto store_den = [&](int h, int t, float den) {
-      if (a.den_out != nullptr && w == 0 && n == 0 && t >= lo && t < hi && row0 + t < a.T)
-        a.den_out[((size_t)b * a.T + row0 + t) * a.Hq + hq0 + hb * HB + h] = den;
+      if (a.den_out != nullptr && w == 0 && n == 0 && t >= lo && t < hi && row0 + t < rows)
+        a.den_out[((size_t)b * a.T + s0 + row0 + t) * a.Hq + hq0 + hb * HB + h] = den;
     };
 #pragma unroll
     for (int h = 0; h < HB; ++h) {
@@ -327,7 +388,7 @@ __global__ void __launch_bounds__(4 * D, 2) gla_walk_kernel(const WalkArgs a) {
     ci = ci1; blk = blk1; hb = hb1;
   }
   // the state after the last token
-  if (blockIdx.y != 0) return;
+  if (blockIdx.y != 0 || (kWide && (int)blockIdx.z != a.nseg - 1)) return;
   if (g == 0) a.z_out[(size_t)bh * D + 16 * w + n] = (float)z;
   const Rows Sout = make_rows(a.S_out, (size_t)bh * D * D * 4, D * 4, D, D * 4);
 #pragma unroll
@@ -335,6 +396,90 @@ __global__ void __launch_bounds__(4 * D, 2) gla_walk_kernel(const WalkArgs a) {
 #pragma unroll
     for (int i = 0; i < 4; ++i)
       __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint((float)X[rt][i]), Sout.rsrc, (int)soff, (16 * rt + i) * D * 4, 0);
+}
+
+// What a segment adds to the state at its end, sum_i (k_i (.) decay from i to the end)^T v_i, its z and its decay, from fp32 storage: products
+// and sums in 64 bits as in the walk.  grid (nseg - 1, B * Hkv), 4 D threads; 32 tokens at a time, the last first.
+// Latency: two lane exchanges, one barrier and D / 2 fp64 MFMAs per wave and 32 tokens: 6 us for 32 tokens at head dim 64, launch included.
+template <int D>
+__global__ void __launch_bounds__(4 * D) gla_span_kernel(const WalkArgs a) {
+  typedef Store<float> St;
+  constexpr int RT = D / 16, NM = kSpan / kC, kRow = 8 * D + 16;
+  extern __shared__ __attribute__((aligned(16))) unsigned char sm[];      // k (.) decay, fp64 rows
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l = threadIdx.x & 63, g = l >> 4, n = l & 15;
+  const Lanes ln = make_lanes(l);
+  const int seg = blockIdx.x, bh = blockIdx.y, b = bh / a.Hkv, hk = bh % a.Hkv, s0 = seg * a.seg_len;
+  const unsigned kvs = (unsigned)a.Hkv * D * 4;
+  const size_t kv1 = (((size_t)b * a.T + s0) * a.Hkv + hk) * D * 4;
+  const Source K{(const char*)a.k + kv1, kvs, D * 4}, V{(const char*)a.v + kv1, kvs, D * 4}, Gt{(const char*)a.g + kv1, kvs, D * 4};
+  const unsigned off = (unsigned)(4 * g) * kvs + (16 * w + n) * 4;
+  const bool gs1 = a.gate_scale == 1.0f;
+  doublex4 S[RT];
+#pragma unroll
+  for (int rt = 0; rt < RT; ++rt) S[rt] = kZero64;
+  double z = 0.0, run = 1.0;
+  St::Raw rk[NM], rg[NM];
+  float rv[NM][4];
+  auto fetch = [&](int t0) {
+#pragma unroll
+    for (int m = 0; m < NM; ++m) {
+      rg[m] = St::load(chunk_rows(Gt, t0 + kC * m, a.seg_len), off, 0);
+      rk[m] = St::load(chunk_rows(K, t0 + kC * m, a.seg_len), off, 0);
+      const Rows v = chunk_rows(V, t0 + kC * m, a.seg_len);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) rv[m][i] = load_one<float>(v, (unsigned)(4 * i + g) * kvs + (16 * w + n) * 4);
+    }
+  };
+  fetch(a.seg_len - kSpan);
+#pragma unroll 1
+  for (int t0 = a.seg_len - kSpan; t0 >= 0; t0 -= kSpan) {      // (only whole segments have a successor)
+#pragma unroll
+    for (int m = NM - 1; m >= 0; --m) {
+      double e[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const float gl = rg[m].v[i];
+        e[i] = (double)(gs1 ? 1.f / (1.f + expf(-gl)) : expf(a.gate_scale * log_sigmoid(gl)));
+      }
+      const double s1 = e[2] * e[3], s0x = e[1] * s1, tot = e[0] * s0x;
+      const double x1 = lane_get(ln.x1, tot), x2 = lane_get(ln.x2, tot), x3 = lane_get(ln.x3, tot), x23 = x2 * x3;
+      const double after = ((g & 1) ? 1.0 : x1) * ((g & 2) ? 1.0 : x23) * run;
+      const double Dc[4] = {s0x * after, s1 * after, e[3] * after, after};
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const double x = (double)rk[m].v[i] * Dc[i];
+        z += x;
+        *reinterpret_cast<double*>(sm + (kC * m + 4 * g + i) * kRow + (16 * w + n) * 8) = x;
+      }
+      run *= (tot * x1) * x23;
+    }
+    __syncthreads();
+    float vv[NM][4];
+#pragma unroll
+    for (int m = 0; m < NM; ++m)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) vv[m][i] = rv[m][i];
+    if (t0 > 0) fetch(t0 - kSpan);
+#pragma unroll
+    for (int m = 0; m < NM; ++m)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt)     // rows of the operand in strided order: the tile comes out as a patch
+          S[rt] = mfma_f64(*reinterpret_cast<const double*>(sm + (kC * m + 4 * i + g) * kRow + (16 * rt + strided(n)) * 8), (double)vv[m][i], S[rt]);
+    __syncthreads();
+  }
+  double *slot = a.slots + ((size_t)bh * (a.nseg - 1) + seg) * slot_doubles<D>(), *zd = slot + D * D;
+#pragma unroll
+  for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) slot[(16 * rt + 4 * g + i) * D + 16 * w + n] = S[rt][i];
+  z += lane_get(ln.x1, z);
+  z += lane_get(ln.x2, z);
+  if (g == 0) {
+    zd[16 * w + n] = z;
+    zd[D + 16 * w + n] = run;
+  }
 }
 
 // Decode step (T = 1), state in place.  One block per (batch, kv head).  Thread t owns value column
@@ -506,16 +651,32 @@ template <typename T, int D, int HB>
 hipError_t launch_sized(const WalkArgs& a, int heads, hipStream_t stream) {
   const hipError_t e = set_lds<gla_walk_kernel<T, D, HB>>(WalkLds<D, HB>::kBytes);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((gla_walk_kernel<T, D, HB>), dim3(heads, a.group / a.heads), dim3(4 * D), (WalkLds<D, HB>::kBytes), stream, a);
+  hipLaunchKernelGGL((gla_walk_kernel<T, D, HB>), dim3(heads, a.group / a.heads, a.nseg), dim3(4 * D), (WalkLds<D, HB>::kBytes), stream, a);
   return hipGetLastError();
 }
+
+// Segments of a fp32 prefill: the walk is one serial chain per query head, so while those are few each is cut into up to kMostSegments
+// that are walked side by side, from states that two more steps provide (gla_span_kernel, and the fold at the head of the walk).
+// A training pass of 2 heads, us, whole / up to 4 / 8 / 16 segments: 256 tokens of 64 143.7 / 105.5 / 98.7 / 99.1, 512 of 128 427 / 276 / 232 /
+// 295 (the fold grows with the segments; 2048 tokens, 32 heads of 64, 684 / 341 / 257 / 240).  Two segments of 32 tokens at head dim 128 gain
+// nothing (151 / 152).
+constexpr int kMostSegments = 8;
+struct Split { int seg_len, nseg; };
+Split split_of(int B, int T, int Hq, int Hkv, int d) {
+  const long long places = (d == 64 ? 512 : 256) / ((long long)B * Hq > 0 ? (long long)B * Hq : 1);
+  const int most = (int)std::min<long long>(places, kMostSegments);
+  if (most < 2 || T < (d == 64 ? 2 : 3) * kSpan) return {T, 1};
+  const int len = ((T + most - 1) / most + kSpan - 1) / kSpan * kSpan;
+  return {len, (T + len - 1) / len};
+}
+size_t slots_bytes(int heads, int d, int nseg) { return (size_t)heads * (nseg - 1) * (d * d + 2 * d) * sizeof(double); }
 
 template <typename T, int D>
 hipError_t launch_walk(const RecurrentParams& p, bool in_place, hipStream_t stream) {
   WalkArgs a{};
   a.q = p.q; a.k = p.k; a.v = p.v; a.g = p.g; a.S0 = p.S0; a.z0 = p.z0; a.o = p.o; a.den_out = p.den_out;
   a.S_out = p.S_out; a.z_out = p.z_out; a.T = p.T; a.Hq = p.Hq; a.Hkv = p.Hkv; a.group = p.Hq / p.Hkv;
-  a.gate_scale = p.gate_scale; a.eps = p.eps;
+  a.gate_scale = p.gate_scale; a.eps = p.eps; a.seg_len = p.T; a.nseg = 1;
   const int heads = p.B * p.Hkv;
   a.heads = a.group;
   // A workgroup per query head where they are all resident at once (two of four waves per compute unit at head dim 64, one of
@@ -536,6 +697,16 @@ hipError_t launch_walk(const RecurrentParams& p, bool in_place, hipStream_t stre
     return hipGetLastError();
   }
   if (spread) a.heads = 1;
+  if constexpr (sizeof(T) == 4) {
+    const Split s = in_place ? Split{p.T, 1} : split_of(p.B, p.T, p.Hq, p.Hkv, D);
+    if (s.nseg > 1 && p.workspace != nullptr && p.workspace_bytes >= slots_bytes(heads, D, s.nseg)) {
+      a.seg_len = s.seg_len; a.nseg = s.nseg; a.slots = static_cast<double*>(p.workspace);
+      constexpr int lds = kSpan * (8 * D + 16);
+      const hipError_t e = set_lds<gla_span_kernel<D>>(lds);
+      if (e != hipSuccess) return e;
+      hipLaunchKernelGGL(gla_span_kernel<D>, dim3(a.nseg - 1, heads), dim3(4 * D), lds, stream, a);
+    }
+  }
   // four query heads at a time; two where fp64 sums at head dim 128 would not leave registers for four (256, and 44 spilled)
   if constexpr (sizeof(T) == 2 || D == 64)
     if (a.heads % 4 == 0) return launch_sized<T, D, 4>(a, heads, stream);
@@ -553,6 +724,11 @@ hipError_t launch_walk(const RecurrentParams& p, bool in_place, hipStream_t stre
 hipError_t launch_gla_step(const RecurrentParams& p, hipStream_t stream) {
   if (p.bf16) return p.d == 64 ? launch_step_d<bf16_t, 64>(p, stream) : launch_step_d<bf16_t, 128>(p, stream);
   return p.d == 64 ? launch_step_d<float, 64>(p, stream) : launch_step_d<float, 128>(p, stream);
+}
+
+size_t gla_recurrent_workspace_bytes(int B, int T, int Hq, int Hkv, int d) {
+  const Split s = split_of(B, T, Hq, Hkv, d);
+  return s.nseg > 1 ? slots_bytes(B * Hkv, d, s.nseg) : 0;
 }
 
 // S0, z0 may be the same memory as S_out, z_out here too

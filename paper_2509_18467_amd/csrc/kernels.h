@@ -82,7 +82,10 @@ struct RecurrentParams {
   int B, T, Hq, Hkv, d;
   float gate_scale, eps;
   int bf16;
+  void* workspace;         // fp32 storage, launch_gla_recurrent only: nullable; with gla_recurrent_workspace_bytes() of it short
+  size_t workspace_bytes;  // sequences are cut into segments
 };
+size_t gla_recurrent_workspace_bytes(int B, int T, int Hq, int Hkv, int d);
 hipError_t launch_gla_recurrent(const RecurrentParams& p, hipStream_t stream);
 // One token per sequence, S_out/z_out updated in place (S0, z0, den_out, T are not read).
 hipError_t launch_gla_step(const RecurrentParams& p, hipStream_t stream);
