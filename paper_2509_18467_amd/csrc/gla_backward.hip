@@ -31,11 +31,15 @@
 // The gate's sum over all later tokens is split at segment ends, where it equals sum_j S^[c, j] Gr[c, j], the states on the two
 // sides of the boundary: no pass over the sequence is needed for it.
 //
-// What it measures (32768 tokens, 32 query heads on 8 kv heads, d = 64, bf16), a call back to back with itself: 412 us.  Kernel by
-// kernel under a profiler, at their quickest: state 17, scans 4 each, forward sweep 198, reverse sweep 225.  The two sweeps move
-// 0.57 and 0.54 GB (q, dO, k, v, g once each, the gate term in fp32, the gradients), 105 us each at the rate of a large copy; what
-// they spend beyond that is vector-ALU issue (splits, gates, the reduction of q . u over the channels) and the waits of two waves
-// per SIMD: their registers (232 and 225) leave room for no third, and a limit of 168 spilled (forward 636 us, reverse 423).
+// What it measures (32768 tokens, 32 query heads on 8 kv heads, d = 64, bf16), a call back to back with itself: 406 us.  Kernel by
+// kernel under a profiler, at their quickest: state 17, scans 4 each, forward sweep 190, reverse sweep 215.  The two sweeps move
+// 0.57 and 0.54 GB (q, dO, k, v, g once each, the gate term in fp32, the gradients), 105 us each at the rate of a large copy.  A chunk
+// takes a workgroup 6.1 us (two share a compute unit), spread over all of its sections (timestamps, us: forward, gates and rows 1.3, K' and z 1.1, u 1.3,
+// reduction of q . u 0.4, dden and dq 0.7, gradients' and state's update 1.1; reverse, gates, rows and decays 1.1, R~ v and K' R~ 2.0,
+// scores 0.6, dk 0.8, update 0.8, dv and outputs 0.6; barriers 0.1 each): dependent chains at two waves per SIMD, whose
+// registers (239 and 231) leave room for no third, and a limit of 168 spilled (forward 636 us, reverse 423).  With one chunk's rows
+// written only when all waves were done with the chunk before (three barriers a chunk in the forward sweep, five in the
+// reverse one, now two each) and the four gates of a lane formed one after the other: 418.
 //
 // fp32 storage: the sums of every contraction are fp64 MFMAs and decays are multiplied up in 64 bits, rounded per chunk, because
 // chains of fp32 MFMAs alone were up to 2.4 times further from 64-bit arithmetic than sums token by token.  2-norm errors of
@@ -156,8 +160,7 @@ __global__ void __launch_bounds__(4 * D) bwd_state_kernel(const BwdArgs a) {
       float gl[4], kk[4], al[4];
       St::patch(qd, rg[m], gl);
       St::patch(qd, rk[m], kk);
-#pragma unroll
-      for (int i = 0; i < 4; ++i) al[i] = t0 + kC * m + 4 * g + i < rows ? alpha_of(gl[i], a.gate_scale) : 1.f;
+      alphas_of(gl, a.gate_scale, rows - (t0 + kC * m + 4 * g), al);
       const float s2 = al[3], s1 = al[2] * s2, s0x = al[1] * s1, tot = al[0] * s0x;
       const float x1 = lane_get(ln.x1, tot), x2 = lane_get(ln.x2, tot), x3 = lane_get(ln.x3, tot);
       const float after = ((g & 1) ? 1.f : x1) * ((g & 2) ? 1.f : x2 * x3) * run;
@@ -198,27 +201,35 @@ struct Sweep {
   static constexpr int NW = D / 16;                               // waves: 16 key channels each
   static constexpr int kRow = St::template row_bytes<D>();
   static constexpr int kSet = kC * kRow;                          // one head's (or v's) rows of a chunk
-  // LDS of both sweeps: dO rows of HB heads | v rows | 1 / den (and dden) per head and token | one word per wave
-  static constexpr int oV = HB * kSet;
-  static constexpr int oDen = oV + kSet;
-  static constexpr int oFlag = oDen + 2 * HB * kC * 4;
-  static constexpr int oEnd = oFlag + 32;
+  static constexpr int kO = HB * kSet;                            // dO rows of HB heads
+  static constexpr int kPairs = 2 * HB * kC * 4;                  // two floats per head and token
   // fp32 storage at head dim 64: dO . v (and the scores) formed by each wave over its own channels and added up, where otherwise
   // every wave forms all of it (32768 tokens of 32 / 8 heads: 1077 us and 1256); at 128 the tiles would not fit
   static constexpr bool kParts = sizeof(T) == 4 && D == 64;
   static constexpr int kTile = 2048;
-  // forward: partial q . u of every wave | parts of dO . v | the state before a chunk that goes token by token
-  static constexpr int oDa = oEnd + NW * HB * kC * 4;
+  // forward, twice, in turn, so that no wave waits for the others to be done with a chunk before it begins the next: dO rows | v rows |
+  // 1 / den, den per head and token | one word per wave
+  static constexpr int oV = kO;
+  static constexpr int oDen = oV + kSet;
+  static constexpr int oFlag = oDen + kPairs;
+  static constexpr int kTurn = oFlag + 32;
+  // once: partial q . u of every wave | parts of dO . v | the state before a chunk that goes token by token
+  static constexpr int oPart = 2 * kTurn;
+  static constexpr int oDa = oPart + NW * HB * kC * 4;
   static constexpr int oX = oDa + (kParts ? NW * HB * kTile : 0);
   static constexpr int kForward = oX + D * D * 4;
-  // reverse: K' rows | R~ [channel][value column], later Q' rows of HB heads | scores
-  static constexpr int oK = oEnd;
-  static constexpr int oU = oK + kC * f32_row_bytes<D>();
-  static constexpr int kU = (D > HB * kC ? D : HB * kC) * f32_row_bytes<D>();
-  static constexpr int oSc = oU + kU;
+  // reverse: dO rows (twice, in turn, where they are read last in a chunk) | v rows | 1 / den, dden | K' rows | R~ [channel][value
+  // column] | Q' rows of HB heads | scores
+  static constexpr int rV = kParts ? kO : 2 * kO;
+  static constexpr int rDen = rV + kSet;
+  static constexpr int rK = rDen + kPairs;
+  static constexpr int rR = rK + kC * f32_row_bytes<D>();
+  static constexpr int rQ = rR + D * f32_row_bytes<D>();
+  static constexpr int rSc = rQ + HB * kC * f32_row_bytes<D>();
   static constexpr int kScore = sizeof(T) == 2 ? 3 * 512 : 2048;  // per head: three terms of 8 bytes per lane, or one fp64 tile
   // (or parts of the scores, then of dO . v)
-  static constexpr int kReverse = oSc + (kParts ? 2 * NW * HB * kTile : HB * kScore);
+  static constexpr int kReverse = rSc + (kParts ? 2 * NW * HB * kTile : HB * kScore);
+  static_assert(kForward <= 160 * 1024 / (D == 64 ? 2 : 1) && kReverse <= 160 * 1024 / (D == 64 ? 2 : 1));
 };
 
 // ---- forward sweep: dq, dden, sum_h q (.) dq, and the segment's contribution to the gradient flowing backwards.
@@ -228,7 +239,8 @@ __global__ void __launch_bounds__(4 * D, 2) bwd_forward_kernel(const BwdArgs a) 
   typedef Store<T> St;
   typedef Sweep<T, D, HB> L;
   constexpr int NW = L::NW;
-  extern __shared__ __attribute__((aligned(16))) unsigned char sm[];
+  extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
+  unsigned char* sm = lds;      // this chunk's turn of the rows
   const int tid = threadIdx.x;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63, g = l >> 4, n = l & 15;
   const Lanes ln = make_lanes(l);
@@ -299,23 +311,21 @@ __global__ void __launch_bounds__(4 * D, 2) bwd_forward_kernel(const BwdArgs a) 
       float gl[4];
       St::patch(qd, rg, gl);
       St::patch(qd, rk, kk);
+      alphas_of(gl, a.gate_scale, rows - (row0 + 4 * g), d.al);
       bool tame = true;
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        d.al[i] = row0 + 4 * g + i < rows ? alpha_of(gl[i], a.gate_scale) : 1.f;
-        tame = tame && fabsf(kk[i]) < kTame;
-      }
+      for (int i = 0; i < 4; ++i) tame = tame && fabsf(kk[i]) < kTame;
       whole_chunk<Wide<T>>(d, ln, g);
       sharp = __builtin_amdgcn_ballot_w64(!tame || !(d.last >= kWhole)) != 0;
       bad = false;
-      St::template to_lds<D>(sm + L::oV, g, n, 16 * w, rv);
     }
+    St::template to_lds<D>(sm + L::oV, g, n, 16 * w, rv);      // (in every turn: the registers hold them for all of the chunk's heads)
 #pragma unroll
     for (int h = 0; h < HB; ++h) St::template to_lds<D>(sm + h * L::kSet, g, n, 16 * w, ro[h]);
     if constexpr (L::kParts) {
       __builtin_amdgcn_wave_barrier();   // LDS serves one wave's requests in order: its rows are complete below
 #pragma unroll
-      for (int h = 0; h < HB; ++h) dot_part64<D>(sm + L::oV, sm + h * L::kSet, w, g, n, sm + L::oDa + (w * HB + h) * L::kTile);
+      for (int h = 0; h < HB; ++h) dot_part64<D>(sm + L::oV, sm + h * L::kSet, w, g, n, lds + L::oDa + (w * HB + h) * L::kTile);
     }
     if (tid < HB * kC) {
       float* den = reinterpret_cast<float*>(sm + L::oDen);
@@ -384,7 +394,7 @@ __global__ void __launch_bounds__(4 * D, 2) bwd_forward_kernel(const BwdArgs a) 
       asm volatile("" : "+v"(lane));
       const int gs = lane >> 4, ns = lane & 15;
       const Lanes lns = make_lanes(lane);
-      floatx4* before = reinterpret_cast<floatx4*>(sm + L::oX) + tid;
+      floatx4* before = reinterpret_cast<floatx4*>(lds + L::oX) + tid;
       const float z0 = z;
       if (!last_head) {
 #pragma unroll
@@ -437,7 +447,7 @@ __global__ void __launch_bounds__(4 * D, 2) bwd_forward_kernel(const BwdArgs a) 
 #pragma unroll
       for (int h = 0; h < HB; ++h) {
         floatx4 da;    // [token i of v][token `row` of dO]
-        if constexpr (L::kParts) da = add64(floatx4{0.f, 0.f, 0.f, 0.f}, sum_parts64<NW>(sm + L::oDa + h * L::kTile, HB * L::kTile, g, n));
+        if constexpr (L::kParts) da = add64(floatx4{0.f, 0.f, 0.f, 0.f}, sum_parts64<NW>(lds + L::oDa + h * L::kTile, HB * L::kTile, g, n));
         else da = dot_rows<T, D, kWide>(sm + L::oV, sm + h * L::kSet, g, n);
         float am[4];
 #pragma unroll
@@ -447,7 +457,7 @@ __global__ void __launch_bounds__(4 * D, 2) bwd_forward_kernel(const BwdArgs a) 
         for (int i = 0; i < 4; ++i) u[h][i] = (u[h][i] + s[i]) * d.E[i];
       }
     }
-    float* part = reinterpret_cast<float*>(sm + L::oEnd);
+    float* part = reinterpret_cast<float*>(lds + L::oPart);
 #pragma unroll
     for (int h = 0; h < HB; ++h) {
       floatx4 s;
@@ -517,8 +527,8 @@ __global__ void __launch_bounds__(4 * D, 2) bwd_forward_kernel(const BwdArgs a) 
 #pragma unroll
       for (int i = 0; i < 4; ++i) qdq[i] = 0.f;
     }
-    __syncthreads();
     ci = ci1; hb = hb1;
+    sm = sm == lds ? lds + L::kTurn : lds;
   }
   if (tid == 0) a.serial[(size_t)bh * a.nseg + seg] = any_serial;
   if (seg > 0) {
@@ -544,6 +554,7 @@ __device__ __forceinline__ void reverse_sweep(const BwdArgs& a) {
   typedef Sweep<T, D, HB> L;
   constexpr int NW = L::NW;
   extern __shared__ __attribute__((aligned(16))) unsigned char sm[];
+  unsigned char* orows = sm;    // this chunk's turn of the dO rows
   const int tid = threadIdx.x;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63, g = l >> 4, n = l & 15;
   const Lanes ln = make_lanes(l);
@@ -632,9 +643,9 @@ __device__ __forceinline__ void reverse_sweep(const BwdArgs& a) {
       float gl[4];
       St::patch(qd, rg, gl);
       St::patch(qd, rk, kk);
+      alphas_of(gl, a.gate_scale, rows - (row0 + 4 * g), d.al);
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        d.al[i] = row0 + 4 * g + i < rows ? alpha_of(gl[i], a.gate_scale) : 1.f;
         sig[i] = __builtin_amdgcn_rcpf(1.f + __expf(gl[i]));       // 1 - sigmoid(g)
         qdq[i] = rqdq[i];
       }
@@ -658,26 +669,26 @@ __device__ __forceinline__ void reverse_sweep(const BwdArgs& a) {
           rE[i] = inverse<T>(d.E[i]);
           kp[i] = kk[i] * rE[i];
         }
-        f32_to_lds<D>(sm + L::oK, g, n, 16 * w, kp);
+        f32_to_lds<D>(sm + L::rK, g, n, 16 * w, kp);
 #pragma unroll
         for (int jt = 0; jt < D / 16; ++jt) {
 #pragma unroll
           for (int i = 0; i < 4; ++i) R[jt][i] *= f;
-          *reinterpret_cast<floatx4*>(sm + L::oU + c * f32_row_bytes<D>() + (16 * jt + 4 * g) * 4) = R[jt];
+          *reinterpret_cast<floatx4*>(sm + L::rR + c * f32_row_bytes<D>() + (16 * jt + 4 * g) * 4) = R[jt];
         }
       }
       pend = d.first;
-      St::template to_lds<D>(sm + L::oV, g, n, 16 * w, rv);
+      St::template to_lds<D>(sm + L::rV, g, n, 16 * w, rv);
     }
 #pragma unroll
-    for (int h = 0; h < HB; ++h) St::template to_lds<D>(sm + h * L::kSet, g, n, 16 * w, ro[h]);
-    unsigned char* das = sm + L::oSc + NW * HB * L::kTile;     // parts of dO . v
+    for (int h = 0; h < HB; ++h) St::template to_lds<D>(orows + h * L::kSet, g, n, 16 * w, ro[h]);
+    unsigned char* das = sm + L::rSc + NW * HB * L::kTile;     // parts of dO . v
     if constexpr (L::kParts) {
       __builtin_amdgcn_wave_barrier();
 #pragma unroll
-      for (int h = 0; h < HB; ++h) dot_part64<D>(sm + h * L::kSet, sm + L::oV, w, g, n, das + (w * HB + h) * L::kTile);
+      for (int h = 0; h < HB; ++h) dot_part64<D>(orows + h * L::kSet, sm + L::rV, w, g, n, das + (w * HB + h) * L::kTile);
     }
-    float* den = reinterpret_cast<float*>(sm + L::oDen);
+    float* den = reinterpret_cast<float*>(sm + L::rDen);
     if (tid < HB * kC) {
       den[tid] = 1.f / rden;
       den[HB * kC + tid] = rdd;
@@ -688,6 +699,12 @@ __device__ __forceinline__ void reverse_sweep(const BwdArgs& a) {
       St::patch(qd, rq[h], qp[h]);
 #pragma unroll
       for (int i = 0; i < 4; ++i) qp[h][i] *= d.E[i];
+      if constexpr (!kTokens) f32_to_lds<D>(sm + L::rQ + h * kC * f32_row_bytes<D>(), g, n, 16 * w, qp[h]);
+    }
+    if constexpr (L::kParts && !kTokens) {
+      __builtin_amdgcn_wave_barrier();
+#pragma unroll
+      for (int h = 0; h < HB; ++h) dot_part64<D>(sm + L::rQ + h * kC * f32_row_bytes<D>(), sm + L::rK, w, g, n, sm + L::rSc + (w * HB + h) * L::kTile);
     }
     __syncthreads();
     const int hb1 = hb + 1 < nb ? hb + 1 : 0;
@@ -703,14 +720,14 @@ __device__ __forceinline__ void reverse_sweep(const BwdArgs& a) {
       double y = hb == 0 ? Rz : 0.0;
 #pragma unroll
       for (int jt = 0; jt < D / 16; ++jt) Y[jt] = hb == 0 ? R[jt] : floatx4{0.f, 0.f, 0.f, 0.f};
-      float* dvp = reinterpret_cast<float*>(sm + L::oU);
+      float* dvp = reinterpret_cast<float*>(sm + L::rR);
       float aln = 1.f;       // alpha of the token after
 #pragma unroll 1
       for (int tg = 3; tg >= 0; --tg) {
         const int from = ((tg << 4) + ns) << 2;
 #pragma unroll
         for (int i = 3; i >= 0; --i) {
-          const unsigned char* col = sm + (4 * tg + i) * L::kRow + 4 * gs * St::kBytes;
+          const unsigned char *col = sm + L::rV + (4 * tg + i) * L::kRow + 4 * gs * St::kBytes, *ocol = orows + (4 * tg + i) * L::kRow + 4 * gs * St::kBytes;
           const float kt = lane_get(from, kk[i]);
           float wt[HB];
           y *= aln;
@@ -726,12 +743,12 @@ __device__ __forceinline__ void reverse_sweep(const BwdArgs& a) {
             floatx4 x = Y[jt] * aln;
 #pragma unroll
             for (int h = 0; h < HB; ++h) {
-              const floatx4 o4 = St::four(col + h * L::kSet + 16 * jt * St::kBytes);
+              const floatx4 o4 = St::four(ocol + h * L::kSet + 16 * jt * St::kBytes);
 #pragma unroll
               for (int e = 0; e < 4; ++e) x[e] = fmaf(wt[h], o4[e], x[e]);
             }
             Y[jt] = x;
-            const floatx4 v4 = St::four(col + L::oV + 16 * jt * St::kBytes);
+            const floatx4 v4 = St::four(col + 16 * jt * St::kBytes);
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
               part[e] = fmaf(x[e], v4[e], part[e]);
@@ -764,18 +781,18 @@ __device__ __forceinline__ void reverse_sweep(const BwdArgs& a) {
     if (hb == 0) {
       // ---- what flows in from after the chunk: dk gets R~ v^, dv gets K' R~
       floatx4 acc[1] = {floatx4{(float)Rz, (float)Rz, (float)Rz, (float)Rz}};
-      contract<T, D, 1>(R, sm + L::oV, g, n, acc);
+      contract<T, D, 1>(R, sm + L::rV, g, n, acc);
       dk0 = acc[0];
       dk = dv0 = dv = floatx4{0.f, 0.f, 0.f, 0.f};
       dvw = kZero64;
 #pragma unroll
       for (int ct = 0; ct < D / 16; ++ct) {
-        const floatx4 f = f32_row_frag<D>(sm + L::oK, g, row, ct);
+        const floatx4 f = f32_row_frag<D>(sm + L::rK, g, row, ct);
         float fa[4], r[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
           fa[i] = f[i];
-          r[i] = *reinterpret_cast<const float*>(sm + L::oU + (16 * ct + 4 * g + i) * f32_row_bytes<D>() + c * 4);
+          r[i] = *reinterpret_cast<const float*>(sm + L::rR + (16 * ct + 4 * g + i) * f32_row_bytes<D>() + c * 4);
         }
         if constexpr (kWide) {
 #pragma unroll
@@ -784,30 +801,21 @@ __device__ __forceinline__ void reverse_sweep(const BwdArgs& a) {
           dv0 = token_steps<false>(fa, r, dv0);
         }
       }
-      __syncthreads();
     }
-#pragma unroll
-    for (int h = 0; h < HB; ++h) f32_to_lds<D>(sm + L::oU + h * kC * f32_row_bytes<D>(), g, n, 16 * w, qp[h]);
-    if constexpr (L::kParts) {
-      __builtin_amdgcn_wave_barrier();
-#pragma unroll
-      for (int h = 0; h < HB; ++h) dot_part64<D>(sm + L::oU + h * kC * f32_row_bytes<D>(), sm + L::oK, w, g, n, sm + L::oSc + (w * HB + h) * L::kTile);
-    }
-    __syncthreads();
     // ---- scores of head w: Q'_s . K'_i / den_s for i <= s, shared through LDS (in the terms the product below uses)
     if (!L::kParts && w < HB) {
-      const unsigned char* qrows = sm + L::oU + w * kC * f32_row_bytes<D>();
-      const floatx4 rd = *reinterpret_cast<const floatx4*>(sm + L::oDen + (w * kC + 4 * g) * 4);
-      unsigned char* p = sm + L::oSc + w * L::kScore;
+      const unsigned char* qrows = sm + L::rQ + w * kC * f32_row_bytes<D>();
+      const floatx4 rd = *reinterpret_cast<const floatx4*>(sm + L::rDen + (w * kC + 4 * g) * 4);
+      unsigned char* p = sm + L::rSc + w * L::kScore;
       if constexpr (sizeof(T) == 2) {
-        floatx4 sc = dot_rows<float, D>(qrows, sm + L::oK, g, n);   // [s][`row`]
+        floatx4 sc = dot_rows<float, D>(qrows, sm + L::rK, g, n);   // [s][`row`]
 #pragma unroll
         for (int i = 0; i < 4; ++i) sc[i] = row <= 4 * g + i ? sc[i] * rd[i] : 0.f;
         const Split4 s = split4(sc[0], sc[1], sc[2], sc[3]);
 #pragma unroll
         for (int k = 0; k < 3; ++k) *reinterpret_cast<uint2*>(p + k * 512 + l * 8) = s.t[k];
       } else {
-        doublex4 sc = dot_rows64<D>(qrows, sm + L::oK, g, n);
+        doublex4 sc = dot_rows64<D>(qrows, sm + L::rK, g, n);
 #pragma unroll
         for (int i = 0; i < 4; ++i) sc[i] = row <= 4 * g + i ? sc[i] * (double)rd[i] : 0.0;
         *reinterpret_cast<doublex4*>(p + l * 32) = sc;
@@ -818,11 +826,11 @@ __device__ __forceinline__ void reverse_sweep(const BwdArgs& a) {
     Wide<T> rzt[4] = {0, 0, 0, 0};
 #pragma unroll
     for (int h = 0; h < HB; ++h) {
-      const floatx4 rd = *reinterpret_cast<const floatx4*>(sm + L::oDen + (h * kC + 4 * g) * 4);
-      const floatx4 dd = *reinterpret_cast<const floatx4*>(sm + L::oDen + ((HB + h) * kC + 4 * g) * 4);
+      const floatx4 rd = *reinterpret_cast<const floatx4*>(sm + L::rDen + (h * kC + 4 * g) * 4);
+      const floatx4 dd = *reinterpret_cast<const floatx4*>(sm + L::rDen + ((HB + h) * kC + 4 * g) * 4);
       floatx4 da;    // [token s of dO][token `row` of v]
       if constexpr (L::kParts) da = add64(floatx4{0.f, 0.f, 0.f, 0.f}, sum_parts64<NW>(das + h * L::kTile, HB * L::kTile, g, n));
-      else da = dot_rows<T, D, kWide>(sm + h * L::kSet, sm + L::oV, g, n);
+      else da = dot_rows<T, D, kWide>(orows + h * L::kSet, sm + L::rV, g, n);
       float am[4];
 #pragma unroll
       for (int i = 0; i < 4; ++i) am[i] = row <= 4 * g + i ? fmaf(da[i], rd[i], dd[i]) : 0.f;
@@ -833,8 +841,8 @@ __device__ __forceinline__ void reverse_sweep(const BwdArgs& a) {
         qw[h][i] = qp[h][i] * rd[i];
       }
     }
-    if (seg == 0 && ci == 0 && a.dS0 != nullptr) accumulate_wide<T, D, HB>(R, sm, g, n, qw);     // dS0 is fp32 whatever the storage
-    else accumulate<T, D, HB>(R, sm, g, n, qw);
+    if (seg == 0 && ci == 0 && a.dS0 != nullptr) accumulate_wide<T, D, HB>(R, orows, g, n, qw);     // dS0 is fp32 whatever the storage
+    else accumulate<T, D, HB>(R, orows, g, n, qw);
     double rz = (((double)rzt[3] + (double)rzt[2]) + (double)rzt[1]) + (double)rzt[0];
     rz += lane_get(ln.x1, rz);
     rz += lane_get(ln.x2, rz);
@@ -843,15 +851,15 @@ __device__ __forceinline__ void reverse_sweep(const BwdArgs& a) {
     // ---- dv within the chunk: this wave's 16 value columns
     if constexpr (sizeof(T) == 2) {
       if constexpr (HB == 1) {
-        const unsigned char* p = sm + L::oSc + l * 8;
-        const uint2 f = St::template col_frag<D>(sm, g, n, w);
+        const unsigned char* p = sm + L::rSc + l * 8;
+        const uint2 f = St::template col_frag<D>(orows, g, n, w);
 #pragma unroll
         for (int k = 2; k >= 0; --k) dv = mfma_bf16_k16(*reinterpret_cast<const uint2*>(p + k * 512), f, dv);
       } else {
 #pragma unroll
         for (int h = 0; h < HB; h += 2) {
-          const unsigned char* p = sm + L::oSc + h * L::kScore + l * 8;
-          const bf16x8 f = make8(St::template col_frag<D>(sm + h * L::kSet, g, n, w), St::template col_frag<D>(sm + (h + 1) * L::kSet, g, n, w));
+          const unsigned char* p = sm + L::rSc + h * L::kScore + l * 8;
+          const bf16x8 f = make8(St::template col_frag<D>(orows + h * L::kSet, g, n, w), St::template col_frag<D>(orows + (h + 1) * L::kSet, g, n, w));
 #pragma unroll
           for (int k = 2; k >= 0; --k)
             dv = mfma_bf16(make8(*reinterpret_cast<const uint2*>(p + k * 512), *reinterpret_cast<const uint2*>(p + L::kScore + k * 512)), f, dv);
@@ -862,14 +870,14 @@ __device__ __forceinline__ void reverse_sweep(const BwdArgs& a) {
       for (int h = 0; h < HB; ++h) {
         doublex4 sc;
         if constexpr (L::kParts) {
-          const floatx4 rd = *reinterpret_cast<const floatx4*>(sm + L::oDen + (h * kC + 4 * g) * 4);
-          sc = sum_parts64<NW>(sm + L::oSc + h * L::kTile, HB * L::kTile, g, n);
+          const floatx4 rd = *reinterpret_cast<const floatx4*>(sm + L::rDen + (h * kC + 4 * g) * 4);
+          sc = sum_parts64<NW>(sm + L::rSc + h * L::kTile, HB * L::kTile, g, n);
 #pragma unroll
           for (int i = 0; i < 4; ++i) sc[i] = row <= 4 * g + i ? sc[i] * (double)rd[i] : 0.0;
         } else {
-          sc = *reinterpret_cast<const doublex4*>(sm + L::oSc + h * L::kScore + l * 32);
+          sc = *reinterpret_cast<const doublex4*>(sm + L::rSc + h * L::kScore + l * 32);
         }
-        const floatx4 f = f32_col_frag<D>(sm + h * L::kSet, g, n, w);
+        const floatx4 f = f32_col_frag<D>(orows + h * L::kSet, g, n, w);
 #pragma unroll
         for (int i = 0; i < 4; ++i) dvw = mfma_f64(sc[i], f[i], dvw);
       }
@@ -898,7 +906,10 @@ __device__ __forceinline__ void reverse_sweep(const BwdArgs& a) {
       St::store(dV, qd, offk, row0, g, n, 0, kC, dvv);
       St::store(dG, qd, offk, row0, g, n, 0, kC, dgv);
     }
-    __syncthreads();
+    // What is read after the barrier before dv (the scores, dO) is written next after the first barrier of the next chunk, or in the other
+    // turn's rows; everything else was read before it.  (Parts, and tokens one by one, are read up to here.)
+    if constexpr (L::kParts || kTokens) __syncthreads();
+    else orows = orows == sm ? sm + L::kO : sm;
     ci = ci1; hb = hb1;
   }
   if (seg == 0) {
