@@ -485,7 +485,12 @@ __global__ void __launch_bounds__(4 * D) gla_span_kernel(const WalkArgs a) {
 // Decode step (T = 1), state in place.  One block per (batch, kv head).  Thread t owns value column
 // t % D and a contiguous band of D*D/256 key channels of it, so a wave reads and writes whole 256-byte
 // rows of S; alpha, k, z and the query heads are staged in LDS and read as broadcasts; the partial
-// q.S sums of the 256/D bands are combined through LDS.  Query heads go four at a time.
+// q.S sums of the 256/D bands are combined through LDS.  Query heads go four at a time, a wave holds one of them and
+// forms its q.z.
+// Few sequences: bound by latency, so everything is requested at once, before the first barrier (state and queries behind one each,
+// and q.z summed by every thread, were three latencies in a row).  Many: by the state's traffic, 5.5 TB/s for 256.  With both convs, in
+// a graph, 32 query heads on 8 kv heads, us (before, the convs included, in brackets): head dim 64, one sequence 9.6 (11.4), 200 16.6 (19.5);
+// 128, one 11.2 (14.2), 64 18.3 (23.1), 200 42.7 (47.0).
 template <typename T, int D>
 __global__ void __launch_bounds__(256) gla_step_kernel(const T* __restrict__ q, const T* __restrict__ k,
                                                        const T* __restrict__ v, const T* __restrict__ g,
@@ -494,48 +499,64 @@ __global__ void __launch_bounds__(256) gla_step_kernel(const T* __restrict__ q, 
   constexpr int NPART = 256 / D;      // bands of key channels
   constexpr int RPT = D / NPART;      // key channels per thread
   constexpr int HT = 4;               // query heads per pass
-  __shared__ float sh_a[D], sh_k[D], sh_z[D], sh_q[HT][D], sh_part[HT][NPART][D];
-  const int tid = threadIdx.x;
+  constexpr int NQ = D / 64;          // channels of its head in a lane: l, l + 64
+  __shared__ float sh_a[D], sh_k[D], sh_z[D], sh_q[HT][D], sh_part[HT][NPART][D], sh_den[HT];
+  const int tid = threadIdx.x, w = tid >> 6, l = tid & 63;
+  const Lanes ln = make_lanes(l);
   const int bh = blockIdx.x;  // b * Hkv + hk
   const int b = bh / Hkv, hk = bh % Hkv;
   const int group = Hq / Hkv;
-  const T* kt = k + (size_t)bh * D;
-  const T* gt = g + (size_t)bh * D;
-  const T* vt = v + (size_t)bh * D;
+  const size_t head0 = (size_t)b * Hq + (size_t)hk * group;
   float* Sh = S + (size_t)bh * D * D;
-  float* zh = z + (size_t)bh * D;
-  if (tid < D) {
-    const float alpha = expf(gate_scale * log_sigmoid(ldf(gt + tid)));
-    const float kk = ldf(kt + tid);
-    const float zn = fmaf(alpha, zh[tid], kk);
-    sh_a[tid] = alpha;
-    sh_k[tid] = kk;
-    sh_z[tid] = zn;
-    zh[tid] = zn;
-  }
-  __syncthreads();
   const int col = tid % D, part = tid / D;
-  const float vv = ldf(vt + col);
+  float gl = 0.f, kk = 0.f, z0 = 0.f;
+  if (tid < D) {
+    gl = ldf(g + (size_t)bh * D + tid);
+    kk = ldf(k + (size_t)bh * D + tid);
+    z0 = z[(size_t)bh * D + tid];
+  }
+  float qv[NQ];
+  auto fetch_q = [&](int h0) {
+#pragma unroll
+    for (int i = 0; i < NQ; ++i) qv[i] = h0 + w < group ? ldf(q + (head0 + h0 + w) * D + 64 * i + l) : 0.f;
+  };
+  fetch_q(0);
+  const float vv = ldf(v + (size_t)bh * D + col);
   float sreg[RPT];
 #pragma unroll
   for (int r = 0; r < RPT; ++r) sreg[r] = Sh[(size_t)(part * RPT + r) * D + col];
+  if (tid < D) {
+    const float alpha = expf(gate_scale * log_sigmoid(gl));
+    const float zn = fmaf(alpha, z0, kk);
+    sh_a[tid] = alpha;
+    sh_k[tid] = kk;
+    sh_z[tid] = zn;
+    z[(size_t)bh * D + tid] = zn;
+  }
+  auto stage_q = [&] {
+#pragma unroll
+    for (int i = 0; i < NQ; ++i) sh_q[w][64 * i + l] = qv[i];
+    __syncthreads();
+  };
+  stage_q();
 #pragma unroll
   for (int r = 0; r < RPT; ++r) {
     const int c = part * RPT + r;
     sreg[r] = fmaf(sh_a[c], sreg[r], sh_k[c] * vv);
     Sh[(size_t)c * D + col] = sreg[r];
   }
-  for (int h0 = 0; h0 < group; h0 += HT) {
-    const int nh = min(HT, group - h0);
-    __syncthreads();  // previous pass is done with sh_q / sh_part
-    for (int e = tid; e < nh * D; e += 256) {
-      const int hh = e / D, c = e % D;
-      sh_q[hh][c] = ldf(q + ((size_t)b * Hq + hk * group + h0 + hh) * D + c);
-    }
-    __syncthreads();
+  for (int h0 = 0;;) {
+    float d = qv[0] * sh_z[l];
+#pragma unroll
+    for (int i = 1; i < NQ; ++i) d = fmaf(qv[i], sh_z[64 * i + l], d);
+    d = row16_sum(d);
+    d += lane_get(ln.x1, d);
+    d += lane_get(ln.x2, d);
+    if (l == 0) sh_den[w] = d + eps;
     float pn[HT] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int r = 0; r < RPT; ++r) {
+      if (D == 128 && r % 16 == 0) __builtin_amdgcn_sched_barrier(0);     // bounds the operands in flight
       const int c = part * RPT + r;
 #pragma unroll
       for (int hh = 0; hh < HT; ++hh) pn[hh] = fmaf(sh_q[hh][c], sreg[r], pn[hh]);
@@ -544,13 +565,17 @@ __global__ void __launch_bounds__(256) gla_step_kernel(const T* __restrict__ q, 
     for (int hh = 0; hh < HT; ++hh) sh_part[hh][part][col] = pn[hh];
     __syncthreads();
     // thread (hh = part', col): one output element each for up to 256 / D heads at a time
-    for (int hh = part; hh < nh; hh += NPART) {
-      float num = 0.f, den = eps;
+    for (int hh = part; hh < min(HT, group - h0); hh += NPART) {
+      float num = 0.f;
 #pragma unroll
       for (int pp = 0; pp < NPART; ++pp) num += sh_part[hh][pp][col];
-      for (int c = 0; c < D; ++c) den = fmaf(sh_q[hh][c], sh_z[c], den);
-      stf(o + ((size_t)b * Hq + hk * group + h0 + hh) * D + col, num / den);
+      stf(o + (head0 + h0 + hh) * D + col, num / sh_den[hh]);
     }
+    h0 += HT;
+    if (h0 >= group) break;
+    fetch_q(h0);
+    __syncthreads();  // this pass is done with sh_q / sh_part
+    stage_q();
   }
 }
 
