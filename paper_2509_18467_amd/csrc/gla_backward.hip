@@ -203,9 +203,10 @@ struct Sweep {
   static constexpr int kSet = kC * kRow;                          // one head's (or v's) rows of a chunk
   static constexpr int kO = HB * kSet;                            // dO rows of HB heads
   static constexpr int kPairs = 2 * HB * kC * 4;                  // two floats per head and token
-  // fp32 storage at head dim 64: dO . v (and the scores) formed by each wave over its own channels and added up, where otherwise
-  // every wave forms all of it (32768 tokens of 32 / 8 heads: 1077 us and 1256); at 128 the tiles would not fit
-  static constexpr bool kParts = sizeof(T) == 4 && D == 64;
+  // fp32 storage: dO . v (at head dim 64 also the scores, whose tiles would not fit at 128) formed by each wave over its own channels
+  // and added up, where otherwise every wave forms all of it in fp64 MFMAs, which bound these sweeps (32768 tokens of 32 / 8 heads of
+  // 64: 1077 us and 1256; of 128, dO . v alone, 4000 tokens 500 and 586, 500 tokens of 8 / 2 heads 243 and 287)
+  static constexpr bool kDaParts = sizeof(T) == 4, kParts = kDaParts && D == 64;
   static constexpr int kTile = 2048;
   // forward, twice, in turn, so that no wave waits for the others to be done with a chunk before it begins the next: dO rows | v rows |
   // 1 / den, den per head and token | one word per wave
@@ -216,19 +217,20 @@ struct Sweep {
   // once: partial q . u of every wave | parts of dO . v | the state before a chunk that goes token by token
   static constexpr int oPart = 2 * kTurn;
   static constexpr int oDa = oPart + NW * HB * kC * 4;
-  static constexpr int oX = oDa + (kParts ? NW * HB * kTile : 0);
+  static constexpr int oX = oDa + (kDaParts ? NW * HB * kTile : 0);
   static constexpr int kForward = oX + D * D * 4;
-  // reverse: dO rows (twice, in turn, where they are read last in a chunk) | v rows | 1 / den, dden | K' rows | R~ [channel][value
+  // reverse: dO rows (in bf16 storage twice, in turn: they are read last in a chunk) | v rows | 1 / den, dden | K' rows | R~ [channel][value
   // column] | Q' rows of HB heads | scores
-  static constexpr int rV = kParts ? kO : 2 * kO;
+  static constexpr int rV = kDaParts ? kO : 2 * kO;
   static constexpr int rDen = rV + kSet;
   static constexpr int rK = rDen + kPairs;
   static constexpr int rR = rK + kC * f32_row_bytes<D>();
   static constexpr int rQ = rR + D * f32_row_bytes<D>();
   static constexpr int rSc = rQ + HB * kC * f32_row_bytes<D>();
   static constexpr int kScore = sizeof(T) == 2 ? 3 * 512 : 2048;  // per head: three terms of 8 bytes per lane, or one fp64 tile
-  // (or parts of the scores, then of dO . v)
-  static constexpr int kReverse = rSc + (kParts ? 2 * NW * HB * kTile : HB * kScore);
+  // (or parts of the scores), then parts of dO . v
+  static constexpr int rDa = rSc + HB * (kParts ? NW * kTile : kScore);
+  static constexpr int kReverse = rDa + (kDaParts ? NW * HB * kTile : 0);
   static_assert(kForward <= 160 * 1024 / (D == 64 ? 2 : 1) && kReverse <= 160 * 1024 / (D == 64 ? 2 : 1));
 };
 
@@ -322,7 +324,7 @@ __global__ void __launch_bounds__(4 * D, 2) bwd_forward_kernel(const BwdArgs a) 
     St::template to_lds<D>(sm + L::oV, g, n, 16 * w, rv);      // (in every turn: the registers hold them for all of the chunk's heads)
 #pragma unroll
     for (int h = 0; h < HB; ++h) St::template to_lds<D>(sm + h * L::kSet, g, n, 16 * w, ro[h]);
-    if constexpr (L::kParts) {
+    if constexpr (L::kDaParts) {
       __builtin_amdgcn_wave_barrier();   // LDS serves one wave's requests in order: its rows are complete below
 #pragma unroll
       for (int h = 0; h < HB; ++h) dot_part64<D>(sm + L::oV, sm + h * L::kSet, w, g, n, lds + L::oDa + (w * HB + h) * L::kTile);
@@ -447,7 +449,7 @@ __global__ void __launch_bounds__(4 * D, 2) bwd_forward_kernel(const BwdArgs a) 
 #pragma unroll
       for (int h = 0; h < HB; ++h) {
         floatx4 da;    // [token i of v][token `row` of dO]
-        if constexpr (L::kParts) da = add64(floatx4{0.f, 0.f, 0.f, 0.f}, sum_parts64<NW>(lds + L::oDa + h * L::kTile, HB * L::kTile, g, n));
+        if constexpr (L::kDaParts) da = add64(floatx4{0.f, 0.f, 0.f, 0.f}, sum_parts64<NW>(lds + L::oDa + h * L::kTile, HB * L::kTile, g, n));
         else da = dot_rows<T, D, kWide>(sm + L::oV, sm + h * L::kSet, g, n);
         float am[4];
 #pragma unroll
@@ -682,8 +684,8 @@ __device__ __forceinline__ void reverse_sweep(const BwdArgs& a) {
     }
 #pragma unroll
     for (int h = 0; h < HB; ++h) St::template to_lds<D>(orows + h * L::kSet, g, n, 16 * w, ro[h]);
-    unsigned char* das = sm + L::rSc + NW * HB * L::kTile;     // parts of dO . v
-    if constexpr (L::kParts) {
+    unsigned char* das = sm + L::rDa;     // parts of dO . v
+    if constexpr (L::kDaParts) {
       __builtin_amdgcn_wave_barrier();
 #pragma unroll
       for (int h = 0; h < HB; ++h) dot_part64<D>(orows + h * L::kSet, sm + L::rV, w, g, n, das + (w * HB + h) * L::kTile);
@@ -829,7 +831,7 @@ __device__ __forceinline__ void reverse_sweep(const BwdArgs& a) {
       const floatx4 rd = *reinterpret_cast<const floatx4*>(sm + L::rDen + (h * kC + 4 * g) * 4);
       const floatx4 dd = *reinterpret_cast<const floatx4*>(sm + L::rDen + ((HB + h) * kC + 4 * g) * 4);
       floatx4 da;    // [token s of dO][token `row` of v]
-      if constexpr (L::kParts) da = add64(floatx4{0.f, 0.f, 0.f, 0.f}, sum_parts64<NW>(das + h * L::kTile, HB * L::kTile, g, n));
+      if constexpr (L::kDaParts) da = add64(floatx4{0.f, 0.f, 0.f, 0.f}, sum_parts64<NW>(das + h * L::kTile, HB * L::kTile, g, n));
       else da = dot_rows<T, D, kWide>(orows + h * L::kSet, sm + L::rV, g, n);
       float am[4];
 #pragma unroll
@@ -907,8 +909,8 @@ __device__ __forceinline__ void reverse_sweep(const BwdArgs& a) {
       St::store(dG, qd, offk, row0, g, n, 0, kC, dgv);
     }
     // What is read after the barrier before dv (the scores, dO) is written next after the first barrier of the next chunk, or in the other
-    // turn's rows; everything else was read before it.  (Parts, and tokens one by one, are read up to here.)
-    if constexpr (L::kParts || kTokens) __syncthreads();
+    // turn's rows; everything else was read before it.  (One turn of rows, parts, and tokens one by one, are read up to here.)
+    if constexpr (L::kDaParts || kTokens) __syncthreads();
     else orows = orows == sm ? sm + L::kO : sm;
     ci = ci1; hb = hb1;
   }
