@@ -488,7 +488,7 @@ __global__ void __launch_bounds__(4 * D) gla_span_kernel(const WalkArgs a) {
 // q.S sums of the 256/D bands are combined through LDS.  Query heads go four at a time, a wave holds one of them and
 // forms its q.z.
 // Few sequences: bound by latency, so everything is requested at once, before the first barrier (state and queries behind one each,
-// and q.z summed by every thread, were three latencies in a row).  Many: by the state's traffic, 5.5 TB/s for 256.  With both convs, in
+// and q.z summed by every thread, were three latencies in a row).  Many: by the state's traffic, about 5 TB/s for 256.  With both convs, in
 // a graph, 32 query heads on 8 kv heads, us (before, the convs included, in brackets): head dim 64, one sequence 9.6 (11.4), 200 16.6 (19.5);
 // 128, one 11.2 (14.2), 64 18.3 (23.1), 200 42.7 (47.0).
 template <typename T, int D>
