@@ -229,6 +229,11 @@ hipError_t launch_typed(const ConvParams& p, hipStream_t stream) {
   constexpr long long kWant = 512 * 256;
   const long long few = (p.W == 2 || p.W == 3) ? 50000 : 80000;
   if (p.T <= 4 || threads(16) < few) return launch(conv1d_causal_kernel<T, 4>, 4, 64);
+  // Strips of 8 between that and one round of 16: twice the waves, which read 11 rows for 8 (four taps, bf16, strips of 16 / 8: 5003
+  // tokens 15.7 / 14.3 us, 6000 16.7 / 15.5, 7000 18.1 / 17.8, 8100 19.2 / 19.2, 7 x 777 16.3 / 14.8; 4096 tokens, strips of 4 / 8,
+  // 12.0 / 12.5; fp32 storage, where they move twice the bytes, the same within 1 %).
+  if constexpr (sizeof(T) == 2)
+    if (p.W == 4 && threads(16) < kWant) return launch(conv1d_causal_kernel<T, 8>, 8, 64);
   if (threads(64) >= kWant) return launch(conv1d_causal_kernel<T, 64>, 64, 256);
   if (threads(32) >= kWant) return launch(conv1d_causal_kernel<T, 32>, 32, 256);
   return launch(conv1d_causal_kernel<T, 16>, 16, 256);
