@@ -76,7 +76,7 @@ hipError_t launch_gla_chunk(const ChunkParams& p, hipStream_t stream) {
   // 50.6 / 52.7.
   a.ordered = p.seq_start && p.B <= 64 && walks * std::max(1, group / 4) > 256 && a.seg_len > 128;
   const int passes = group % 4 == 0 || a.most == 1 ? 1 : group / 4 + (group % 4 + 1) / 2;
-  a.fold = nseg > 1 && nseg * passes <= (p.d == 64 ? std::min(12, 8 + heads / 8) : std::min(7, 3 + heads / 16));
+  a.fold = nseg > 1 && nseg * passes <= (p.d == 64 ? std::min(chunk::kFoldMost<64> + 1, 8 + heads / 8) : std::min(chunk::kFoldMost<128> + 1, 3 + heads / 16));
   a.gate_scale = p.gate_scale; a.eps = p.eps;
   const int mode = !p.fuse_conv ? chunk::kPlain : (p.phi == 1 ? chunk::kConvElu : chunk::kConvId);
   const chunk::TraceEvents ev{p.ev_start, p.ev_stop};

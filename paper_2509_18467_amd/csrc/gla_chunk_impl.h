@@ -86,6 +86,9 @@ struct ChunkArgs {
   float gate_scale, eps;
 };
 
+// most segments before one whose contributions the output pass folds
+template <int D> constexpr int kFoldMost = D == 64 ? 11 : 6;
+
 template <int D, int GR>
 struct Geo {
   static constexpr int NW = D / 16;          // waves per team: one per 16 value columns
@@ -558,6 +561,17 @@ __global__ void __launch_bounds__(D * 4, D == 64 ? 2 : 1)
     else
       for (int j = tid; j < nseg - 1; j += G::TEAM) live_any |= a.seg_live[slot0 + j];
   }
+  // ... and z and decay of every segment before this one
+  constexpr int kZd = OUTPUT ? (kFoldMost<D> * 2 * D + G::TEAM - 1) / G::TEAM : 1;
+  static_assert(!OUTPUT || kFoldMost<D> * 2 * D * 4 <= G::kWl);
+  float zraw[kZd];
+  if (OUTPUT && a.fold) {
+#pragma unroll
+    for (int j = 0; j < kZd; ++j) {
+      const int e = tid + j * G::TEAM;
+      zraw[j] = e < seg * 2 * D ? a.ws[(slot0 + e / (2 * D)) * G::kSlot + D * D + e % (2 * D)] : 0.f;
+    }
+  }
 
   float* wl = reinterpret_cast<float*>(smem + G::kWl);
   // conv weights as fp32 [head][channel][4 taps], taps beyond W zero; row GR is the key head.  All of a thread's loads are issued
@@ -665,46 +679,60 @@ __global__ void __launch_bounds__(D * 4, D == 64 ? 2 : 1)
               floatx4{bf_lo(wraw[j].x) * wscale, bf_hi(wraw[j].x) * wscale, bf_lo(wraw[j].y) * wscale, bf_hi(wraw[j].y) * wscale};
       }
     }
-    if (OUTPUT && a.fold) {
-      // state <- decay (.) state + contribution, segment by segment (in the scan's order); at head dim 64 the next segment's
-      // slot travels meanwhile (at 128 there are no registers for it)
-      struct Slot { float s[G::RT][4]; floatx4 z[G::RT], dec[G::RT]; };
-      auto load_slot = [&](int j, Slot& o) {
-        const float* slot = a.ws + (slot0 + j) * G::kSlot;
+    if (OUTPUT && first < seg) {
+      // state <- decay (.) state + contribution, segment by segment (in the scan's order).  z and the decays, alike in 16 lanes, come
+      // through LDS, all predecessors' at once; S goes straight to its lanes, the next segment's on its way meanwhile.  (With z and
+      // decays in registers too, 64 of the 96 a slot took at head dim 128: spills there, and at 64 226 registers instead of 158 in the
+      // one-head kernels, two workgroups a compute unit instead of three: 200 sequences of 64 tokens, 8 heads, 27.5 us, now 23.6;
+      // one of 130 tokens of 8 heads of 128, 22.8 and 21.8.)
+      float* zd = reinterpret_cast<float*>(smem);      // [predecessor][z | decay]: free until the first granule
 #pragma unroll
-        for (int rt = 0; rt < G::RT; ++rt) {
-          const int c = 16 * rt + 4 * g4;
-          o.z[rt] = *reinterpret_cast<const floatx4*>(slot + D * D + c);
-          o.dec[rt] = *reinterpret_cast<const floatx4*>(slot + D * D + D + c);
+      for (int j = 0; j < kZd; ++j) {
+        const int e = tid + j * G::TEAM;
+        if (e < seg * 2 * D) zd[e] = zraw[j];
+      }
+      struct Rows { float s[4][4]; };      // 4 row tiles of S: a slot at head dim 64, half of one at 128
+      auto load = [&](int j, int r0, Rows& o) {
+        // (a descriptor: one offset register for all rows)
+        const __amdgpu_buffer_rsrc_t slot =
+            __builtin_amdgcn_make_buffer_rsrc((void*)(a.ws + (slot0 + j) * G::kSlot), 0, D * D * 4, 0x00020000);
 #pragma unroll
-          for (int i = 0; i < 4; ++i) o.s[rt][i] = slot[(size_t)(c + i) * D + 16 * w + n];
-        }
+        for (int rt = 0; rt < 4; ++rt)
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            o.s[rt][i] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(slot, (4 * g4 * D + 16 * w + n) * 4, (16 * (r0 + rt) + i) * D * 4, 0));
       };
-      auto add_slot = [&](const Slot& o) {
+      auto add = [&](int j, int r0, const Rows& o) {
 #pragma unroll
-        for (int rt = 0; rt < G::RT; ++rt)
+        for (int rt = 0; rt < 4; ++rt) {
+          const floatx4 dz = *reinterpret_cast<const floatx4*>(zd + j * 2 * D + 16 * (r0 + rt) + 4 * g4);
+          const floatx4 dec = *reinterpret_cast<const floatx4*>(zd + j * 2 * D + D + 16 * (r0 + rt) + 4 * g4);
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
-            Sacc[rt][0][i] = fmaf(o.dec[rt][i], Sacc[rt][0][i], o.s[rt][i]);
-            Sacc[rt][G::CT][i] = fmaf(o.dec[rt][i], Sacc[rt][G::CT][i], o.z[rt][i]);
+            Sacc[r0 + rt][0][i] = fmaf(dec[i], Sacc[r0 + rt][0][i], o.s[rt][i]);
+            Sacc[r0 + rt][G::CT][i] = fmaf(dec[i], Sacc[r0 + rt][G::CT][i], dz[i]);
           }
+        }
       };
-      Slot x, y;
+      Rows x, y;
+      load(first, 0, x);
+      __syncthreads();
       if constexpr (D == 64) {
-        if (first < seg) load_slot(first, x);
 #pragma unroll 1
         for (int j = first; j < seg; j += 2) {
-          load_slot(min(j + 1, seg - 1), y);
-          add_slot(x);
+          load(min(j + 1, seg - 1), 0, y);
+          add(j, 0, x);
           if (j + 1 >= seg) break;
-          load_slot(min(j + 2, seg - 1), x);
-          add_slot(y);
+          load(min(j + 2, seg - 1), 0, x);
+          add(j + 1, 0, y);
         }
       } else {
 #pragma unroll 1
         for (int j = first; j < seg; ++j) {
-          load_slot(j, x);
-          add_slot(x);
+          load(j, 4, y);
+          add(j, 0, x);
+          load(min(j + 1, seg - 1), 0, x);
+          add(j, 4, y);
         }
       }
     }

@@ -1,0 +1,59 @@
+"""What the compiler made of the prefill's kernels, read from the built library: registers, spills and loops over lanes that a
+change of their prologue once brought in without any result changing.  CPU only."""
+import os
+import re
+import shutil
+import subprocess
+
+import msgpack
+import pytest
+
+from paper_2509_18467_amd import lawcat
+
+OBJDUMP = shutil.which("llvm-objdump") or "/opt/rocm/llvm/bin/llvm-objdump"
+MAGIC = b"__CLANG_OFFLOAD_BUNDLE__"
+
+
+def code_objects():
+    """The gfx950 code objects (ELF images) inside the library, one per translation unit."""
+    blob = open(lawcat.LIB_PATH, "rb").read()
+    at = blob.find(MAGIC)
+    while at >= 0:
+        p = at + len(MAGIC)
+        n, p = int.from_bytes(blob[p:p + 8], "little"), p + 8
+        for _ in range(n):
+            offset, size, idlen = (int.from_bytes(blob[p + 8 * i:p + 8 * i + 8], "little") for i in range(3))
+            if b"gfx950" in blob[p + 24:p + 24 + idlen]:
+                yield blob[at + offset:at + offset + size]
+            p += 24 + idlen
+        at = blob.find(MAGIC, p)
+
+
+@pytest.fixture(scope="module")
+def kernels():
+    """Metadata of every kernel, under its demangled name without arguments."""
+    found = {}
+    for image in code_objects():
+        # the note of the code object: name size 7, description size, type 32 (metadata), "AMDGPU"
+        m = re.search(rb"\x07\0\0\0(....)\x20\0\0\0AMDGPU\0\0", image, re.S)
+        if m is None:
+            continue
+        meta = msgpack.unpackb(image[m.end():m.end() + int.from_bytes(m.group(1), "little")], strict_map_key=False)
+        found.update({k[".name"]: k for k in meta["amdhsa.kernels"]})
+    assert found
+    return found
+
+
+def chunk(kernels, d, heads, mode, output=True):
+    name = f"gla_chunk_kernelILi{d}ELi{heads}ELi{mode}ELb{int(output)}E"
+    one, = [k for n, k in kernels.items() if name in n]
+    return one
+
+
+# (modes: 0 = queries and keys as they are, 1 = conv, 2 = conv and 1 + ELU)
+@pytest.mark.parametrize("heads", [1, 2])
+def test_three_workgroups_a_compute_unit(kernels, heads):
+    """Head dim 64, few query heads, no conv: 512 registers a lane of a SIMD, in granules of 8, for three waves."""
+    assert chunk(kernels, 64, heads, 0)[".vgpr_count"] <= 168
+
+
