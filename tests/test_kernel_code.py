@@ -62,3 +62,20 @@ def test_three_workgroups_a_compute_unit(kernels, heads):
 @pytest.mark.parametrize("heads,mode,most", [(1, 0, 0), (1, 1, 0), (1, 2, 0), (2, 0, 0), (2, 1, 27), (2, 2, 0)])
 def test_spills(kernels, heads, mode, most):
     assert chunk(kernels, 128, heads, mode)[".vgpr_spill_count"] <= most
+
+
+@pytest.mark.skipif(not os.path.exists(OBJDUMP), reason="no disassembler")
+def test_uniform_descriptors(tmp_path):
+    """No load of the prefill's kernels looks for lanes with equal descriptors: that takes four v_readfirstlane per load, hundreds a
+    kernel where the workgroup's sequence and segment are not known to be uniform, about a dozen otherwise."""
+    seen = 0
+    for i, image in enumerate(code_objects()):
+        if b"gla_chunk_kernel" not in image:
+            continue
+        path = tmp_path / f"{i}.o"
+        path.write_bytes(image)
+        text = subprocess.run([OBJDUMP, "-d", str(path)], check=True, capture_output=True, text=True).stdout
+        for name, body in re.findall(r"^[0-9a-f]+ <(\S*gla_chunk_kernel\S*)>:\n(.*?)(?=^\S|\Z)", text, re.S | re.M):
+            seen += 1
+            assert body.count("v_readfirstlane_b32") < 40, name
+    assert seen >= 24
