@@ -10,6 +10,11 @@ hipError_t launch_d128(const ChunkArgs& a, int group, int mode, hipStream_t stre
 
 bool chunk_path_supports(int group) { return group >= 1 && group <= 64; }
 
+// Most segments of a head whose contributions the output pass folds in one launch (see launch_gla_chunk).
+static int fold_most(int heads, int d) {
+  return d == 64 ? std::min(chunk::kFoldMost<64> + 1, 8 + heads / 8) : std::min(chunk::kFoldMost<128> + 1, 3 + heads / 16);
+}
+
 ChunkPlan make_chunk_plan(int B, int T, int Hq, int Hkv, int d, int carry_mode, int segment) {
   ChunkPlan p{};
   const int heads = B * Hkv;
@@ -20,19 +25,26 @@ ChunkPlan make_chunk_plan(int B, int T, int Hq, int Hkv, int d, int carry_mode, 
     seg_len = segment;
   } else {
     // enough workgroups (of up to four query heads each) to fill 256 compute units once (two 4-wave teams per unit at head dim
-    // 64, one 8-wave team at 128).  Segments of two granules (128 tokens) at least, except where even those would leave
-    // more than half of the chip without a workgroup: short sequences are bound by the serial work of one
-    // workgroup, and one-granule segments halve it (T = 1K .. 2K: 31 -> 23 us at head dim 64, 51 -> 41 at 128)
+    // 64, one 8-wave team at 128), in segments of two granules (128 tokens) at least ...
     const int slots = d == 64 ? 512 : 256;
     const long long groups = (long long)heads * std::max(1, Hq / Hkv / 4);   // workgroups per segment
     const int want = (int)((slots + groups - 1) / groups);
     seg_len = (T + want - 1) / want;
     seg_len = (seg_len + 63) / 64 * 64;
     if (seg_len < 128) {
-      // (not where segments of 128 leave few contributions per head, which the output pass folds, and keep half of the compute
-      // units busy: one granule / two, 4 x 1000 tokens, 32 query heads on 8 of 64, 36 / 34 us, 4 x 500, of 128, 47 / 43)
-      const int n = (T + 127) / 128;
-      seg_len = n * groups * 2 <= slots && (n > 8 || n * heads <= (d == 64 ? 160 : 112)) ? 64 : 128;
+      // ... or of one granule, which halves the serial work of a workgroup, where they still fit the chip at once, unless
+      //   two granules hold the whole sequence: no state pass then (one granule / two, 128 tokens, 8 heads of 64 x 2 15.3 / 14.7 us, x 24
+      //     20.2 / 16.2, of 128 23.1 / 20.2, 30.9 / 21.9 x 16);
+      //   at head dim 64 twice the contributions to fold cost more than the granule saves, which grows with both their number and the
+      //     workgroups that read them: 8 heads x 3, 512 tokens 22.1 / 23.8, 800 27.4 / 23.9; x 5, 448 22.1 / 22.7, 512 27.2 / 24.4; x 8, 300
+      //     21.1 / 22.1, 500 30.0 / 25.7; 32 on 8 x 12, 190 25.4 / 27.3, 390 39.1 / 37.4;
+      //   at head dim 128 they would be a granule too many to fold, and half as many are not: 32 on 8 x 8, 256 tokens 39.3 / 41.7, 300
+      //     53.8 / 45.4; 8 x 3, 380 38.6 / 36.9, 600, where both take the scan, 39.7 / 45.2.
+      // (Few heads leave most of the chip idle: there the shorter walk is the better one at any length, 8 x 2, 1000 tokens 24.3 / 26.5,
+      // of 128 40.0 / 45.0.)
+      const int one = (T + 63) / 64, two = (T + 127) / 128, fold = fold_most(heads, d);
+      const bool pays = heads <= 16 || (d == 64 ? (long long)one * (heads + 18) <= 460 : one <= fold || two > fold);
+      seg_len = two > 1 && one * groups <= slots && pays ? 64 : 128;
     }
   }
   p.seg_len = seg_len;
@@ -76,7 +88,7 @@ hipError_t launch_gla_chunk(const ChunkParams& p, hipStream_t stream) {
   // 50.6 / 52.7.
   a.ordered = p.seq_start && p.B <= 64 && walks * std::max(1, group / 4) > 256 && a.seg_len > 128;
   const int passes = group % 4 == 0 || a.most == 1 ? 1 : group / 4 + (group % 4 + 1) / 2;
-  a.fold = nseg > 1 && nseg * passes <= (p.d == 64 ? std::min(chunk::kFoldMost<64> + 1, 8 + heads / 8) : std::min(chunk::kFoldMost<128> + 1, 3 + heads / 16));
+  a.fold = nseg > 1 && nseg * passes <= fold_most(heads, p.d);
   a.gate_scale = p.gate_scale; a.eps = p.eps;
   const int mode = !p.fuse_conv ? chunk::kPlain : (p.phi == 1 ? chunk::kConvElu : chunk::kConvId);
   const chunk::TraceEvents ev{p.ev_start, p.ev_stop};

@@ -1,0 +1,25 @@
+"""How many segments the prefill cuts a sequence into, on both sides of every line of the rule for short ones (segments of 64 tokens or
+of 128), read from the workspace it asks for.  CPU only."""
+import pytest
+
+from paper_2509_18467_amd import lawcat
+
+
+def segments(d, Hq, Hkv, B, T):
+    need = lawcat.workspace_bytes(lawcat.make_desc(B, T, Hq, Hkv, d), lawcat.CALL_LAYER_PREFILL)
+    slot = B * Hkv * ((d * d + 2 * d) * 4 + 4)
+    assert need % slot == 0
+    return need // slot or 1
+
+
+@pytest.mark.parametrize("d,Hq,Hkv,B,T,n", [
+    # one segment of 128 tokens needs no state pass
+    (64, 8, 8, 1, 64, 1), (64, 8, 8, 2, 65, 1), (64, 32, 8, 16, 128, 1), (64, 32, 8, 1, 129, 3), (128, 8, 8, 4, 128, 1), (128, 8, 8, 4, 129, 3),
+    # head dim 64: by segments and heads
+    (64, 8, 8, 2, 1000, 16), (64, 8, 8, 3, 600, 10), (64, 8, 8, 3, 800, 7), (64, 8, 8, 5, 448, 7), (64, 8, 8, 5, 512, 4), (64, 32, 8, 8, 260, 5),
+    (64, 32, 8, 8, 390, 4), (64, 8, 8, 16, 130, 3), (64, 8, 8, 16, 200, 2), (64, 32, 4, 12, 300, 5), (64, 32, 4, 12, 390, 4),
+    # head dim 128: by what the output pass folds
+    (128, 8, 8, 2, 1000, 16), (128, 8, 8, 3, 256, 4), (128, 8, 8, 3, 380, 3), (128, 8, 8, 3, 600, 10), (128, 32, 8, 8, 130, 3), (128, 32, 8, 8, 256, 4),
+    (128, 32, 8, 8, 300, 3), (128, 32, 8, 12, 130, 2), (128, 32, 4, 6, 300, 3)])
+def test_segments(d, Hq, Hkv, B, T, n):
+    assert segments(d, Hq, Hkv, B, T) == n
