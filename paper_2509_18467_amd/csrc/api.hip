@@ -133,6 +133,7 @@ ChunkPlan varlen_plan(const lawcat_desc* d, const int32_t* seq_start) {
     while (p.seg_len < whole && groups(p.seg_len) > slots) p.seg_len += 64;
   }
   p.nseg = cut_sequence(longest, p.seg_len).nseg;
+  for (int i = 0; i < d->B; ++i) p.segments += cut_sequence(seq_start[i + 1] - seq_start[i], p.seg_len).nseg;
   p.per_head = (int)((total + p.seg_len - 1) / p.seg_len) + d->B - 1;
   p.workspace_bytes = p.nseg > 1 ? (size_t)d->B * d->Hkv * p.nseg * ((d->dk * d->dk + 2 * d->dk) * sizeof(float) + sizeof(int)) : 0;
   return p;

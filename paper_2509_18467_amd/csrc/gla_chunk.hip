@@ -73,7 +73,7 @@ hipError_t launch_gla_chunk(const ChunkParams& p, hipStream_t stream) {
   // two would be 384 workgroups, 21.8 / 22.6 / 27 (on 4 kv heads); of 128, 64 tokens 19.2 / 16.6 / 14.2, 1000 36.6 / 33.9 / 41.9 (512).
   // (Not in place: a workgroup would read a start state that another one replaces.)
   const int nseg = p.plan.nseg, heads = p.B * p.Hkv, group = p.Hq / p.Hkv;
-  const long long walks = p.seq_start ? (long long)p.Hkv * p.plan.per_head : (long long)nseg * heads;
+  const long long walks = p.seq_start ? (long long)p.Hkv * p.plan.segments : (long long)nseg * heads;
   a.most = 4;
   if (!(p.S0 == p.S_out || p.z0 == p.z_out)) a.most = walks * group <= 256 ? 1 : walks * ((group + 1) / 2) <= 256 ? 2 : 4;
   // With few segments the output pass folds its predecessors' contributions itself instead of waiting for a scan: a launch less,
@@ -82,11 +82,22 @@ hipError_t launch_gla_chunk(const ChunkParams& p, hipStream_t stream) {
   // 19.2 / 18.7, 10 20.6 / 21.2; 32 on 8 3 segments 18.0 / 14.9, 8 20.5 / 19.5, 10 21.6 / 21.9; x 4 4 segments 26.4 / 20.3, 10
   // 35.2 / 32.0, 12 44.6 / 41.3, 16 36.1 / 38.2; x 16 8 segments 76 / 59.  Of 128, 8 heads, 3 segments 23.6 / 22.1, 4 26.2 / 27.5; x 4
   // 4 segments 40.1 / 33.6, 8 46.6 / 46.5; 32 on 4 x 16 4 segments 74 / 64, 8 121 / 149.
-  // Packed batches: by the length of the segments where there are more workgroups than compute units and they run long enough to repay
-  // finding out (0.7 us a pass).  us a call in order / by length, 32 query heads on 8 kv heads: of 64, 24 sequences, 25947 tokens 142 / 109,
-  // 8 sequences, 29399 tokens 112.5 / 106.6, 12 sequences, 2064 tokens 28.2 / 30.4; of 128, 16 sequences, 16917 tokens 235 / 175, 12, 2064
-  // 50.6 / 52.7.
-  a.ordered = p.seq_start && p.B <= 64 && walks * std::max(1, group / 4) > 256 && a.seg_len > 128;
+  // Packed batches (see find_place): a grid of all sequences by the longest one's segments where it has no workgroup without work, or
+  // they all find a place on the chip at once: to find its segment costs a workgroup of the other grids 0.3 to 1 us a pass.  Else in
+  // order of the rows, where that grid fits, else by length.  us a call by sequence / in order / by length, 32 query heads on 8 kv heads:
+  // of 64, 128 x 200 tokens 96 / 122 / 120, 30 x 333 47 / 65 / 52, 12 of 60 to 280 24.2 / 26.4 / 29.3; 4 short ones beside one of 2000 47.5 /
+  // 29.8 / 30.9, 12 of 88 to 1439 54.9 / 39.2 / 41.8; 24 of 101 to 3364 190 / 115 / 95, 48 of 204 to 691 135 / 120 / 97.  Of 128, 16 of 480 to
+  // 520 84 / 128 / 88; 3 of 337 to 855 63 / 47 / 48; 24 of 300 to 498 161 / 146 / 106.  (At head dim 64 a few workgroups too many, which leave
+  // at once, cost less than to order them: 24 of 300 to 498, 9/8 of the chip, 48.8 / 50.1 / 51.1; of 128, 12 of 208 to 352, 63 / 71 / 50.)
+  a.places = chunk::kDirect;
+  if (p.seq_start) {
+    const long long places = p.d == 64 ? 512 : 256, parts = std::max(1, group / a.most);     // at once on the chip; workgroups per segment
+    const long long direct = (long long)p.B * nseg, in_order = p.plan.per_head;
+    if (direct <= p.plan.segments || direct * p.Hkv * parts <= places) a.places = chunk::kDirect;
+    else if (p.B > 64) a.places = direct <= in_order ? chunk::kDirect : chunk::kInOrder;
+    else if (in_order * p.Hkv * parts <= places) a.places = chunk::kInOrder;
+    else a.places = p.d == 64 && direct * p.Hkv * parts <= places * 9 / 8 ? chunk::kDirect : chunk::kByLength;
+  }
   const int passes = group % 4 == 0 || a.most == 1 ? 1 : group / 4 + (group % 4 + 1) / 2;
   a.fold = nseg > 1 && nseg * passes <= fold_most(heads, p.d);
   a.gate_scale = p.gate_scale; a.eps = p.eps;

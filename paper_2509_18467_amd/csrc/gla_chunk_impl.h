@@ -71,7 +71,7 @@ struct ChunkArgs {
   int* seg_live;   // one per workspace slot: written by the state pass, 0 = the segment's total decay is exactly zero in every channel
   // Sequences of different lengths packed along the token axis: device array of B + 1 row offsets, or null for B
   // sequences of T tokens each (nseg segments of seg_len, grid (nseg, B * Hkv)).  With it, T is the longest length and nseg the segment
-  // count of that length: every sequence has nseg workspace slots, is cut by cut_sequence(), and find_place() says which workgroup
+  // count of that length: every sequence has nseg workspace slots, is cut by cut_sequence(), and `places` says which workgroup
   // takes which segment.
   const int* seq_start;
   int B, T, Hq, Hkv, W;
@@ -79,15 +79,18 @@ struct ChunkArgs {
   int qh0;     // first query head, within its group, that this launch of the output pass covers (its z index: GR heads each)
   int most;    // most query heads that a workgroup of the output pass takes: 4, 2 or 1
   int seg_len, nseg;
-  int per_head;     // packed batches: bound of the segments per kv head, whatever the lengths
+  int per_head;     // packed batches: workgroups per kv head
   double inv_len;   // 1 / seg_len
-  int ordered;      // packed batches: workgroups by the length of their segments
+  int places;       // which workgroup takes which segment
   int fold;    // few segments: the output pass folds its predecessors' contributions itself, there is no scan
   float gate_scale, eps;
 };
 
 // most segments before one whose contributions the output pass folds
 template <int D> constexpr int kFoldMost = D == 64 ? 11 : 6;
+
+// which workgroup takes which segment (see find_place)
+constexpr int kDirect = 0, kInOrder = 1, kByLength = 2;
 
 template <int D, int GR>
 struct Geo {
@@ -442,21 +445,26 @@ struct Kernel {
 // x / most for 0 <= x < 2^31, most >= 64: the quotient is off by less than 2^-20, and x + 1/2 lies 1 / (2 most) from the next whole multiple
 __device__ inline int over(int x, double inv_most) { return (int)(((double)x + 0.5) * inv_most); }
 
-// What workgroup (x, hk) of a packed batch works on (uniform): sequence and segment; seg < 0: nothing.  64 lanes look at 64 sequences at a
-// time.
-//   in order (few workgroups): sequence b has those from first row / seg_len + b on (no more tokens lie before it than first row / seg_len
-//     segments hold, and each of the b sequences rounds up once, so these ranges do not overlap, whatever the lengths; a few at
-//     their ends have nothing to do).
-//   by length (`ordered`, up to 64 sequences, one per lane): the longest segments first (workgroups are placed in order, and those
+// What workgroup (x, y) of a packed batch works on (uniform): sequence and segment; seg < 0: nothing.
+//   kDirect: segment x of sequence y / Hkv, as where all sequences are equally long; shorter ones leave workgroups without work.
+//   kInOrder: 64 lanes look at 64 sequences at a time: sequence b has those from first row / seg_len + b on (no more tokens lie before it
+//     than first row / seg_len segments hold, and each of the b sequences rounds up once, so these ranges do not overlap, whatever the
+//     lengths; a few at their ends have nothing to do).
+//   kByLength (up to 64 sequences, one per lane): the longest segments first (workgroups are placed in order, and those
 //     past what the chip holds at once should be the shortest ones), a kv head's after the other's, an odd number each, so that the
 //     segments of all heads spread alike over the eight dies, and no workgroup without work among them: one that leaves at
 //     once still takes a place in turn, and those behind it wait for that place (24 sequences, 26K tokens: the last began 57 us late).
 struct Place { int hk, b, seg, T, nseg, len, row0; };
+__device__ inline void cut_place(const ChunkArgs& a, Place& p) {
+  // cut_sequence(), with a division only where it matters
+  p.nseg = over(p.T + a.seg_len - 1, a.inv_len);
+  if (p.nseg > 1 && a.seg_len > 64) p.len = cut_sequence(p.T, a.seg_len).len;
+}
 __device__ inline Place find_place(const ChunkArgs& a, int l) {
   const int* seq_start = a.seq_start;
   int row = 0, end = 0, at, lane;
-  Place p{(int)blockIdx.y, 0, -1, 0, 0, 0, 0};
-  if (a.ordered) {
+  Place p{(int)blockIdx.y, 0, (int)blockIdx.x, 0, 0, a.seg_len, 0};
+  if (a.places == kByLength) {
     int n = 0;
     float len = 0.f;       // about how long its segments are
     if (l < a.B) {
@@ -476,7 +484,10 @@ __device__ inline Place find_place(const ChunkArgs& a, int l) {
     const unsigned odd = all | 1;
     p.hk = blockIdx.x / odd;
     const int e = blockIdx.x - p.hk * odd;
-    if (p.hk >= a.Hkv || e >= all) return p;
+    if (p.hk >= a.Hkv || e >= all) {
+      p.seg = -1;
+      return p;
+    }
     lane = __builtin_ctzll(__builtin_amdgcn_ballot_w64(first <= e && e < first + n));
     p.seg = e - __builtin_amdgcn_readlane(first, lane);
     p.b = lane;
@@ -496,13 +507,9 @@ __device__ inline Place find_place(const ChunkArgs& a, int l) {
     p.b = lo;
     p.seg = e - __builtin_amdgcn_readlane(at, lane);
   }
-  const int row0 = __builtin_amdgcn_readlane(row, lane);
-  p.row0 = row0;
-  p.T = __builtin_amdgcn_readlane(end, lane) - row0;
-  // cut_sequence(), with a division only where it matters
-  p.nseg = over(p.T + a.seg_len - 1, a.inv_len);
-  p.len = a.seg_len;
-  if (p.nseg > 1 && a.seg_len > 64) p.len = cut_sequence(p.T, a.seg_len).len;
+  p.row0 = __builtin_amdgcn_readlane(row, lane);
+  p.T = __builtin_amdgcn_readlane(end, lane) - p.row0;
+  cut_place(a, p);
   return p;
 }
 
@@ -524,20 +531,27 @@ __global__ void __launch_bounds__(D * 4, D == 64 ? 2 : 1)
   const int n = l & 15;     // MFMA row/column within a tile
   // this workgroup's sequence (first row in the packed tensors, length, segments; token indices below are relative to row0), kv head
   // and segment
-  int seg = blockIdx.x, b, hk, T = a.T, nseg = a.nseg, seg_len = a.seg_len;
+  Place p{0, 0, (int)blockIdx.x, a.T, a.nseg, a.seg_len, 0};
   size_t row0;
-  if (a.seq_start == nullptr) {
-    b = blockIdx.y / a.Hkv; hk = blockIdx.y % a.Hkv;
-    row0 = (size_t)b * a.T;
+  if (__builtin_expect(a.places == kDirect, 1)) {
+    p.b = blockIdx.y / a.Hkv;
+    p.hk = blockIdx.y - p.b * a.Hkv;
+    row0 = (size_t)p.b * a.T;
+    if (a.seq_start != nullptr) {
+      p.row0 = a.seq_start[p.b];
+      p.T = a.seq_start[p.b + 1] - p.row0;
+      cut_place(a, p);
+      row0 = (size_t)p.row0;
+    }
   } else {
-    const Place p = find_place(a, l);
+    p = find_place(a, l);
     if (p.seg < 0) return;      // (the whole team, before the first barrier)
-    // (left in vector registers, as divisions leave them, they make every load of the state pass without conv a loop over lanes that
-    // looks for equal descriptors: 16384 tokens, 8 heads, 13.5 us instead of 10.7)
-    auto uniform = [](int x) { return __builtin_amdgcn_readfirstlane(x); };
-    hk = uniform(p.hk); b = uniform(p.b); seg = uniform(p.seg); T = uniform(p.T); nseg = uniform(p.nseg); seg_len = uniform(p.len);
-    row0 = (size_t)uniform(p.row0);
+    row0 = (size_t)__builtin_amdgcn_readfirstlane(p.row0);
   }
+  // (left in vector registers, as divisions leave them, they make every load of the state pass without conv a loop over lanes that
+  // looks for equal descriptors: 16384 tokens, 8 heads, 13.5 us instead of 10.7)
+  auto uniform = [](int x) { return __builtin_amdgcn_readfirstlane(x); };
+  const int hk = uniform(p.hk), b = uniform(p.b), seg = uniform(p.seg), T = uniform(p.T), nseg = uniform(p.nseg), seg_len = uniform(p.len);
   const int bh = b * a.Hkv + hk;
   const size_t slot0 = (size_t)bh * a.nseg;      // workspace slot of this head's first segment
   const int qh0 = OUTPUT ? a.qh0 + (int)blockIdx.z * GR : 0;   // first query head, within its group, of this workgroup
@@ -1033,7 +1047,8 @@ template <int D, int GR, int MODE>
 hipError_t launch_all(const ChunkArgs& a, int parts, hipStream_t stream, bool with_state_pass, const TraceEvents& ev) {
   using G = Geo<D, GR>;
   const int heads = a.B * a.Hkv;
-  const int x = !a.seq_start ? a.nseg : a.ordered ? (a.per_head | 1) * a.Hkv : a.per_head | 1, y = !a.seq_start ? heads : a.ordered ? 1 : a.Hkv;
+  const bool direct = !a.seq_start || a.places == kDirect;
+  const int x = direct ? a.nseg : a.places == kByLength ? (a.per_head | 1) * a.Hkv : a.per_head | 1, y = direct ? heads : a.places == kByLength ? 1 : a.Hkv;
   hipError_t e;
   if (a.nseg > 1 && with_state_pass) {
     // GR = 0: key side only
@@ -1041,7 +1056,7 @@ hipError_t launch_all(const ChunkArgs& a, int parts, hipStream_t stream, bool wi
     constexpr int lds1 = Geo<D, 0>::kBytes;
     e = set_lds<gla_chunk_kernel<D, 0, MODE, false>>(lds1);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k1, dim3(a.seq_start ? x : x - 1, y), dim3(G::TEAM), lds1, stream, a);
+    hipLaunchKernelGGL(k1, dim3(direct ? x - 1 : x, y), dim3(G::TEAM), lds1, stream, a);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
     if (!a.fold) {

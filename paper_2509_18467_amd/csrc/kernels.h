@@ -99,7 +99,8 @@ struct ChunkPlan {
   int seg_len;
   int nseg;
   size_t workspace_bytes;
-  int per_head;       // packed batches: bound of the segments per kv head; elsewhere 0
+  int segments;       // packed batches: segments per kv head, and a bound of them whatever the lengths; elsewhere 0
+  int per_head;
 };
 ChunkPlan make_chunk_plan(int B, int T, int Hq, int Hkv, int d, int carry_mode, int segment);
 bool chunk_path_supports(int group);  // query heads per kv head the kernel is built for

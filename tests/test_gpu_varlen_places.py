@@ -1,5 +1,5 @@
 """Which workgroup of a packed batch takes which segment: one sequence, 64 (a wave's lanes) and more, lengths around multiples of the
-segment and of a granule, in order and by length.  Against the oracle, sequence by sequence."""
+segment and of a granule, by sequence, in order and by length.  Against the oracle, sequence by sequence."""
 import numpy as np
 import pytest
 import torch
@@ -16,9 +16,13 @@ RAGGED = (1, 63, 64, 65, 191, 192, 193, 384, 385, 577, 130, 320)
 
 @pytest.mark.parametrize("d,Hkv,group,segment,lengths", [
     (64, 2, 2, 64, (130,)), (64, 2, 1, 64, RAGGED), (64, 2, 1, 64, (1,) * 64), (64, 1, 1, 128, (1, 129) * 33), (64, 1, 2, 64, (65, 1, 7) * 50),
-    # more workgroups than compute units, segments of three granules: by length
-    (64, 16, 1, 192, RAGGED + (700, 700, 96)), (64, 12, 1, 192, (193, 40, 385, 192) * 16), (64, 32, 4, 192, (500, 20, 200)), (128, 16, 1, 192, RAGGED + (700, 96)),
-    (128, 3, 2, 192, (20, 200) * 36)])
+    (64, 32, 4, 192, (500, 20, 200)),
+    # a grid by sequences would not fit the chip, one by segments in order does
+    (64, 2, 1, 64, (2000,) + (30,) * 20), (128, 2, 4, 64, (20, 900, 1, 63)),
+    # nor that: by length
+    (64, 16, 1, 192, RAGGED + (700, 700, 96)), (64, 12, 1, 192, (193, 40, 385, 192) * 16), (64, 8, 8, 192, RAGGED + (700, 700, 96)), (128, 16, 1, 192, RAGGED + (700, 96)),
+    # more than 64 sequences: in order where that is the smaller grid
+    (64, 4, 1, 64, (1,) * 70 + (1200,)), (128, 3, 2, 192, (20, 200) * 36)])
 def test_packed_places(oracle, d, Hkv, group, segment, lengths):
     total, B = sum(lengths), len(lengths)
     wl = Workload("packed", 1, total, Hkv * group, Hkv, d, 4, "bf16")
