@@ -83,7 +83,8 @@ hipError_t launch_gla_chunk(const ChunkParams& p, hipStream_t stream) {
   // 35.2 / 32.0, 12 44.6 / 41.3, 16 36.1 / 38.2; x 16 8 segments 76 / 59.  Of 128, 8 heads, 3 segments 23.6 / 22.1, 4 26.2 / 27.5; x 4
   // 4 segments 40.1 / 33.6, 8 46.6 / 46.5; 32 on 4 x 16 4 segments 74 / 64, 8 121 / 149.
   // Packed batches (see find_place): a grid of all sequences by the longest one's segments where it has no workgroup without work, or
-  // they all find a place on the chip at once: to find its segment costs a workgroup of the other grids 0.3 to 1 us a pass.  Else in
+  // they all find a place on the chip at once: to find its segment costs a workgroup of the other grids 0.3 to 1 us a pass (by length up to 6 with 64
+  // sequences, 10 before its loop lost its branches).  Else in
   // order of the rows, where that grid fits, else by length.  us a call by sequence / in order / by length, 32 query heads on 8 kv heads:
   // of 64, 128 x 200 tokens 96 / 122 / 120, 30 x 333 47 / 65 / 52, 12 of 60 to 280 24.2 / 26.4 / 29.3; 4 short ones beside one of 2000 47.5 /
   // 29.8 / 30.9, 12 of 88 to 1439 54.9 / 39.2 / 41.8; 24 of 101 to 3364 190 / 115 / 95, 48 of 204 to 691 135 / 120 / 97.  Of 128, 16 of 480 to

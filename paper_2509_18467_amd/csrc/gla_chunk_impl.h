@@ -474,11 +474,11 @@ __device__ inline Place find_place(const ChunkArgs& a, int l) {
       len = (float)(end - row) * __builtin_amdgcn_rcpf((float)n);
     }
     int first = 0, all = 0;
-#pragma unroll 1
-    for (int j = 0; j < a.B; ++j) {
+#pragma unroll 4
+    for (int j = 0; j < ((a.B + 3) & ~3); ++j) {      // (lanes past the last sequence hold none)
       const float lj = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(len), j));
       const int nj = __builtin_amdgcn_readlane(n, j);
-      first += (lj > len || (lj == len && j < l)) ? nj : 0;
+      first += ((lj > len) | ((lj == len) & (j < l))) ? nj : 0;
       all += nj;
     }
     const unsigned odd = all | 1;
