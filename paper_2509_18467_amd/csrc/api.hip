@@ -4,6 +4,7 @@
 #include "../../include/lawcat.h"
 
 #include <algorithm>
+#include <climits>
 #include <cmath>
 #include <mutex>
 
@@ -123,14 +124,25 @@ ChunkPlan varlen_plan(const lawcat_desc* d, const int32_t* seq_start) {
   if (d->carry_mode == LAWCAT_CARRY_SEQUENTIAL) p.seg_len = whole;
   if (d->segment == 0 && d->carry_mode != LAWCAT_CARRY_SEQUENTIAL) {
     // every sequence rounds its segment count up: lengthen the segments until the workgroups fit the chip in one
-    // round (a few too many would double the time of the pass)
-    const long long slots = d->dk == 64 ? 512 : 256;
-    auto groups = [&](int seg_len) {
+    // round (a few too many would double the time of the pass), or, where a group takes several workgroups, in as many rounds as
+    // cost least (a few long sequences among many short ones: 32 of 20 to 1405 tokens, 32 query heads on 4 of 128, one round / two
+    // 259 / 161 us)
+    const long long slots = d->dk == 64 ? 512 : 256, parts = std::max(1, d->Hq / d->Hkv / 4);   // workgroups take up to four query heads
+    auto rounds = [&](int seg_len) {
       long long n = 0;
       for (int i = 0; i < d->B; ++i) n += (seq_start[i + 1] - seq_start[i] + seg_len - 1) / seg_len;
-      return n * d->Hkv * std::max(1, d->Hq / d->Hkv / 4);     // workgroups take up to four query heads
+      return (n * d->Hkv * parts + slots - 1) / slots;
     };
-    while (p.seg_len < whole && groups(p.seg_len) > slots) p.seg_len += 64;
+    long long cost = LLONG_MAX;
+    int len = p.seg_len;
+    for (long long most = parts; most >= 1; --most) {
+      long long r = rounds(len);
+      while (len < whole && r > most) r = rounds(len += 64);
+      if (r * len <= cost) {
+        cost = r * len;
+        p.seg_len = len;
+      }
+    }
   }
   p.nseg = cut_sequence(longest, p.seg_len).nseg;
   for (int i = 0; i < d->B; ++i) p.segments += cut_sequence(seq_start[i + 1] - seq_start[i], p.seg_len).nseg;

@@ -23,3 +23,17 @@ def segments(d, Hq, Hkv, B, T):
     (128, 32, 8, 8, 300, 3), (128, 32, 8, 12, 130, 2), (128, 32, 4, 6, 300, 3)])
 def test_segments(d, Hq, Hkv, B, T, n):
     assert segments(d, Hq, Hkv, B, T) == n
+
+
+@pytest.mark.parametrize("Hq,Hkv,lengths,n", [
+    # groups of eight: two rounds of workgroups where one would take segments of the longest sequence, one where they are about equal
+    (32, 4, [1400] + [200] * 31, 6), (32, 4, [400] * 24, 1),
+    # groups of four: one round
+    (16, 4, [1400] + [200] * 31, 6), (32, 8, [1400] + [200] * 31, 1)])
+def test_segments_of_packed_batches(Hq, Hkv, lengths, n):
+    d, B = 128, len(lengths)
+    starts = [0]
+    for x in lengths:
+        starts.append(starts[-1] + x)
+    need = lawcat.varlen_workspace_bytes(lawcat.make_desc(B, max(lengths), Hq, Hkv, d), starts, True)
+    assert need == (B * Hkv * n * ((d * d + 2 * d) * 4 + 4) if n > 1 else 0)
