@@ -12,7 +12,7 @@ bool chunk_path_supports(int group) { return group >= 1 && group <= 64; }
 
 // Most segments of a head whose contributions the output pass folds in one launch (see launch_gla_chunk).
 static int fold_most(int heads, int d) {
-  return d == 64 ? std::min(chunk::kFoldMost<64> + 1, 8 + heads / 8) : std::min(chunk::kFoldMost<128> + 1, 3 + heads / 16);
+  return d == 64 ? std::min(chunk::kFoldMost<64> + 1, 9 + heads / 4) : std::min(chunk::kFoldMost<128> + 1, 4 + heads / 8);
 }
 
 ChunkPlan make_chunk_plan(int B, int T, int Hq, int Hkv, int d, int carry_mode, int segment) {
@@ -38,10 +38,10 @@ ChunkPlan make_chunk_plan(int B, int T, int Hq, int Hkv, int d, int carry_mode, 
       //   at head dim 64 twice the contributions to fold cost more than the granule saves, which grows with both their number and the
       //     workgroups that read them: 8 heads x 3, 512 tokens 22.1 / 23.8, 800 27.4 / 23.9; x 5, 448 22.1 / 22.7, 512 27.2 / 24.4; x 8, 300
       //     21.1 / 22.1, 500 30.0 / 25.7; 32 on 8 x 12, 190 25.4 / 27.3, 390 39.1 / 37.4;
-      //   at head dim 128 they would be a granule too many to fold, and half as many are not: 32 on 8 x 8, 256 tokens 39.3 / 41.7, 300
-      //     53.8 / 45.4; 8 x 3, 380 38.6 / 36.9, 600, where both take the scan, 39.7 / 45.2.
+      //   at head dim 128 they are too many to fold, and half as many are not: 8 heads x 3, 390 tokens 32.0 / 33.5, 512 40.5 / 37.1, 600 38.8 /
+      //     36.9.
       // (Few heads leave most of the chip idle: there the shorter walk is the better one at any length, 8 x 2, 1000 tokens 24.3 / 26.5,
-      // of 128 40.0 / 45.0.)
+      // of 128 39.0 / 42.7.)
       const int one = (T + 63) / 64, two = (T + 127) / 128, fold = fold_most(heads, d);
       const bool pays = heads <= 16 || (d == 64 ? (long long)one * (heads + 18) <= 460 : one <= fold || two > fold);
       seg_len = two > 1 && one * groups <= slots && pays ? 64 : 128;
@@ -78,10 +78,9 @@ hipError_t launch_gla_chunk(const ChunkParams& p, hipStream_t stream) {
   if (!(p.S0 == p.S_out || p.z0 == p.z_out)) a.most = walks * group <= 256 ? 1 : walks * ((group + 1) / 2) <= 256 ? 2 : 4;
   // With few segments the output pass folds its predecessors' contributions itself instead of waiting for a scan: a launch less,
   // and, with many heads, less traffic, against a walk over the predecessors' slots in each of the output pass's launches (more than
-  // one for groups that are no multiple of 4).  Scan / fold, us a call, query heads on kv heads x sequences: of 64, 32 on 4 8 segments
-  // 19.2 / 18.7, 10 20.6 / 21.2; 32 on 8 3 segments 18.0 / 14.9, 8 20.5 / 19.5, 10 21.6 / 21.9; x 4 4 segments 26.4 / 20.3, 10
-  // 35.2 / 32.0, 12 44.6 / 41.3, 16 36.1 / 38.2; x 16 8 segments 76 / 59.  Of 128, 8 heads, 3 segments 23.6 / 22.1, 4 26.2 / 27.5; x 4
-  // 4 segments 40.1 / 33.6, 8 46.6 / 46.5; 32 on 4 x 16 4 segments 74 / 64, 8 121 / 149.
+  // one for groups that are no multiple of 4).  Scan / fold, us a call in segments of 128 tokens: of 64, 2 heads, 8 segments 23.3 / 22.6,
+  // 9 23.4 / 23.1, 11 23.2 / 23.9; 8 heads, 11 25.2 / 24.9, 12 25.7 / 25.8; 32 on 8 x 2 12 35.2 / 33.3, x 8 10 69.4 / 59.4.  Of 128, 2 heads,
+  // 4 segments 32.2 / 32.3, 5 32.4 / 33.3; 8 heads, 5 34.9 / 34.6, 6 35.9 / 36.9; 32 on 8 x 2 6 44.2 / 42.6, x 8 7 106.5 / 95.7.
   // Packed batches (see find_place): a grid of all sequences by the longest one's segments where it has no workgroup without work, or
   // they all find a place on the chip at once: to find its segment costs a workgroup of the other grids 0.3 to 1 us a pass (by length up to 6 with 64
   // sequences, 10 before its loop lost its branches).  Else in

@@ -19,8 +19,8 @@ def segments(d, Hq, Hkv, B, T):
     (64, 8, 8, 2, 1000, 16), (64, 8, 8, 3, 600, 10), (64, 8, 8, 3, 800, 7), (64, 8, 8, 5, 448, 7), (64, 8, 8, 5, 512, 4), (64, 32, 8, 8, 260, 5),
     (64, 32, 8, 8, 390, 4), (64, 8, 8, 16, 130, 3), (64, 8, 8, 16, 200, 2), (64, 32, 4, 12, 300, 5), (64, 32, 4, 12, 390, 4),
     # head dim 128: by what the output pass folds
-    (128, 8, 8, 2, 1000, 16), (128, 8, 8, 3, 256, 4), (128, 8, 8, 3, 380, 3), (128, 8, 8, 3, 600, 10), (128, 32, 8, 8, 130, 3), (128, 32, 8, 8, 256, 4),
-    (128, 32, 8, 8, 300, 3), (128, 32, 8, 12, 130, 2), (128, 32, 4, 6, 300, 3)])
+    (128, 8, 8, 2, 1000, 16), (128, 8, 8, 3, 256, 4), (128, 8, 8, 3, 390, 7), (128, 8, 8, 3, 512, 4), (128, 8, 8, 3, 600, 5), (128, 2, 2, 9, 850, 14), (128, 32, 8, 8, 130, 3), (128, 32, 8, 8, 256, 4),
+    (128, 32, 8, 8, 300, 3), (128, 32, 8, 12, 130, 2), (128, 32, 4, 6, 300, 5)])
 def test_segments(d, Hq, Hkv, B, T, n):
     assert segments(d, Hq, Hkv, B, T) == n
 
