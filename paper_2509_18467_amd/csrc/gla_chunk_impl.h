@@ -572,7 +572,7 @@ __global__ void __launch_bounds__(D * 4, D == 64 ? 2 : 1)
   // passes anything on (every total decay exactly zero): then a segment starts from its predecessor's
   // contribution as the state pass wrote it, the first from S0, z0.  With few segments (fold): lane j, whether segment j, before
   // this one, passes anything on.  The prologue's loads are issued in the order in which they are waited for: these, the conv
-  // weights, the first granule's rows, the start state.
+  // weights, the start state, the first granule's rows.
   int live_any = 0;
   if (OUTPUT) {
     if (a.fold) live_any = l >= seg || a.seg_live[slot0 + l] != 0;
@@ -637,9 +637,11 @@ __global__ void __launch_bounds__(D * 4, D == 64 ? 2 : 1)
   const int tfirst = OUTPUT ? s0 : s0 + (nseg_gran - 1) * G::NTG;
   const int tstep = OUTPUT ? G::NTG : -G::NTG;
   Raw<KK::NQ> raw;
-  // The first rows are on their way before the start state, except where a workgroup has little else to do (one query head, no conv): 200
-  // sequences of 64 tokens, 8 heads of 128, 69.4 us, after it 68.2; two heads 81.9 and 85.6.
-  constexpr bool kRowsFirst = CONV || !OUTPUT || GR > 1;
+  // The output pass requests its first rows after its start state, so that it does not wait for that behind them: 1984 tokens, 8 heads of
+  // 128, 35.4 -> 33.7 us, 64 tokens of 64 9.4 -> 9.2; 8192, 32 heads on 8 of 64, 44.0 -> 43.4.  Before it where that measured better (of
+  // 128, 32 on 8, 16384 tokens, 128.3, after it 129.8; without conv, 200 sequences of 64 tokens, 16 heads on 8, 27.3 and 28.8), and behind the
+  // fold with one head and no conv (16 of 300 20.9, before the state 21.2).
+  constexpr bool kRowsFirst = !OUTPUT || (CONV ? D == 128 && GR == 4 : GR > 1), kRowsLast = OUTPUT && !CONV && GR == 1;
   if (kRowsFirst) KK::fetch(raw, srcK, srcG, srcV, tfirst, tl0, coff, a.W);
   // ---- state in accumulators: Sacc[rt][ct][i] = S[16 rt + 4 g4 + i][16 tile(ct) + n]; ct == CT holds z replicated
   floatx4 Sacc[G::RT][G::NT];
@@ -689,6 +691,7 @@ __global__ void __launch_bounds__(D * 4, D == 64 ? 2 : 1)
         }
       }
     }
+    if (!kRowsFirst && !kRowsLast) KK::fetch(raw, srcK, srcG, srcV, tfirst, tl0, coff, a.W);
     if (CONV) {
       const float wscale = MODE == kConvElu ? kLog2e : 1.f;
 #pragma unroll
@@ -760,7 +763,7 @@ __global__ void __launch_bounds__(D * 4, D == 64 ? 2 : 1)
   float rgran[2] = {1.f, 1.f};  // state pass: decay of everything after the current granule, this lane's 2 channels
 
   const bool gs1 = a.gate_scale == 1.0f;
-  if (!kRowsFirst) KK::fetch(raw, srcK, srcG, srcV, tfirst, tl0, coff, a.W);
+  if (kRowsLast) KK::fetch(raw, srcK, srcG, srcV, tfirst, tl0, coff, a.W);
   __syncthreads();  // conv weights are in LDS
 
   // Per granule: compute stage, barrier, MFMA stage, barrier.
