@@ -11,8 +11,8 @@ hipError_t launch_d128(const ChunkArgs& a, int group, int mode, hipStream_t stre
 bool chunk_path_supports(int group) { return group >= 1 && group <= 64; }
 
 // Most segments of a head whose contributions the output pass folds in one launch (see launch_gla_chunk).
-static int fold_most(int heads, int d) {
-  return d == 64 ? std::min(chunk::kFoldMost<64> + 1, 9 + heads / 4) : std::min(chunk::kFoldMost<128> + 1, 4 + heads / 8);
+static int fold_most(int heads, int group, int d) {
+  return d == 64 ? std::min(chunk::kFoldMost<64> + 1, 9 + heads / 4) : std::min(group < 8 ? chunk::kFoldMost<128> + 1 : 7, 4 + heads / 8);
 }
 
 ChunkPlan make_chunk_plan(int B, int T, int Hq, int Hkv, int d, int carry_mode, int segment) {
@@ -42,7 +42,7 @@ ChunkPlan make_chunk_plan(int B, int T, int Hq, int Hkv, int d, int carry_mode, 
       //     36.9.
       // (Few heads leave most of the chip idle: there the shorter walk is the better one at any length, 8 x 2, 1000 tokens 24.3 / 26.5,
       // of 128 39.0 / 42.7.)
-      const int one = (T + 63) / 64, two = (T + 127) / 128, fold = fold_most(heads, d);
+      const int one = (T + 63) / 64, two = (T + 127) / 128, fold = std::min(7, fold_most(heads, Hq / Hkv, d));
       const bool pays = heads <= 16 || (d == 64 ? (long long)one * (heads + 18) <= 460 : one <= fold || two > fold);
       seg_len = two > 1 && one * groups <= slots && pays ? 64 : 128;
     }
@@ -80,7 +80,8 @@ hipError_t launch_gla_chunk(const ChunkParams& p, hipStream_t stream) {
   // and, with many heads, less traffic, against a walk over the predecessors' slots in each of the output pass's launches (more than
   // one for groups that are no multiple of 4).  Scan / fold, us a call in segments of 128 tokens: of 64, 2 heads, 8 segments 23.3 / 22.6,
   // 9 23.4 / 23.1, 11 23.2 / 23.9; 8 heads, 11 25.2 / 24.9, 12 25.7 / 25.8; 32 on 8 x 2 12 35.2 / 33.3, x 8 10 69.4 / 59.4.  Of 128, 2 heads,
-  // 4 segments 32.2 / 32.3, 5 32.4 / 33.3; 8 heads, 5 34.9 / 34.6, 6 35.9 / 36.9; 32 on 8 x 2 6 44.2 / 42.6, x 8 7 106.5 / 95.7.
+  // 4 segments 32.2 / 32.3, 5 32.4 / 33.3; 8 heads, 5 34.9 / 34.6, 6 35.9 / 36.9; 32 on 8 x 2 6 44.2 / 42.6, x 4 9 83.8 / 82.7, x 8 8
+  // 115.3 / 113.3; 32 on 4, whose groups are two workgroups, x 8 7 87.6 / 85.8, 8 92.9 / 102.0.
   // Packed batches (see find_place): a grid of all sequences by the longest one's segments where it has no workgroup without work, or
   // they all find a place on the chip at once: to find its segment costs a workgroup of the other grids 0.3 to 1 us a pass (by length up to 6 with 64
   // sequences, 10 before its loop lost its branches).  Else in
@@ -99,7 +100,7 @@ hipError_t launch_gla_chunk(const ChunkParams& p, hipStream_t stream) {
     else a.places = p.d == 64 && direct * p.Hkv * parts <= places * 9 / 8 ? chunk::kDirect : chunk::kByLength;
   }
   const int passes = group % 4 == 0 || a.most == 1 ? 1 : group / 4 + (group % 4 + 1) / 2;
-  a.fold = nseg > 1 && nseg * passes <= fold_most(heads, p.d);
+  a.fold = nseg > 1 && nseg * passes <= fold_most(heads, group, p.d);
   a.gate_scale = p.gate_scale; a.eps = p.eps;
   const int mode = !p.fuse_conv ? chunk::kPlain : (p.phi == 1 ? chunk::kConvElu : chunk::kConvId);
   const chunk::TraceEvents ev{p.ev_start, p.ev_stop};

@@ -87,7 +87,7 @@ struct ChunkArgs {
 };
 
 // most segments before one whose contributions the output pass folds
-template <int D> constexpr int kFoldMost = D == 64 ? 11 : 6;
+template <int D> constexpr int kFoldMost = D == 64 ? 11 : 8;
 
 // which workgroup takes which segment (see find_place)
 constexpr int kDirect = 0, kInOrder = 1, kByLength = 2;

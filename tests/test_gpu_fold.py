@@ -12,9 +12,9 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("shut", [(), (0,), (1,), (0, 1)])
 @pytest.mark.parametrize("d,B,Hkv,nseg", [
-    # head dim 64 folds up to 9 segments with 2 heads, 11 with 8, 12 with 12 and more; 128 up to 4, 5, and 7 with 24 and more
+    # head dim 64 folds up to 9 segments with 2 heads, 11 with 8, 12 with 12 and more; 128 up to 4, 5, 7 with 24, and (groups below eight) 8 with 32, 9 with 40
     (64, 1, 2, 2), (64, 1, 2, 9), (64, 1, 2, 10), (64, 1, 8, 11), (64, 1, 8, 12), (64, 2, 8, 12), (64, 2, 8, 13),
-    (128, 1, 2, 2), (128, 1, 2, 4), (128, 1, 2, 5), (128, 1, 8, 5), (128, 1, 8, 6), (128, 3, 8, 7), (128, 8, 8, 8), (128, 8, 8, 9)])
+    (128, 1, 2, 2), (128, 1, 2, 4), (128, 1, 2, 5), (128, 1, 8, 5), (128, 1, 8, 6), (128, 3, 8, 7), (128, 3, 8, 8), (128, 4, 8, 8), (128, 8, 8, 9), (128, 8, 8, 10)])
 def test_start_states(oracle, d, B, Hkv, nseg, shut):
     wl = Workload("fold", B, 64 * nseg - 11, Hkv, Hkv, d, 4, "bf16")
     x = make_inputs(wl, seed=61, halo=True, state=not shut or shut == (1,))
@@ -34,7 +34,8 @@ def test_start_states(oracle, d, B, Hkv, nseg, shut):
 @pytest.mark.parametrize("shut", [(), (1,)])
 @pytest.mark.parametrize("d,B,Hkv,group,nseg", [(64, 1, 2, 4, 6), (64, 1, 2, 4, 7), (64, 1, 1, 8, 3), (64, 1, 1, 8, 4), (64, 1, 1, 7, 2), (64, 4, 4, 16, 3), (64, 4, 4, 16, 4), (128, 1, 2, 2, 3), (128, 1, 2, 2, 4),
                                                 (128, 4, 4, 8, 3), (128, 4, 4, 8, 4), (128, 4, 16, 4, 9), (128, 4, 16, 4, 10),
-                                                (64, 2, 8, 6, 6), (64, 2, 8, 6, 7), (64, 4, 8, 7, 4), (64, 4, 8, 7, 5), (128, 4, 16, 6, 3), (128, 4, 16, 6, 4)])
+                                                (64, 2, 8, 6, 6), (64, 2, 8, 6, 7), (64, 4, 8, 7, 4), (64, 4, 8, 7, 5), (128, 4, 16, 6, 3), (128, 4, 16, 6, 4), (128, 4, 16, 6, 5),
+                                                (128, 4, 8, 8, 7), (128, 4, 8, 8, 8)])
 def test_start_states_of_several_output_launches(oracle, d, B, Hkv, group, nseg, shut):
     wl = Workload("fold", B, 64 * nseg - 11, Hkv * group, Hkv, d, 4, "bf16")
     x = make_inputs(wl, seed=62, halo=True, state=True)
