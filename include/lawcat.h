@@ -250,7 +250,8 @@ LAWCAT_API int lawcat_layer_prefill_varlen(const lawcat_desc* desc, const int32_
  * wf [Hkv,dk,dk] as in lawcat_conv1d_feature; with identity matrices the call equals lawcat_layer_prefill.
  * Every other argument as in lawcat_layer_prefill; workspace from
  * lawcat_workspace_bytes(desc, LAWCAT_CALL_LAYER_PREFILL_FM): q-dot and k-dot are staged there in the storage
- * type, B*T*(Hq+Hkv)*dk elements, ahead of what lawcat_gla_prefill needs.
+ * type, B*T*(Hq+Hkv)*dk elements, ahead of what lawcat_gla_prefill needs in bf16 storage; in fp32 storage, here as in
+ * lawcat_layer_prefill, the attention walks each sequence in one piece, whatever the size of the workspace.
  */
 LAWCAT_API int lawcat_layer_prefill_fm(const lawcat_desc* desc, const void* Q, const void* K, const void* V,
                             const void* gate_logits, const void* wq, const void* wk, const void* wf,

@@ -491,7 +491,9 @@ int lawcat_layer_prefill_fm(const lawcat_desc* desc, const void* Q, const void* 
   void* qd = ws;
   void* kd = ws + align_up(rows * desc->Hq * desc->dk * elem_bytes(desc), 256);
   char* inner = static_cast<char*>(kd) + align_up(rows * desc->Hkv * desc->dk * elem_bytes(desc), 256);
-  const size_t inner_bytes = workspace_bytes - (size_t)(inner - ws);
+  // in fp32 storage no more than the call asks for: bits that do not depend on the size of the caller's buffer
+  const bool chunked = prefill_path(desc) == Path::kChunkBf16;
+  const size_t inner_bytes = chunked ? workspace_bytes - (size_t)(inner - ws) : 0;
   // queries: each head with the matrix of the kv head whose state it reads
   ConvParams c{};
   c.B = desc->B; c.T = desc->T; c.d = desc->dk; c.W = desc->conv_width;
@@ -502,7 +504,7 @@ int lawcat_layer_prefill_fm(const lawcat_desc* desc, const void* Q, const void* 
   ck.x = K; ck.w = wk; ck.halo = cached ? k_halo : nullptr; ck.y = kd; ck.tail_out = cached ? k_tail_out : nullptr; ck.H = desc->Hkv;
   if (launch_conv_feature_pair(cq, ck, wf, static_cast<hipStream_t>(stream)) != hipSuccess) return LAWCAT_E_HIP;
   // the attention on the transformed q-dot, k-dot
-  return lawcat_gla_prefill(desc, qd, kd, V, gate_logits, S0, z0, O, den_out, S_out, z_out, inner, inner_bytes, stream);
+  return lawcat_gla_prefill(desc, qd, kd, V, gate_logits, S0, z0, O, den_out, S_out, z_out, chunked ? inner : nullptr, inner_bytes, stream);
 }
 
 int lawcat_layer_prefill_static(const lawcat_desc* desc, const void* Q, const void* K, const void* V,

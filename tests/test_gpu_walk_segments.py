@@ -77,3 +77,22 @@ def test_tokens_that_are_not_finite(what, value):
     for n in got:
         assert np.array_equal(np.isfinite(got[n]), np.isfinite(whole[n])), n
     assert np.isfinite(got["o"][0, :100]).all()
+
+
+def test_the_feature_map_layer_whatever_the_workspace():
+    """lawcat_layer_prefill_fm in fp32 storage asks for no segments' workspace: more than it asks for changes no bit."""
+    wl = Workload("segments", 1, 300, 4, 2, 64, 4, "fp32")
+    x = make_inputs(wl, seed=94)
+    wf = np.stack([np.eye(64, dtype=np.float32)] * 2)
+    D = H.desc_for(wl, feature_map=1, gate_scale=0.0625)
+    Q, K, V, G, wq, wk = (H.dev(x[n]) for n in ("Q", "K", "V", "G", "wq", "wk"))
+    need = lawcat.workspace_bytes(D, lawcat.CALL_LAYER_PREFILL_FM)
+    out = []
+    for more in (0, 4 << 20):
+        O, S, z = torch.empty_like(Q), torch.empty(1, 2, 64, 64, device="cuda"), torch.empty(1, 2, 64, device="cuda")
+        ws = torch.empty(need + more, dtype=torch.uint8, device="cuda")
+        lawcat.layer_prefill_fm(D, Q, K, V, G, wq, wk, H.dev(wf), None, None, None, None, O, None, S, z, None, None, ws)
+        torch.cuda.synchronize()
+        out.append((H.host(O), H.host(S), H.host(z)))
+    for a, b in zip(*out):
+        assert np.array_equal(a, b)
