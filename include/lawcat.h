@@ -36,8 +36,9 @@
  *    the host before anything is enqueued; after an error the outputs are unspecified.
  *    A zero denominator is not an error: IEEE inf/nan is returned as the last equation
  *    of section 4.2 gives it.
- *  - Inputs and outputs must not overlap, except S/z in lawcat_gla_step and lawcat_gla_steps (updated
- *    in place).  All pointers must be 16-byte aligned.
+ *  - Inputs and outputs must not overlap, except S/z in lawcat_gla_step and lawcat_gla_steps (updated in place),
+ *    and S_out, z_out of the prefill calls, which may be the very buffers S0, z0 (a little slower: query heads of a
+ *    group and segments then share what they otherwise do apart).  All pointers must be 16-byte aligned.
  */
 #ifndef LAWCAT_H_
 #define LAWCAT_H_

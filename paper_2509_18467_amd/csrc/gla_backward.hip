@@ -934,10 +934,10 @@ __global__ void __launch_bounds__(4 * D, 2) bwd_reverse_kernel(const BwdArgs a) 
 }
 
 template <int D>
-void launch_scan(float* slots, const int* live, const float* S0, const float* z0, const BwdArgs& a, hipStream_t stream) {
+void launch_scan(float* slots, int* live, const float* S0, const float* z0, const BwdArgs& a, hipStream_t stream) {
   const int heads = a.B * a.Hkv, x = scan_blocks<D>(heads);
   hipLaunchKernelGGL((segment_scan_kernel<D, true>), dim3(x, heads), dim3(256), 0, stream, slots, live, S0, z0, a.nseg,
-                     (const int*)nullptr, a.Hkv, a.seg_len);
+                     (const int*)nullptr, a.Hkv, a.seg_len, false);
 }
 
 template <typename T, int D, int HB>

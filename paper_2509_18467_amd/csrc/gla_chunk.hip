@@ -71,11 +71,13 @@ hipError_t launch_gla_chunk(const ChunkParams& p, hipStream_t stream) {
   // compute units: each is a serial walk, and those for two heads or one are shorter, at the price of forming the keys' side again.
   // us a call with four / two / one, 8 kv heads: of 64, 32 query heads, 64 tokens 13.7 / 11.9 / 10.7, 517 20.4 / 19.1 / -; 1500, where
   // two would be 384 workgroups, 21.8 / 22.6 / 27 (on 4 kv heads); of 128, 64 tokens 19.2 / 16.6 / 14.2, 1000 36.6 / 33.9 / 41.9 (512).
-  // (Not in place: a workgroup would read a start state that another one replaces.)
+  // In place one workgroup per launch takes a segment, so that none reads a start state that another one replaces: the last launch
+  // stores the state, and with several segments they all start from their slots (no fold).
   const int nseg = p.plan.nseg, heads = p.B * p.Hkv, group = p.Hq / p.Hkv;
   const long long walks = p.seq_start ? (long long)p.Hkv * p.plan.segments : (long long)nseg * heads;
+  const bool in_place = chunk::in_place(a);
   a.most = 4;
-  if (!(p.S0 == p.S_out || p.z0 == p.z_out)) a.most = walks * group <= 256 ? 1 : walks * ((group + 1) / 2) <= 256 ? 2 : 4;
+  if (!in_place) a.most = walks * group <= 256 ? 1 : walks * ((group + 1) / 2) <= 256 ? 2 : 4;
   // With few segments the output pass folds its predecessors' contributions itself instead of waiting for a scan: a launch less,
   // and, with many heads, less traffic, against a walk over the predecessors' slots in each of the output pass's launches (more than
   // one for groups that are no multiple of 4).  Scan / fold, us a call in segments of 128 tokens: of 64, 2 heads, 8 segments 23.3 / 22.6,
@@ -92,7 +94,7 @@ hipError_t launch_gla_chunk(const ChunkParams& p, hipStream_t stream) {
   // at once, cost less than to order them: 24 of 300 to 498, 9/8 of the chip, 48.8 / 50.1 / 51.1; of 128, 12 of 208 to 352, 63 / 71 / 50.)
   a.places = chunk::kDirect;
   if (p.seq_start) {
-    const long long places = p.d == 64 ? 512 : 256, parts = std::max(1, group / a.most);     // at once on the chip; workgroups per segment
+    const long long places = p.d == 64 ? 512 : 256, parts = in_place ? 1 : std::max(1, group / a.most);     // at once on the chip; workgroups per segment
     const long long direct = (long long)p.B * nseg, in_order = p.plan.per_head;
     if (direct <= p.plan.segments || direct * p.Hkv * parts <= places) a.places = chunk::kDirect;
     else if (p.B > 64) a.places = direct <= in_order ? chunk::kDirect : chunk::kInOrder;
@@ -100,7 +102,7 @@ hipError_t launch_gla_chunk(const ChunkParams& p, hipStream_t stream) {
     else a.places = p.d == 64 && direct * p.Hkv * parts <= places * 9 / 8 ? chunk::kDirect : chunk::kByLength;
   }
   const int passes = group % 4 == 0 || a.most == 1 ? 1 : group / 4 + (group % 4 + 1) / 2;
-  a.fold = nseg > 1 && nseg * passes <= fold_most(heads, group, p.d);
+  a.fold = !in_place && nseg > 1 && nseg * passes <= fold_most(heads, group, p.d);
   a.gate_scale = p.gate_scale; a.eps = p.eps;
   const int mode = !p.fuse_conv ? chunk::kPlain : (p.phi == 1 ? chunk::kConvElu : chunk::kConvId);
   const chunk::TraceEvents ev{p.ev_start, p.ev_stop};

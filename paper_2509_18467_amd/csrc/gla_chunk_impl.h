@@ -86,6 +86,9 @@ struct ChunkArgs {
   float gate_scale, eps;
 };
 
+// S_out, z_out are S0, z0
+inline bool in_place(const ChunkArgs& a) { return a.S0 == a.S_out || a.z0 == a.z_out; }
+
 // most segments before one whose contributions the output pass folds
 template <int D> constexpr int kFoldMost = D == 64 ? 11 : 8;
 
@@ -1068,7 +1071,7 @@ hipError_t launch_all(const ChunkArgs& a, int parts, hipStream_t stream, bool wi
     if (e != hipSuccess) return e;
     if (!a.fold) {
       hipLaunchKernelGGL(segment_scan_kernel<D>, dim3(scan_blocks<D>(heads), heads), dim3(256), 0, stream, a.ws, a.seg_live,
-                         a.S0, a.z0, a.nseg, a.seq_start, a.Hkv, a.seg_len);
+                         a.S0, a.z0, a.nseg, a.seq_start, a.Hkv, a.seg_len, in_place(a));
       e = hipGetLastError();
       if (e != hipSuccess) return e;
     }
@@ -1085,15 +1088,18 @@ hipError_t launch_all(const ChunkArgs& a, int parts, hipStream_t stream, bool wi
 }
 
 // A group of any size is covered by output-pass launches whose workgroups take 4, 2 or 1 of its query heads each; they
-// share one state pass and one scan (the key side does not depend on the query heads).
+// share one state pass and one scan (the key side does not depend on the query heads).  The workgroup of the first heads stores the
+// state; in place its launch is the last, after all that read the start state, and takes four heads at most (see launch_gla_chunk).
 template <int D>
 hipError_t launch_d(const ChunkArgs& a0, int group, int mode, hipStream_t stream, const TraceEvents& ev0) {
   ChunkArgs a = a0;
   a.group = group;
   bool first = true;
-  for (int qh0 = 0; qh0 < group;) {
-    const int left = group - qh0, gr = left >= a.most ? a.most : (left >= 2 ? 2 : 1), parts = left / gr;
-    a.qh0 = qh0;
+  for (int done = 0; done < group;) {
+    const int left = group - done, rest = left % 4;
+    const int gr = in_place(a) ? (rest == 0 ? 4 : rest == 2 ? 2 : 1) : left >= a.most ? a.most : (left >= 2 ? 2 : 1);
+    const int parts = in_place(a) ? 1 : left / gr;
+    a.qh0 = in_place(a) ? left - gr : done;
     const TraceEvents ev = first ? ev0 : TraceEvents{nullptr, nullptr};
     hipError_t e;
 #define LAWCAT_CASE(GRV)                                                                      \
@@ -1111,7 +1117,7 @@ hipError_t launch_d(const ChunkArgs& a0, int group, int mode, hipStream_t stream
 #undef LAWCAT_CASE
     if (e != hipSuccess) return e;
     first = false;
-    qh0 += gr * parts;
+    done += gr * parts;
   }
   return hipSuccess;
 }

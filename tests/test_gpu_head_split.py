@@ -1,6 +1,6 @@
 """Output-pass workgroups that take four query heads of a group, two or one: group sizes around each, on both sides of the number of
 segments at which the split changes, with a start state, conv caches and the smallest sequences; and calls in place, which are not
-split."""
+split, for every kind of group and of segments."""
 import numpy as np
 import pytest
 import torch
@@ -48,3 +48,61 @@ def test_in_place(d):
     assert np.array_equal(out[0][1], out[1][1]) and np.array_equal(out[0][2], out[1][2])
     # the outputs of another instantiation: the same products in the same order, up to how the compiler fuses them
     H.assert_close(out[1][0], out[0][0], wl, "o")
+
+
+def _in_place_run(x, wl, segment, starts=None):
+    """S_out, z_out over S0, z0; with offsets one packed batch."""
+    lens = None if starts is None else np.diff(starts)
+    B, T = (wl.B, wl.T) if lens is None else (len(lens), int(lens.max()))
+    D = lawcat.make_desc(B, T, wl.Hq, wl.Hkv, wl.d, feature_map=1, segment=segment, gate_scale=0.25)
+    bf = torch.bfloat16
+    Q, K, V, G, wq, wk, qh, kh = (H.dev(x[n], bf) for n in ("Q", "K", "V", "G", "wq", "wk", "q_halo", "k_halo"))
+    S, z, O = H.dev(x["S0"]), H.dev(x["z0"]), torch.empty_like(Q)
+    den = torch.empty(*Q.shape[:-1], device="cuda")
+    qt, kt = torch.empty_like(qh), torch.empty_like(kh)
+    if starts is None:
+        lawcat.layer_prefill(D, Q, K, V, G, wq, wk, S, z, qh, kh, O, den, S, z, qt, kt, lawcat.alloc_workspace(D, lawcat.CALL_LAYER_PREFILL))
+    else:
+        ws = torch.empty(max(16, lawcat.varlen_workspace_bytes(D, starts, True)), dtype=torch.uint8, device="cuda")
+        lawcat.layer_prefill_varlen(D, starts, Q, K, V, G, wq, wk, S, z, qh, kh, O, den, S, z, qt, kt, ws,
+                                    seq_start_dev=torch.from_numpy(starts).cuda())
+    torch.cuda.synchronize()
+    return {"o": H.host(O), "den": H.host(den), "S": H.host(S), "z": H.host(z), "k_tail": H.host(kt)}
+
+
+# one segment and several (folded or scanned where not in place), groups of one launch and of several; closed: no segment passes anything on
+@pytest.mark.parametrize("closed", [False, True])
+@pytest.mark.parametrize("d,B,Hkv,group,T,segment", [
+    (64, 2, 2, 1, 60, 0), (64, 2, 2, 3, 60, 0), (64, 1, 2, 8, 60, 0), (64, 2, 2, 7, 300, 64), (64, 1, 2, 8, 300, 64), (64, 1, 2, 4, 1300, 64),
+    (128, 1, 2, 8, 50, 0), (128, 2, 1, 6, 300, 64), (128, 1, 2, 4, 900, 64)])
+def test_in_place_groups_and_segments(oracle, d, B, Hkv, group, T, segment, closed):
+    wl = Workload("split", B, T, Hkv * group, Hkv, d, 4, "bf16")
+    x = make_inputs(wl, seed=73, halo=True, state=True)
+    if closed:
+        x["G"][:, 20:] = -40.0
+    print("in place", wl, segment, closed, flush=True)
+    got = _in_place_run(x, wl, segment)
+    ref = oracle.layer_prefill(x["Q"], x["K"], x["V"], x["G"], x["wq"], x["wk"], 1, 0.25, 0.0, x["S0"], x["z0"], x["q_halo"], x["k_halo"])
+    for n in ("o", "den", "S", "z"):
+        # closed gates leave an output of one product of a value with a weight that is rounded to bf16
+        H.assert_close(got[n], ref[n], wl, n, 1 if closed and n == "o" else 0)
+    rows = np.concatenate([x["k_halo"], x["K"]], axis=1)[:, -3:]
+    assert np.array_equal(got["k_tail"], rows.astype(np.float64))
+
+
+@pytest.mark.parametrize("d,group", [(64, 8), (64, 3), (128, 4)])
+def test_in_place_packed(oracle, d, group):
+    starts = np.array([0, 50, 51, 400, 530], dtype=np.int32)
+    wl = Workload("split", 1, 530, 2 * group, 2, d, 4, "bf16")
+    x = make_inputs(wl, seed=74)
+    x.update({n: v for n, v in make_inputs(Workload("split", 4, 1, 2 * group, 2, d, 4, "bf16"), seed=75, halo=True, state=True).items()
+              if n in ("S0", "z0", "q_halo", "k_halo")})
+    x0 = {n: x[n].copy() for n in ("S0", "z0")}
+    print("in place, packed", wl, flush=True)
+    got = _in_place_run(x, wl, 64, starts)
+    for i, (a, b) in enumerate(zip(starts[:-1], starts[1:])):
+        ref = oracle.layer_prefill(x["Q"][:, a:b], x["K"][:, a:b], x["V"][:, a:b], x["G"][:, a:b], x["wq"], x["wk"], 1, 0.25, 0.0,
+                                   x0["S0"][i:i + 1], x0["z0"][i:i + 1], x["q_halo"][i:i + 1], x["k_halo"][i:i + 1])
+        for n, g in (("o", got["o"][:, a:b]), ("den", got["den"][:, a:b]), ("S", got["S"][i:i + 1]), ("z", got["z"][i:i + 1])):
+            # (a few tokens are too few for an RMS: a half-ulp of the stored value beside it)
+            H.assert_close(g, ref[n], wl, f"sequence {i} {n}", 1 if n == "o" else 0)
