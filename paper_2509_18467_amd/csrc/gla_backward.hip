@@ -937,7 +937,7 @@ template <int D>
 void launch_scan(float* slots, int* live, const float* S0, const float* z0, const BwdArgs& a, hipStream_t stream) {
   const int heads = a.B * a.Hkv, x = scan_blocks<D>(heads);
   hipLaunchKernelGGL((segment_scan_kernel<D, true>), dim3(x, heads), dim3(256), 0, stream, slots, live, S0, z0, a.nseg,
-                     (const int*)nullptr, a.Hkv, a.seg_len);
+                     (const int*)nullptr, a.Hkv, a.seg_len, false);
 }
 
 template <typename T, int D, int HB>

@@ -1070,9 +1070,8 @@ hipError_t launch_all(const ChunkArgs& a, int parts, hipStream_t stream, bool wi
     e = hipGetLastError();
     if (e != hipSuccess) return e;
     if (!a.fold) {
-      auto scan = in_place(a) ? segment_scan_kernel<D, false, true> : segment_scan_kernel<D>;
-      hipLaunchKernelGGL(scan, dim3(scan_blocks<D>(heads), heads), dim3(256), 0, stream, a.ws, a.seg_live,
-                         a.S0, a.z0, a.nseg, a.seq_start, a.Hkv, a.seg_len);
+      hipLaunchKernelGGL(segment_scan_kernel<D>, dim3(scan_blocks<D>(heads), heads), dim3(256), 0, stream, a.ws, a.seg_live,
+                         a.S0, a.z0, a.nseg, a.seq_start, a.Hkv, a.seg_len, in_place(a));
       e = hipGetLastError();
       if (e != hipSuccess) return e;
     }

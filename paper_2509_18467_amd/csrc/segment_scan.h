@@ -19,8 +19,7 @@ __host__ __device__ inline Cut cut_sequence(int T, int most) {
 
 // Turns per-segment contributions into segment start states, in place:
 //   slot[seg] <- state before segment seg;  state <- decay[seg] (.) state + contribution[seg].
-// ALWAYS: for a call whose final state replaces its start state, also where no segment passes anything on (an instance of its own: chosen by
-// an argument, every call paid for it, 8192 tokens of 32 heads on 8 of 64 46.3 us, now 45.9).
+// `always`: for a call whose final state replaces its start state, also where no segment passes anything on.
 // AFTER: slot[seg] <- state after segment seg, for all but the last, which has no slot (nseg_max - 1 of them per head).
 // The recurrence is linear, so the segments are cut into 8 groups: 8 threads per 1 or 4 state elements each
 // reduce their group to (product of decays, contribution from a zero start), the eight pairs are
@@ -35,11 +34,11 @@ __host__ __device__ inline Cut cut_sequence(int T, int most) {
 // slots a second time.
 // adjacent state elements of a thread: one at head dim 64, four at 128
 template <int D> constexpr int kScanVec = D == 64 ? 1 : 4;
-template <int D, bool AFTER = false, bool ALWAYS = false>
+template <int D, bool AFTER = false>
 __global__ void __launch_bounds__(256) segment_scan_kernel(float* __restrict__ ws, int* __restrict__ seg_live,
                                                           const float* __restrict__ S0, const float* __restrict__ z0,
                                                           int nseg_max, const int* __restrict__ seq_start, int Hkv,
-                                                          int seg_len) {
+                                                          int seg_len, bool always) {
   constexpr int kSlot = D * D + 2 * D;
   constexpr int NG = 8, V = kScanVec<D>, U = D == 64 ? 8 : 4;
   typedef float Vec __attribute__((ext_vector_type(V)));
@@ -53,7 +52,7 @@ __global__ void __launch_bounds__(256) segment_scan_kernel(float* __restrict__ w
     nseg = cut_sequence(seq_start[b + 1] - seq_start[b], seg_len).nseg;
   }
   if (nseg < 2) return;
-  if constexpr (ALWAYS) {
+  if (always) {
     if (blockIdx.x == 0 && threadIdx.x == 0) seg_live[(size_t)bh * nseg_max] = 1;      // the output pass finds every start state in its slot
   } else {
     // No segment of this head passes anything on (every total decay is exactly zero: the usual case with gate
