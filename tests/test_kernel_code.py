@@ -57,8 +57,6 @@ def test_three_workgroups_a_compute_unit(kernels, heads):
     assert chunk(kernels, 64, heads, 0)[".vgpr_count"] <= 168
 
 
-
-
 @pytest.mark.parametrize("heads,mode,most", [(1, 0, 0), (1, 1, 0), (1, 2, 0), (2, 0, 0), (2, 1, 27), (2, 2, 0)])
 def test_spills(kernels, heads, mode, most):
     assert chunk(kernels, 128, heads, mode)[".vgpr_spill_count"] <= most
