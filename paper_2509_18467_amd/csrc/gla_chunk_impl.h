@@ -13,16 +13,21 @@
 // rho/E_i spans more than eight steps of decay.  A chunk in which every channel has rho = 1 (the usual case)
 // skips the scaling of the state operand.
 // All the products are bf16 MFMAs with fp32 accumulation.  The normalizer z is carried as one more
-// (replicated) column tile of the state, updated by the same MFMAs against an all-ones value operand;
-// den_t is computed once per query head, by the wave that computes that head's scores, and shared
-// through LDS.
+// (replicated) column tile of the state, updated by the same MFMAs against an all-ones value operand.
 //
-// Parallel decomposition.  One team of d/16 waves (one per 16 value columns) owns one (batch,
-// kv head) and one segment of the sequence, and walks it 16 tokens at a time with its [dk x (16+16)]
-// slice of the state in MFMA accumulators; the query heads of the group share k, v, the decay and the
-// state.  With more than one segment a first pass computes each segment's state contribution and total
+// Parallel decomposition.  One team of d/16 waves owns one (batch, kv head) and one segment of the sequence and walks it in granules
+// of 64 tokens; a wave holds 16 value columns of the state in MFMA accumulators (and its share of z); the query heads of the group share
+// k, v, the decay and the state.  With more than one segment a first pass computes each segment's state contribution and total
 // decay, a small scan turns them into segment start states (or, with few segments, each workgroup of the output pass folds
 // its predecessors' contributions itself), and the output pass starts from those.
+//
+// Output pass, head dim 64: a wave forms Q' and K' of one of the granule's four chunks and takes the outputs of that chunk, all value
+// columns of them, so that they never leave it; only k (.) E_last/E and V go to the other waves, and the state at each chunk's start, as
+// bf16 operands, comes back from them: two barriers a granule, and a wave's stores cover 64 bytes of a row.  With every wave forming 16
+// columns of all outputs (scores and denominators shared per chunk, six barriers a granule, 32 bytes of a row per store) 32768 tokens
+// of 32 heads on 8 took 107.4 us, now 96.7; 8192 46.5 and 43.3, 64 9.5 and 7.7.  What bounds it: the output pass moves 386 MB in 80 us, 93 %
+// of the rate of a large copy; the state pass and the launches in between are the rest.
+// Head dim 128: the state at four chunks' starts would fill the LDS; the waves share all chunks (see the MFMA stage).
 //
 // Per-step decay is floored at 2^-13 so that eight steps of 1/alpha stay below 2^104; the floor changes
 // a state by at most 2^-13 of what the step before it held.
@@ -103,21 +108,25 @@ struct Geo {
   static constexpr int NTG = 64;             // tokens per granule (one load stage of the team)
   static constexpr int MCG = NTG / kChunk;   // chunks per granule
   static constexpr int RT = D / 16;          // 16-row tiles of the state (key channels)
-  static constexpr int CT = 1;               // value-column tiles owned by a wave
-  static constexpr int NT = CT + 1;          // plus the normalizer tile
   static constexpr int KS = D / 32;          // k-steps of a 16x16x32 MFMA over the key channels
   static constexpr int QRS = D * 2 + 8;      // LDS row stride (bytes) of token-major bf16 rows
   static constexpr int TRS = NTG * 2 + 8;    // LDS row stride (bytes) of channel-major bf16 rows
+  // OWN: a wave keeps its chunk's Q', K' (see the top); S at each chunk's start, in MFMA operands, [chunk][16 value columns][k-step]
+  // [64 lanes] x 16 B.
+  static constexpr bool OWN = D == 64 && GR > 0;
+  static constexpr int kSn = 0;
+  static constexpr int kSnChunk = D * D * 2;
   static constexpr int kQp = 0;
   static constexpr int kKp = kQp + GR * NTG * QRS;
-  static constexpr int kKd = kKp + (GR > 0 ? NTG * QRS : 0);  // GR == 0: the state pass keeps no Q', K' 
+  static constexpr int kKd = OWN ? MCG * kSnChunk : kKp + (GR > 0 ? NTG * QRS : 0);  // GR == 0: the state pass keeps no Q', K'
   static constexpr int kVt = kKd + D * TRS;
   static constexpr int kEb = kVt + D * TRS;
   static constexpr int kEf = kEb + MCG * D * 4;   // the reference rho of each chunk and channel, fp32
   static constexpr int kWl = kEf + MCG * D * 4;
   static constexpr int kPs = kWl + (GR + 1) * D * 16;   // shared scores: [2 buffers][GR heads][64 lanes] x 16 B (4 high parts, 4 residuals)
-  static constexpr int kDn = kPs + 2 * GR * 2 * 512;      // shared denominators: [2 buffers][GR heads][16 queries] fp32
-  static constexpr int kFl = kDn + 2 * GR * 64;           // per load-stage wave: 1 if one of its channels uses the mid-chunk reference
+  static constexpr int kDn = kPs + (OWN ? 0 : 2 * GR * 2 * 512);   // shared denominators: [2 buffers][GR heads][16 queries] fp32
+  static constexpr int kZs = kDn + (OWN ? 0 : 2 * GR * 64);        // z at each chunk's start, bf16
+  static constexpr int kFl = kZs + (OWN ? MCG * D * 2 : 0);        // per load-stage wave: 1 if one of its channels uses the mid-chunk reference
   static constexpr int kBytes = kFl + 32;
   static constexpr int kSlot = D * D + 2 * D;  // floats per workspace slot: S | z | decay
 };
@@ -133,6 +142,7 @@ __device__ inline uint32_t pack2(float a, float b) {
 __device__ inline float lane_get(int byte_index, float v) {
   return __int_as_float(__builtin_amdgcn_ds_bpermute(byte_index, __float_as_int(v)));
 }
+__device__ inline bf16x8 make8(uint2 a, uint2 b) { return __builtin_bit_cast(bf16x8, make_uint4(a.x, a.y, b.x, b.y)); }
 __device__ inline float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 __device__ inline float fast_rcp(float x) { return __builtin_amdgcn_rcpf(x); }
 __device__ inline float fast_log2(float x) { return __builtin_amdgcn_logf(x); }
@@ -166,14 +176,15 @@ __device__ inline RowSrc make_row_src(const char* base, const char* halo, unsign
   return RowSrc{__builtin_amdgcn_make_buffer_rsrc((void*)base, 0, (int)bytes, 0x00020000), halo, stride, width};
 }
 
-// Rows t0-3 .. t0+7 (+ this thread's patch offset, folded into voff) of one tensor.  t0 is uniform.
-template <bool CONV>
+// Rows t0-3 .. t0+7 (+ this thread's patch offset, folded into voff) of one tensor.  t0 is uniform.  HALO: it may be 0 (elsewhere the
+// halo's branch would only lead the compiler to wait for rows in flight: 98.4 -> 96.8 us at 32768 tokens of 64).
+template <bool CONV, bool HALO>
 __device__ inline void load_rows(const RowSrc& s, int t0, int tl0, int W, unsigned voff, unsigned coff,
                                  uint32_t (&raw)[11]) {
 #pragma unroll
   for (int j = CONV ? 0 : 3; j < 11; ++j)
     raw[j] = __builtin_amdgcn_raw_buffer_load_b32(s.rsrc, (int)(voff + (unsigned)(t0 - 3 + j) * s.stride), 0, 0);
-  if (CONV && t0 == 0 && s.halo != nullptr && tl0 == 0) {
+  if (HALO && t0 == 0 && s.halo != nullptr && tl0 == 0) {
     // the rows before the first token come from the caller's halo (oldest row first, W-1 rows), read through a
     // descriptor of its own with 32-bit offsets (64-bit row addresses would be kept in registers across the
     // whole granule loop for this one use)
@@ -217,9 +228,29 @@ __device__ inline void conv_phi(const uint32_t (&raw)[11], const float* wts /*[2
   }
 }
 
+// What a wave keeps of its chunk between the stages (head dim 64): Q' as MFMA operands, masked scores as high parts and residuals
+template <int D, int NQ>
+struct Chunk {
+  bf16x8 q[NQ][D / 32];
+  uint4 p[NQ];
+};
+
+// Causal scores of a chunk, P^T[key 4 g4 + i][query n] for key <= query, as a k = 32 operand: slots 0..3 the high parts, 4..7 the
+// residuals of this lane's 4 keys.  The weights of the few nearest keys dominate the output, so their bf16 rounding would not
+// average out.
+__device__ inline uint4 pack_scores(floatx4 pt, int g4, int n) {
+#pragma unroll
+  for (int i = 0; i < 4; ++i) pt[i] = (4 * g4 + i <= n) ? pt[i] : 0.f;
+  const uint32_t ph0 = pack2(pt[0], pt[1]), ph1 = pack2(pt[2], pt[3]);
+  const uint32_t pl0 = pack2(pt[0] - bf_lo(ph0), pt[1] - bf_hi(ph0));
+  const uint32_t pl1 = pack2(pt[2] - bf_lo(ph1), pt[3] - bf_hi(ph1));
+  return make_uint4(ph0, ph1, pl0, pl1);
+}
+
 template <int D, int GR, int MODE, bool OUTPUT>
 struct Kernel {
   using G = Geo<D, GR>;
+  static constexpr bool OWN = OUTPUT && G::OWN;
   static constexpr bool CONV = MODE != kPlain;
   static constexpr int NQ = OUTPUT ? GR : 1;
 
@@ -228,30 +259,35 @@ struct Kernel {
   // inside the compute stage, two heads ahead of their use (fetch_head).  Prefetching query heads a stage ahead
   // as well measured slower at every count tried (larger bursts into the memory pipeline, more registers live
   // across the MFMA stage).
+  template <bool FIRST>     // the granule may be the sequence's first
   __device__ static inline void fetch(Raw<NQ>& raw, const RowSrc& srcK, const RowSrc& srcG, const RowSrc& srcV,
                                       int t0, int tl0, unsigned coff, int W) {
     const unsigned voffkv = (unsigned)tl0 * srcK.stride + coff;
-    load_rows<false>(srcG, t0, tl0, 1, voffkv, coff, raw.g);
-    load_rows<CONV>(srcK, t0, tl0, W, voffkv, coff, raw.k);
-    load_rows<false>(srcV, t0, tl0, 1, voffkv, coff, raw.v);
+    load_rows<false, false>(srcG, t0, tl0, 1, voffkv, coff, raw.g);
+    load_rows<CONV, CONV && FIRST>(srcK, t0, tl0, W, voffkv, coff, raw.k);
+    load_rows<false, false>(srcV, t0, tl0, 1, voffkv, coff, raw.v);
   }
 
   // One query head of the granule at t0.
+  template <bool FIRST>
   __device__ static inline void fetch_head(Raw<NQ>& raw, const RowSrc& srcQ, int hh, int t0, int tl0,
                                            unsigned coff, int W) {
-    load_rows<CONV>(srcQ, t0, tl0, W, (unsigned)tl0 * srcQ.stride + coff + hh * D * 2, coff + hh * D * 2, raw.q[hh]);
+    load_rows<CONV, CONV && FIRST>(srcQ, t0, tl0, W, (unsigned)tl0 * srcQ.stride + coff + hh * D * 2, coff + hh * D * 2, raw.q[hh]);
   }
 
   // ---- registers -> LDS operands: gate products, conv + phi, scaling by the decay, bf16 packing
   template <bool EDGE, bool GS1>
   __device__ static inline void compute(Raw<NQ>& raw, const RowSrc& srcQ, unsigned coff, int W, unsigned char* smem,
                                         const float* wl, int t0, int s1, int tl0, int c0, int mcw, int th,
-                                        float gate_scale) {
+                                        float gate_scale, Chunk<D, NQ>& own) {
     const int tok0 = t0 + tl0;
     const int idx32 = (int)(((threadIdx.x & 63) ^ 32) << 2);  // the lane that holds the other half of the chunk
+    // OWN: rows of the wave's chunk in LDS on their way from patches to operands, where S of the same chunk will be: nothing else
+    // reads either
+    unsigned char* rows = smem + G::kSn + mcw * G::kSnChunk;
     // query heads are fetched two heads ahead of their use
-    if (OUTPUT) fetch_head(raw, srcQ, 0, t0, tl0, coff, W);
-    if (OUTPUT && NQ > 1) fetch_head(raw, srcQ, 1, t0, tl0, coff, W);
+    if (OUTPUT) fetch_head<EDGE>(raw, srcQ, 0, t0, tl0, coff, W);
+    if (OUTPUT && NQ > 1) fetch_head<EDGE>(raw, srcQ, 1, t0, tl0, coff, W);
     // keys first: conv + phi into kf, which the gate loop below scales in place by 1/E as it goes
     float kf[8][2];
     conv_phi<MODE>(raw.k, wl + ((size_t)GR * D + c0) * 4, kf);
@@ -314,7 +350,7 @@ struct Kernel {
     }
     __builtin_amdgcn_sched_barrier(0);  // keep the sections apart: bounds live registers
     // keys: K' = k/E (in-chunk scores) and Kdec = k E_last/E (state update)
-    unsigned char* kp = smem + G::kKp + tl0 * G::QRS + c0 * 2;
+    unsigned char* kp = (OWN ? rows + 8 * th * G::QRS : smem + G::kKp + tl0 * G::QRS) + c0 * 2;
     float kdv[8][2];
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
@@ -348,19 +384,46 @@ struct Kernel {
     *reinterpret_cast<uint2*>(vp + G::TRS) = make_uint2(v1[0], v1[1]);
     *reinterpret_cast<uint2*>(vp + G::TRS + 8) = make_uint2(v1[2], v1[3]);
     if (OUTPUT) {
+      const int g4 = (threadIdx.x >> 4) & 3, n = threadIdx.x & 15;
+      bf16x8 kop[G::KS];
+      auto operands = [&](bf16x8 (&o)[G::KS]) {
+        __builtin_amdgcn_wave_barrier();   // LDS serves one wave's requests in order: the rows are complete here, and read before they change
+#pragma unroll
+        for (int ks = 0; ks < G::KS; ++ks) {
+          const unsigned char* p = rows + n * G::QRS + g4 * 8 + 64 * ks;
+          o[ks] = make8(*reinterpret_cast<const uint2*>(p), *reinterpret_cast<const uint2*>(p + 32));
+        }
+        __builtin_amdgcn_wave_barrier();
+      };
+      auto scores = [&](int hh) {
+        floatx4 pt = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int ks = 0; ks < G::KS; ++ks) pt = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kop[ks], own.q[hh][ks], pt, 0, 0, 0);
+        own.p[hh] = pack_scores(pt, g4, n);
+      };
+      if constexpr (OWN) operands(kop);
       // queries: conv + phi, times E
 #pragma unroll
       for (int hh = 0; hh < NQ; ++hh) {
         __builtin_amdgcn_sched_barrier(0);
-        if (hh + 2 < NQ) fetch_head(raw, srcQ, hh + 2, t0, tl0, coff, W);
+        if (hh + 2 < NQ) fetch_head<EDGE>(raw, srcQ, hh + 2, t0, tl0, coff, W);
         float qf[8][2];
         conv_phi<MODE>(raw.q[hh], wl + ((size_t)hh * D + c0) * 4, qf);
-        unsigned char* qp = smem + G::kQp + (hh * G::NTG + tl0) * G::QRS + c0 * 2;
+        unsigned char* qp = (OWN ? rows + 8 * th * G::QRS : smem + G::kQp + (hh * G::NTG + tl0) * G::QRS) + c0 * 2;
 #pragma unroll
         for (int i = 0; i < 8; ++i)
           *reinterpret_cast<uint32_t*>(qp + i * G::QRS) = pack2(qf[i][0] * E[i][0], qf[i][1] * E[i][1]);
+        if constexpr (OWN) {
+          operands(own.q[hh]);
+          if (hh > 0) scores(hh - 1);
+        }
       }
+      if constexpr (OWN) scores(NQ - 1);
     }
+    // vmcnt(0): every row has been used, nothing is in flight; said so that the compiler, which merges what is in flight in the four
+    // forms of this function, does not wait after it, or before the last of them, for the next granule's rows and for all stores.  (The
+    // count of exports, of which there are none, keeps it from moving the four waits to one behind where they merge.)
+    __builtin_amdgcn_s_waitcnt(0x0F70 - (EDGE ? 0x20 : 0) - (GS1 ? 0x10 : 0));
   }
   // ---- state pass only: registers -> LDS operands for S_segment = sum_i (k_i (.) D_i)^T v_i, where D_i is the
   // decay from token i to the END of the segment.  The segment is walked backwards, so D_i is a product of
@@ -516,13 +579,16 @@ __device__ inline Place find_place(const ChunkArgs& a, int l) {
   return p;
 }
 
+// one or two query heads, no conv: registers and LDS for three workgroups a compute unit
+template <int D, int GR, int MODE, bool OUTPUT> constexpr bool three_share = OUTPUT && D == 64 && GR <= 2 && MODE == kPlain;
+
 // One workgroup = one team of d/16 waves.  At head dim 64 two workgroups share a compute unit (256 VGPRs each).
 template <int D, int GR, int MODE, bool OUTPUT>
-__global__ void __launch_bounds__(D * 4, D == 64 ? 2 : 1)
+__global__ void __launch_bounds__(D * 4, D == 64 ? (three_share<D, GR, MODE, OUTPUT> ? 3 : 2) : 1)
     gla_chunk_kernel(const ChunkArgs a) {
   using KK = Kernel<D, GR, MODE, OUTPUT>;
   using G = Geo<D, GR>;
-  constexpr bool CONV = MODE != kPlain;
+  constexpr bool CONV = MODE != kPlain, OWN = KK::OWN, kThree = three_share<D, GR, MODE, OUTPUT>;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_all[];
   unsigned char* smem = smem_all;
   const int tid = threadIdx.x;
@@ -634,6 +700,9 @@ __global__ void __launch_bounds__(D * 4, D == 64 ? 2 : 1)
   // high half aliased a register with a prefetch in flight, and the chunk loop then began by waiting for the
   // whole prefetch.)
   const unsigned lrow = (unsigned)n * G::QRS + (unsigned)g4 * 8;
+  // This lane's value column.  OWN: of each two waves the columns alternate by fours, so that a lane of an output tile pair holds
+  // eight adjacent ones.
+  const int col = OWN ? 32 * (w >> 1) + 8 * (n >> 2) + 4 * (w & 1) + (n & 3) : 16 * w + n;
 
   // the output pass walks its segment forwards, the state pass backwards (see compute_state)
   const int nseg_gran = (s1 - s0 + G::NTG - 1) / G::NTG;
@@ -645,9 +714,13 @@ __global__ void __launch_bounds__(D * 4, D == 64 ? 2 : 1)
   // 128, 32 on 8, 16384 tokens, 128.3, after it 129.8; without conv, 200 sequences of 64 tokens, 16 heads on 8, 27.3 and 28.8), and behind the
   // fold with one head and no conv (16 of 300 20.9, before the state 21.2).
   constexpr bool kRowsFirst = !OUTPUT || (CONV ? D == 128 && GR == 4 : GR > 1), kRowsLast = OUTPUT && !CONV && GR == 1;
-  if (kRowsFirst) KK::fetch(raw, srcK, srcG, srcV, tfirst, tl0, coff, a.W);
-  // ---- state in accumulators: Sacc[rt][ct][i] = S[16 rt + 4 g4 + i][16 tile(ct) + n]; ct == CT holds z replicated
-  floatx4 Sacc[G::RT][G::NT];
+  if (kRowsFirst) KK::template fetch<true>(raw, srcK, srcG, srcV, tfirst, tl0, coff, a.W);
+  // ---- state in accumulators: Sacc[rt][i] = S[16 rt + 4 g4 + i][col], zacc[.][i] = z, the same in all n: channels 16 w + 4 g4 + i,
+  // or all of them where each wave needs them (ZT)
+  constexpr bool ZALL = OUTPUT && !OWN;
+  constexpr int ZT = ZALL ? G::RT : 1;
+  floatx4 Sacc[G::RT], zacc[ZT];
+  auto zrow = [&](int rt) { return 16 * (ZALL ? rt : w) + 4 * g4; };
   {
     const float* Sin = nullptr;
     const float* zin = nullptr;
@@ -678,23 +751,14 @@ __global__ void __launch_bounds__(D * 4, D == 64 ? 2 : 1)
       }
     }
 #pragma unroll
-    for (int rt = 0; rt < G::RT; ++rt) {
+    for (int rt = 0; rt < G::RT; ++rt)
 #pragma unroll
-      for (int ct = 0; ct < G::NT; ++ct) {
+      for (int i = 0; i < 4; ++i) Sacc[rt][i] = Sin ? Sin[(size_t)(16 * rt + 4 * g4 + i) * D + col] : 0.f;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int c = 16 * rt + 4 * g4 + i;
-          float val = 0.f;
-          if (ct < G::CT) {
-            if (Sin) val = Sin[(size_t)c * D + 16 * (w * G::CT + ct) + n];
-          } else {
-            if (zin) val = zin[c];
-          }
-          Sacc[rt][ct][i] = val;
-        }
-      }
-    }
-    if (!kRowsFirst && !kRowsLast) KK::fetch(raw, srcK, srcG, srcV, tfirst, tl0, coff, a.W);
+    for (int rt = 0; rt < ZT; ++rt)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) zacc[rt][i] = zin ? zin[zrow(rt) + i] : 0.f;
+    if (!kRowsFirst && !kRowsLast) KK::template fetch<true>(raw, srcK, srcG, srcV, tfirst, tl0, coff, a.W);
     if (CONV) {
       const float wscale = MODE == kConvElu ? kLog2e : 1.f;
 #pragma unroll
@@ -726,18 +790,20 @@ __global__ void __launch_bounds__(D * 4, D == 64 ? 2 : 1)
         for (int rt = 0; rt < 4; ++rt)
 #pragma unroll
           for (int i = 0; i < 4; ++i)
-            o.s[rt][i] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(slot, (4 * g4 * D + 16 * w + n) * 4, (16 * (r0 + rt) + i) * D * 4, 0));
+            o.s[rt][i] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(slot, (4 * g4 * D + col) * 4, (16 * (r0 + rt) + i) * D * 4, 0));
       };
       auto add = [&](int j, int r0, const Rows& o) {
 #pragma unroll
         for (int rt = 0; rt < 4; ++rt) {
-          const floatx4 dz = *reinterpret_cast<const floatx4*>(zd + j * 2 * D + 16 * (r0 + rt) + 4 * g4);
           const floatx4 dec = *reinterpret_cast<const floatx4*>(zd + j * 2 * D + D + 16 * (r0 + rt) + 4 * g4);
 #pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            Sacc[r0 + rt][0][i] = fmaf(dec[i], Sacc[r0 + rt][0][i], o.s[rt][i]);
-            Sacc[r0 + rt][G::CT][i] = fmaf(dec[i], Sacc[r0 + rt][G::CT][i], dz[i]);
-          }
+          for (int i = 0; i < 4; ++i) Sacc[r0 + rt][i] = fmaf(dec[i], Sacc[r0 + rt][i], o.s[rt][i]);
+        }
+#pragma unroll
+        for (int rt = ZALL ? r0 : 0; rt < (ZALL ? r0 + 4 : 1); ++rt) {
+          const floatx4 dz = *reinterpret_cast<const floatx4*>(zd + j * 2 * D + zrow(rt)), dec = *reinterpret_cast<const floatx4*>(zd + j * 2 * D + D + zrow(rt));
+#pragma unroll
+          for (int i = 0; i < 4; ++i) zacc[rt][i] = fmaf(dec[i], zacc[rt][i], dz[i]);
         }
       };
       Rows x, y;
@@ -766,10 +832,11 @@ __global__ void __launch_bounds__(D * 4, D == 64 ? 2 : 1)
   float rgran[2] = {1.f, 1.f};  // state pass: decay of everything after the current granule, this lane's 2 channels
 
   const bool gs1 = a.gate_scale == 1.0f;
-  if (kRowsLast) KK::fetch(raw, srcK, srcG, srcV, tfirst, tl0, coff, a.W);
+  Chunk<D, KK::NQ> own;
+  if (kRowsLast) KK::template fetch<true>(raw, srcK, srcG, srcV, tfirst, tl0, coff, a.W);
   __syncthreads();  // conv weights are in LDS
 
-  // Per granule: compute stage, barrier, MFMA stage, barrier.
+  // Per granule: compute stage, barrier, MFMA stage, barrier (OWN: none at its end, as only this wave reads its chunk's S and V there).
   bool dead = false;   // state pass: after the last granule walked, the segment's total decay is exactly zero
 #pragma unroll 1
   for (int gi = 0; gi < nseg_gran; ++gi) {
@@ -787,13 +854,13 @@ __global__ void __launch_bounds__(D * 4, D == 64 ? 2 : 1)
           else
             KK::template compute_state<true, false>(raw, smem, wl, t0, s1, tl0, c0, mcw, th, a.gate_scale, rgran);
         } else if (!edge && gs1)
-          KK::template compute<false, true>(raw, srcQ, coff, a.W, smem, wl, t0, s1, tl0, c0, mcw, th, a.gate_scale);
+          KK::template compute<false, true>(raw, srcQ, coff, a.W, smem, wl, t0, s1, tl0, c0, mcw, th, a.gate_scale, own);
         else if (!edge)
-          KK::template compute<false, false>(raw, srcQ, coff, a.W, smem, wl, t0, s1, tl0, c0, mcw, th, a.gate_scale);
+          KK::template compute<false, false>(raw, srcQ, coff, a.W, smem, wl, t0, s1, tl0, c0, mcw, th, a.gate_scale, own);
         else if (gs1)
-          KK::template compute<true, true>(raw, srcQ, coff, a.W, smem, wl, t0, s1, tl0, c0, mcw, th, a.gate_scale);
+          KK::template compute<true, true>(raw, srcQ, coff, a.W, smem, wl, t0, s1, tl0, c0, mcw, th, a.gate_scale, own);
         else
-          KK::template compute<true, false>(raw, srcQ, coff, a.W, smem, wl, t0, s1, tl0, c0, mcw, th, a.gate_scale);
+          KK::template compute<true, false>(raw, srcQ, coff, a.W, smem, wl, t0, s1, tl0, c0, mcw, th, a.gate_scale, own);
       }
       if (!OUTPUT) {
         // State pass: everything before this granule is multiplied by rgran.  Once that is exactly zero in every
@@ -803,6 +870,9 @@ __global__ void __launch_bounds__(D * 4, D == 64 ? 2 : 1)
         const bool alive = __builtin_amdgcn_ballot_w64(rgran[0] != 0.f || rgran[1] != 0.f) != 0;
         if (l == 0) *reinterpret_cast<int*>(smem + G::kFl + w * 4) = alive ? 1 : 0;
       }
+      // (and nothing of the prologue's is: with waits for it in the MFMA stage and at the loop's end 32768 tokens of 64 took 102.5 us,
+      // without 98.4; 700 of 128 28.2 and 27.9)
+      if (OUTPUT) __builtin_amdgcn_s_waitcnt(0x0F70);
       __syncthreads();
       dead = false;
       if (!OUTPUT) {
@@ -815,7 +885,7 @@ __global__ void __launch_bounds__(D * 4, D == 64 ? 2 : 1)
       if (OUTPUT && D == 64) __builtin_amdgcn_s_setprio(3);
       {
         // next granule's rows travel while the matrix cores work
-        if (gi + 1 < nseg_gran && !dead) KK::fetch(raw, srcK, srcG, srcV, t0 + tstep, tl0, coff, a.W);
+        if (gi + 1 < nseg_gran && !dead) KK::template fetch<!OUTPUT>(raw, srcK, srcG, srcV, t0 + tstep, tl0, coff, a.W);
 
         // chunks of this granule in which some channel uses the mid-chunk reference (bit mc)
         int midmask = 0;
@@ -825,6 +895,129 @@ __global__ void __launch_bounds__(D * 4, D == 64 ? 2 : 1)
             midmask |= *reinterpret_cast<const int*>(smem + G::kFl + j * 4) << (j / G::CH);
           midmask = __builtin_amdgcn_readfirstlane(midmask);
         }
+        const short4v ones4 = {0x3F80, 0x3F80, 0x3F80, 0x3F80};   // the state update of the normalizer z
+        if constexpr (OWN) {
+          // =========================== MFMA stage, head dim 64 ===========================
+          // The state through the granule's chunks, 16 value columns a wave; what it is at each chunk's start goes to LDS as bf16
+          // operands (rows = value columns, k = key channels {4 g4 + i, 16 + 4 g4 + i} of each 32).
+          struct Update { uint2 kd; floatx4 eb; };     // (j == RT: this wave's share of z)
+          auto load_value = [&](int mc) { return *reinterpret_cast<const uint2*>(smem + G::kVt + col * G::TRS + (kChunk * mc + 4 * g4) * 2); };
+          auto load_update = [&](int mc, int j) {
+            const int rt = j < G::RT ? j : w;
+            return Update{*reinterpret_cast<const uint2*>(smem + G::kKd + (16 * rt + n) * G::TRS + (kChunk * mc + 4 * g4) * 2),
+                          *reinterpret_cast<const floatx4*>(smem + G::kEb + (mc * D + 16 * rt + 4 * g4) * 4)};
+          };
+          // With one or two query heads, whose calls are latency, the next chunk's operands are requested before this one's results are
+          // awaited (8192 tokens of 8 heads 30.2 -> 29.6 us); with four they spill
+          constexpr bool kAhead = CONV && GR < 4;
+          Update up[kAhead ? G::RT + 1 : 1];
+          uint2 vb = load_value(0);
+          if constexpr (kAhead) {
+#pragma unroll
+            for (int j = 0; j <= G::RT; ++j) up[j] = load_update(0, j);
+          }
+          auto through = [&](auto mid) {
+#pragma unroll
+            for (int mc = 0; mc < G::MCG; ++mc) {
+              if (!kAhead && mc > 0) vb = load_value(mc);
+              if constexpr (decltype(mid)::value) {
+                // Some channel of the granule uses the mid-chunk reference.  The accumulators take rho in place (rho (.) S is what
+                // the chunk's MFMAs need), and the update below continues from there: its decay factor is E_last / rho.
+                const float* ef = reinterpret_cast<const float*>(smem + G::kEf) + mc * D + 4 * g4;
+#pragma unroll
+                for (int rt = 0; rt < G::RT; ++rt) Sacc[rt] *= *reinterpret_cast<const floatx4*>(ef + 16 * rt);
+                zacc[0] *= *reinterpret_cast<const floatx4*>(ef + 16 * w);
+              }
+#pragma unroll
+              for (int ks = 0; ks < G::KS; ++ks) {
+                const floatx4 lo = Sacc[2 * ks], hi = Sacc[2 * ks + 1];
+                *reinterpret_cast<uint4*>(smem + G::kSn + mc * G::kSnChunk + (w * G::KS + ks) * 1024 + l * 16) =
+                    make_uint4(pack2(lo[0], lo[1]), pack2(lo[2], lo[3]), pack2(hi[0], hi[1]), pack2(hi[2], hi[3]));
+              }
+              if (n == 0)
+                *reinterpret_cast<uint2*>(smem + G::kZs + (mc * D + 16 * w + 4 * g4) * 2) = make_uint2(pack2(zacc[0][0], zacc[0][1]), pack2(zacc[0][2], zacc[0][3]));
+              if (kAhead) __builtin_amdgcn_sched_barrier(0);
+              // S <- diag(E_last / rho) (rho S) + Kdec^T V, z likewise with ones
+#pragma unroll
+              for (int j = 0; j <= G::RT; ++j) {
+                const Update u = kAhead ? up[j % (kAhead ? G::RT + 1 : 1)] : load_update(mc, j);
+                floatx4& acc = j < G::RT ? Sacc[j % G::RT] : zacc[0];
+                acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(short4v, u.kd), j < G::RT ? __builtin_bit_cast(short4v, vb) : ones4,
+                                                                acc * u.eb, 0, 0, 0);
+              }
+              if (kAhead && mc + 1 < G::MCG) {
+                __builtin_amdgcn_sched_barrier(0);
+                vb = load_value(mc + 1);
+#pragma unroll
+                for (int j = 0; j <= G::RT; ++j) up[j % (kAhead ? G::RT + 1 : 1)] = load_update(mc + 1, j);
+                __builtin_amdgcn_sched_barrier(0);
+              }
+            }
+          };
+          if (midmask != 0) through(std::true_type{});
+          else through(std::false_type{});
+          __syncthreads();  // S and z at every chunk's start are in LDS
+          // Outputs of the wave's own chunk: o^T[dv][query] = S^T (q (.) E)^T + [V,V]^T [P_hi;P_lo]^T, den = q' . z + (column sums of
+          // P), by a ones operand against the packed scores: it sums exactly the high parts and residuals that the values meet.
+          if (t0 + kChunk * w < s1) {
+            const bf16x8 ones8 = __builtin_bit_cast(bf16x8, make_uint4(0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u));
+            const int tok = t0 + kChunk * w + n;
+            const size_t orow = (row0 + tok) * a.Hq + hk * a.group + qh0;
+            float rden[GR];
+            bf16x8 zf[G::KS];
+#pragma unroll
+            for (int ks = 0; ks < G::KS; ++ks) {
+              const unsigned char* pz = smem + G::kZs + (w * D + 32 * ks + 4 * g4) * 2;
+              zf[ks] = make8(*reinterpret_cast<const uint2*>(pz), *reinterpret_cast<const uint2*>(pz + 32));
+            }
+            // All four tiles of a head at a time (two at a time: 96.2 -> 98.0 us at 32768 tokens), or two where that keeps three
+            // workgroups on a compute unit.  Each two hold a lane's eight adjacent columns of its token.
+            constexpr int CT = kThree ? 2 : G::NW;
+#pragma unroll
+            for (int ct0 = 0; ct0 < G::NW; ct0 += CT) {
+              if (kThree) __builtin_amdgcn_sched_barrier(0);
+              bf16x8 sf[CT][G::KS], vf[CT];
+#pragma unroll
+              for (int e = 0; e < CT; ++e) {
+                const int ct = ct0 + e;
+#pragma unroll
+                for (int ks = 0; ks < G::KS; ++ks)
+                  sf[e][ks] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(smem + G::kSn + w * G::kSnChunk + (ct * G::KS + ks) * 1024 + l * 16));
+                // (the same four tokens fill both halves of the operand)
+                const uint2 v = *reinterpret_cast<const uint2*>(smem + G::kVt + (32 * (ct >> 1) + 8 * (n >> 2) + 4 * (ct & 1) + (n & 3)) * G::TRS + (kChunk * w + 4 * g4) * 2);
+                vf[e] = make8(v, v);
+              }
+#pragma unroll
+              for (int hh = 0; hh < GR; ++hh) {
+                const bf16x8 pp = __builtin_bit_cast(bf16x8, own.p[hh]);
+                floatx4 dz = {0.f, 0.f, 0.f, 0.f};
+                if (ct0 == 0) {
+#pragma unroll
+                  for (int ks = 0; ks < G::KS; ++ks) dz = __builtin_amdgcn_mfma_f32_16x16x32_bf16(zf[ks], own.q[hh][ks], dz, 0, 0, 0);
+                  dz = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones8, pp, dz, 0, 0, 0);
+                }
+                floatx4 acc[CT];
+#pragma unroll
+                for (int e = 0; e < CT; ++e) {
+                  acc[e] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                  for (int ks = 0; ks < G::KS; ++ks) acc[e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(sf[e][ks], own.q[hh][ks], acc[e], 0, 0, 0);
+                  acc[e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[e], pp, acc[e], 0, 0, 0);
+                }
+                const float den = dz[0] + a.eps;
+                if (ct0 == 0) rden[hh] = fast_rcp(den);
+                if (tok < s1) {
+#pragma unroll
+                  for (int e = 0; e < CT; e += 2) {
+                    const floatx4 x = acc[e] * rden[hh], y = acc[e + 1] * rden[hh];
+                    *reinterpret_cast<uint4*>(a.o + (orow + hh) * D + 16 * (ct0 + e) + 8 * g4) = make_uint4(pack2(x[0], x[1]), pack2(x[2], x[3]), pack2(y[0], y[1]), pack2(y[2], y[3]));
+                  }
+                  if (ct0 == 0 && a.den_out != nullptr && g4 == 0) a.den_out[orow + hh] = den;
+                }
+              }
+            }
+          }
+        } else {
         // =========================== MFMA stage: 16 tokens at a time ===========================
 #pragma unroll 1
         for (int mc = 0; mc < G::MCG; ++mc) {
@@ -838,35 +1031,26 @@ __global__ void __launch_bounds__(D * 4, D == 64 ? 2 : 1)
 #pragma unroll
             for (int rt = 0; rt < G::RT; ++rt) {
               const floatx4 r = *reinterpret_cast<const floatx4*>(smem + G::kEf + (mc * D + 16 * rt + 4 * g4) * 4);
-#pragma unroll
-              for (int ct = 0; ct < G::NT; ++ct)
-#pragma unroll
-                for (int i = 0; i < 4; ++i) Sacc[rt][ct][i] *= r[i];
+              Sacc[rt] *= r;
+              zacc[rt % ZT] *= r;
             }
           }
-          // value fragments: lane (g4, n) holds V[tok 4 g4 .. +3][dv 16 tile + n]; serves as A (V^T) and as B (V)
-          short4v vfrag[G::NT];
-#pragma unroll
-          for (int ct = 0; ct < G::CT; ++ct) {
-            const uint2 r = *reinterpret_cast<const uint2*>(smem + G::kVt + (16 * (w * G::CT + ct) + n) * G::TRS +
-                                                            (kChunk * mc + 4 * g4) * 2);
-            vfrag[ct] = __builtin_bit_cast(short4v, r);
-          }
-          vfrag[G::CT] = short4v{0x3F80, 0x3F80, 0x3F80, 0x3F80};  // ones: the state update of the normalizer z
+          // value fragments: lane (g4, n) holds V[tok 4 g4 .. +3][dv 16 w + n]; serves as A (V^T) and as B (V)
+          const uint2 vraw = *reinterpret_cast<const uint2*>(smem + G::kVt + (16 * w + n) * G::TRS + (kChunk * mc + 4 * g4) * 2);
+          const short4v vfrag = __builtin_bit_cast(short4v, vraw);
 
-          if (OUTPUT) {
+          if constexpr (ZALL) {
             // state (rho (.) S, see above) as bf16 A-fragments: rows = value columns, k = key channels
-            // {4 g4 + i, 16 + 4 g4 + i} of each 32; tile CT is the normalizer z, the same in every row
-            bf16x8 sa[G::NT][G::KS];
+            // {4 g4 + i, 16 + 4 g4 + i} of each 32; za is the normalizer z, the same in every row
+            bf16x8 sa[G::KS], za[G::KS];
+            auto operand = [](const floatx4& lo, const floatx4& hi) {
+              return __builtin_bit_cast(bf16x8, make_uint4(pack2(lo[0], lo[1]), pack2(lo[2], lo[3]), pack2(hi[0], hi[1]), pack2(hi[2], hi[3])));
+            };
 #pragma unroll
-            for (int ct = 0; ct < G::NT; ++ct)
+            for (int ks = 0; ks < G::KS; ++ks) sa[ks] = operand(Sacc[2 * ks], Sacc[2 * ks + 1]);
 #pragma unroll
-              for (int ks = 0; ks < G::KS; ++ks) {
-                const floatx4 lo = Sacc[2 * ks][ct], hi = Sacc[2 * ks + 1][ct];
-                sa[ct][ks] = __builtin_bit_cast(
-                    bf16x8, make_uint4(pack2(lo[0], lo[1]), pack2(lo[2], lo[3]), pack2(hi[0], hi[1]), pack2(hi[2], hi[3])));
-              }
-            // ---- scores and denominators: wave w < GR computes, for query head w alone, P^T = K' Q'^T and
+            for (int ks = 0; ks < G::KS; ++ks) za[ks] = operand(zacc[2 * ks], zacc[2 * ks + 1]);
+            // ---- scores and denominators (head dim 128): wave w < GR computes, for query head w alone, P^T = K' Q'^T and
             // den = q' . z + (column sums of the masked P), and shares both through LDS.  Computing the denominator
             // once per head instead of once per wave saves every wave a whole accumulator tile per head.
             if (w < GR) {
@@ -881,33 +1065,21 @@ __global__ void __launch_bounds__(D * 4, D == 64 ? 2 : 1)
                 const bf16x8 qf = __builtin_bit_cast(bf16x8, make_uint4(qlo.x, qlo.y, qhi.x, qhi.y));
                 pt = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
                     __builtin_bit_cast(bf16x8, make_uint4(klo.x, klo.y, khi.x, khi.y)), qf, pt, 0, 0, 0);
-                dz = __builtin_amdgcn_mfma_f32_16x16x32_bf16(sa[G::CT][ks], qf, dz, 0, 0, 0);
+                dz = __builtin_amdgcn_mfma_f32_16x16x32_bf16(za[ks], qf, dz, 0, 0, 0);
               }
-              // P^T[key 4 g4 + i][query n], causal: key <= query
-#pragma unroll
-              for (int i = 0; i < 4; ++i) pt[i] = (4 * g4 + i <= n) ? pt[i] : 0.f;
-              // The weights of the few nearest keys dominate the output, so their bf16 rounding would not
-              // average out: carry P as a bf16 pair (high part + residual) in one k = 32 operand.
-              const uint32_t ph0 = pack2(pt[0], pt[1]), ph1 = pack2(pt[2], pt[3]);
-              const uint32_t pl0 = pack2(pt[0] - bf_lo(ph0), pt[1] - bf_hi(ph0));
-              const uint32_t pl1 = pack2(pt[2] - bf_lo(ph1), pt[3] - bf_hi(ph1));
+              const uint4 pp = pack_scores(pt, g4, n);
               unsigned char* ps = smem + G::kPs + ((mc & 1) * GR + myh) * 1024 + l * 16;
-              *reinterpret_cast<uint4*>(ps) = make_uint4(ph0, ph1, pl0, pl1);
+              *reinterpret_cast<uint4*>(ps) = pp;
               // column sums over the 16 keys: a ones operand against the packed scores adds them to q'.z in every
               // row of the tile (one MFMA instead of two cross-lane exchanges; it sums exactly the high parts
               // and residuals that the value product below uses)
               const bf16x8 ones8 = __builtin_bit_cast(bf16x8, make_uint4(0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u));
-              dz = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones8, __builtin_bit_cast(bf16x8, make_uint4(ph0, ph1, pl0, pl1)), dz, 0, 0, 0);
+              dz = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones8, __builtin_bit_cast(bf16x8, pp), dz, 0, 0, 0);
               if (g4 == 0)
                 *reinterpret_cast<float*>(smem + G::kDn + (((mc & 1) * GR + myh) * 16 + n) * 4) = dz[0] + a.eps;
             }
             // [V|1]^T against (high, residual) in one k = 32 MFMA: the same four tokens fill both halves of A
-            bf16x8 vv[G::CT];
-#pragma unroll
-            for (int ct = 0; ct < G::CT; ++ct) {
-              const uint2 r = __builtin_bit_cast(uint2, vfrag[ct]);
-              vv[ct] = __builtin_bit_cast(bf16x8, make_uint4(r.x, r.y, r.x, r.y));
-            }
+            const bf16x8 vv = make8(vraw, vraw);
             __syncthreads();  // scores and denominators of this chunk are in LDS (double-buffered by chunk parity)
             // Query heads one at a time, operands of the next head fetched from LDS while this head's MFMA chain
             // runs.  Order matters on gfx950: a load may only target registers whose last MFMA reader has
@@ -931,26 +1103,15 @@ __global__ void __launch_bounds__(D * 4, D == 64 ? 2 : 1)
             };
             auto do_head = [&](int hh, const HeadOps& o) {
               // o^T[dv][query] = S^T (q (.) E)^T + [V,V]^T [P_hi;P_lo]^T
-              floatx4 oacc[G::CT];
+              floatx4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-              for (int ct = 0; ct < G::CT; ++ct) {
-                floatx4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                for (int ks = 0; ks < G::KS; ++ks)
-                  acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(sa[ct][ks], o.qb[ks], acc, 0, 0, 0);
-                acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vv[ct], o.pp, acc, 0, 0, 0);
-                oacc[ct] = acc;
-              }
+              for (int ks = 0; ks < G::KS; ++ks) acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(sa[ks], o.qb[ks], acc, 0, 0, 0);
+              acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vv, o.pp, acc, 0, 0, 0);
               const int tok = tq + n;
               const float rden = fast_rcp(o.den);
               if (tok < s1) {
                 bf16_t* orow = a.o + ((row0 + tok) * a.Hq + hk * a.group + qh0 + hh) * D;
-#pragma unroll
-                for (int ct = 0; ct < G::CT; ++ct) {
-                  const uint2 pk = make_uint2(pack2(oacc[ct][0] * rden, oacc[ct][1] * rden),
-                                              pack2(oacc[ct][2] * rden, oacc[ct][3] * rden));
-                  *reinterpret_cast<uint2*>(orow + 16 * (w * G::CT + ct) + 4 * g4) = pk;
-                }
+                *reinterpret_cast<uint2*>(orow + 16 * w + 4 * g4) = make_uint2(pack2(acc[0] * rden, acc[1] * rden), pack2(acc[2] * rden, acc[3] * rden));
                 if (a.den_out != nullptr && w == 0 && g4 == 0)
                   a.den_out[(row0 + tok) * a.Hq + hk * a.group + qh0 + hh] = o.den;
               }
@@ -961,8 +1122,7 @@ __global__ void __launch_bounds__(D * 4, D == 64 ? 2 : 1)
               do_head(0, opA);
             } else {
               // a pair of heads per step, the scheduling barriers pinning loads and MFMA chains in the order
-              // described above; unrolled at head dim 64 (saves the loop control, -2 %), rolled at 128 (+1.4 %
-              // when unrolled)
+              // described above (unrolled: +1.4 %)
               auto head_pair = [&](int h0) {
                 load_ops(h0 + 1, opB);
                 __builtin_amdgcn_sched_barrier(0);
@@ -973,13 +1133,8 @@ __global__ void __launch_bounds__(D * 4, D == 64 ? 2 : 1)
                 do_head(h0 + 1, opB);
                 __builtin_amdgcn_sched_barrier(0);
               };
-              if (D == 64) {
-#pragma unroll
-                for (int h0 = 0; h0 < GR; h0 += 2) head_pair(h0);
-              } else {
 #pragma unroll 1
-                for (int h0 = 0; h0 < GR; h0 += 2) head_pair(h0);
-              }
+              for (int h0 = 0; h0 < GR; h0 += 2) head_pair(h0);
             }
           }
           // ---- state update: S <- diag(E_last / rho) (rho S) + Kdec^T [V | 1]
@@ -988,22 +1143,23 @@ __global__ void __launch_bounds__(D * 4, D == 64 ? 2 : 1)
             const uint2 kr = *reinterpret_cast<const uint2*>(smem + G::kKd + (16 * rt + n) * G::TRS +
                                                              (kChunk * mc + 4 * g4) * 2);
             const short4v kdf = __builtin_bit_cast(short4v, kr);
+            // (the state pass pre-decays its operands to the end of the segment instead)
             floatx4 eb = {1.f, 1.f, 1.f, 1.f};
             if (OUTPUT) eb = *reinterpret_cast<const floatx4*>(smem + G::kEb + (mc * D + 16 * rt + 4 * g4) * 4);
-#pragma unroll
-            for (int ct = 0; ct < G::NT; ++ct) {
-              floatx4 acc = Sacc[rt][ct];
-              if (OUTPUT) {  // the state pass pre-decays its operands to the end of the segment instead
-#pragma unroll
-                for (int i = 0; i < 4; ++i) acc[i] *= eb[i];
-              }
-              Sacc[rt][ct] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(kdf, vfrag[ct], acc, 0, 0, 0);
-            }
+            floatx4 acc = Sacc[rt];
+            if (OUTPUT) acc *= eb;
+            Sacc[rt] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(kdf, vfrag, acc, 0, 0, 0);
+            if constexpr (ZALL) zacc[rt] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(kdf, ones4, zacc[rt] * eb, 0, 0, 0);
           }
+          if constexpr (!ZALL) {
+            const uint2 kr = *reinterpret_cast<const uint2*>(smem + G::kKd + (16 * w + n) * G::TRS + (kChunk * mc + 4 * g4) * 2);
+            zacc[0] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(short4v, kr), ones4, zacc[0], 0, 0, 0);
+          }
+        }
         }
       }  // MFMA stage
     if (OUTPUT && D == 64) __builtin_amdgcn_s_setprio(0);
-    __syncthreads();
+    if (!OWN) __syncthreads();
     if (dead) break;
   }
 
@@ -1025,10 +1181,11 @@ __global__ void __launch_bounds__(D * 4, D == 64 ? 2 : 1)
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         const int c = 16 * rt + 4 * g4 + i;
-#pragma unroll
-        for (int ct = 0; ct < G::CT; ++ct) Sdst[(size_t)c * D + 16 * (w * G::CT + ct) + n] = Sacc[rt][ct][i];
-        if (w == 0 && n == 0) zdst[c] = Sacc[rt][G::CT][i];
+        Sdst[(size_t)c * D + col] = Sacc[rt][i];
       }
+#pragma unroll
+    for (int rt = 0; rt < ZT; ++rt)
+      if (n == 0 && (!ZALL || w == 0)) *reinterpret_cast<floatx4*>(zdst + zrow(rt)) = zacc[rt];
     // total decay of the segment: the waves that loaded chunk 0 hold it for their two channels
     if (ddst != nullptr && mcw == 0 && th == 0) *reinterpret_cast<float2*>(ddst + c0) = make_float2(rgran[0], rgran[1]);
     if (!OUTPUT && tid == 0) a.seg_live[slot0 + seg] = dead ? 0 : 1;
