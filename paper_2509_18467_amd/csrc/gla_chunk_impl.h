@@ -27,7 +27,12 @@
 // columns of all outputs (scores and denominators shared per chunk, six barriers a granule, 32 bytes of a row per store) 32768 tokens
 // of 32 heads on 8 took 107.4 us, now 96.7; 8192 46.5 and 43.3, 64 9.5 and 7.7.  What bounds it: the output pass moves 386 MB in 80 us, 93 %
 // of the rate of a large copy; the state pass and the launches in between are the rest.
-// Head dim 128: the state at four chunks' starts would fill the LDS; the waves share all chunks (see the MFMA stage).
+// Head dim 128: the state at four chunks' starts would fill the LDS, so each wave forms its 16 columns of all outputs.  z, scores and
+// denominators of a granule come first, two (chunk, head) a wave, then outputs and state without a barrier: 16384 tokens of 32 heads
+// on 8 127.5 -> 123 us, 5000 of 16 on 8 50.2 -> 46.6, 700 27.9 -> 26.3, 128K tokens 830 -> 800 (scores per chunk, by half of the waves
+// while the others waited, z in all waves' registers).  Its stages do not overlap: the compute stage (5.9 of 14.3 us a granule) is
+// bound by the vector ALUs, outputs and state (5.7) by LDS, 26 KB a wave and chunk.  Granules of 32 tokens in two sets of operands, the
+// two waves of a SIMD in opposite stages, took 151 us.
 //
 // Per-step decay is floored at 2^-13 so that eight steps of 1/alpha stay below 2^104; the floor changes
 // a state by at most 2^-13 of what the step before it held.
@@ -123,10 +128,10 @@ struct Geo {
   static constexpr int kEb = kVt + D * TRS;
   static constexpr int kEf = kEb + MCG * D * 4;   // the reference rho of each chunk and channel, fp32
   static constexpr int kWl = kEf + MCG * D * 4;
-  static constexpr int kPs = kWl + (GR + 1) * D * 16;   // shared scores: [2 buffers][GR heads][64 lanes] x 16 B (4 high parts, 4 residuals)
-  static constexpr int kDn = kPs + (OWN ? 0 : 2 * GR * 2 * 512);   // shared denominators: [2 buffers][GR heads][16 queries] fp32
-  static constexpr int kZs = kDn + (OWN ? 0 : 2 * GR * 64);        // z at each chunk's start, bf16
-  static constexpr int kFl = kZs + (OWN ? MCG * D * 2 : 0);        // per load-stage wave: 1 if one of its channels uses the mid-chunk reference
+  static constexpr int kPs = kWl + (GR + 1) * D * 16;   // shared scores: [chunk][head][64 lanes] x 16 B (4 high parts, 4 residuals)
+  static constexpr int kDn = kPs + (OWN ? 0 : MCG * GR * 1024);    // shared denominators: [chunk][head][16 queries] fp32
+  static constexpr int kZs = kDn + (OWN ? 0 : MCG * GR * 64);      // z at each chunk's start, bf16
+  static constexpr int kFl = kZs + (GR > 0 ? MCG * D * 2 : 0);     // per load-stage wave: 1 if one of its channels uses the mid-chunk reference
   static constexpr int kBytes = kFl + 32;
   static constexpr int kSlot = D * D + 2 * D;  // floats per workspace slot: S | z | decay
 };
@@ -298,8 +303,9 @@ struct Kernel {
 #pragma unroll
       for (int ch = 0; ch < 2; ++ch) {
         const float gl = ch ? bf_hi(raw.g[i + 3]) : bf_lo(raw.g[i + 3]);
-        const float u = fminf(fast_exp2(-kLog2e * gl), 1e30f);  // exp(-g)
+        float u = fast_exp2(-kLog2e * gl);  // exp(-g)
         float al, ia;
+        if (!GS1) u = fminf(u, 1e30f);      // (else an infinity ends at the floor too)
         if (GS1) {
           ia = fminf(1.f + u, kInvAlphaMax);  // 1/sigmoid(g) = 1 + exp(-g)
           al = fmaxf(fast_rcp(1.f + u), kAlphaMin);
@@ -441,7 +447,8 @@ struct Kernel {
 #pragma unroll
       for (int ch = 0; ch < 2; ++ch) {
         const float gl = ch ? bf_hi(raw.g[i + 3]) : bf_lo(raw.g[i + 3]);
-        const float u = fminf(fast_exp2(-kLog2e * gl), 1e30f);  // exp(-g)
+        float u = fast_exp2(-kLog2e * gl);  // exp(-g)
+        if (!GS1) u = fminf(u, 1e30f);
         float a1;
         if (GS1) a1 = fmaxf(fast_rcp(1.f + u), kAlphaMin);
         else a1 = fast_exp2(fmaxf(-gate_scale * fast_log2(1.f + u), kLog2AlphaMin));
@@ -715,12 +722,9 @@ __global__ void __launch_bounds__(D * 4, D == 64 ? (three_share<D, GR, MODE, OUT
   // fold with one head and no conv (16 of 300 20.9, before the state 21.2).
   constexpr bool kRowsFirst = !OUTPUT || (CONV ? D == 128 && GR == 4 : GR > 1), kRowsLast = OUTPUT && !CONV && GR == 1;
   if (kRowsFirst) KK::template fetch<true>(raw, srcK, srcG, srcV, tfirst, tl0, coff, a.W);
-  // ---- state in accumulators: Sacc[rt][i] = S[16 rt + 4 g4 + i][col], zacc[.][i] = z, the same in all n: channels 16 w + 4 g4 + i,
-  // or all of them where each wave needs them (ZT)
-  constexpr bool ZALL = OUTPUT && !OWN;
-  constexpr int ZT = ZALL ? G::RT : 1;
-  floatx4 Sacc[G::RT], zacc[ZT];
-  auto zrow = [&](int rt) { return 16 * (ZALL ? rt : w) + 4 * g4; };
+  // ---- state in accumulators: Sacc[rt][i] = S[16 rt + 4 g4 + i][col], zacc[i] = z[16 w + 4 g4 + i], the same in all n
+  floatx4 Sacc[G::RT], zacc;
+  const int zrow = 16 * w + 4 * g4;
   {
     const float* Sin = nullptr;
     const float* zin = nullptr;
@@ -755,9 +759,7 @@ __global__ void __launch_bounds__(D * 4, D == 64 ? (three_share<D, GR, MODE, OUT
 #pragma unroll
       for (int i = 0; i < 4; ++i) Sacc[rt][i] = Sin ? Sin[(size_t)(16 * rt + 4 * g4 + i) * D + col] : 0.f;
 #pragma unroll
-    for (int rt = 0; rt < ZT; ++rt)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) zacc[rt][i] = zin ? zin[zrow(rt) + i] : 0.f;
+    for (int i = 0; i < 4; ++i) zacc[i] = zin ? zin[zrow + i] : 0.f;
     if (!kRowsFirst && !kRowsLast) KK::template fetch<true>(raw, srcK, srcG, srcV, tfirst, tl0, coff, a.W);
     if (CONV) {
       const float wscale = MODE == kConvElu ? kLog2e : 1.f;
@@ -799,11 +801,10 @@ __global__ void __launch_bounds__(D * 4, D == 64 ? (three_share<D, GR, MODE, OUT
 #pragma unroll
           for (int i = 0; i < 4; ++i) Sacc[r0 + rt][i] = fmaf(dec[i], Sacc[r0 + rt][i], o.s[rt][i]);
         }
+        if (r0 == 0) {
+          const floatx4 dz = *reinterpret_cast<const floatx4*>(zd + j * 2 * D + zrow), dec = *reinterpret_cast<const floatx4*>(zd + j * 2 * D + D + zrow);
 #pragma unroll
-        for (int rt = ZALL ? r0 : 0; rt < (ZALL ? r0 + 4 : 1); ++rt) {
-          const floatx4 dz = *reinterpret_cast<const floatx4*>(zd + j * 2 * D + zrow(rt)), dec = *reinterpret_cast<const floatx4*>(zd + j * 2 * D + D + zrow(rt));
-#pragma unroll
-          for (int i = 0; i < 4; ++i) zacc[rt][i] = fmaf(dec[i], zacc[rt][i], dz[i]);
+          for (int i = 0; i < 4; ++i) zacc[i] = fmaf(dec[i], zacc[i], dz[i]);
         }
       };
       Rows x, y;
@@ -926,7 +927,7 @@ __global__ void __launch_bounds__(D * 4, D == 64 ? (three_share<D, GR, MODE, OUT
                 const float* ef = reinterpret_cast<const float*>(smem + G::kEf) + mc * D + 4 * g4;
 #pragma unroll
                 for (int rt = 0; rt < G::RT; ++rt) Sacc[rt] *= *reinterpret_cast<const floatx4*>(ef + 16 * rt);
-                zacc[0] *= *reinterpret_cast<const floatx4*>(ef + 16 * w);
+                zacc *= *reinterpret_cast<const floatx4*>(ef + 16 * w);
               }
 #pragma unroll
               for (int ks = 0; ks < G::KS; ++ks) {
@@ -935,13 +936,13 @@ __global__ void __launch_bounds__(D * 4, D == 64 ? (three_share<D, GR, MODE, OUT
                     make_uint4(pack2(lo[0], lo[1]), pack2(lo[2], lo[3]), pack2(hi[0], hi[1]), pack2(hi[2], hi[3]));
               }
               if (n == 0)
-                *reinterpret_cast<uint2*>(smem + G::kZs + (mc * D + 16 * w + 4 * g4) * 2) = make_uint2(pack2(zacc[0][0], zacc[0][1]), pack2(zacc[0][2], zacc[0][3]));
+                *reinterpret_cast<uint2*>(smem + G::kZs + (mc * D + 16 * w + 4 * g4) * 2) = make_uint2(pack2(zacc[0], zacc[1]), pack2(zacc[2], zacc[3]));
               if (kAhead) __builtin_amdgcn_sched_barrier(0);
               // S <- diag(E_last / rho) (rho S) + Kdec^T V, z likewise with ones
 #pragma unroll
               for (int j = 0; j <= G::RT; ++j) {
                 const Update u = kAhead ? up[j % (kAhead ? G::RT + 1 : 1)] : load_update(mc, j);
-                floatx4& acc = j < G::RT ? Sacc[j % G::RT] : zacc[0];
+                floatx4& acc = j < G::RT ? Sacc[j % G::RT] : zacc;
                 acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(short4v, u.kd), j < G::RT ? __builtin_bit_cast(short4v, vb) : ones4,
                                                                 acc * u.eb, 0, 0, 0);
               }
@@ -1017,145 +1018,162 @@ __global__ void __launch_bounds__(D * 4, D == 64 ? (three_share<D, GR, MODE, OUT
               }
             }
           }
-        } else {
-        // =========================== MFMA stage: 16 tokens at a time ===========================
-#pragma unroll 1
-        for (int mc = 0; mc < G::MCG; ++mc) {
-          const int tq = t0 + kChunk * mc;  // first token of the chunk
-          if (tq >= s1) break;
-          if (OUTPUT && ((midmask >> mc) & 1)) {
-            // Rare: some channel of this chunk uses the mid-chunk reference.  The accumulators take rho in place
-            // (rho (.) S is what the chunk's MFMAs need), and the state update below continues from there: its
-            // decay factor is E_last / rho.  Placed at the head of the loop body so that the rest of the chunk
-            // stays one scheduling block.
+        } else if constexpr (OUTPUT) {
+          // =========================== MFMA stage, head dim 128 ===========================
+          // z through the granule's chunks, a wave's 16 channels; what it is at each chunk's start goes to LDS as bf16
 #pragma unroll
-            for (int rt = 0; rt < G::RT; ++rt) {
-              const floatx4 r = *reinterpret_cast<const floatx4*>(smem + G::kEf + (mc * D + 16 * rt + 4 * g4) * 4);
-              Sacc[rt] *= r;
-              zacc[rt % ZT] *= r;
-            }
+          for (int mc = 0; mc < G::MCG; ++mc) {
+            const unsigned at = (mc * D + 16 * w + 4 * g4) * 4;
+            const uint2 kd = *reinterpret_cast<const uint2*>(smem + G::kKd + (16 * w + n) * G::TRS + (kChunk * mc + 4 * g4) * 2);
+            if (midmask != 0) zacc *= *reinterpret_cast<const floatx4*>(smem + G::kEf + at);      // (see the state below)
+            if (n == 0)
+              *reinterpret_cast<uint2*>(smem + G::kZs + (mc * D + 16 * w + 4 * g4) * 2) = make_uint2(pack2(zacc[0], zacc[1]), pack2(zacc[2], zacc[3]));
+            zacc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(short4v, kd), ones4, zacc * *reinterpret_cast<const floatx4*>(smem + G::kEb + at), 0, 0, 0);
           }
-          // value fragments: lane (g4, n) holds V[tok 4 g4 .. +3][dv 16 w + n]; serves as A (V^T) and as B (V)
-          const uint2 vraw = *reinterpret_cast<const uint2*>(smem + G::kVt + (16 * w + n) * G::TRS + (kChunk * mc + 4 * g4) * 2);
-          const short4v vfrag = __builtin_bit_cast(short4v, vraw);
-
-          if constexpr (ZALL) {
-            // state (rho (.) S, see above) as bf16 A-fragments: rows = value columns, k = key channels
-            // {4 g4 + i, 16 + 4 g4 + i} of each 32; za is the normalizer z, the same in every row
-            bf16x8 sa[G::KS], za[G::KS];
-            auto operand = [](const floatx4& lo, const floatx4& hi) {
-              return __builtin_bit_cast(bf16x8, make_uint4(pack2(lo[0], lo[1]), pack2(lo[2], lo[3]), pack2(hi[0], hi[1]), pack2(hi[2], hi[3])));
-            };
-#pragma unroll
-            for (int ks = 0; ks < G::KS; ++ks) sa[ks] = operand(Sacc[2 * ks], Sacc[2 * ks + 1]);
-#pragma unroll
-            for (int ks = 0; ks < G::KS; ++ks) za[ks] = operand(zacc[2 * ks], zacc[2 * ks + 1]);
-            // ---- scores and denominators (head dim 128): wave w < GR computes, for query head w alone, P^T = K' Q'^T and
-            // den = q' . z + (column sums of the masked P), and shares both through LDS.  Computing the denominator
-            // once per head instead of once per wave saves every wave a whole accumulator tile per head.
-            if (w < GR) {
-              const int myh = w;
-              floatx4 pt = {0.f, 0.f, 0.f, 0.f}, dz = {0.f, 0.f, 0.f, 0.f};
+          __syncthreads();
+          // Scores and denominators, P^T = K' Q'^T and den = q' . z + (column sums of the masked P), of chunk w % 4, half of the heads a
+          // wave, shared through LDS.
+          {
+            constexpr int HW = (GR + 1) / 2;
+            const int bc = w % G::MCG, bh0 = w / G::MCG * HW;
+            if (bh0 < GR && t0 + kChunk * bc < s1) {
+              bf16x8 kf[G::KS], zf[G::KS];
 #pragma unroll
               for (int ks = 0; ks < G::KS; ++ks) {
-                const unsigned char* pk = smem + G::kKp + (kChunk * mc) * G::QRS + lrow + 64 * ks;
-                const unsigned char* pq = smem + G::kQp + (myh * G::NTG + kChunk * mc) * G::QRS + lrow + 64 * ks;
-                const uint2 klo = *reinterpret_cast<const uint2*>(pk), khi = *reinterpret_cast<const uint2*>(pk + 32);
-                const uint2 qlo = *reinterpret_cast<const uint2*>(pq), qhi = *reinterpret_cast<const uint2*>(pq + 32);
-                const bf16x8 qf = __builtin_bit_cast(bf16x8, make_uint4(qlo.x, qlo.y, qhi.x, qhi.y));
-                pt = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                    __builtin_bit_cast(bf16x8, make_uint4(klo.x, klo.y, khi.x, khi.y)), qf, pt, 0, 0, 0);
-                dz = __builtin_amdgcn_mfma_f32_16x16x32_bf16(za[ks], qf, dz, 0, 0, 0);
+                const unsigned char* pk = smem + G::kKp + (kChunk * bc) * G::QRS + lrow + 64 * ks;
+                const unsigned char* pz = smem + G::kZs + (bc * D + 32 * ks + 4 * g4) * 2;
+                kf[ks] = make8(*reinterpret_cast<const uint2*>(pk), *reinterpret_cast<const uint2*>(pk + 32));
+                zf[ks] = make8(*reinterpret_cast<const uint2*>(pz), *reinterpret_cast<const uint2*>(pz + 32));
               }
-              const uint4 pp = pack_scores(pt, g4, n);
-              unsigned char* ps = smem + G::kPs + ((mc & 1) * GR + myh) * 1024 + l * 16;
-              *reinterpret_cast<uint4*>(ps) = pp;
-              // column sums over the 16 keys: a ones operand against the packed scores adds them to q'.z in every
-              // row of the tile (one MFMA instead of two cross-lane exchanges; it sums exactly the high parts
-              // and residuals that the value product below uses)
-              const bf16x8 ones8 = __builtin_bit_cast(bf16x8, make_uint4(0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u));
-              dz = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones8, __builtin_bit_cast(bf16x8, pp), dz, 0, 0, 0);
-              if (g4 == 0)
-                *reinterpret_cast<float*>(smem + G::kDn + (((mc & 1) * GR + myh) * 16 + n) * 4) = dz[0] + a.eps;
+#pragma unroll
+              for (int j = 0; j < HW; ++j) {
+                const int hh = bh0 + j;
+                floatx4 pt = {0.f, 0.f, 0.f, 0.f}, dz = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int ks = 0; ks < G::KS; ++ks) {
+                  const unsigned char* pq = smem + G::kQp + (hh * G::NTG + kChunk * bc) * G::QRS + lrow + 64 * ks;
+                  const bf16x8 qf = make8(*reinterpret_cast<const uint2*>(pq), *reinterpret_cast<const uint2*>(pq + 32));
+                  pt = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[ks], qf, pt, 0, 0, 0);
+                  dz = __builtin_amdgcn_mfma_f32_16x16x32_bf16(zf[ks], qf, dz, 0, 0, 0);
+                }
+                const uint4 pp = pack_scores(pt, g4, n);
+                *reinterpret_cast<uint4*>(smem + G::kPs + (bc * GR + hh) * 1024 + l * 16) = pp;
+                // column sums over the 16 keys: a ones operand against the packed scores adds them to q'.z in every row of the tile (it
+                // sums exactly the high parts and residuals that the value product below uses)
+                const bf16x8 ones8 = __builtin_bit_cast(bf16x8, make_uint4(0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u));
+                dz = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones8, __builtin_bit_cast(bf16x8, pp), dz, 0, 0, 0);
+                if (g4 == 0) *reinterpret_cast<float*>(smem + G::kDn + ((bc * GR + hh) * 16 + n) * 4) = dz[0] + a.eps;
+              }
             }
-            // [V|1]^T against (high, residual) in one k = 32 MFMA: the same four tokens fill both halves of A
-            const bf16x8 vv = make8(vraw, vraw);
-            __syncthreads();  // scores and denominators of this chunk are in LDS (double-buffered by chunk parity)
-            // Query heads one at a time, operands of the next head fetched from LDS while this head's MFMA chain
-            // runs.  Order matters on gfx950: a load may only target registers whose last MFMA reader has
-            // completed.  Here the loads for head h + 1 are issued BEFORE the MFMAs of head h, into the registers
-            // that head h - 1 used, and head h - 1's chain was waited for by its own epilogue (MFMAs complete in
-            // order); scheduling barriers keep the compiler from moving a load below a later MFMA.  Variants that
-            // issued the loads after queued MFMAs (two interleaved chains, a loop unrolled without the scheduling
-            // barriers) gave results that varied from run to run; the repeated-run GPU test guards this shape.
+          }
+          __syncthreads();
+          // Outputs and state, 16 value columns a wave, from here on without a barrier: o^T[dv][query] = S^T (q (.) E)^T + [V,V]^T
+          // [P_hi;P_lo]^T, then S <- diag(E_last / rho) (rho S) + Kdec^T V.  Operands of the next head travel while this head's chain
+          // runs, those of the state's update while the heads' do.  Order matters on gfx950: a load may only target registers whose
+          // last MFMA reader has completed.  The loads for head h + 1 are issued BEFORE the MFMAs of head h, into the registers that
+          // head h - 1 used, and head h - 1's chain was waited for by its own epilogue (MFMAs complete in order); scheduling
+          // barriers keep the compiler from moving a load below a later MFMA.  (Loads issued after queued MFMAs gave results that
+          // varied from run to run; the repeated-run GPU test guards this shape.)
+#pragma unroll 1
+          for (int mc = 0; mc < G::MCG; ++mc) {
+            const int tq = t0 + kChunk * mc;  // first token of the chunk
+            if (tq >= s1) break;
             struct HeadOps { bf16x8 qb[G::KS]; bf16x8 pp; float den; };
             auto load_ops = [&](int hh, HeadOps& o) {
 #pragma unroll
               for (int ks = 0; ks < G::KS; ++ks) {
                 const unsigned char* p = smem + G::kQp + (hh * G::NTG + kChunk * mc) * G::QRS + lrow + 64 * ks;
-                const uint2 lo = *reinterpret_cast<const uint2*>(p);
-                const uint2 hi = *reinterpret_cast<const uint2*>(p + 32);
-                o.qb[ks] = __builtin_bit_cast(bf16x8, make_uint4(lo.x, lo.y, hi.x, hi.y));
+                o.qb[ks] = make8(*reinterpret_cast<const uint2*>(p), *reinterpret_cast<const uint2*>(p + 32));
               }
-              // scores as one k = 32 operand: slots 0..3 the high parts, 4..7 the residuals of this lane's 4 keys
-              o.pp = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(smem + G::kPs + ((mc & 1) * GR + hh) * 1024 + l * 16));
-              o.den = *reinterpret_cast<const float*>(smem + G::kDn + (((mc & 1) * GR + hh) * 16 + n) * 4);
+              o.pp = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(smem + G::kPs + (mc * GR + hh) * 1024 + l * 16));
+              o.den = *reinterpret_cast<const float*>(smem + G::kDn + ((mc * GR + hh) * 16 + n) * 4);
             };
-            auto do_head = [&](int hh, const HeadOps& o) {
-              // o^T[dv][query] = S^T (q (.) E)^T + [V,V]^T [P_hi;P_lo]^T
-              floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+            // V[tok 4 g4 .. +3][dv 16 w + n]; serves as A (V^T, the same four tokens in both halves) and as B (V)
+            const uint2 vraw = *reinterpret_cast<const uint2*>(smem + G::kVt + col * G::TRS + (kChunk * mc + 4 * g4) * 2);
+            // Heads per step, and row tiles of the update requested ahead: two and none with two heads (5000 tokens of 16 heads on 8 46.5 us, one
+            // and all 46.8), one and all with four (16384 tokens 122.0 us, two and all 125.1, two and none 126.0).
+            constexpr int NS = GR == 2 ? 2 : 1, kAheadRows = GR == 4 ? G::RT : 0;
+            HeadOps ops[2][NS];
 #pragma unroll
-              for (int ks = 0; ks < G::KS; ++ks) acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(sa[ks], o.qb[ks], acc, 0, 0, 0);
-              acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vv, o.pp, acc, 0, 0, 0);
-              const int tok = tq + n;
-              const float rden = fast_rcp(o.den);
-              if (tok < s1) {
-                bf16_t* orow = a.o + ((row0 + tok) * a.Hq + hk * a.group + qh0 + hh) * D;
-                *reinterpret_cast<uint2*>(orow + 16 * w + 4 * g4) = make_uint2(pack2(acc[0] * rden, acc[1] * rden), pack2(acc[2] * rden, acc[3] * rden));
-                if (a.den_out != nullptr && w == 0 && g4 == 0)
-                  a.den_out[(row0 + tok) * a.Hq + hk * a.group + qh0 + hh] = o.den;
-              }
-            };
-            HeadOps opA, opB;
-            load_ops(0, opA);
-            if (GR == 1) {
-              do_head(0, opA);
-            } else {
-              // a pair of heads per step, the scheduling barriers pinning loads and MFMA chains in the order
-              // described above (unrolled: +1.4 %)
-              auto head_pair = [&](int h0) {
-                load_ops(h0 + 1, opB);
-                __builtin_amdgcn_sched_barrier(0);
-                do_head(h0, opA);
-                __builtin_amdgcn_sched_barrier(0);
-                if (h0 + 2 < GR) load_ops(h0 + 2, opA);
-                __builtin_amdgcn_sched_barrier(0);
-                do_head(h0 + 1, opB);
-                __builtin_amdgcn_sched_barrier(0);
-              };
-#pragma unroll 1
-              for (int h0 = 0; h0 < GR; h0 += 2) head_pair(h0);
+            for (int e = 0; e < NS; ++e) load_ops(e, ops[0][e]);
+            if ((midmask >> mc) & 1) {
+              // Rare: some channel of this chunk uses the mid-chunk reference.  The accumulators take rho in place (rho (.) S is
+              // what the chunk's MFMAs need), and the state update below continues from there: its decay factor is E_last / rho.
+#pragma unroll
+              for (int rt = 0; rt < G::RT; ++rt) Sacc[rt] *= *reinterpret_cast<const floatx4*>(smem + G::kEf + (mc * D + 16 * rt + 4 * g4) * 4);
             }
-          }
-          // ---- state update: S <- diag(E_last / rho) (rho S) + Kdec^T [V | 1]
+            bf16x8 sa[G::KS];   // rows = value columns, k = key channels {4 g4 + i, 16 + 4 g4 + i} of each 32
 #pragma unroll
-          for (int rt = 0; rt < G::RT; ++rt) {
-            const uint2 kr = *reinterpret_cast<const uint2*>(smem + G::kKd + (16 * rt + n) * G::TRS +
-                                                             (kChunk * mc + 4 * g4) * 2);
-            const short4v kdf = __builtin_bit_cast(short4v, kr);
-            // (the state pass pre-decays its operands to the end of the segment instead)
-            floatx4 eb = {1.f, 1.f, 1.f, 1.f};
-            if (OUTPUT) eb = *reinterpret_cast<const floatx4*>(smem + G::kEb + (mc * D + 16 * rt + 4 * g4) * 4);
-            floatx4 acc = Sacc[rt];
-            if (OUTPUT) acc *= eb;
-            Sacc[rt] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(kdf, vfrag, acc, 0, 0, 0);
-            if constexpr (ZALL) zacc[rt] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(kdf, ones4, zacc[rt] * eb, 0, 0, 0);
+            for (int ks = 0; ks < G::KS; ++ks) {
+              const floatx4 lo = Sacc[2 * ks], hi = Sacc[2 * ks + 1];
+              sa[ks] = __builtin_bit_cast(bf16x8, make_uint4(pack2(lo[0], lo[1]), pack2(lo[2], lo[3]), pack2(hi[0], hi[1]), pack2(hi[2], hi[3])));
+            }
+            const bf16x8 vv = make8(vraw, vraw);
+            uint2 kd[G::RT];
+            floatx4 eb[G::RT];
+            auto load_update = [&](int rt) {
+              kd[rt] = *reinterpret_cast<const uint2*>(smem + G::kKd + (16 * rt + n) * G::TRS + (kChunk * mc + 4 * g4) * 2);
+              eb[rt] = *reinterpret_cast<const floatx4*>(smem + G::kEb + (mc * D + 16 * rt + 4 * g4) * 4);
+            };
+#pragma unroll
+            for (int h0 = 0; h0 < GR; h0 += NS) {
+              const HeadOps(&o)[NS] = ops[(h0 / NS) & 1];
+#pragma unroll
+              for (int e = 0; e < NS; ++e)
+                if (h0 + NS + e < GR) load_ops(h0 + NS + e, ops[(h0 / NS + 1) & 1][e]);
+              if (h0 + NS == GR) {
+#pragma unroll
+                for (int rt = 0; rt < kAheadRows; ++rt) load_update(rt);
+              }
+              __builtin_amdgcn_sched_barrier(0);
+              floatx4 acc[NS];
+#pragma unroll
+              for (int e = 0; e < NS; ++e) acc[e] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+              for (int ks = 0; ks < G::KS; ++ks)
+#pragma unroll
+                for (int e = 0; e < NS; ++e) acc[e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(sa[ks], o[e].qb[ks], acc[e], 0, 0, 0);
+#pragma unroll
+              for (int e = 0; e < NS; ++e) acc[e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vv, o[e].pp, acc[e], 0, 0, 0);
+              const int tok = tq + n;
+#pragma unroll
+              for (int e = 0; e < NS; ++e) acc[e] *= fast_rcp(o[e].den);
+              if (tok < s1) {
+                const size_t orow = (row0 + tok) * a.Hq + hk * a.group + qh0 + h0;
+#pragma unroll
+                for (int e = 0; e < NS; ++e) {
+                  *reinterpret_cast<uint2*>(a.o + (orow + e) * D + 16 * w + 4 * g4) = make_uint2(pack2(acc[e][0], acc[e][1]), pack2(acc[e][2], acc[e][3]));
+                  if (a.den_out != nullptr && w == 0 && g4 == 0) a.den_out[orow + e] = o[e].den;
+                }
+              }
+              __builtin_amdgcn_sched_barrier(0);
+            }
+#pragma unroll
+            for (int rt = kAheadRows; rt < G::RT; ++rt) load_update(rt);
+#pragma unroll
+            for (int rt = 0; rt < G::RT; ++rt)
+              Sacc[rt] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(short4v, kd[rt]), __builtin_bit_cast(short4v, vraw), Sacc[rt] * eb[rt], 0, 0, 0);
           }
-          if constexpr (!ZALL) {
-            const uint2 kr = *reinterpret_cast<const uint2*>(smem + G::kKd + (16 * w + n) * G::TRS + (kChunk * mc + 4 * g4) * 2);
-            zacc[0] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(short4v, kr), ones4, zacc[0], 0, 0, 0);
+        } else {
+          // =========================== MFMA stage, state pass: operands decayed to the segment's end ===========================
+          struct Update { uint2 v, kd[G::RT + 1]; } up[2];
+          auto load_update = [&](int mc, Update& u) {
+            u.v = *reinterpret_cast<const uint2*>(smem + G::kVt + col * G::TRS + (kChunk * mc + 4 * g4) * 2);
+#pragma unroll
+            for (int j = 0; j <= G::RT; ++j)      // (the last: this wave's share of z)
+              u.kd[j] = *reinterpret_cast<const uint2*>(smem + G::kKd + (16 * (j < G::RT ? j : w) + n) * G::TRS + (kChunk * mc + 4 * g4) * 2);
+          };
+          load_update(0, up[0]);
+#pragma unroll
+          for (int mc = 0; mc < G::MCG; ++mc) {
+            if (mc + 1 < G::MCG) load_update(mc + 1, up[(mc + 1) & 1]);
+            __builtin_amdgcn_sched_barrier(0);
+            const Update& u = up[mc & 1];
+#pragma unroll
+            for (int rt = 0; rt < G::RT; ++rt)
+              Sacc[rt] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(short4v, u.kd[rt]), __builtin_bit_cast(short4v, u.v), Sacc[rt], 0, 0, 0);
+            zacc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(short4v, u.kd[G::RT]), ones4, zacc, 0, 0, 0);
           }
-        }
         }
       }  // MFMA stage
     if (OUTPUT && D == 64) __builtin_amdgcn_s_setprio(0);
@@ -1183,9 +1201,7 @@ __global__ void __launch_bounds__(D * 4, D == 64 ? (three_share<D, GR, MODE, OUT
         const int c = 16 * rt + 4 * g4 + i;
         Sdst[(size_t)c * D + col] = Sacc[rt][i];
       }
-#pragma unroll
-    for (int rt = 0; rt < ZT; ++rt)
-      if (n == 0 && (!ZALL || w == 0)) *reinterpret_cast<floatx4*>(zdst + zrow(rt)) = zacc[rt];
+    if (n == 0) *reinterpret_cast<floatx4*>(zdst + zrow) = zacc;
     // total decay of the segment: the waves that loaded chunk 0 hold it for their two channels
     if (ddst != nullptr && mcw == 0 && th == 0) *reinterpret_cast<float2*>(ddst + c0) = make_float2(rgran[0], rgran[1]);
     if (!OUTPUT && tid == 0) a.seg_live[slot0 + seg] = dead ? 0 : 1;

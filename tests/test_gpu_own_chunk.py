@@ -1,5 +1,6 @@
-"""Head dim 64, where a wave of the output pass takes one of a granule's four chunks: lengths around chunks and granules, every number of
-query heads a workgroup takes, chunks whose decay is referred to their middle, alone and beside ordinary ones."""
+"""Which wave of the output pass takes which of a granule's four chunks (head dim 64: all of one; 128: scores and denominators of one):
+lengths around chunks and granules, every number of query heads a workgroup takes, chunks whose decay is referred to their middle,
+alone and beside ordinary ones, gate logits without bound."""
 import numpy as np
 import pytest
 
@@ -39,3 +40,33 @@ def test_without_conv_many_heads(oracle, group):
     ref = oracle.gla_prefill(q, k, x["V"], x["G"], 1.0, 0.0, x["S0"], x["z0"])
     for n in ("o", "den", "S", "z"):
         H.assert_close(got[n], ref[n], wl, n)
+
+
+@pytest.mark.parametrize("shut", [(), (0, 5)])
+@pytest.mark.parametrize("group", [1, 2, 4])
+@pytest.mark.parametrize("T", (1, 16, 17, 49, 64, 81, 191))
+def test_chunks_of_128_channels(oracle, T, group, shut):
+    wl = Workload("own", 1, T, 2 * group, 2, 128, 4, "bf16")
+    x = make_inputs(wl, seed=83, halo=True, state=True)
+    for c in shut:
+        x["G"][:, 16 * c + 5:16 * c + 8, :, ::2] = -40.0
+    print("own chunk", wl, shut, flush=True)
+    ref = oracle.layer_prefill(x["Q"], x["K"], x["V"], x["G"], x["wq"], x["wk"], 1, 1.0, 0.0, x["S0"], x["z0"], x["q_halo"], x["k_halo"])
+    for segment in (192, 64):
+        got = H.run_layer_prefill(wl, x, segment=segment)
+        for n in ("o", "den", "S", "z"):
+            H.assert_close(got[n], ref[n], wl, n)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_unbounded_logits(oracle, d):
+    """Logits of -200 and of -infinity close a channel as -30 does: e^200 and infinity both end at the floor of the decay."""
+    wl = Workload("own", 1, 200, 8, 2, d, 4, "bf16")
+    x = make_inputs(wl, seed=84, halo=True, state=True)
+    out = []
+    for low in (-30.0, -200.0, -np.inf):
+        x["G"][:, 40:150:7, :, ::3] = low
+        out.append(H.run_layer_prefill(wl, x, segment=64))
+    for got in out[1:]:
+        for n in ("o", "den", "S", "z"):
+            assert np.array_equal(got[n], out[0][n])
