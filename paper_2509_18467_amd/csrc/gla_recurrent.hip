@@ -22,8 +22,9 @@
 // ones in bf16 storage.  2-norm errors against the fp64 oracle, 256 tokens, fp32 storage: o 5.8e-8, S 3.5e-8, z 3.9e-8; token
 // by token 6.5e-8, 4.5e-8, 3.9e-8 (gates of unit scale; with slowly decaying ones the gap is wider).
 //
-// What bounds it: the serial chain of one workgroup (gates, lane exchanges, LDS round trips, dependent MFMAs), about 4 us per
-// chunk in fp32 storage and 6 for four query heads in bf16, at head dim 64.  8 sequences of 32 tokens, 32 query heads on 8 kv
+// What bounds it: the serial chain of one workgroup (gates, lane exchanges, LDS round trips, dependent MFMAs: of a chunk's 16K
+// cycles 112 fp32 MFMAs take 3.6K and 16 fp64 ones 1K), about 4 us per chunk in fp32 storage and 6 for four query heads in bf16, at head
+// dim 64.  8 sequences of 32 tokens, 32 query heads on 8 kv
 // heads, bf16: 18 us, fp32, 256 tokens, 2 heads: 67 us; token by token on the vector ALUs the same took 115 and 235.
 #include <algorithm>
 
@@ -76,8 +77,9 @@ struct WalkLds {
   static constexpr int oQ = oKd + kC * kRow64;
   static constexpr int oPart = oQ + HB * kSet;           // scores, one tile per wave and head
   static constexpr int oQz = oPart + NW * HB * 1024;     // Q' . z~, 16 tokens per wave and head
-  static constexpr int oF = oQz + NW * HB * 64;          // per channel: alpha of the block's first token (fp32), decay of the whole block (fp64)
-  static constexpr int oFlag = oF + D * 16;
+  static constexpr int oA = oQz + NW * HB * 64;          // per channel: alpha of the block's first token (fp32) ...
+  static constexpr int oF = oA + D * 4;                  // ... decay of the whole block (fp64)
+  static constexpr int oFlag = oF + D * 8;
   static constexpr int kBytes = oFlag + 32;
 };
 
@@ -98,6 +100,8 @@ __global__ void __launch_bounds__(4 * D, 2) gla_walk_kernel(const WalkArgs a) {
   typedef WalkLds<D, HB> L;
   constexpr int NW = L::NW, RT = D / 16;
   constexpr bool kWide = sizeof(T) == 4;      // outputs stored in fp32: fp64 sums
+  constexpr bool kLean = kWide && D == 128;   // no registers for operands ahead of their use
+  constexpr int kBatch = HB > 1 && D == 64 ? 2 : 1;      // heads whose operands are in registers at once
   extern __shared__ __attribute__((aligned(16))) unsigned char sm[];
   const int tid = threadIdx.x;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63, g = l >> 4, n = l & 15;
@@ -269,8 +273,8 @@ __global__ void __launch_bounds__(4 * D, 2) gla_walk_kernel(const WalkArgs a) {
       zt = (float)z * firstc;
       z = fma(z, F, s);
       if (g == 0) {
-        *reinterpret_cast<float*>(sm + L::oF + (16 * w + n) * 16) = firstc;
-        *reinterpret_cast<double*>(sm + L::oF + (16 * w + n) * 16 + 8) = F;
+        *reinterpret_cast<float*>(sm + L::oA + (16 * w + n) * 4) = firstc;
+        *reinterpret_cast<double*>(sm + L::oF + (16 * w + n) * 8) = F;
       }
       __builtin_amdgcn_wave_barrier();   // LDS serves one wave's requests in order: its rows are complete below
       // the scores' rows come out in strided order: row m of the operand is token 4 (m % 4) + m / 4
@@ -292,6 +296,9 @@ __global__ void __launch_bounds__(4 * D, 2) gla_walk_kernel(const WalkArgs a) {
     const int hb1 = hb + 1 < nb ? hb + 1 : 0;
     const int blk1 = hb1 ? blk : (blk + 1 < nblk ? blk + 1 : 0);
     const int ci1 = (hb1 || blk1) ? ci : ci + 1;
+    // vmcnt(0): nothing is in flight but the outputs of the chunk before and, the first time, the start state.  (Taken to be possibly in
+    // flight, it let every chunk wait for the next one's rows below.)
+    __builtin_amdgcn_s_waitcnt(0x0F70);
     if (ci1 < nchunk) fetch(ci1, hb1);
     __builtin_amdgcn_wave_barrier();
 #pragma unroll
@@ -308,21 +315,53 @@ __global__ void __launch_bounds__(4 * D, 2) gla_walk_kernel(const WalkArgs a) {
     float vm[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) vm[i] = (4 * i + g >= lo && 4 * i + g < hi) ? vv[i] : 0.f;
-    auto first_alpha = [&](int rt, int i) { return *reinterpret_cast<const float*>(sm + L::oF + (16 * rt + 4 * g + i) * 16); };
+    // Operands come from LDS in batches, the next head's while this one's products run.  One by one, as the compiler places them, each
+    // was a latency of its own, and S~ was formed per head: 4 sequences of 200 tokens, 32 heads on 8, with the wait above 101.0 -> 98.8
+    // us, 8 of 32 of 128 45.1 -> 42.6, of 64 25.8 -> 25.4.
+    auto first_alpha = [&](int rt) { return *reinterpret_cast<const floatx4*>(sm + L::oA + (16 * rt + 4 * g) * 4); };
+    floatx4 Xs[kLean ? 1 : RT];      // S~
+    if constexpr (!kLean) {
+#pragma unroll
+      for (int rt = 0; rt < RT; ++rt) Xs[rt] = first_alpha(rt);
+    }
+    struct HeadOps { floatx4 p[NW], q[kLean ? 1 : RT], z[kWide ? 1 : NW]; } ops[kBatch];      // scores, Q', and Q' . z~ in parts
+    auto load_z = [&](int h, HeadOps& o) {
+      const float* qz = reinterpret_cast<const float*>(sm + L::oQz) + h * kC;
+#pragma unroll
+      for (int j = 0; j < NW; ++j) o.z[j] = *reinterpret_cast<const floatx4*>(qz + j * HB * kC + 4 * g);
+    };
+    auto load_ops = [&](int h, HeadOps& o) {
+#pragma unroll
+      for (int j = 0; j < NW; ++j) o.p[j] = *reinterpret_cast<const floatx4*>(sm + L::oPart + (j * HB + h) * 1024 + l * 16);
+      if constexpr (!kLean) {
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt) o.q[rt] = f32_row_frag<D>(sm + L::oQ + h * L::kSet, g, n, rt);
+      }
+      if constexpr (D == 64 && !kWide) load_z(h, o);
+    };
+    load_ops(0, ops[0]);
+    if (!kLean) __builtin_amdgcn_sched_barrier(0);
+    if constexpr (!kLean) {
+#pragma unroll
+      for (int rt = 0; rt < RT; ++rt) Xs[rt] *= X[rt];
+    }
     auto store_den = [&](int h, int t, float den) {
       if (a.den_out != nullptr && w == 0 && n == 0 && t >= lo && t < hi && row0 + t < rows)
         a.den_out[((size_t)b * a.T + s0 + row0 + t) * a.Hq + hq0 + hb * HB + h] = den;
     };
 #pragma unroll
     for (int h = 0; h < HB; ++h) {
-      const unsigned char* qrows = sm + L::oQ + h * L::kSet;
+      HeadOps& o = ops[h % kBatch];
+      if (kBatch == 1 && h > 0) load_ops(h, o);
+      if (kBatch > 1 && h + 1 < HB) load_ops(h + 1, ops[(h + 1) % kBatch]);
+      if (!kLean) __builtin_amdgcn_sched_barrier(0);
       floatx4 p = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int j = 0; j < NW; ++j) p += *reinterpret_cast<const floatx4*>(sm + L::oPart + (j * HB + h) * 1024 + l * 16);
+      for (int j = 0; j < NW; ++j) p += o.p[j];
 #pragma unroll
       for (int i = 0; i < 4; ++i) p[i] = (4 * i + g >= lo && 4 * i + g <= n) ? p[i] : 0.f;
-      const float* qz = reinterpret_cast<const float*>(sm + L::oQz) + h * kC;
       if constexpr (kWide) {
+        const float* qz = reinterpret_cast<const float*>(sm + L::oQz) + h * kC;
         doublex4 num = {0.0, 0.0, 0.0, 0.0}, ps = num;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
@@ -331,9 +370,9 @@ __global__ void __launch_bounds__(4 * D, 2) gla_walk_kernel(const WalkArgs a) {
         }
 #pragma unroll
         for (int rt = 0; rt < RT; ++rt) {
-          const floatx4 qf = f32_row_frag<D>(qrows, g, n, rt);
+          const floatx4 qf = kLean ? f32_row_frag<D>(sm + L::oQ + h * L::kSet, g, n, rt) : o.q[kLean ? 0 : rt], xs = kLean ? X[rt] * first_alpha(rt) : Xs[kLean ? 0 : rt];
 #pragma unroll
-          for (int i = 0; i < 4; ++i) num = mfma_f64((double)qf[i], (double)(X[rt][i] * first_alpha(rt, i)), num);
+          for (int i = 0; i < 4; ++i) num = mfma_f64((double)qf[i], (double)xs[i], num);
         }
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
@@ -354,35 +393,56 @@ __global__ void __launch_bounds__(4 * D, 2) gla_walk_kernel(const WalkArgs a) {
         }
 #pragma unroll
         for (int rt = 0; rt < RT; ++rt) {
-          const floatx4 qf = f32_row_frag<D>(qrows, g, n, rt);
 #pragma unroll
-          for (int i = 0; i < 4; ++i) num = mfma_f32(qf[i], (float)X[rt][i] * first_alpha(rt, i), num);
+          for (int i = 0; i < 4; ++i) num = mfma_f32(o.q[rt][i], Xs[rt][i], num);
         }
+        if constexpr (D == 128) load_z(h, o);
         floatx4 den = {a.eps, a.eps, a.eps, a.eps};
 #pragma unroll
-        for (int j = 0; j < NW; ++j) den += *reinterpret_cast<const floatx4*>(qz + j * HB * kC + 4 * g);
-        float o[4];
+        for (int j = 0; j < NW; ++j) den += o.z[j];
+        float ov[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
           den[i] += ps[i];
-          o[i] = (num[i] + pv[i]) / den[i];
+          ov[i] = (num[i] + pv[i]) / den[i];
           store_den(h, 4 * g + i, den[i]);
         }
-        St::store(orow, qd, offq + (unsigned)(hb * HB + h) * D * St::kBytes, 0, g, n, lo, hi, o);
+        St::store(orow, qd, offq + (unsigned)(hb * HB + h) * D * St::kBytes, 0, g, n, lo, hi, ov);
       }
     }
     if (hb1 == 0) {
+      // rows of the operand in strided order: the tile comes out as a patch
+      struct Update { double kd[4]; double F[4]; };
+      auto load_update = [&](int rt) {
+        const double* kd = reinterpret_cast<const double*>(sm + L::oKd + (16 * rt + strided(n)) * 8);
+        const double* F = reinterpret_cast<const double*>(sm + L::oF) + 16 * rt + 4 * g;
+        Update u;
 #pragma unroll
-      for (int rt = 0; rt < RT; ++rt) {
-        if (D == 128) __builtin_amdgcn_sched_barrier(0);     // bounds the operands in flight: no spills
-        // rows of the operand in strided order: the tile comes out as a patch
-        const double* kd = reinterpret_cast<const double*>(sm + L::oKd + (16 * rt + 4 * (n & 3) + (n >> 2)) * 8);
-        doublex4 s = {0.0, 0.0, 0.0, 0.0};
+        for (int i = 0; i < 4; ++i) {
+          u.kd[i] = kd[(4 * i + g) * (L::kRow64 / 8)];
+          u.F[i] = F[i];
+        }
+        return u;
+      };
+      constexpr int kRows = D == 64 ? 4 : kLean ? 1 : 2;      // row tiles at a time
 #pragma unroll
-        for (int i = 0; i < 4; ++i) s = mfma_f64(kd[(4 * i + g) * (L::kRow64 / 8)], (double)vm[i], s);
+      for (int r0 = 0; r0 < RT; r0 += kRows) {
+        Update u[kRows];
+        if (kLean) __builtin_amdgcn_sched_barrier(0);      // bounds the operands in flight: fewer spills
+#pragma unroll
+        for (int e = 0; e < kRows; ++e) u[e] = load_update(r0 + e);
+        if (!kLean) __builtin_amdgcn_sched_barrier(0);
+        doublex4 t[kRows];
+#pragma unroll
+        for (int e = 0; e < kRows; ++e) t[e] = kZero64;
 #pragma unroll
         for (int i = 0; i < 4; ++i)
-          X[rt][i] = (float)fma((double)X[rt][i], *reinterpret_cast<const double*>(sm + L::oF + (16 * rt + 4 * g + i) * 16 + 8), s[i]);
+#pragma unroll
+          for (int e = 0; e < kRows; ++e) t[e] = mfma_f64(u[e].kd[i], (double)vm[i], t[e]);
+#pragma unroll
+        for (int e = 0; e < kRows; ++e)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) X[r0 + e][i] = (float)fma((double)X[r0 + e][i], u[e].F[i], t[e][i]);
       }
       if (ci1 > ci && ci1 < nchunk) gates(ci1 * kC);
     }
