@@ -795,16 +795,23 @@ __global__ void __launch_bounds__(D * 4, D == 64 ? (three_share<D, GR, MODE, OUT
             o.s[rt][i] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(slot, (4 * g4 * D + col) * 4, (16 * (r0 + rt) + i) * D * 4, 0));
       };
       auto add = [&](int j, int r0, const Rows& o) {
+        // (all of a piece's decays at once: one latency, not one per row tile: 517 tokens 16.6 -> 15.95 us, 700 17.2 -> 16.5)
+        const float* at = zd + j * 2 * D;
+        floatx4 dec[4], dz, zdec;
 #pragma unroll
-        for (int rt = 0; rt < 4; ++rt) {
-          const floatx4 dec = *reinterpret_cast<const floatx4*>(zd + j * 2 * D + D + 16 * (r0 + rt) + 4 * g4);
-#pragma unroll
-          for (int i = 0; i < 4; ++i) Sacc[r0 + rt][i] = fmaf(dec[i], Sacc[r0 + rt][i], o.s[rt][i]);
-        }
+        for (int rt = 0; rt < 4; ++rt) dec[rt] = *reinterpret_cast<const floatx4*>(at + D + 16 * (r0 + rt) + 4 * g4);
         if (r0 == 0) {
-          const floatx4 dz = *reinterpret_cast<const floatx4*>(zd + j * 2 * D + zrow), dec = *reinterpret_cast<const floatx4*>(zd + j * 2 * D + D + zrow);
+          dz = *reinterpret_cast<const floatx4*>(at + zrow);
+          zdec = *reinterpret_cast<const floatx4*>(at + D + zrow);
+        }
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-          for (int i = 0; i < 4; ++i) zacc[i] = fmaf(dec[i], zacc[i], dz[i]);
+        for (int rt = 0; rt < 4; ++rt)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) Sacc[r0 + rt][i] = fmaf(dec[rt][i], Sacc[r0 + rt][i], o.s[rt][i]);
+        if (r0 == 0) {
+#pragma unroll
+          for (int i = 0; i < 4; ++i) zacc[i] = fmaf(zdec[i], zacc[i], dz[i]);
         }
       };
       Rows x, y;
