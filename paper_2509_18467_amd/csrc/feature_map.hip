@@ -22,6 +22,7 @@ typedef float floatx4 __attribute__((ext_vector_type(4)));
 
 constexpr int kTile = 64;        // fp32 kernel: tokens per tile
 constexpr int kTilesPerBlock = 4;
+constexpr int kShare = 3;        // bf16 kernel: workgroups that share a compute unit
 
 typedef unsigned int u32x4 __attribute__((vector_size(16)));
 
@@ -110,10 +111,13 @@ __device__ inline void conv_tile(const T* __restrict__ x, const T* __restrict__ 
 //           rows are requested before the current tile's products start
 //   conv  : in registers, fp32; rounded to bf16 into LDS, row = token * GH + head (the order in memory)
 //   matrix: wave w takes the 16-row groups w, w + 4, ...: B operand = the 16 rows, A operand = Wf^T (Wf read transposed from LDS),
-//           so a lane ends up with 4 adjacent features of one row; phi; back into the same LDS rows
-//   store : the wave reads its 16 finished rows back 16 bytes per lane and stores whole 128/256-byte rows
-//           (buffer stores: rows past the last token are dropped)
+//           so a lane ends up with 4 adjacent features of one row; phi; back into the same LDS rows.  Head dim 128: wave w takes features
+//           32 w .. of all rows, its share of the matrix in registers (from LDS, 64 reads of it per 16 rows, each a latency of its own:
+//           the layer at 5003 tokens 103.1 -> 102.1 us, at 16000 235.5 -> 232.5), results in LDS rows of their own
+//   store : the wave reads its 16 finished rows (head dim 128: the workgroup the tile) back 16 bytes per lane and stores whole
+//           128/256-byte rows (buffer stores: rows past the last token are dropped)
 // WT: the conv width when it is the paper's 4 (no per-tap branches), 0 = any width up to 4, read from W.
+template <int D> constexpr bool held = D == 128;
 struct FeatureArgs {
   const bf16_t *x, *w, *halo, *wf;
   bf16_t *y, *tail;
@@ -135,8 +139,13 @@ __device__ __forceinline__ void feature_tiles(const FeatureArgs& a, int block, u
   constexpr int NTOK = ROWS * VPH / 256;      // tokens per thread
   constexpr int kRsrcFlags = 0x00020000;      // raw buffer, 32-bit data format of gfx9-family descriptors
   static_assert(ROWS * VPH == 256 * NTOK && 256 % VECS == 0, "tile must give every thread NTOK tokens of one vector");
+  // HELD (head dim 128): a wave keeps 32 features' columns of the matrix in registers and takes all rows of a tile, results in LDS rows of
+  // their own; the matrix passes through both.  Otherwise it stays in LDS and a wave takes 16 rows at a time.
+  constexpr bool HELD = held<D>;
+  static_assert(!HELD || 2 * ROWS == D);
   unsigned char* wts = smem;                  // Wf: [c][f] bf16
-  unsigned char* xs = smem + D * RS;          // the tile: [row][c] bf16
+  unsigned char* xs = smem + (HELD ? 0 : D * RS);     // the tile: [row][c] bf16
+  unsigned char* ys = smem + ROWS * RS;       // HELD: its results
   const int hgroups = H / GH;
   const int b = by / hgroups, h0 = (by % hgroups) * GH;
   const int tid = threadIdx.x, l = tid & 63, wv = tid >> 6;
@@ -203,6 +212,19 @@ __device__ __forceinline__ void feature_tiles(const FeatureArgs& a, int block, u
     }
   }
 
+  bf16x8 held_a[HELD ? 2 : 1][KS];     // features 32 wv + 16 f + n of channels 32 ks + {4 g + i, 16 + 4 g + i}
+  if constexpr (HELD) {
+    __syncthreads();
+#pragma unroll
+    for (int f = 0; f < 2; ++f)
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) {
+        const unsigned char* p = wts + (32 * ks + 4 * g + (n >> 2)) * RS + (32 * wv + 16 * f + 4 * (n & 3)) * 2;
+        held_a[f][ks] = make8(read_tr(p), read_tr(p + 16 * RS));
+      }
+    __syncthreads();
+  }
+
   for (int tile = tile0; tile < tile_end; ++tile) {
     const int t0 = tile * TT;
     // conv of this thread's 8 tokens x 8 channels; taps beyond W are skipped, not multiplied by zero
@@ -227,6 +249,41 @@ __device__ __forceinline__ void feature_tiles(const FeatureArgs& a, int block, u
     }
     __syncthreads();                          // the tile (and, the first time, the matrix) is in LDS
     if (tile + 1 < tile_end) load_tile(t0 + TT);
+    if constexpr (HELD) {
+      bf16x8 b[2][KS];          // the next row group's operands travel while this one's products run
+      auto load_rows = [&](int rg, bf16x8 (&o)[KS]) {
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+          const unsigned char* p = xs + (16 * rg + n) * RS + (32 * ks + 4 * g) * 2;
+          o[ks] = make8(*reinterpret_cast<const uint2*>(p), *reinterpret_cast<const uint2*>(p + 32));
+        }
+      };
+      load_rows(0, b[0]);
+#pragma unroll
+      for (int rg = 0; rg < ROWS / 16; ++rg) {
+        if (rg + 1 < ROWS / 16) load_rows(rg + 1, b[(rg + 1) & 1]);
+        __builtin_amdgcn_sched_barrier(0);
+        floatx4 acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+          for (int f = 0; f < 2; ++f) acc[f] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(held_a[f][ks], b[rg & 1][ks], acc[f], 0, 0, 0);
+        // lane (n, g): features 32 wv + 16 f + 4 g + i of row n
+#pragma unroll
+        for (int f = 0; f < 2; ++f)
+          *reinterpret_cast<uint2*>(ys + (16 * rg + n) * RS + (32 * wv + 16 * f + 4 * g) * 2) =
+              make_uint2(pack2(apply_phi<ELU>(acc[f][0]), apply_phi<ELU>(acc[f][1])), pack2(apply_phi<ELU>(acc[f][2]), apply_phi<ELU>(acc[f][3])));
+      }
+      __syncthreads();       // (the next tile's rows go to xs, its results to ys, behind another barrier)
+#pragma unroll
+      for (int it = 0; it < ROWS * VPH / 256; ++it) {
+        const int idx = it * 256 + tid, grow = idx / VPH, vec = idx % VPH;
+        const u32x4 u = *reinterpret_cast<const u32x4*>(ys + grow * RS + vec * 16);
+        const unsigned off = (unsigned)(t0 - first + grow / GH) * stride + (unsigned)((h0 + grow % GH) * D + vec * 8) * 2;
+        __builtin_amdgcn_raw_buffer_store_b128(u, dst, (int)off, 0, 0);
+      }
+      continue;
+    }
 #pragma unroll 1
     for (int rg = wv; rg < ROWS / 16; rg += 4) {
       unsigned char* rows = xs + (size_t)(16 * rg) * RS;
@@ -281,7 +338,7 @@ __device__ __forceinline__ void feature_tiles(const FeatureArgs& a, int block, u
 // grid: the workgroups of one tensor, or of the queries and then of the keys (two shapes of tile, one launch: the keys' few bytes
 // travel beside the queries').  The whole layer, 5003 tokens, 32 / 8 heads of 128, gates included: 112.6 -> 106.2 us, 500 tokens 55.2 -> 47.5.
 template <int D, int GH, int TT, int GH2, int TT2, bool ELU, int WT>
-__global__ void __launch_bounds__(256) conv_feature_mfma_kernel(const FeatureArgs a, const FeatureArgs a2, int first) {
+__global__ void __launch_bounds__(256, kShare) conv_feature_mfma_kernel(const FeatureArgs a, const FeatureArgs a2, int first) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   if ((int)blockIdx.x < first) feature_tiles<D, GH, TT, ELU, WT>(a, blockIdx.x, smem);
   else if constexpr (GH2 > 0) feature_tiles<D, GH2, TT2, ELU, WT>(a2, blockIdx.x - first, smem);
@@ -321,9 +378,9 @@ namespace {
 
 constexpr int kComputeUnits = 256;   // MI355X
 
-constexpr int feature_lds(int d, int rows) { return (d + rows) * (d * 2 + 16); }
+constexpr int feature_lds(int d, int rows) { return (d == 128 ? 2 * rows : d + rows) * (d * 2 + 16); }
 // workgroups per compute unit (LDS, registers)
-constexpr int resident(int lds) { return (160 * 1024 / lds) < 3 ? (160 * 1024 / lds) : 3; }
+constexpr int resident(int lds) { return (160 * 1024 / lds) < kShare ? (160 * 1024 / lds) : kShare; }
 
 // Tiles of one tensor: `places` workgroups for all of its (batch, head group) pairs, each walking a contiguous run of tiles (the
 // matrix goes into LDS once per workgroup).
@@ -382,9 +439,9 @@ hipError_t launch_conv_feature(const ConvParams& p, const void* wf, int group, h
   if (p.bf16) {
     // four adjacent heads per workgroup where they share a matrix (wider contiguous rows), else one
     const bool four = group % 4 == 0;
-    // rows per tile: 256 (four heads) or 128 at d = 64; at d = 128 the matrix takes 34 KB of LDS, and 64-row tiles leave three
-    // workgroups per compute unit instead of two.  Single heads, 5003 tokens, tiles twice as long and as taken: 7.4 / 6.3 us
-    // at d = 64, 11.1 / 9.8 at 128
+    // rows per tile: 256 (four heads) or 128 at d = 64, 64 at d = 128: three workgroups to a compute unit in LDS and registers, where
+    // tiles twice as long leave two.  Single heads at d = 64, 5003 tokens: 6.3 us as taken, 7.4 twice as long; the layer at d = 128,
+    // 5003 tokens: 102.6 and 105.7
     if (p.d == 64) return four ? launch_mfma<64, 4, 64, 0, 0>(p, nullptr, wf, group, stream) : launch_mfma<64, 1, 128, 0, 0>(p, nullptr, wf, group, stream);
     return four ? launch_mfma<128, 4, 16, 0, 0>(p, nullptr, wf, group, stream) : launch_mfma<128, 1, 64, 0, 0>(p, nullptr, wf, group, stream);
   }
