@@ -10,9 +10,11 @@
 //     G^T = W2 H^T   (the two accumulator tiles of H^T, rounded to bf16, ARE the B operand: k slot s < 4 is
 //                     rank 4g + s, slot s >= 4 rank 16 + 4g + s - 4; w2 rows are read with the same permutation),
 //     a lane then holds 4 adjacent channels of one token; they pass through the wave's own LDS rows and leave
-//     as whole 256-byte row pieces.  The waves of a workgroup share 16 or 32 tokens and split the channels
+//     as whole 256-byte row pieces.  The waves of a workgroup share up to 16 or 32 tokens and split the channels
 //     of both products.
 //   anything else (fp32 storage, other ranks): one workgroup per token, plain fp32 FMAs.
+#include <algorithm>
+
 #include "kernels.h"
 
 namespace lawcat {
@@ -35,7 +37,7 @@ __device__ inline uint32_t pack2(float a, float b) {
 __device__ inline float bf_lo(uint32_t u) { return __uint_as_float(u << 16); }
 __device__ inline float bf_hi(uint32_t u) { return __uint_as_float(u & 0xffff0000u); }
 
-// grid (ceil(rows / (16 TT))), kWaves waves; rows = B * T tokens.  A workgroup owns 16 TT tokens (TT tiles of 16): its
+// grid (ceil(rows / tokens)), kWaves waves; rows = B * T tokens.  A workgroup owns `tokens` of them (at most TT tiles of 16): its
 // waves split the channels of x for the first product (slab w, w + kWaves, ...), add their partial H^T
 // through LDS, and split the output channels for the second (group w, w + kWaves, ...): short dependent
 // chains and many waves per compute unit, which is what a streaming kernel needs to keep HBM busy.
@@ -48,8 +50,8 @@ __global__ void __launch_bounds__(64 * kWaves) gate_project_mfma_kernel(const bf
                                                                         const bf16_t* __restrict__ w1,
                                                                         const bf16_t* __restrict__ w2,
                                                                         const bf16_t* __restrict__ bias,
-                                                                        bf16_t* __restrict__ g, long long rows, int dm, int N) {
-  constexpr int NR = 16 * TT;             // tokens of the workgroup
+                                                                        bf16_t* __restrict__ g, long long rows, int dm, int N, int tokens) {
+  constexpr int NR = 16 * TT;             // most tokens of a workgroup, which takes `tokens` of them
   constexpr int SS = kSlab * 2 + 16;      // LDS row stride of a slab's rows of x and of w1, bytes
   constexpr int RS = kGroupCh * 2 + 16;   // of staged logits (a 256-byte row piece plus padding)
   constexpr int kMine = (NR + kRank) * SS > NR * RS ? (NR + kRank) * SS : NR * RS;
@@ -57,8 +59,8 @@ __global__ void __launch_bounds__(64 * kWaves) gate_project_mfma_kernel(const bf
   __shared__ __attribute__((aligned(16))) float part[kWaves][TT][2][64][4];
   const int l = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int n = l & 15, gq = l >> 4;
-  const long long row0 = (long long)blockIdx.x * NR;   // first token of this workgroup
-  const int nrows = (int)((rows - row0) < NR ? (rows - row0) : NR);
+  const long long row0 = (long long)blockIdx.x * tokens;   // first token of this workgroup
+  const int nrows = (int)((rows - row0) < tokens ? (rows - row0) : tokens);
   // the rows of x and of g, each through a descriptor of its own: rows past the last token read as zero and are
   // not written
   const __amdgpu_buffer_rsrc_t xsrc = __builtin_amdgcn_make_buffer_rsrc(
@@ -227,18 +229,21 @@ hipError_t launch_gate_project(const GateProjectParams& p, hipStream_t stream) {
   if (rows > 0x7fffffffLL) return hipErrorInvalidValue;
   if (p.bf16 && p.rank == kRank && p.dm % 128 == 0 && p.N % kGroupCh == 0 && (long long)32 * p.dm * 2 < (1ll << 31) &&
       (long long)32 * p.N * 2 < (1ll << 31)) {
-    // Few tokens: eight waves share 16, or 32 once 16 would be more workgroups than compute units (each reads all of w1); many:
-    // four waves, and 32 tokens once that leaves two workgroups for every compute unit.  us, d_model 4096 with 1024 outputs / 2048 with
-    // 512: 4096 tokens, 16 to eight waves 12.7 / 8.4; 5003, 16 / 32 18.6, 12.1 / 16.3, 10.0; 10006, 16 to four waves / 32 29.9, 17.2 /
-    // 32.4, 16.2 (32 to eight waves 34.1, 18.9); 16384, 32 to four / to eight 39.0, 18.8 / 41.9, 23.2.
+    // The tokens are spread evenly over the compute units: as many workgroups for each as 32 tokens a workgroup call for, and of those the
+    // same number of tokens.  Eight waves share a workgroup's tokens while a unit has one, four after that (two slabs on their way): 16384
+    // tokens at d_model 4096 with 1024 outputs, 32 to four / to eight 39.0 / 41.9 us; 4096, to eight 12.7.  At least four tokens: the
+    // bytes of w1 per token grow below that (100 tokens 28.1 us with four, 27.9 with one, 28.2 with 16; 700 at d_model 2048 27.3, 27.4, 27.5).
+    // The whole layer (feature maps and gates, 32 / 8 heads of 128, d_model 4096), this rule / 16 or 32 tokens a workgroup whatever the count:
+    // 4200 tokens 93.6 / 95.6 us, 5003 101.2 / 102.6, 9000 151.6 / 157.2, 12500 193.2 / 203.1, 17000 242 / 250.7, 32006 416.8 / 416.8.
     auto launch = [&](auto kernel, int tokens, int waves) {
       hipLaunchKernelGGL(kernel, dim3((unsigned)((rows + tokens - 1) / tokens)), dim3(64 * waves), 0, stream, (const bf16_t*)p.x,
-                         (const bf16_t*)p.w1, (const bf16_t*)p.w2, (const bf16_t*)p.bias, (bf16_t*)p.g, rows, p.dm, p.N);
+                         (const bf16_t*)p.w1, (const bf16_t*)p.w2, (const bf16_t*)p.bias, (bf16_t*)p.g, rows, p.dm, p.N, tokens);
     };
-    if (rows <= 16 * 256) launch(gate_project_mfma_kernel<1, 8, 1>, 16, 8);
-    else if (rows <= 32 * 256) launch(gate_project_mfma_kernel<2, 8, 1>, 32, 8);
-    else if ((rows + 31) / 32 < 512) launch(gate_project_mfma_kernel<1, 4, 1>, 16, 4);
-    else launch(gate_project_mfma_kernel<2, 4, 2>, 32, 4);
+    const long long each = (rows + 32 * 256 - 1) / (32 * 256);   // workgroups per compute unit
+    const int share = std::max(4, (int)((rows + 256 * each - 1) / (256 * each)));
+    if (share <= 16 && each == 1) launch(gate_project_mfma_kernel<1, 8, 1>, share, 8);
+    else if (each == 1) launch(gate_project_mfma_kernel<2, 8, 1>, share, 8);
+    else launch(gate_project_mfma_kernel<2, 4, 2>, share, 4);
     return hipGetLastError();
   }
   const size_t lds = (size_t)(p.dm + p.rank) * sizeof(float);

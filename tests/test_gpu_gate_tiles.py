@@ -23,3 +23,10 @@ def test_gate_project_tiles(oracle, T, dm, Hkv, d):
     h = np.asarray(gi["x"], dtype=np.float64) @ np.asarray(gi["w1"], dtype=np.float64).T
     terms = (np.abs(h) @ np.abs(np.asarray(gi["w2"], dtype=np.float64)).T).reshape(ref.shape)
     H.assert_close(got, ref, wl, "gate logits", roundings=1, terms=terms + np.abs(ref))
+
+
+# tokens spread over the compute units: the four that a workgroup takes at least with three in the last one, 5, 20, 31 with one left, and
+# 18 and 27 of two and three workgroups to a unit
+@pytest.mark.parametrize("T", [511, 1025, 5003, 7906, 8705, 20480])
+def test_gate_project_shares(oracle, T):
+    test_gate_project_tiles(oracle, T, 256, 2, 64)
