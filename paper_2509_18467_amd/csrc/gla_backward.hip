@@ -297,6 +297,11 @@ __global__ void __launch_bounds__(4 * D, 2) bwd_forward_kernel(const BwdArgs a) 
 
   const int nchunk = (rows + kC - 1) / kC;
   int ci = 0, hb = 0;
+  // What follows takes some instructions out of the four heads' pass, with row16_sums() below: 32768 tokens of 32 / 8 heads of 64, the
+  // training pass 680.0 -> 673.5 us, 16000 that decay slowly 426.0 -> 421.1 (with one or two heads it gives nothing).
+  constexpr bool kAlways = HB == 4;           // rows past the last chunk are requested too (they read as zero): no registers change places
+  constexpr bool kSkip = HB == 4 && D == 64;  // no sums for the segment's start that nothing reaches; at head dim 128 the branch's
+                                              // registers spill (8000 tokens 498.6 / 519)
   constexpr int kSharp = 1, kBad = 2;
   bool sharp = false, serial = false;   // a wave's channels decay too fast for products over the chunk; any wave's: token by token
   bool any_serial = false;
@@ -354,7 +359,7 @@ __global__ void __launch_bounds__(4 * D, 2) bwd_forward_kernel(const BwdArgs a) 
     }
     const int hb1 = hb + 1 < nb ? hb + 1 : 0;
     const int ci1 = hb1 ? ci : ci + 1;
-    if (!serial && ci1 < nchunk) fetch(ci1, hb1);
+    if (!serial && (kAlways || ci1 < nchunk)) fetch(ci1, hb1);
     // ---- once per chunk: decays, K', the state decayed up to the first token, z_t
     if (hb == 0 && serial) {
 #pragma unroll
@@ -435,7 +440,7 @@ __global__ void __launch_bounds__(4 * D, 2) bwd_forward_kernel(const BwdArgs a) 
           __builtin_amdgcn_sched_barrier(0);
         }
       }
-      if (ci1 < nchunk) fetch(ci1, hb1);     // not before: its registers are the loop's
+      if (kAlways || ci1 < nchunk) fetch(ci1, hb1);     // not before: its registers are the loop's
       if (!last_head) {
         z = z0;
 #pragma unroll
@@ -460,12 +465,19 @@ __global__ void __launch_bounds__(4 * D, 2) bwd_forward_kernel(const BwdArgs a) 
       }
     }
     float* part = reinterpret_cast<float*>(lds + L::oPart);
+    if constexpr (HB == 4) {
+      float qu[16];
 #pragma unroll
-    for (int h = 0; h < HB; ++h) {
-      floatx4 s;
+      for (int j = 0; j < 16; ++j) qu[j] = qq[j >> 2][j & 3] * u[j >> 2][j & 3];
+      part[(w * HB + (n >> 2)) * kC + 4 * g + (n & 3)] = row16_sums(qu, n);
+    } else {
 #pragma unroll
-      for (int i = 0; i < 4; ++i) s[i] = row16_sum(qq[h][i] * u[h][i]);
-      if (n == 0) *reinterpret_cast<floatx4*>(part + (w * HB + h) * kC + 4 * g) = s;
+      for (int h = 0; h < HB; ++h) {
+        floatx4 s;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) s[i] = row16_sum(qq[h][i] * u[h][i]);
+        if (n == 0) *reinterpret_cast<floatx4*>(part + (w * HB + h) * kC + 4 * g) = s;
+      }
     }
     __syncthreads();
     // ---- dden = -(q . u) / den^2, dq = u / den + z dden
@@ -499,15 +511,20 @@ __global__ void __launch_bounds__(4 * D, 2) bwd_forward_kernel(const BwdArgs a) 
         dd[i] = dds[4 * h + i];
         dq[i] = fmaf(zt[i], dd[i], u[h][i] * rd[i]);
         qdq[i] = fmaf(qq[h][i], dq[i], qdq[i]);
-        const float qe = wf * d.E[i] * qq[h][i];
-        rz = fma((Wide<T>)qe, (Wide<T>)dd[i], rz);
-        qw[h][i] = qe * rd[i];
+      }
+      if (carries || !kSkip) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const float qe = wf * d.E[i] * qq[h][i];
+          rz = fma((Wide<T>)qe, (Wide<T>)dd[i], rz);
+          qw[h][i] = qe * rd[i];
+        }
       }
       St::store(dQ, qd, offq + (unsigned)(hb * HB + h) * D * St::kBytes, row0, g, n, 0, kC, dq);
     }
     Rz += rz;
     // q and dO reach rz through dden, and a denominator of zero does: what is not finite in any of them shows here
-    bad = bad || __builtin_amdgcn_ballot_w64(!(rz - rz == 0)) != 0;
+    bad = bad || __builtin_amdgcn_ballot_w64(!(rz - rz == 0) || (kSkip && !(mine - mine == 0))) != 0;
     if (seg > 0 && carries) accumulate<T, D, HB>(R, sm, g, n, qw);
     if (last_head) {
       float kp1[1][4] = {{kp[0], kp[1], kp[2], kp[3]}};

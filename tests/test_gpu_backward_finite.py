@@ -133,3 +133,23 @@ def test_tiny_and_huge_values_in_channels_that_nearly_close(oracle, shape, level
         ratio = np.abs(back - ref[n]) / lim
         print(f"  {n}: {ratio.max():.3f} of its bar", flush=True)
         assert ratio.max() <= 1.0, n
+
+
+@pytest.mark.parametrize("which", ["q", "dO", "den"])
+@pytest.mark.parametrize("Hq,Hkv", [(8, 2), (4, 1), (8, 1)])
+def test_not_finite_where_nothing_reaches_the_segments_start(oracle, which, Hq, Hkv):
+    """Four query heads of 64 at a time: 50 tokens into the second segment the decay from its start, 2^-3.7 a token in every channel, is zero."""
+    p = 114
+    wl, x, start = _inputs(Hq, Hkv, 64, "bf16", 150, True)
+    x[3][:] = -2.5
+    print("backward, not finite far from the start:", which, wl, flush=True)
+    ref = oracle.gla_backward(*x, 1.0, 0.0, *start)
+    den = oracle.gla_prefill(*x[:4], 1.0, 0.0, *start)["den"].astype(np.float32)
+    if which == "den":
+        den[0, p, Hq // Hkv - 1] = 0.0
+    else:
+        x["q k v g dO".split().index(which)][0, p, 0, 5] = np.inf
+    got = _run(wl, *x, den, *start)
+    after = np.s_[:, p + 1:]
+    _check(wl, got, ref, "after", dq=after, dk=after, dv=after, dg=after)
+    _check(wl, got, ref, "before", dq=np.s_[:, :p])
