@@ -207,6 +207,11 @@ struct Sweep {
   // and added up, where otherwise every wave forms all of it in fp64 MFMAs, which bound these sweeps (32768 tokens of 32 / 8 heads of
   // 64: 1077 us and 1256; of 128, dO . v alone, 4000 tokens 500 and 586, 500 tokens of 8 / 2 heads 243 and 287)
   static constexpr bool kDaParts = sizeof(T) == 4, kParts = kDaParts && D == 64;
+  // bf16 storage, reverse: a head's dO . v formed by one wave and read by all from behind the barrier that the scores need.  32768 tokens
+  // of 32 / 8 heads of 64, the training pass 678.3 -> 669.5 us, 8000 of 128 494.6 -> 485.0, 4000 of 8 / 8 heads of 128 209.1 -> 207.1; 8000
+  // of 8 / 8 heads of 64, where it is two MFMAs, 174.7 / 175.7.
+  static constexpr bool kDaOnce = !kDaParts && (HB > 1 || D == 128);
+  static constexpr int kDaWave = NW >= 2 * HB ? HB : 0;           // the first of these waves, after those with the scores where there are
   static constexpr int kTile = 2048;
   // forward, twice, in turn, so that no wave waits for the others to be done with a chunk before it begins the next: dO rows | v rows |
   // 1 / den, den per head and token | one word per wave
@@ -228,9 +233,9 @@ struct Sweep {
   static constexpr int rQ = rR + D * f32_row_bytes<D>();
   static constexpr int rSc = rQ + HB * kC * f32_row_bytes<D>();
   static constexpr int kScore = sizeof(T) == 2 ? 3 * 512 : 2048;  // per head: three terms of 8 bytes per lane, or one fp64 tile
-  // (or parts of the scores), then parts of dO . v
+  // (or parts of the scores), then dO . v per head or its parts
   static constexpr int rDa = rSc + HB * (kParts ? NW * kTile : kScore);
-  static constexpr int kReverse = rDa + (kDaParts ? NW * HB * kTile : 0);
+  static constexpr int kReverse = rDa + (kDaParts ? NW * HB * kTile : kDaOnce ? HB * 1024 : 0);
   static_assert(kForward <= 160 * 1024 / (D == 64 ? 2 : 1) && kReverse <= 160 * 1024 / (D == 64 ? 2 : 1));
 };
 
@@ -840,6 +845,19 @@ __device__ __forceinline__ void reverse_sweep(const BwdArgs& a) {
         *reinterpret_cast<doublex4*>(p + l * 32) = sc;
       }
     }
+    // ---- dO_s . v_i / den_s + dden_s for i <= s, of a head, the same way
+    if constexpr (L::kDaOnce) {
+      if (w >= L::kDaWave && w < L::kDaWave + HB) {
+        const int h = w - L::kDaWave;
+        const floatx4 rd = *reinterpret_cast<const floatx4*>(sm + L::rDen + (h * kC + 4 * g) * 4);
+        const floatx4 dd = *reinterpret_cast<const floatx4*>(sm + L::rDen + ((HB + h) * kC + 4 * g) * 4);
+        const floatx4 da = dot_rows<T, D, kWide>(orows + h * L::kSet, sm + L::rV, g, n);
+        floatx4 am;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) am[i] = row <= 4 * g + i ? fmaf(da[i], rd[i], dd[i]) : 0.f;
+        *reinterpret_cast<floatx4*>(das + h * 1024 + l * 16) = am;
+      }
+    }
     // ---- dk within the chunk, and what the chunk adds to the gradient flowing on
     float qw[HB][4];
     Wide<T> rzt[4] = {0, 0, 0, 0};
@@ -847,13 +865,15 @@ __device__ __forceinline__ void reverse_sweep(const BwdArgs& a) {
     for (int h = 0; h < HB; ++h) {
       const floatx4 rd = *reinterpret_cast<const floatx4*>(sm + L::rDen + (h * kC + 4 * g) * 4);
       const floatx4 dd = *reinterpret_cast<const floatx4*>(sm + L::rDen + ((HB + h) * kC + 4 * g) * 4);
-      floatx4 da;    // [token s of dO][token `row` of v]
-      if constexpr (L::kDaParts) da = add64(floatx4{0.f, 0.f, 0.f, 0.f}, sum_parts64<NW>(das + h * L::kTile, HB * L::kTile, g, n));
-      else da = dot_rows<T, D, kWide>(orows + h * L::kSet, sm + L::rV, g, n);
-      float am[4];
+      if constexpr (!L::kDaOnce) {
+        floatx4 da;    // [token s of dO][token `row` of v]
+        if constexpr (L::kDaParts) da = add64(floatx4{0.f, 0.f, 0.f, 0.f}, sum_parts64<NW>(das + h * L::kTile, HB * L::kTile, g, n));
+        else da = dot_rows<T, D, kWide>(orows + h * L::kSet, sm + L::rV, g, n);
+        float am[4];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) am[i] = row <= 4 * g + i ? fmaf(da[i], rd[i], dd[i]) : 0.f;
-      dk = token_steps<kWide>(am, qp[h], dk);
+        for (int i = 0; i < 4; ++i) am[i] = row <= 4 * g + i ? fmaf(da[i], rd[i], dd[i]) : 0.f;
+        dk = token_steps<kWide>(am, qp[h], dk);
+      }
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         rzt[i] = fma((Wide<T>)qp[h][i], (Wide<T>)dd[i], rzt[i]);
@@ -867,6 +887,14 @@ __device__ __forceinline__ void reverse_sweep(const BwdArgs& a) {
     rz += lane_get(ln.x2, rz);
     Rz += rz;
     if constexpr (!L::kParts) __syncthreads();
+    if constexpr (L::kDaOnce) {
+#pragma unroll
+      for (int h = 0; h < HB; ++h) {
+        const floatx4 f = *reinterpret_cast<const floatx4*>(das + h * 1024 + l * 16);
+        const float am[4] = {f[0], f[1], f[2], f[3]};
+        dk = token_steps<kWide>(am, qp[h], dk);
+      }
+    }
     // ---- dv within the chunk: this wave's 16 value columns
     if constexpr (sizeof(T) == 2) {
       if constexpr (HB == 1) {
@@ -925,7 +953,7 @@ __device__ __forceinline__ void reverse_sweep(const BwdArgs& a) {
       St::store(dV, qd, offk, row0, g, n, 0, kC, dvv);
       St::store(dG, qd, offk, row0, g, n, 0, kC, dgv);
     }
-    // What is read after the barrier before dv (the scores, dO) is written next after the first barrier of the next chunk, or in the other
+    // What is read after the barrier before dv (the scores, dO . v, dO) is written next after the first barrier of the next chunk, or in the other
     // turn's rows; everything else was read before it.  (One turn of rows, parts, and tokens one by one, are read up to here.)
     if constexpr (L::kDaParts || kTokens) __syncthreads();
     else orows = orows == sm ? sm + L::kO : sm;
