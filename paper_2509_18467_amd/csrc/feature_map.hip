@@ -10,7 +10,7 @@
 // Streaming and HBM-bound: 2 bytes read and 2 written per element; the matrix (8 or 32 KB) is read from L2 once
 // per workgroup, which walks a run of tiles.  5003 tokens, 32 / 8 heads of 128: 24.7 / 9.6 us with the rows kept for a
 // continuation (3.3 and 2.1 TB/s); 32.9 / 18.0 when the matrix was transposed into LDS two bytes at a time, the taps were
-// read one by one and a second launch copied those rows.
+// read one by one and a second launch copied those rows.  Both in the layer's one launch 28.3, now 26.0 (the matrix in registers).
 #include "segment_scan.h"
 
 namespace lawcat {
