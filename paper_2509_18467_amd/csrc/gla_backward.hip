@@ -211,6 +211,11 @@ struct Sweep {
   // of 32 / 8 heads of 64, the training pass 678.3 -> 669.5 us, 8000 of 128 494.6 -> 485.0, 4000 of 8 / 8 heads of 128 209.1 -> 207.1; 8000
   // of 8 / 8 heads of 64, where it is two MFMAs, 174.7 / 175.7.
   static constexpr bool kDaOnce = !kDaParts && (HB > 1 || D == 128);
+  // bf16 storage, head dim 64, two workgroups to a compute unit: the one in its chain of products goes first (forward: between the two
+  // barriers; reverse: from the scores on to the next chunk's rows).  32768 tokens of 32 / 8 heads, the training pass 659.0 -> 648.6 us,
+  // 16000 slowly decaying 415.6 -> 403.8, 8000 of 8 / 8 heads 173.4 -> 170.0; the other way round in either sweep 663-674 of 670 to 659.
+  // 500 tokens, where units have one workgroup, 91.8 / 92.5; fp32 storage 256 tokens of 2 heads 96.3 / 96.9 with it.
+  static constexpr bool kPair = sizeof(T) == 2 && D == 64;
   static constexpr int kDaWave = NW >= 2 * HB ? HB : 0;           // the first of these waves, after those with the scores where there are
   static constexpr int kTile = 2048;
   // forward, twice, in turn, so that no wave waits for the others to be done with a chunk before it begins the next: dO rows | v rows |
@@ -356,6 +361,7 @@ __global__ void __launch_bounds__(4 * D, 2) bwd_forward_kernel(const BwdArgs a) 
     int* flags = reinterpret_cast<int*>(sm + L::oFlag);
     if (l == 0) flags[w] = (sharp ? kSharp : 0) | (bad ? kBad : 0);
     __syncthreads();
+    if (L::kPair) __builtin_amdgcn_s_setprio(1);
     if (hb == 0) {
       int any = 0;
 #pragma unroll
@@ -485,6 +491,7 @@ __global__ void __launch_bounds__(4 * D, 2) bwd_forward_kernel(const BwdArgs a) 
       }
     }
     __syncthreads();
+    if (L::kPair) __builtin_amdgcn_s_setprio(0);
     // ---- dden = -(q . u) / den^2, dq = u / den + z dden
     const bool carries = __builtin_amdgcn_ballot_w64(wf != 0.f) != 0;   // this wave's channels still reach the segment's start
     float qw[HB][4];
@@ -731,6 +738,7 @@ __device__ __forceinline__ void reverse_sweep(const BwdArgs& a) {
       for (int h = 0; h < HB; ++h) dot_part64<D>(sm + L::rQ + h * kC * f32_row_bytes<D>(), sm + L::rK, w, g, n, sm + L::rSc + (w * HB + h) * L::kTile);
     }
     __syncthreads();
+    if (L::kPair) __builtin_amdgcn_s_setprio(0);
     const int hb1 = hb + 1 < nb ? hb + 1 : 0;
     const int ci1 = hb1 ? ci : ci - 1;
     if (!kTokens && ci1 >= 0) fetch(ci1, hb1);
@@ -887,6 +895,7 @@ __device__ __forceinline__ void reverse_sweep(const BwdArgs& a) {
     rz += lane_get(ln.x2, rz);
     Rz += rz;
     if constexpr (!L::kParts) __syncthreads();
+    if (L::kPair) __builtin_amdgcn_s_setprio(1);
     if constexpr (L::kDaOnce) {
 #pragma unroll
       for (int h = 0; h < HB; ++h) {
