@@ -105,7 +105,7 @@ template <int D> constexpr int kFoldMost = D == 64 ? 11 : 8;
 // which workgroup takes which segment (see find_place)
 constexpr int kDirect = 0, kInOrder = 1, kByLength = 2;
 
-template <int D, int GR>
+template <int D, int GR, int MODE>
 struct Geo {
   static constexpr int NW = D / 16;          // waves per team: one per 16 value columns
   static constexpr int TEAM = 64 * NW;       // threads per team
@@ -128,7 +128,8 @@ struct Geo {
   static constexpr int kEb = kVt + D * TRS;
   static constexpr int kEf = kEb + MCG * D * 4;   // the reference rho of each chunk and channel, fp32
   static constexpr int kWl = kEf + MCG * D * 4;
-  static constexpr int kPs = kWl + (GR + 1) * D * 16;   // shared scores: [chunk][head][64 lanes] x 16 B (4 high parts, 4 residuals)
+  // conv weights (none without conv: 54.8 KB at head dim 64 would leave two workgroups a compute unit, 52.8 leave three), then
+  static constexpr int kPs = kWl + (MODE == kPlain ? 0 : (GR + 1) * D * 16);   // shared scores: [chunk][head][64 lanes] x 16 B (4 high parts, 4 residuals)
   static constexpr int kDn = kPs + (OWN ? 0 : MCG * GR * 1024);    // shared denominators: [chunk][head][16 queries] fp32
   static constexpr int kZs = kDn + (OWN ? 0 : MCG * GR * 64);      // z at each chunk's start, bf16
   static constexpr int kFl = kZs + (GR > 0 ? MCG * D * 2 : 0);     // per load-stage wave: 1 if one of its channels uses the mid-chunk reference
@@ -254,7 +255,7 @@ __device__ inline uint4 pack_scores(floatx4 pt, int g4, int n) {
 
 template <int D, int GR, int MODE, bool OUTPUT>
 struct Kernel {
-  using G = Geo<D, GR>;
+  using G = Geo<D, GR, MODE>;
   static constexpr bool OWN = OUTPUT && G::OWN;
   static constexpr bool CONV = MODE != kPlain;
   static constexpr int NQ = OUTPUT ? GR : 1;
@@ -586,7 +587,9 @@ __device__ inline Place find_place(const ChunkArgs& a, int l) {
   return p;
 }
 
-// one or two query heads, no conv: registers and LDS for three workgroups a compute unit
+// One or two query heads, no conv: registers and LDS for three workgroups a compute unit.  Calls of more than 512 workgroups, three / two
+// to a unit, us: 8 heads of 64, 200 sequences of 64 tokens 21.4 / 24.3, 800 81.2 / 92.4, 96 of 300 44.8 / 47.0 (256 of 300, where two make
+// whole rounds, 106.3 / 102.6); 16 on 8, 29.6 / 30.8, 97.3 / 101.3, 52.3 / 56.0 (129.4 / 126.3).  Up to 512 both take the same.
 template <int D, int GR, int MODE, bool OUTPUT> constexpr bool three_share = OUTPUT && D == 64 && GR <= 2 && MODE == kPlain;
 
 // One workgroup = one team of d/16 waves.  At head dim 64 two workgroups share a compute unit (256 VGPRs each).
@@ -594,8 +597,9 @@ template <int D, int GR, int MODE, bool OUTPUT>
 __global__ void __launch_bounds__(D * 4, D == 64 ? (three_share<D, GR, MODE, OUTPUT> ? 3 : 2) : 1)
     gla_chunk_kernel(const ChunkArgs a) {
   using KK = Kernel<D, GR, MODE, OUTPUT>;
-  using G = Geo<D, GR>;
+  using G = Geo<D, GR, MODE>;
   constexpr bool CONV = MODE != kPlain, OWN = KK::OWN, kThree = three_share<D, GR, MODE, OUTPUT>;
+  static_assert(!kThree || 3 * ((G::kBytes + 1279) / 1280 * 1280) <= 160 * 1024);      // (LDS is given out in pieces of 1280 bytes)
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_all[];
   unsigned char* smem = smem_all;
   const int tid = threadIdx.x;
@@ -775,7 +779,7 @@ __global__ void __launch_bounds__(D * 4, D == 64 ? (three_share<D, GR, MODE, OUT
       // state <- decay (.) state + contribution, segment by segment (in the scan's order).  z and the decays, alike in 16 lanes, come
       // through LDS, all predecessors' at once; S goes straight to its lanes, the next segment's on its way meanwhile.  (With z and
       // decays in registers too, 64 of the 96 a slot took at head dim 128: spills there, and at 64 226 registers instead of 158 in the
-      // one-head kernels, two workgroups a compute unit instead of three: 200 sequences of 64 tokens, 8 heads, 27.5 us, now 23.6;
+      // one-head kernels, two workgroups a compute unit instead of three: 200 sequences of 64 tokens, 8 heads, 27.5 us and 23.6;
       // one of 130 tokens of 8 heads of 128, 22.8 and 21.8.)
       float* zd = reinterpret_cast<float*>(smem);      // [predecessor][z | decay]: free until the first granule
 #pragma unroll
@@ -1235,7 +1239,7 @@ __global__ void __launch_bounds__(D * 4, D == 64 ? (three_share<D, GR, MODE, OUT
 
 template <int D, int GR, int MODE>
 hipError_t launch_all(const ChunkArgs& a, int parts, hipStream_t stream, bool with_state_pass, const TraceEvents& ev) {
-  using G = Geo<D, GR>;
+  using G = Geo<D, GR, MODE>;
   const int heads = a.B * a.Hkv;
   const bool direct = !a.seq_start || a.places == kDirect;
   const int x = direct ? a.nseg : a.places == kByLength ? (a.per_head | 1) * a.Hkv : a.per_head | 1, y = direct ? heads : a.places == kByLength ? 1 : a.Hkv;
@@ -1243,7 +1247,7 @@ hipError_t launch_all(const ChunkArgs& a, int parts, hipStream_t stream, bool wi
   if (a.nseg > 1 && with_state_pass) {
     // GR = 0: key side only
     auto k1 = gla_chunk_kernel<D, 0, MODE, false>;
-    constexpr int lds1 = Geo<D, 0>::kBytes;
+    constexpr int lds1 = Geo<D, 0, MODE>::kBytes;
     e = set_lds<gla_chunk_kernel<D, 0, MODE, false>>(lds1);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k1, dim3(direct ? x - 1 : x, y), dim3(G::TEAM), lds1, stream, a);

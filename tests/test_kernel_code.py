@@ -8,7 +8,7 @@ import subprocess
 import msgpack
 import pytest
 
-from paper_2509_18467_amd import lawcat
+from paper_2509_18467_amd import build, lawcat
 
 OBJDUMP = shutil.which("llvm-objdump") or "/opt/rocm/llvm/bin/llvm-objdump"
 MAGIC = b"__CLANG_OFFLOAD_BUNDLE__"
@@ -50,16 +50,29 @@ def chunk(kernels, d, heads, mode, output=True):
     return one
 
 
+def launch_lds(d, heads, mode, tmp_path):
+    """The LDS that the output pass is launched with, from the header that the launch takes it from."""
+    source, program = tmp_path / "lds.hip", tmp_path / "lds"
+    source.write_text('#include "gla_chunk_impl.h"\n#include <cstdio>\n'
+                      f'int main() {{ printf("%d", lawcat::chunk::Kernel<{d}, {heads}, {mode}, true>::G::kBytes); }}\n')
+    subprocess.run([build.HIPCC, "--offload-host-only", "-std=c++17", "-I", build.CSRC, str(source), "-o", str(program)], check=True)
+    return int(subprocess.run([str(program)], check=True, capture_output=True, text=True).stdout)
+
+
 # (modes: 0 = queries and keys as they are, 1 = conv, 2 = conv and 1 + ELU)
 @pytest.mark.parametrize("heads", [1, 2])
-def test_three_workgroups_a_compute_unit(kernels, heads):
-    """Head dim 64, few query heads, no conv: 512 registers a lane of a SIMD, in granules of 8, for three waves."""
+def test_three_workgroups_a_compute_unit(kernels, heads, tmp_path):
+    """Head dim 64, few query heads, no conv: 512 registers a lane of a SIMD, in granules of 8, for three waves, and 160 KB of LDS, in
+    pieces of 1280 bytes, for three workgroups."""
     assert chunk(kernels, 64, heads, 0)[".vgpr_count"] <= 168
+    assert 3 * -(-launch_lds(64, heads, 0, tmp_path) // 1280) * 1280 <= 160 * 1024
 
 
-@pytest.mark.parametrize("heads,mode,most", [(1, 0, 0), (1, 1, 0), (1, 2, 0), (2, 0, 0), (2, 1, 27), (2, 2, 0)])
-def test_spills(kernels, heads, mode, most):
-    assert chunk(kernels, 128, heads, mode)[".vgpr_spill_count"] <= most
+# (three registers at head dim 64 are the price of three workgroups, see three_share)
+@pytest.mark.parametrize("d,heads,mode,most", [(128, 1, 0, 0), (128, 1, 1, 0), (128, 1, 2, 0), (128, 2, 0, 0), (128, 2, 1, 27), (128, 2, 2, 0),
+                                               (64, 1, 0, 0), (64, 2, 0, 3)])
+def test_spills(kernels, d, heads, mode, most):
+    assert chunk(kernels, d, heads, mode)[".vgpr_spill_count"] <= most
 
 
 @pytest.mark.skipif(not os.path.exists(OBJDUMP), reason="no disassembler")
