@@ -100,7 +100,11 @@ __global__ void __launch_bounds__(4 * D, 2) gla_walk_kernel(const WalkArgs a) {
   typedef WalkLds<D, HB> L;
   constexpr int NW = L::NW, RT = D / 16;
   constexpr bool kWide = sizeof(T) == 4;      // outputs stored in fp32: fp64 sums
-  constexpr bool kLean = kWide && D == 128;   // no registers for operands ahead of their use
+  // fp32 storage: operands from LDS as they are used.  At head dim 128 there are no registers for more, and at 64 the fp64 chains hide
+  // those reads: in batches, with the wait in the loop below, 8 sequences of 300 tokens of 8 heads on 2 took 34.0 us, now 32.9, 2000
+  // tokens of 32 on 8 98.4 and 95.7, 16 of 100 45.8 and 43.5, 8192 361 and 351, blocks of 200 tokens 120.5 and 117.8.
+  constexpr bool kLean = kWide;
+  constexpr bool kWaitOnce = kWide && D == 64;
   constexpr int kBatch = HB > 1 && D == 64 ? 2 : 1;      // heads whose operands are in registers at once
   extern __shared__ __attribute__((aligned(16))) unsigned char sm[];
   const int tid = threadIdx.x;
@@ -228,6 +232,7 @@ __global__ void __launch_bounds__(4 * D, 2) gla_walk_kernel(const WalkArgs a) {
   gates(0);
   __syncthreads();
 
+  if (kWaitOnce) __builtin_amdgcn_s_waitcnt(0x0F70);     // vmcnt(0): the start state and the first rows (see the loop's)
   int ci = 0, blk = 0, hb = 0, nblk = 1, lo = 0, hi = kC;
   while (ci < nchunk) {
     const int row0 = ci * kC;
@@ -298,7 +303,7 @@ __global__ void __launch_bounds__(4 * D, 2) gla_walk_kernel(const WalkArgs a) {
     const int ci1 = (hb1 || blk1) ? ci : ci + 1;
     // vmcnt(0): nothing is in flight but the outputs of the chunk before and, the first time, the start state.  (Taken to be possibly in
     // flight, it let every chunk wait for the next one's rows below.)
-    __builtin_amdgcn_s_waitcnt(0x0F70);
+    if (!kWaitOnce) __builtin_amdgcn_s_waitcnt(0x0F70);
     if (ci1 < nchunk) fetch(ci1, hb1);
     __builtin_amdgcn_wave_barrier();
 #pragma unroll
@@ -424,7 +429,7 @@ __global__ void __launch_bounds__(4 * D, 2) gla_walk_kernel(const WalkArgs a) {
         }
         return u;
       };
-      constexpr int kRows = D == 64 ? 4 : kLean ? 1 : 2;      // row tiles at a time
+      constexpr int kRows = kLean ? 1 : D == 64 ? 4 : 2;      // row tiles at a time
 #pragma unroll
       for (int r0 = 0; r0 < RT; r0 += kRows) {
         Update u[kRows];

@@ -75,6 +75,13 @@ def test_spills(kernels, d, heads, mode, most):
     assert chunk(kernels, d, heads, mode)[".vgpr_spill_count"] <= most
 
 
+@pytest.mark.parametrize("heads,most", [(1, 200), (2, 204), (4, 212)])
+def test_walk_of_fp32_storage_reads_operands_as_it_uses_them(kernels, heads, most):
+    """Head dim 64: none are held in registers ahead of their use, which is the slower way there (203, 217 and 255 registers)."""
+    one, = [k for n, k in kernels.items() if f"gla_walk_kernelIfLi64ELi{heads}E" in n]
+    assert one[".vgpr_count"] <= most
+
+
 @pytest.mark.skipif(not os.path.exists(OBJDUMP), reason="no disassembler")
 def test_uniform_descriptors(tmp_path):
     """No load of the prefill's kernels looks for lanes with equal descriptors: that takes four v_readfirstlane per load, hundreds a
