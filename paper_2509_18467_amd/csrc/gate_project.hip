@@ -231,19 +231,28 @@ hipError_t launch_gate_project(const GateProjectParams& p, hipStream_t stream) {
       (long long)32 * p.N * 2 < (1ll << 31)) {
     // The tokens are spread evenly over the compute units: as many workgroups for each as 32 tokens a workgroup call for, and of those the
     // same number of tokens.  Eight waves share a workgroup's tokens while a unit has one, four after that (two slabs on their way): 16384
-    // tokens at d_model 4096 with 1024 outputs, 32 to four / to eight 39.0 / 41.9 us; 4096, to eight 12.7.  At least four tokens: the
-    // bytes of w1 per token grow below that (100 tokens 28.1 us with four, 27.9 with one, 28.2 with 16; 700 at d_model 2048 27.3, 27.4, 27.5).
-    // The whole layer (feature maps and gates, 32 / 8 heads of 128, d_model 4096), this rule / 16 or 32 tokens a workgroup whatever the count:
-    // 4200 tokens 93.6 / 95.6 us, 5003 101.2 / 102.6, 9000 151.6 / 157.2, 12500 193.2 / 203.1, 17000 242 / 250.7, 32006 416.8 / 416.8.
+    // tokens at d_model 4096 with 1024 outputs, 32 to four / to eight 39.0 / 41.9 us; 4096, to eight 12.7.  us, spread evenly / 16 tokens a
+    // workgroup up to 4096 and from 8193 to 16352, else 32, whatever the count: d_model 4096 with 1024 outputs, 4200 tokens 12.3 / 16.2, 9500
+    // 26.5 / 31.5, 12500 34.0 / 45.4, 17500 46.9 / 56.7; 2048 with 512, 5003 8.9 / 9.5, 12500 14.6 / 21.3, 17500 21.1 / 23.9.
+    // Not where the workgroups added cost more, which is w1 and w2 once each:
+    //   up to 4096 tokens 12 a workgroup at least, or 16 where x is narrow.  4 at least / 12 / 16: d_model 4096 with 1024, 300 tokens 8.19 /
+    //     8.06 / 8.05, 1024 9.03 / 8.77 / 8.84, 2048 (8 each) 10.21 / 9.25 / 9.51; 3200, 13 each / 16, 10.2 / 11.0; 1024 with 512, 5.66 / 5.42;
+    //   a narrow x past that: d_model 512 with 512, 6000 tokens 6.48 / 6.45, 8200 8.31 / 7.72 (12500 9.57 / 9.70, 17500 12.1 / 12.6);
+    //   from the fourth to a unit on, which waits for one of three to end, with narrow x and few outputs: 2048 with 512, 24600 37.9 / 36.7, 26000
+    //     39.1 / 37.6 (30000 42.6 / 44.1); 1024 with 512, 28000 23.7 / 22.3; 2048 with 1024, 24600 43.6 / 48.9; 4096 with 512, 54.5 / 64.8.
     auto launch = [&](auto kernel, int tokens, int waves) {
       hipLaunchKernelGGL(kernel, dim3((unsigned)((rows + tokens - 1) / tokens)), dim3(64 * waves), 0, stream, (const bf16_t*)p.x,
                          (const bf16_t*)p.w1, (const bf16_t*)p.w2, (const bf16_t*)p.bias, (bf16_t*)p.g, rows, p.dm, p.N, tokens);
     };
     const long long each = (rows + 32 * 256 - 1) / (32 * 256);   // workgroups per compute unit
-    const int share = std::max(4, (int)((rows + 256 * each - 1) / (256 * each)));
-    if (share <= 16 && each == 1) launch(gate_project_mfma_kernel<1, 8, 1>, share, 8);
-    else if (each == 1) launch(gate_project_mfma_kernel<2, 8, 1>, share, 8);
-    else launch(gate_project_mfma_kernel<2, 4, 2>, share, 4);
+    const int share = (int)((rows + 256 * each - 1) / (256 * each));
+    if (rows <= 16 * 256) {
+      launch(gate_project_mfma_kernel<1, 8, 1>, p.dm < 2048 ? 16 : std::max(12, share), 8);
+    } else {
+      const bool even = p.dm >= 1024 && (each <= 3 || (long long)p.dm * p.N >= 2048 * 1024);
+      if (each == 1) launch(gate_project_mfma_kernel<2, 8, 1>, even ? share : 32, 8);
+      else launch(gate_project_mfma_kernel<2, 4, 2>, even ? share : 32, 4);
+    }
     return hipGetLastError();
   }
   const size_t lds = (size_t)(p.dm + p.rank) * sizeof(float);

@@ -25,8 +25,10 @@ def test_gate_project_tiles(oracle, T, dm, Hkv, d):
     H.assert_close(got, ref, wl, "gate logits", roundings=1, terms=terms + np.abs(ref))
 
 
-# tokens spread over the compute units: the four that a workgroup takes at least with three in the last one, 5, 20, 31 with one left, and
-# 18 and 27 of two and three workgroups to a unit
-@pytest.mark.parametrize("T", [511, 1025, 5003, 7906, 8705, 20480])
-def test_gate_project_shares(oracle, T):
-    test_gate_project_tiles(oracle, T, 256, 2, 64)
+# tokens a workgroup: 12 with 7 in the last one, 14 with 3; 20 and 31 of eight waves, one left of 31; 17 and 28 with x of 1024 channels; 18 and
+# 27 of four waves, two and three workgroups to a unit, 25 of four to a unit; 32 with x or outputs too narrow for that, and 16
+@pytest.mark.parametrize("T,dm,Hkv", [(511, 2048, 2), (3335, 2048, 2), (5003, 2048, 2), (7906, 2048, 2), (4100, 1024, 2), (7000, 1024, 2),
+                                      (8705, 1024, 2), (20480, 1024, 2), (24605, 2048, 16), (24605, 2048, 2), (5003, 256, 2), (8705, 256, 2),
+                                      (3335, 1024, 2)])
+def test_gate_project_shares(oracle, T, dm, Hkv):
+    test_gate_project_tiles(oracle, T, dm, Hkv, 64)
