@@ -213,8 +213,9 @@ struct Sweep {
   static constexpr bool kDaOnce = !kDaParts && (HB > 1 || D == 128);
   // bf16 storage, head dim 64, two workgroups to a compute unit: the one in its chain of products goes first (forward: between the two
   // barriers; reverse: from the scores on to the next chunk's rows).  32768 tokens of 32 / 8 heads, the training pass 659.0 -> 648.6 us,
-  // 16000 slowly decaying 415.6 -> 403.8, 8000 of 8 / 8 heads 173.4 -> 170.0; the other way round in either sweep 663-674 of 670 to 659.
-  // 500 tokens, where units have one workgroup, 91.8 / 92.5; fp32 storage 256 tokens of 2 heads 96.3 / 96.9 with it.
+  // 16000 slowly decaying 415.6 -> 403.8; the other way round in either sweep 663-674 of 670 to 659.  500 tokens, where units have one
+  // workgroup, 91.8 / 92.5; fp32 storage 256 tokens of 2 heads 96.3 / 96.9 with it.  Which sweeps take it for how many workgroups: see
+  // launch_sized().
   static constexpr bool kPair = sizeof(T) == 2 && D == 64;
   static constexpr int kDaWave = NW >= 2 * HB ? HB : 0;           // the first of these waves, after those with the scores where there are
   static constexpr int kTile = 2048;
@@ -246,7 +247,7 @@ struct Sweep {
 
 // ---- forward sweep: dq, dden, sum_h q (.) dq, and the segment's contribution to the gradient flowing backwards.
 // grid (nseg, heads), 4 D threads.
-template <typename T, int D, int HB>
+template <typename T, int D, int HB, bool PAIR>
 __global__ void __launch_bounds__(4 * D, 2) bwd_forward_kernel(const BwdArgs a) {
   typedef Store<T> St;
   typedef Sweep<T, D, HB> L;
@@ -361,7 +362,7 @@ __global__ void __launch_bounds__(4 * D, 2) bwd_forward_kernel(const BwdArgs a) 
     int* flags = reinterpret_cast<int*>(sm + L::oFlag);
     if (l == 0) flags[w] = (sharp ? kSharp : 0) | (bad ? kBad : 0);
     __syncthreads();
-    if (L::kPair) __builtin_amdgcn_s_setprio(1);
+    if (PAIR) __builtin_amdgcn_s_setprio(1);
     if (hb == 0) {
       int any = 0;
 #pragma unroll
@@ -491,7 +492,7 @@ __global__ void __launch_bounds__(4 * D, 2) bwd_forward_kernel(const BwdArgs a) 
       }
     }
     __syncthreads();
-    if (L::kPair) __builtin_amdgcn_s_setprio(0);
+    if (PAIR) __builtin_amdgcn_s_setprio(0);
     // ---- dden = -(q . u) / den^2, dq = u / den + z dden
     const bool carries = __builtin_amdgcn_ballot_w64(wf != 0.f) != 0;   // this wave's channels still reach the segment's start
     float qw[HB][4];
@@ -579,7 +580,7 @@ __global__ void __launch_bounds__(4 * D, 2) bwd_forward_kernel(const BwdArgs a) 
 
 // ---- reverse sweep: dk, dv, dg, and the start state's gradient.  grid (nseg, heads), 4 D threads.
 // kTokens: every chunk of the segment token by token.
-template <typename T, int D, int HB, bool kTokens>
+template <typename T, int D, int HB, bool PAIR, bool kTokens>
 __device__ __forceinline__ void reverse_sweep(const BwdArgs& a) {
   typedef Store<T> St;
   typedef Sweep<T, D, HB> L;
@@ -738,7 +739,7 @@ __device__ __forceinline__ void reverse_sweep(const BwdArgs& a) {
       for (int h = 0; h < HB; ++h) dot_part64<D>(sm + L::rQ + h * kC * f32_row_bytes<D>(), sm + L::rK, w, g, n, sm + L::rSc + (w * HB + h) * L::kTile);
     }
     __syncthreads();
-    if (L::kPair) __builtin_amdgcn_s_setprio(0);
+    if (PAIR) __builtin_amdgcn_s_setprio(0);
     const int hb1 = hb + 1 < nb ? hb + 1 : 0;
     const int ci1 = hb1 ? ci : ci - 1;
     if (!kTokens && ci1 >= 0) fetch(ci1, hb1);
@@ -895,7 +896,7 @@ __device__ __forceinline__ void reverse_sweep(const BwdArgs& a) {
     rz += lane_get(ln.x2, rz);
     Rz += rz;
     if constexpr (!L::kParts) __syncthreads();
-    if (L::kPair) __builtin_amdgcn_s_setprio(1);
+    if (PAIR) __builtin_amdgcn_s_setprio(1);
     if constexpr (L::kDaOnce) {
 #pragma unroll
       for (int h = 0; h < HB; ++h) {
@@ -981,10 +982,10 @@ __device__ __forceinline__ void reverse_sweep(const BwdArgs& a) {
   }
 }
 
-template <typename T, int D, int HB>
+template <typename T, int D, int HB, bool PAIR>
 __global__ void __launch_bounds__(4 * D, 2) bwd_reverse_kernel(const BwdArgs a) {
-  if (a.serial[(size_t)blockIdx.y * a.nseg + blockIdx.x] != 0) reverse_sweep<T, D, HB, true>(a);
-  else reverse_sweep<T, D, HB, false>(a);
+  if (a.serial[(size_t)blockIdx.y * a.nseg + blockIdx.x] != 0) reverse_sweep<T, D, HB, PAIR, true>(a);
+  else reverse_sweep<T, D, HB, PAIR, false>(a);
 }
 
 template <int D>
@@ -994,22 +995,40 @@ void launch_scan(float* slots, int* live, const float* S0, const float* z0, cons
                      (const int*)nullptr, a.Hkv, a.seg_len, false);
 }
 
-template <typename T, int D, int HB>
-hipError_t launch_sized(const BwdArgs& a, hipStream_t stream) {
+template <typename T, int D, int HB, bool FORWARD_PAIR, bool REVERSE_PAIR>
+hipError_t launch_sweeps(const BwdArgs& a, hipStream_t stream) {
   typedef Sweep<T, D, HB> L;
+  const auto forward = bwd_forward_kernel<T, D, HB, FORWARD_PAIR>;
+  const auto reverse = bwd_reverse_kernel<T, D, HB, REVERSE_PAIR>;
   const int heads = a.B * a.Hkv;
-  hipError_t e = set_lds<bwd_forward_kernel<T, D, HB>>(L::kForward);
+  hipError_t e = set_lds<bwd_forward_kernel<T, D, HB, FORWARD_PAIR>>(L::kForward);
   if (e != hipSuccess) return e;
-  e = set_lds<bwd_reverse_kernel<T, D, HB>>(L::kReverse);
+  e = set_lds<bwd_reverse_kernel<T, D, HB, REVERSE_PAIR>>(L::kReverse);
   if (e != hipSuccess) return e;
   if (a.nseg > 1) {
     hipLaunchKernelGGL((bwd_state_kernel<T, D>), dim3(a.nseg - 1, heads), dim3(4 * D), 0, stream, a);
     if (!a.fold) launch_scan<D>(a.slots_f, a.live_f, a.S0, a.z0, a, stream);
   }
-  hipLaunchKernelGGL((bwd_forward_kernel<T, D, HB>), dim3(a.nseg, heads), dim3(4 * D), L::kForward, stream, a);
+  hipLaunchKernelGGL(forward, dim3(a.nseg, heads), dim3(4 * D), L::kForward, stream, a);
   if (a.nseg > 1 && !a.fold) launch_scan<D>(a.slots_r, a.live_r, nullptr, nullptr, a, stream);
-  hipLaunchKernelGGL((bwd_reverse_kernel<T, D, HB>), dim3(a.nseg, heads), dim3(4 * D), L::kReverse, stream, a);
+  hipLaunchKernelGGL(reverse, dim3(a.nseg, heads), dim3(4 * D), L::kReverse, stream, a);
   return hipGetLastError();
+}
+
+template <typename T, int D, int HB>
+hipError_t launch_sized(const BwdArgs& a, hipStream_t stream) {
+  constexpr bool kPair = Sweep<T, D, HB>::kPair;
+  if constexpr (kPair) {
+    // The order of two workgroups (kPair): in the forward sweep where there are up to two to a compute unit, in the reverse one also past
+    // that; with one query head per pass in neither where units have one.  us, neither / both / reverse only: 500 tokens of 24 heads on 8 (64
+    // workgroups) 65.2 / 66.2 / 66.0, 2000 of 8 (256) 47.4 / 47.8 / 47.7; 8000 of 8 (504) 92.0 / 89.2 / 90.3, of 24 on 8 145.8 / 143.6 / 145.0,
+    // of 32 on 8 130.8 / 126.3; 16000 of 8 (672) 168.4 / 168.9 / 165.1, of 24 on 8 283.8 / 291.0 / 281.0; 40 x 100 of 16 on 8 (640) 71.3 / 73.4 /
+    // 72.4, 66 x 64 of 32 on 8 (528) 76.1 / 77.4 / 76.7, 35 x 300 (840) 197.4 / 194.6 / 196.0.
+    const long long blocks = (long long)a.nseg * a.B * a.Hkv;
+    if (HB == 1 && blocks <= 256) return launch_sweeps<T, D, HB, false, false>(a, stream);
+    if (blocks > 512) return launch_sweeps<T, D, HB, false, true>(a, stream);
+  }
+  return launch_sweeps<T, D, HB, kPair, kPair>(a, stream);
 }
 
 template <typename T, int D>

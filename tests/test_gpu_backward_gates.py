@@ -82,3 +82,18 @@ GATES = {"channel -3": _channel(-3.0), "channel -8": _channel(-8.0), "channel -3
 def test_gates_that_close(oracle, Hq, Hkv, d, dtype, gates):
     """Every number of query heads a pass takes, one pass and two."""
     _check(oracle, Workload("gates", B=2, T=149, Hq=Hq, Hkv=Hkv, d=d, dtype=dtype), GATES[gates], True, gates)
+
+
+@pytest.mark.parametrize("gates", ["tokens", "wide"])
+@pytest.mark.parametrize("T,Hq", [(2048, 8), (2049, 8), (4096, 8), (4097, 8), (4097, 24)])
+def test_workgroups_of_one_query_head(oracle, T, Hq, gates):
+    """One query head per pass, segments of 64 tokens: 256 workgroups, 264, 512 and 520, on both sides of where the sweeps' forms change."""
+    _check(oracle, Workload("heads", B=1, T=T, Hq=Hq, Hkv=8, d=64, dtype="bf16"), GATES[gates], True, gates)
+
+
+@pytest.mark.parametrize("gates", ["tokens", "wide"])
+@pytest.mark.parametrize("B", [64, 65])
+@pytest.mark.parametrize("Hq", [16, 32])
+def test_workgroups_of_several_query_heads(oracle, Hq, B, gates):
+    """Two and four query heads per pass, one segment to each of 512 and 520 heads."""
+    _check(oracle, Workload("heads", B=B, T=40, Hq=Hq, Hkv=8, d=64, dtype="bf16"), GATES[gates], True, gates)
