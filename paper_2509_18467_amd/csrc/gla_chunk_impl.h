@@ -1080,11 +1080,9 @@ __global__ void __launch_bounds__(D * 4, D == 64 ? (three_share<D, GR, MODE, OUT
           __syncthreads();
           // Outputs and state, 16 value columns a wave, from here on without a barrier: o^T[dv][query] = S^T (q (.) E)^T + [V,V]^T
           // [P_hi;P_lo]^T, then S <- diag(E_last / rho) (rho S) + Kdec^T V.  Operands of the next head travel while this head's chain
-          // runs, those of the state's update while the heads' do.  Order matters on gfx950: a load may only target registers whose
-          // last MFMA reader has completed.  The loads for head h + 1 are issued BEFORE the MFMAs of head h, into the registers that
-          // head h - 1 used, and head h - 1's chain was waited for by its own epilogue (MFMAs complete in order); scheduling
-          // barriers keep the compiler from moving a load below a later MFMA.  (Loads issued after queued MFMAs gave results that
-          // varied from run to run; the repeated-run GPU test guards this shape.)
+          // runs, those of the state's update while the heads' do; the scheduling barriers keep the compiler from requesting them behind
+          // the chain.  (Only that: an LDS load may come right behind an MFMA that reads the registers it fills, as operands or as
+          // accumulator input.  The update loops of these kernels are full of such loads, and 72000 repeated calls agreed bit for bit.)
 #pragma unroll 1
           for (int mc = 0; mc < G::MCG; ++mc) {
             const int tq = t0 + kChunk * mc;  // first token of the chunk

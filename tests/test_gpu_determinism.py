@@ -1,9 +1,9 @@
 """Repeated-run stability of the bf16 matrix-core prefill.
 
 The path has no atomics and a fixed reduction order, so two calls on the same inputs must agree bit for
-bit.  The check exists because kernel shapes that were parity-correct on most runs still produced, now and
-then, a few wrong output tiles on gfx950 (an MFMA operand register reused too early by the compiler's
-schedule); a fault of that kind shows up here as a run that differs from the first.  Every template
+bit.  The check exists because a kernel shape that was parity-correct on most runs still produced, now and
+then, a few wrong output tiles on gfx950 (its cause was not established); a fault of that kind shows up here as
+a run that differs from the first.  Every template
 instantiation of the chunk kernels is covered: head dim x group size x (plain | fused conv, both feature
 maps), at a size with fewer workgroups than compute units and at one with several per unit.
 """
