@@ -69,7 +69,7 @@ def test_three_workgroups_a_compute_unit(kernels, heads, tmp_path):
 
 
 # (three registers at head dim 64 are the price of three workgroups, see three_share)
-@pytest.mark.parametrize("d,heads,mode,most", [(128, 1, 0, 0), (128, 1, 1, 0), (128, 1, 2, 0), (128, 2, 0, 0), (128, 2, 1, 27), (128, 2, 2, 0),
+@pytest.mark.parametrize("d,heads,mode,most", [(128, 1, 0, 0), (128, 1, 1, 0), (128, 1, 2, 0), (128, 2, 0, 0), (128, 2, 1, 0), (128, 2, 2, 0),
                                                (64, 1, 0, 0), (64, 2, 0, 3)])
 def test_spills(kernels, d, heads, mode, most):
     assert chunk(kernels, d, heads, mode)[".vgpr_spill_count"] <= most
