@@ -25,8 +25,8 @@
 // columns of them, so that they never leave it; only k (.) E_last/E and V go to the other waves, and the state at each chunk's start, as
 // bf16 operands, comes back from them: two barriers a granule, and a wave's stores cover 64 bytes of a row.  With every wave forming 16
 // columns of all outputs (scores and denominators shared per chunk, six barriers a granule, 32 bytes of a row per store) 32768 tokens
-// of 32 heads on 8 took 107.4 us, now 96.7; 8192 46.5 and 43.3, 64 9.5 and 7.7.  What bounds it: the output pass moves 386 MB in 80 us, 93 %
-// of the rate of a large copy; the state pass and the launches in between are the rest.
+// of 32 heads on 8 took 107.4 us, now 96.7; 8192 46.5 and 43.3, 64 9.5 and 7.7.  What bounds it: the output pass moves 386 MB in 80 us at its
+// quickest, 93 % of the rate of a large copy, in 85 to 92 on average; the state pass and the launches in between are the rest.
 // Head dim 128: the state at four chunks' starts would fill the LDS, so each wave forms its 16 columns of all outputs.  z, scores and
 // denominators of a granule come first, two (chunk, head) a wave, then outputs and state without a barrier: 16384 tokens of 32 heads
 // on 8 127.5 -> 123 us, 5000 of 16 on 8 50.2 -> 46.6, 700 27.9 -> 26.3, 128K tokens 830 -> 800 (scores per chunk, by half of the waves
@@ -680,7 +680,7 @@ __global__ void __launch_bounds__(D * 4, D == 64 ? (three_share<D, GR, MODE, OUT
 #pragma unroll
     for (int j = 0; j < kWeights; ++j) {
       // (threads past the last channel load it again: behind a branch, the two-head kernel without phi spilled 80 registers at
-      // head dim 128, now 27: 16384 tokens, 16 heads on 8, 110.5 -> 101.1 us)
+      // head dim 128, where it spills none now: 16384 tokens, 16 heads on 8, 110.5 -> 101.1 us when the branch went)
       const int e = min(tid + j * G::TEAM, kRows * D - 1), c = e % D, hh = OUTPUT ? e / D : GR;
       const bf16_t* src = hh < GR ? a.wq + ((size_t)(hk * a.group + qh0 + hh) * D + c) * a.W
                                   : a.wk + ((size_t)hk * D + c) * a.W;

@@ -322,7 +322,7 @@ __global__ void __launch_bounds__(4 * D, 2) gla_walk_kernel(const WalkArgs a) {
     for (int i = 0; i < 4; ++i) vm[i] = (4 * i + g >= lo && 4 * i + g < hi) ? vv[i] : 0.f;
     // Operands come from LDS in batches, the next head's while this one's products run.  One by one, as the compiler places them, each
     // was a latency of its own, and S~ was formed per head: 4 sequences of 200 tokens, 32 heads on 8, with the wait above 101.0 -> 98.8
-    // us, 8 of 32 of 128 45.1 -> 42.6, of 64 25.8 -> 25.4.
+    // us, 8 of 32 of 128 45.1 -> 42.6 (for two and five spilled registers with two and four heads at a time), of 64 25.8 -> 25.4.
     auto first_alpha = [&](int rt) { return *reinterpret_cast<const floatx4*>(sm + L::oA + (16 * rt + 4 * g) * 4); };
     floatx4 Xs[kLean ? 1 : RT];      // S~
     if constexpr (!kLean) {
