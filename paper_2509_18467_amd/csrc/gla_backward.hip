@@ -217,6 +217,13 @@ struct Sweep {
   // workgroup, 91.8 / 92.5; fp32 storage 256 tokens of 2 heads 96.3 / 96.9 with it.  Which sweeps take it for how many workgroups: see
   // launch_sized().
   static constexpr bool kPair = sizeof(T) == 2 && D == 64;
+  // bf16 storage, reverse: products of two fp32 operands, too, go through the matrix cores as bf16 terms (mfma_terms(), 192 cycles
+  // where fp32 MFMAs take 512): q E / den is split once, for the update of R~, dk and the scores, R~ for dk and dv, a head's dO . v by the
+  // wave that forms it.  The matrix cores are busy for 1184 cycles a wave and chunk instead of 2144, 32768 tokens of 32 / 8 heads of 64, the
+  // training pass, 649 -> 638 us, 9001 of 16 / 8 heads 217.3 -> 210.4; bf16 results that differ from rounded exact ones: dk 0.89, dv 0.72,
+  // dg 0.96 times as many.  Head dim 128, whose terms do not fit the LDS (dk alone: 389 -> 395 us for 6000 tokens, registers), and one query
+  // head a pass (three workgroups a compute unit) keep fp32 MFMAs.
+  static constexpr bool kScoreTerms = kDaOnce && D == 64;
   static constexpr int kDaWave = NW >= 2 * HB ? HB : 0;           // the first of these waves, after those with the scores where there are
   static constexpr int kTile = 2048;
   // forward, twice, in turn, so that no wave waits for the others to be done with a chunk before it begins the next: dO rows | v rows |
@@ -230,18 +237,22 @@ struct Sweep {
   static constexpr int oDa = oPart + NW * HB * kC * 4;
   static constexpr int oX = oDa + (kDaParts ? NW * HB * kTile : 0);
   static constexpr int kForward = oX + D * D * 4;
-  // reverse: dO rows (in bf16 storage twice, in turn: they are read last in a chunk) | v rows | 1 / den, dden | K' rows | R~ [channel][value
-  // column] | Q' rows of HB heads | scores
-  static constexpr int rV = kDaParts ? kO : 2 * kO;
+  // reverse: dO rows (in bf16 storage twice, in turn: they are read last in a chunk, unless their operands are read ahead) | v rows |
+  // 1 / den, dden | K' rows | R~ [channel][value column] | Q' rows of HB heads | scores
+  static constexpr int rV = kDaParts || kScoreTerms ? kO : 2 * kO;
   static constexpr int rDen = rV + kSet;
-  static constexpr int rK = rDen + kPairs;
-  static constexpr int rR = rK + kC * f32_row_bytes<D>();
-  static constexpr int rQ = rR + D * f32_row_bytes<D>();
-  static constexpr int rSc = rQ + HB * kC * f32_row_bytes<D>();
+  static constexpr int kTriples = 3 * HB * kC * 4;                // (dden as it is, too)
+  static constexpr int rK = rDen + (kScoreTerms ? 2 * kTriples : kPairs);
+  static constexpr int kTerms = 3 * D * kC * 2;                   // a row per channel and term: 16 tokens
+  static constexpr int rR = rK + (kScoreTerms ? kTerms : kC * f32_row_bytes<D>());
+  static constexpr int kStateTerms = 3 * D * D * 2;
+  static constexpr int rQ = rR + (kScoreTerms ? kStateTerms : D * f32_row_bytes<D>());
+  static constexpr int rSc = rQ + HB * (kScoreTerms ? kTerms : kC * f32_row_bytes<D>());
   static constexpr int kScore = sizeof(T) == 2 ? 3 * 512 : 2048;  // per head: three terms of 8 bytes per lane, or one fp64 tile
   // (or parts of the scores), then dO . v per head or its parts
   static constexpr int rDa = rSc + HB * (kParts ? NW * kTile : kScore);
-  static constexpr int kReverse = rDa + (kDaParts ? NW * HB * kTile : kDaOnce ? HB * 1024 : 0);
+  static constexpr int kDa = kScoreTerms ? 3 * 512 : 1024;        // kDaOnce: per head three terms of 8 bytes per lane, or fp32
+  static constexpr int kReverse = rDa + (kDaParts ? NW * HB * kTile : kDaOnce ? HB * kDa : 0);
   static_assert(kForward <= 160 * 1024 / (D == 64 ? 2 : 1) && kReverse <= 160 * 1024 / (D == 64 ? 2 : 1));
 };
 
@@ -629,6 +640,10 @@ __device__ __forceinline__ void reverse_sweep(const BwdArgs& a) {
   double Rz = Rz0;
   float pend = 1.f;      // alpha of the first token of the chunk after
 
+  // 1 / den, and dden (times den where it meets q E / den), of a chunk's heads and tokens: in LDS ahead of its rows where q E / den goes
+  // there
+  constexpr bool kAhead = L::kScoreTerms && !kTokens;
+  unsigned char* dn = sm + L::rDen;      // this chunk's turn
   typename St::Raw rq[HB], ro[HB], rk, rv, rg;
   floatx4 rqdq = {0.f, 0.f, 0.f, 0.f};
   float rden = 1.f, rdd = 0.f;
@@ -636,6 +651,14 @@ __device__ __forceinline__ void reverse_sweep(const BwdArgs& a) {
     const int row0 = ci * kC;
     const size_t token = (size_t)bh * a.T + s0 + row0;
     const int len = min(kC, rows - row0);
+    auto dens = [&] {
+      if (tid < HB * kC) {
+        const int t = row0 + (tid & 15), h = hb * HB + (tid >> 4);
+        rden = t < rows ? a.den[((size_t)b * a.T + s0 + t) * a.Hq + (size_t)hk * a.group + h] : 1.f;
+        rdd = t < rows ? a.dden[token * a.group + h * len + (tid & 15)] : 0.f;
+      }
+    };
+    if (kAhead) dens();
     if (hb == 0) {
       rg = St::load(Gt, offk, row0);
       rk = St::load(K, offk, row0);
@@ -654,20 +677,29 @@ __device__ __forceinline__ void reverse_sweep(const BwdArgs& a) {
       ro[h] = St::load(O, offq + ho, row0);
       rq[h] = St::load(Q, offq + ho, row0);
     }
-    if (tid < HB * kC) {
-      const int t = row0 + (tid & 15), h = hb * HB + (tid >> 4);
-      rden = t < rows ? a.den[((size_t)b * a.T + s0 + t) * a.Hq + (size_t)hk * a.group + h] : 1.f;
-      rdd = t < rows ? a.dden[token * a.group + h * len + (tid & 15)] : 0.f;
-    }
+    if (!kAhead) dens();
   };
 
   const int nchunk = (rows + kC - 1) / kC;
   int ci = nchunk - 1, hb = 0;
   Decay d;
   float kk[4], kp[4], rE[4], sig[4], qdq[4];
+  Split4 rs[L::kScoreTerms ? D / 16 : 1];      // R~
   floatx4 dk0, dk, dv0, dv;     // from after the chunk (state products), within it
   doublex4 dvw;                 // fp32 storage: dv0 + dv
   if (ci >= 0) fetch(ci, 0);
+  auto put_dens = [&](unsigned char* to) {
+    if (tid < HB * kC) {
+      float* den = reinterpret_cast<float*>(to);
+      den[tid] = 1.f / rden;
+      den[HB * kC + tid] = kAhead ? rdd * rden : rdd;
+      if (kAhead) den[2 * HB * kC + tid] = rdd;
+    }
+  };
+  if (kAhead) {
+    put_dens(dn);
+    __syncthreads();
+  }
   while (ci >= 0) {
     const int row0 = ci * kC;
     // ---- once per chunk: decays, K', R~; rows to LDS
@@ -701,12 +733,18 @@ __device__ __forceinline__ void reverse_sweep(const BwdArgs& a) {
           rE[i] = inverse<T>(d.E[i]);
           kp[i] = kk[i] * rE[i];
         }
-        f32_to_lds<D>(sm + L::rK, g, n, 16 * w, kp);
+        if constexpr (L::kScoreTerms) terms_to_lds(sm + L::rK, D * 32, g, n, 16 * w, split4(kp[0], kp[1], kp[2], kp[3]));
+        else f32_to_lds<D>(sm + L::rK, g, n, 16 * w, kp);
 #pragma unroll
         for (int jt = 0; jt < D / 16; ++jt) {
 #pragma unroll
           for (int i = 0; i < 4; ++i) R[jt][i] *= f;
-          *reinterpret_cast<floatx4*>(sm + L::rR + c * f32_row_bytes<D>() + (16 * jt + 4 * g) * 4) = R[jt];
+          if constexpr (L::kScoreTerms) {
+            rs[jt] = split4(R[jt][0], R[jt][1], R[jt][2], R[jt][3]);
+            state_terms_to_lds(sm + L::rR, D * D * 2, g, n, 16 * w, jt, rs[jt]);
+          } else {
+            *reinterpret_cast<floatx4*>(sm + L::rR + c * f32_row_bytes<D>() + (16 * jt + 4 * g) * 4) = R[jt];
+          }
         }
       }
       pend = d.first;
@@ -720,18 +758,29 @@ __device__ __forceinline__ void reverse_sweep(const BwdArgs& a) {
 #pragma unroll
       for (int h = 0; h < HB; ++h) dot_part64<D>(orows + h * L::kSet, sm + L::rV, w, g, n, das + (w * HB + h) * L::kTile);
     }
-    float* den = reinterpret_cast<float*>(sm + L::rDen);
-    if (tid < HB * kC) {
-      den[tid] = 1.f / rden;
-      den[HB * kC + tid] = rdd;
-    }
+    const float* den = reinterpret_cast<const float*>(dn);
+    if (!kAhead) put_dens(dn);
     float qp[HB][4];
+    Split4 qs[HB];         // q E / den
+    Wide<T> rzt[4] = {0, 0, 0, 0};
 #pragma unroll
     for (int h = 0; h < HB; ++h) {
       St::patch(qd, rq[h], qp[h]);
 #pragma unroll
       for (int i = 0; i < 4; ++i) qp[h][i] *= d.E[i];
-      if constexpr (!kTokens) f32_to_lds<D>(sm + L::rQ + h * kC * f32_row_bytes<D>(), g, n, 16 * w, qp[h]);
+      if constexpr (kAhead) {
+        const floatx4 rd = *reinterpret_cast<const floatx4*>(dn + (h * kC + 4 * g) * 4), dd = *reinterpret_cast<const floatx4*>(dn + ((2 * HB + h) * kC + 4 * g) * 4);
+        float qw[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          qw[i] = qp[h][i] * rd[i];
+          rzt[i] = fma((Wide<T>)qp[h][i], (Wide<T>)dd[i], rzt[i]);
+        }
+        qs[h] = split4(qw[0], qw[1], qw[2], qw[3]);
+        terms_to_lds(sm + L::rQ + h * L::kTerms, D * 32, g, n, 16 * w, qs[h]);
+      } else if constexpr (!kTokens) {
+        f32_to_lds<D>(sm + L::rQ + h * kC * f32_row_bytes<D>(), g, n, 16 * w, qp[h]);
+      }
     }
     if constexpr (L::kParts && !kTokens) {
       __builtin_amdgcn_wave_barrier();
@@ -814,10 +863,15 @@ __device__ __forceinline__ void reverse_sweep(const BwdArgs& a) {
     if (hb == 0) {
       // ---- what flows in from after the chunk: dk gets R~ v^, dv gets K' R~
       floatx4 acc[1] = {floatx4{(float)Rz, (float)Rz, (float)Rz, (float)Rz}};
-      contract<T, D, 1>(R, sm + L::rV, g, n, acc);
+      if constexpr (L::kScoreTerms) acc[0] = contract_terms<D>(rs, sm + L::rV, g, n, acc[0]);
+      else contract<T, D, 1>(R, sm + L::rV, g, n, acc);
       dk0 = acc[0];
       dk = dv0 = dv = floatx4{0.f, 0.f, 0.f, 0.f};
       dvw = kZero64;
+      if constexpr (L::kScoreTerms) {
+        dv0 = mfma_terms(terms_frag(sm + L::rK, D * 32, g, n, 0), state_terms_frag(sm + L::rR, D * D * 2, g, n, w, 0),
+                         terms_frag(sm + L::rK, D * 32, g, n, 1), state_terms_frag(sm + L::rR, D * D * 2, g, n, w, 1), dv0);
+      } else
 #pragma unroll
       for (int ct = 0; ct < D / 16; ++ct) {
         const floatx4 f = f32_row_frag<D>(sm + L::rK, g, row, ct);
@@ -838,15 +892,23 @@ __device__ __forceinline__ void reverse_sweep(const BwdArgs& a) {
     // ---- scores of head w: Q'_s . K'_i / den_s for i <= s, shared through LDS (in the terms the product below uses)
     if (!L::kParts && w < HB) {
       const unsigned char* qrows = sm + L::rQ + w * kC * f32_row_bytes<D>();
-      const floatx4 rd = *reinterpret_cast<const floatx4*>(sm + L::rDen + (w * kC + 4 * g) * 4);
+      const floatx4 rd = *reinterpret_cast<const floatx4*>(dn + (w * kC + 4 * g) * 4);
       unsigned char* p = sm + L::rSc + w * L::kScore;
       if constexpr (sizeof(T) == 2) {
-        floatx4 sc = dot_rows<float, D>(qrows, sm + L::rK, g, n);   // [s][`row`]
+        floatx4 sc = {0.f, 0.f, 0.f, 0.f};       // [s][`row`]
+        if constexpr (L::kScoreTerms) {
+          sc = mfma_terms(terms_frag(sm + L::rQ + w * L::kTerms, D * 32, g, n, 0), terms_frag(sm + L::rK, D * 32, g, n, 0),
+                          terms_frag(sm + L::rQ + w * L::kTerms, D * 32, g, n, 1), terms_frag(sm + L::rK, D * 32, g, n, 1), sc);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) sc[i] = row <= 4 * g + i ? sc[i] * rd[i] : 0.f;
+          for (int i = 0; i < 4; ++i) sc[i] = row <= 4 * g + i ? sc[i] : 0.f;
+        } else {
+          sc = dot_rows<float, D>(qrows, sm + L::rK, g, n);
+#pragma unroll
+          for (int i = 0; i < 4; ++i) sc[i] = row <= 4 * g + i ? sc[i] * rd[i] : 0.f;
+        }
         const Split4 s = split4(sc[0], sc[1], sc[2], sc[3]);
 #pragma unroll
-        for (int k = 0; k < 3; ++k) *reinterpret_cast<uint2*>(p + k * 512 + l * 8) = s.t[k];
+        for (int k = 0; k < 3; ++k) *reinterpret_cast<u32x2*>(p + k * 512 + l * 8) = s.t[k];
       } else {
         doublex4 sc = dot_rows64<D>(qrows, sm + L::rK, g, n);
 #pragma unroll
@@ -854,53 +916,86 @@ __device__ __forceinline__ void reverse_sweep(const BwdArgs& a) {
         *reinterpret_cast<doublex4*>(p + l * 32) = sc;
       }
     }
-    // ---- dO_s . v_i / den_s + dden_s for i <= s, of a head, the same way
+    // ---- dO_s . v_i + dden_s den_s for i <= s, of a head, the same way
     if constexpr (L::kDaOnce) {
       if (w >= L::kDaWave && w < L::kDaWave + HB) {
         const int h = w - L::kDaWave;
-        const floatx4 rd = *reinterpret_cast<const floatx4*>(sm + L::rDen + (h * kC + 4 * g) * 4);
-        const floatx4 dd = *reinterpret_cast<const floatx4*>(sm + L::rDen + ((HB + h) * kC + 4 * g) * 4);
+        const floatx4 rd = *reinterpret_cast<const floatx4*>(dn + (h * kC + 4 * g) * 4);
+        const floatx4 dd = *reinterpret_cast<const floatx4*>(dn + ((HB + h) * kC + 4 * g) * 4);      // (kAhead: dden den)
         const floatx4 da = dot_rows<T, D, kWide>(orows + h * L::kSet, sm + L::rV, g, n);
         floatx4 am;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) am[i] = row <= 4 * g + i ? fmaf(da[i], rd[i], dd[i]) : 0.f;
-        *reinterpret_cast<floatx4*>(das + h * 1024 + l * 16) = am;
+        for (int i = 0; i < 4; ++i) am[i] = row <= 4 * g + i ? (kAhead ? da[i] + dd[i] : fmaf(da[i], rd[i], dd[i])) : 0.f;
+        if constexpr (kAhead) {
+          const Split4 s = split4(am[0], am[1], am[2], am[3]);
+#pragma unroll
+          for (int k = 0; k < 3; ++k) *reinterpret_cast<u32x2*>(das + h * L::kDa + k * 512 + l * 8) = s.t[k];
+        } else {
+          *reinterpret_cast<floatx4*>(das + h * L::kDa + l * 16) = am;
+        }
       }
     }
     // ---- dk within the chunk, and what the chunk adds to the gradient flowing on
-    float qw[HB][4];
-    Wide<T> rzt[4] = {0, 0, 0, 0};
+    const bool wide = seg == 0 && ci == 0 && a.dS0 != nullptr;     // dS0 is fp32 whatever the storage
+    if constexpr (kAhead) {
+      if (wide) {
+        float qw[HB][4];
 #pragma unroll
-    for (int h = 0; h < HB; ++h) {
-      const floatx4 rd = *reinterpret_cast<const floatx4*>(sm + L::rDen + (h * kC + 4 * g) * 4);
-      const floatx4 dd = *reinterpret_cast<const floatx4*>(sm + L::rDen + ((HB + h) * kC + 4 * g) * 4);
-      if constexpr (!L::kDaOnce) {
-        floatx4 da;    // [token s of dO][token `row` of v]
-        if constexpr (L::kDaParts) da = add64(floatx4{0.f, 0.f, 0.f, 0.f}, sum_parts64<NW>(das + h * L::kTile, HB * L::kTile, g, n));
-        else da = dot_rows<T, D, kWide>(orows + h * L::kSet, sm + L::rV, g, n);
-        float am[4];
+        for (int h = 0; h < HB; ++h) join4(qs[h], qw[h]);
+        accumulate_wide<T, D, HB>(R, orows, g, n, qw);
+      } else {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) am[i] = row <= 4 * g + i ? fmaf(da[i], rd[i], dd[i]) : 0.f;
-        dk = token_steps<kWide>(am, qp[h], dk);
+        for (int h = 0; h < HB; h += 2) accumulate_pair<D, false>(R, orows + h * L::kSet, orows + (h + 1) * L::kSet, g, n, pair_terms(qs[h], qs[h + 1]));
       }
+    } else {
+      float qw[HB][4];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        rzt[i] = fma((Wide<T>)qp[h][i], (Wide<T>)dd[i], rzt[i]);
-        qw[h][i] = qp[h][i] * rd[i];
+      for (int h = 0; h < HB; ++h) {
+        const floatx4 rd = *reinterpret_cast<const floatx4*>(dn + (h * kC + 4 * g) * 4);
+        const floatx4 dd = *reinterpret_cast<const floatx4*>(dn + ((HB + h) * kC + 4 * g) * 4);
+        if constexpr (!L::kDaOnce) {
+          floatx4 da;    // [token s of dO][token `row` of v]
+          if constexpr (L::kDaParts) da = add64(floatx4{0.f, 0.f, 0.f, 0.f}, sum_parts64<NW>(das + h * L::kTile, HB * L::kTile, g, n));
+          else da = dot_rows<T, D, kWide>(orows + h * L::kSet, sm + L::rV, g, n);
+          float am[4];
+#pragma unroll
+          for (int i = 0; i < 4; ++i) am[i] = row <= 4 * g + i ? fmaf(da[i], rd[i], dd[i]) : 0.f;
+          dk = token_steps<kWide>(am, qp[h], dk);
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          rzt[i] = fma((Wide<T>)qp[h][i], (Wide<T>)dd[i], rzt[i]);
+          qw[h][i] = qp[h][i] * rd[i];
+        }
       }
+      if (wide) accumulate_wide<T, D, HB>(R, orows, g, n, qw);
+      else accumulate<T, D, HB>(R, orows, g, n, qw);
     }
-    if (seg == 0 && ci == 0 && a.dS0 != nullptr) accumulate_wide<T, D, HB>(R, orows, g, n, qw);     // dS0 is fp32 whatever the storage
-    else accumulate<T, D, HB>(R, orows, g, n, qw);
     double rz = (((double)rzt[3] + (double)rzt[2]) + (double)rzt[1]) + (double)rzt[0];
     rz += lane_get(ln.x1, rz);
     rz += lane_get(ln.x2, rz);
     Rz += rz;
+    uint2 of[HB];          // dO as the operands of dv, read ahead where its rows are one set
+    if constexpr (L::kScoreTerms) {
+#pragma unroll
+      for (int h = 0; h < HB; ++h) of[h] = St::template col_frag<D>(orows + h * L::kSet, g, n, w);
+    }
+    if (kAhead) put_dens(dn == sm + L::rDen ? dn + L::kTriples : sm + L::rDen);
     if constexpr (!L::kParts) __syncthreads();
     if (PAIR) __builtin_amdgcn_s_setprio(1);
-    if constexpr (L::kDaOnce) {
+    if constexpr (kAhead) {
+      auto term = [&](int h, int k) { return *reinterpret_cast<const uint2*>(das + h * L::kDa + k * 512 + l * 8); };
+      auto da = [&](int h) { return Terms{make8(term(h, 0), term(h + 1, 0)), make8(term(h, 1), term(h + 1, 1)), make8(term(h, 2), term(h + 1, 2))}; };
+      if constexpr (HB == 4) {
+        dk = mfma_terms(da(0), pair_terms(qs[0], qs[1]), da(2), pair_terms(qs[2], qs[3]), dk);
+      } else {
+        const Terms a0 = da(0), q0 = pair_terms(qs[0], qs[1]);
+        dk = mfma_bf16(a0.t0, q0.t0, mfma_small_terms(a0, q0, dk));
+      }
+    } else if constexpr (L::kDaOnce) {
 #pragma unroll
       for (int h = 0; h < HB; ++h) {
-        const floatx4 f = *reinterpret_cast<const floatx4*>(das + h * 1024 + l * 16);
+        const floatx4 f = *reinterpret_cast<const floatx4*>(das + h * L::kDa + l * 16);
         const float am[4] = {f[0], f[1], f[2], f[3]};
         dk = token_steps<kWide>(am, qp[h], dk);
       }
@@ -916,7 +1011,9 @@ __device__ __forceinline__ void reverse_sweep(const BwdArgs& a) {
 #pragma unroll
         for (int h = 0; h < HB; h += 2) {
           const unsigned char* p = sm + L::rSc + h * L::kScore + l * 8;
-          const bf16x8 f = make8(St::template col_frag<D>(orows + h * L::kSet, g, n, w), St::template col_frag<D>(orows + (h + 1) * L::kSet, g, n, w));
+          bf16x8 f;
+          if constexpr (L::kScoreTerms) f = make8(of[h], of[h + 1]);
+          else f = make8(St::template col_frag<D>(orows + h * L::kSet, g, n, w), St::template col_frag<D>(orows + (h + 1) * L::kSet, g, n, w));
 #pragma unroll
           for (int k = 2; k >= 0; --k)
             dv = mfma_bf16(make8(*reinterpret_cast<const uint2*>(p + k * 512), *reinterpret_cast<const uint2*>(p + L::kScore + k * 512)), f, dv);
@@ -927,7 +1024,7 @@ __device__ __forceinline__ void reverse_sweep(const BwdArgs& a) {
       for (int h = 0; h < HB; ++h) {
         doublex4 sc;
         if constexpr (L::kParts) {
-          const floatx4 rd = *reinterpret_cast<const floatx4*>(sm + L::rDen + (h * kC + 4 * g) * 4);
+          const floatx4 rd = *reinterpret_cast<const floatx4*>(dn + (h * kC + 4 * g) * 4);
           sc = sum_parts64<NW>(sm + L::rSc + h * L::kTile, HB * L::kTile, g, n);
 #pragma unroll
           for (int i = 0; i < 4; ++i) sc[i] = row <= 4 * g + i ? sc[i] * (double)rd[i] : 0.0;
@@ -966,7 +1063,8 @@ __device__ __forceinline__ void reverse_sweep(const BwdArgs& a) {
     // What is read after the barrier before dv (the scores, dO . v, dO) is written next after the first barrier of the next chunk, or in the other
     // turn's rows; everything else was read before it.  (One turn of rows, parts, and tokens one by one, are read up to here.)
     if constexpr (L::kDaParts || kTokens) __syncthreads();
-    else orows = orows == sm ? sm + L::kO : sm;
+    else if constexpr (!L::kScoreTerms) orows = orows == sm ? sm + L::kO : sm;
+    if (kAhead) dn = dn == sm + L::rDen ? dn + L::kTriples : sm + L::rDen;
     ci = ci1; hb = hb1;
   }
   if (seg == 0) {
