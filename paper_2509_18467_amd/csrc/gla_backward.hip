@@ -296,19 +296,25 @@ __global__ void __launch_bounds__(4 * D, 2) bwd_forward_kernel(const BwdArgs a) 
   float qdq[4] = {0.f, 0.f, 0.f, 0.f};
 
   // inputs of the next item, in registers.  Item = (chunk, HB query heads).
-  typename St::Raw rq[HB], ro[HB], rk, rv, rg;
+  constexpr bool kRows = sizeof(T) == 2;        // dO and v as whole rows
+  typename St::Raw rq[HB], rk, rg, ro[kRows ? 1 : HB], rv;
+  WholeRows<D, HB> wo;
+  WholeRows<D, 1> wv;
+  const unsigned offwo = WholeRows<D, HB>::offset(O, tid), offwv = WholeRows<D, 1>::offset(V, tid);
   float rden = 1.f;
   auto fetch = [&](int ci, int hb) {
     const int row0 = ci * kC;
     if (hb == 0) {
       rg = St::load(Gt, offk, row0);
       rk = St::load(K, offk, row0);
-      rv = St::load(V, offk, row0);
+      if constexpr (kRows) wv.load(V, offwv, row0);
+      else rv = St::load(V, offk, row0);
     }
+    if constexpr (kRows) wo.load(O, offwo + (unsigned)(hb * HB) * D * St::kBytes, row0);
 #pragma unroll
     for (int h = 0; h < HB; ++h) {
       const unsigned ho = (unsigned)(hb * HB + h) * D * St::kBytes;
-      ro[h] = St::load(O, offq + ho, row0);
+      if constexpr (!kRows) ro[h] = St::load(O, offq + ho, row0);
       rq[h] = St::load(Q, offq + ho, row0);
     }
     if (tid < HB * kC) {
@@ -348,9 +354,15 @@ __global__ void __launch_bounds__(4 * D, 2) bwd_forward_kernel(const BwdArgs a) 
       sharp = __builtin_amdgcn_ballot_w64(!tame || !(d.last >= kWhole)) != 0;
       bad = false;
     }
-    St::template to_lds<D>(sm + L::oV, g, n, 16 * w, rv);      // (in every turn: the registers hold them for all of the chunk's heads)
+    // (v in every turn: the registers hold it for all of the chunk's heads)
+    if constexpr (kRows) {
+      wv.to_lds(sm + L::oV, L::kRow, tid);
+      wo.to_lds(sm, L::kRow, tid);
+    } else {
+      St::template to_lds<D>(sm + L::oV, g, n, 16 * w, rv);
 #pragma unroll
-    for (int h = 0; h < HB; ++h) St::template to_lds<D>(sm + h * L::kSet, g, n, 16 * w, ro[h]);
+      for (int h = 0; h < HB; ++h) St::template to_lds<D>(sm + h * L::kSet, g, n, 16 * w, ro[h]);
+    }
     if constexpr (L::kDaParts) {
       __builtin_amdgcn_wave_barrier();   // LDS serves one wave's requests in order: its rows are complete below
 #pragma unroll
@@ -644,7 +656,11 @@ __device__ __forceinline__ void reverse_sweep(const BwdArgs& a) {
   // there
   constexpr bool kAhead = L::kScoreTerms && !kTokens;
   unsigned char* dn = sm + L::rDen;      // this chunk's turn
-  typename St::Raw rq[HB], ro[HB], rk, rv, rg;
+  constexpr bool kRows = sizeof(T) == 2;        // dO and v as whole rows
+  typename St::Raw rq[HB], rk, rg, ro[kRows ? 1 : HB], rv;
+  WholeRows<D, HB> wo;
+  WholeRows<D, 1> wv;
+  const unsigned offwo = WholeRows<D, HB>::offset(O, tid), offwv = WholeRows<D, 1>::offset(V, tid);
   floatx4 rqdq = {0.f, 0.f, 0.f, 0.f};
   float rden = 1.f, rdd = 0.f;
   auto fetch = [&](int ci, int hb) {
@@ -662,7 +678,8 @@ __device__ __forceinline__ void reverse_sweep(const BwdArgs& a) {
     if (hb == 0) {
       rg = St::load(Gt, offk, row0);
       rk = St::load(K, offk, row0);
-      rv = St::load(V, offk, row0);
+      if constexpr (kRows) wv.load(V, offwv, row0);
+      else rv = St::load(V, offk, row0);
       const float* in = a.qdq + token * D;
       if (len == kC) {
         rqdq = *reinterpret_cast<const floatx4*>(in + (w * 64 + l) * 4);
@@ -671,10 +688,11 @@ __device__ __forceinline__ void reverse_sweep(const BwdArgs& a) {
         for (int i = 0; i < 4; ++i) rqdq[i] = 4 * g + i < len ? in[c * len + 4 * g + i] : 0.f;
       }
     }
+    if constexpr (kRows) wo.load(O, offwo + (unsigned)(hb * HB) * D * St::kBytes, row0);
 #pragma unroll
     for (int h = 0; h < HB; ++h) {
       const unsigned ho = (unsigned)(hb * HB + h) * D * St::kBytes;
-      ro[h] = St::load(O, offq + ho, row0);
+      if constexpr (!kRows) ro[h] = St::load(O, offq + ho, row0);
       rq[h] = St::load(Q, offq + ho, row0);
     }
     if (!kAhead) dens();
@@ -748,10 +766,15 @@ __device__ __forceinline__ void reverse_sweep(const BwdArgs& a) {
         }
       }
       pend = d.first;
-      St::template to_lds<D>(sm + L::rV, g, n, 16 * w, rv);
+      if constexpr (kRows) wv.to_lds(sm + L::rV, L::kRow, tid);
+      else St::template to_lds<D>(sm + L::rV, g, n, 16 * w, rv);
     }
+    if constexpr (kRows) {
+      wo.to_lds(orows, L::kRow, tid);
+    } else {
 #pragma unroll
-    for (int h = 0; h < HB; ++h) St::template to_lds<D>(orows + h * L::kSet, g, n, 16 * w, ro[h]);
+      for (int h = 0; h < HB; ++h) St::template to_lds<D>(orows + h * L::kSet, g, n, 16 * w, ro[h]);
+    }
     unsigned char* das = sm + L::rDa;     // parts of dO . v
     if constexpr (L::kDaParts) {
       __builtin_amdgcn_wave_barrier();
