@@ -663,7 +663,11 @@ __device__ __forceinline__ void reverse_sweep(const BwdArgs& a) {
   const unsigned offwo = WholeRows<D, HB>::offset(O, tid), offwv = WholeRows<D, 1>::offset(V, tid);
   floatx4 rqdq = {0.f, 0.f, 0.f, 0.f};
   float rden = 1.f, rdd = 0.f;
-  auto fetch = [&](int ci, int hb) {
+  // whole: a chunk that is not the first to be taken and so has 16 tokens, where it matters (of the first one, more query heads at most).
+  // With a load in the loop that depends on it, every chunk waited for all loads under way there, 1500 of its 10100 cycles: 32768 tokens
+  // of 32 / 8 heads of 64, the training pass, 613.9 -> 599.1 us (of 128 nothing, with one query head a pass 205.0 -> 206.5: left as it was).
+  constexpr std::bool_constant<(D == 64 || HB > 1)> kWhole16{};
+  auto fetch = [&](int ci, int hb, auto whole) {
     const int row0 = ci * kC;
     const size_t token = (size_t)bh * a.T + s0 + row0;
     const int len = min(kC, rows - row0);
@@ -681,7 +685,7 @@ __device__ __forceinline__ void reverse_sweep(const BwdArgs& a) {
       if constexpr (kRows) wv.load(V, offwv, row0);
       else rv = St::load(V, offk, row0);
       const float* in = a.qdq + token * D;
-      if (len == kC) {
+      if (whole || len == kC) {
         rqdq = *reinterpret_cast<const floatx4*>(in + (w * 64 + l) * 4);
       } else {
 #pragma unroll
@@ -705,7 +709,7 @@ __device__ __forceinline__ void reverse_sweep(const BwdArgs& a) {
   Split4 rs[L::kScoreTerms ? D / 16 : 1];      // R~
   floatx4 dk0, dk, dv0, dv;     // from after the chunk (state products), within it
   doublex4 dvw;                 // fp32 storage: dv0 + dv
-  if (ci >= 0) fetch(ci, 0);
+  if (ci >= 0) fetch(ci, 0, std::false_type{});
   auto put_dens = [&](unsigned char* to) {
     if (tid < HB * kC) {
       float* den = reinterpret_cast<float*>(to);
@@ -814,7 +818,7 @@ __device__ __forceinline__ void reverse_sweep(const BwdArgs& a) {
     if (PAIR) __builtin_amdgcn_s_setprio(0);
     const int hb1 = hb + 1 < nb ? hb + 1 : 0;
     const int ci1 = hb1 ? ci : ci - 1;
-    if (!kTokens && ci1 >= 0) fetch(ci1, hb1);
+    if (!kTokens && ci1 >= 0) fetch(ci1, hb1, kWhole16);
     if constexpr (kTokens) {
       // ---- token by token, these query heads' part: Gr_t, dk_t = Gr_t v^_t, dv_t = k_t Gr_t (over the channels through LDS)
       int lane = l;                                   // not known to be l: nothing of this loop is formed before it
@@ -872,7 +876,7 @@ __device__ __forceinline__ void reverse_sweep(const BwdArgs& a) {
       Rz = hb == 0 ? y : Rz + y;
 #pragma unroll
       for (int jt = 0; jt < D / 16; ++jt) R[jt] = hb == 0 ? Y[jt] : R[jt] + Y[jt];
-      if (ci1 >= 0) fetch(ci1, hb1);         // not before: its registers are the loop's
+      if (ci1 >= 0) fetch(ci1, hb1, kWhole16);          // not before: its registers are the loop's
       __syncthreads();
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
