@@ -195,6 +195,11 @@ __global__ void __launch_bounds__(4 * D) bwd_state_kernel(const BwdArgs a) {
   if (threadIdx.x == 0) a.live_f[(size_t)bh * a.nseg + seg] = live;
 }
 
+// A word of an array, by a 32-bit offset from a uniform pointer.  (One wave reads the chunk's denominators, and the others wait for it at
+// the next barrier: with 64-bit indices 300 of a chunk's 8500 cycles more.  Training pass, 9001 tokens of 16 / 8 heads of 64 206.1 -> 202.9
+// us, 700 of 32 / 8 95.1 -> 94.2; with a head's denominators per wave 32768 tokens 612.7 -> 622.9.)
+__device__ inline float at32(const float* base, unsigned word) { return *reinterpret_cast<const float*>(reinterpret_cast<const char*>(base) + (size_t)(word * 4u)); }
+
 template <typename T, int D, int HB>
 struct Sweep {
   typedef Store<T> St;
@@ -301,6 +306,7 @@ __global__ void __launch_bounds__(4 * D, 2) bwd_forward_kernel(const BwdArgs a) 
   WholeRows<D, HB> wo;
   WholeRows<D, 1> wv;
   const unsigned offwo = WholeRows<D, HB>::offset(O, tid), offwv = WholeRows<D, 1>::offset(V, tid);
+  const float* dens = a.den + ((size_t)b * a.T + s0) * a.Hq + (size_t)hk * a.group;     // (its rows lie within 32-bit offsets, as those of q do)
   float rden = 1.f;
   auto fetch = [&](int ci, int hb) {
     const int row0 = ci * kC;
@@ -319,7 +325,7 @@ __global__ void __launch_bounds__(4 * D, 2) bwd_forward_kernel(const BwdArgs a) 
     }
     if (tid < HB * kC) {
       const int t = row0 + (tid & 15);
-      rden = t < rows ? a.den[((size_t)b * a.T + s0 + t) * a.Hq + (size_t)hk * a.group + hb * HB + (tid >> 4)] : 1.f;
+      rden = t < rows ? at32(dens, (unsigned)(t * a.Hq + hb * HB + (tid >> 4))) : 1.f;
     }
   };
 
@@ -531,7 +537,7 @@ __global__ void __launch_bounds__(4 * D, 2) bwd_forward_kernel(const BwdArgs a) 
       const float* den = reinterpret_cast<const float*>(sm + L::oDen);
       const double r = den[at], rr = r + r * (1.0 - (double)den[HB * kC + at] * r);
       mine = (float)(-(s * rr) * rr);
-      if (w == 0 && n < 4 * HB && t < len) a.dden[token * a.group + (hb * HB + h) * len + t] = mine;
+      if (w == 0 && n < 4 * HB && t < len) (a.dden + token * a.group)[(unsigned)((hb * HB + h) * len + t)] = mine;
     }
     const float dds[16] = {row16_get<0>(mine), row16_get<1>(mine), row16_get<2>(mine), row16_get<3>(mine),
                            row16_get<4>(mine), row16_get<5>(mine), row16_get<6>(mine), row16_get<7>(mine),
@@ -662,6 +668,7 @@ __device__ __forceinline__ void reverse_sweep(const BwdArgs& a) {
   WholeRows<D, 1> wv;
   const unsigned offwo = WholeRows<D, HB>::offset(O, tid), offwv = WholeRows<D, 1>::offset(V, tid);
   floatx4 rqdq = {0.f, 0.f, 0.f, 0.f};
+  const float* den_rows = a.den + ((size_t)b * a.T + s0) * a.Hq + (size_t)hk * a.group;
   float rden = 1.f, rdd = 0.f;
   // whole: a chunk that is not the first to be taken and so has 16 tokens, where it matters (of the first one, more query heads at most).
   // With a load in the loop that depends on it, every chunk waited for all loads under way there, 1500 of its 10100 cycles: 32768 tokens
@@ -674,8 +681,8 @@ __device__ __forceinline__ void reverse_sweep(const BwdArgs& a) {
     auto dens = [&] {
       if (tid < HB * kC) {
         const int t = row0 + (tid & 15), h = hb * HB + (tid >> 4);
-        rden = t < rows ? a.den[((size_t)b * a.T + s0 + t) * a.Hq + (size_t)hk * a.group + h] : 1.f;
-        rdd = t < rows ? a.dden[token * a.group + h * len + (tid & 15)] : 0.f;
+        rden = t < rows ? at32(den_rows, (unsigned)(t * a.Hq + h)) : 1.f;
+        rdd = t < rows ? at32(a.dden + token * a.group, (unsigned)(h * len + (tid & 15))) : 0.f;
       }
     };
     if (kAhead) dens();
