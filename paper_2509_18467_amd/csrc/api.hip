@@ -76,20 +76,21 @@ inline Path prefill_path(const lawcat_desc* d) {
              : Path::kRecurrentF32;
 }
 
-ChunkPlan plan_for(const lawcat_desc* d) {
-  return make_chunk_plan(d->B, d->T, d->Hq, d->Hkv, d->dk, d->carry_mode, d->segment);
+ChunkPlan plan_for(const lawcat_desc* d, bool conv, size_t room) {
+  return make_chunk_plan(d->B, d->T, d->Hq, d->Hkv, d->dk, d->carry_mode, d->segment, conv, room);
 }
 
-size_t workspace_bytes_checked(const lawcat_desc* d, int which) {
+// room: as for plan_for; 0 gives the least that the call takes
+size_t workspace_bytes_checked(const lawcat_desc* d, int which, size_t room = SIZE_MAX) {
   switch (which) {
     case LAWCAT_CALL_CONV1D:
     case LAWCAT_CALL_GLA_STEP:
       return 0;
     case LAWCAT_CALL_GLA_PREFILL:
-      if (prefill_path(d) == Path::kChunkBf16) return plan_for(d).workspace_bytes;
+      if (prefill_path(d) == Path::kChunkBf16) return plan_for(d, false, room).workspace_bytes;
       return d->dtype == LAWCAT_DTYPE_F32 && d->carry_mode != LAWCAT_CARRY_SEQUENTIAL ? gla_recurrent_workspace_bytes(d->B, d->T, d->Hq, d->Hkv, d->dk) : 0;
     case LAWCAT_CALL_LAYER_PREFILL: {
-      if (prefill_path(d) == Path::kChunkBf16) return plan_for(d).workspace_bytes;
+      if (prefill_path(d) == Path::kChunkBf16) return plan_for(d, true, room).workspace_bytes;
       // unfused: q-dot and k-dot staged in the storage type
       const size_t rows = (size_t)d->B * d->T;
       return align_up(rows * d->Hq * d->dk * elem_bytes(d), 256) + align_up(rows * d->Hkv * d->dk * elem_bytes(d), 256);
@@ -97,7 +98,7 @@ size_t workspace_bytes_checked(const lawcat_desc* d, int which) {
     case LAWCAT_CALL_LAYER_PREFILL_FM: {
       // q-dot and k-dot staged in the storage type, then whatever lawcat_gla_prefill needs
       const size_t rows = (size_t)d->B * d->T;
-      const size_t inner = prefill_path(d) == Path::kChunkBf16 ? plan_for(d).workspace_bytes : 0;
+      const size_t inner = prefill_path(d) == Path::kChunkBf16 ? plan_for(d, false, room).workspace_bytes : 0;
       return align_up(rows * d->Hq * d->dk * elem_bytes(d), 256) + align_up(rows * d->Hkv * d->dk * elem_bytes(d), 256) +
              align_up(inner, 256);
     }
@@ -117,7 +118,7 @@ ChunkPlan varlen_plan(const lawcat_desc* d, const int32_t* seq_start) {
   const long long total = seq_start[d->B];
   int longest = 1;
   for (int i = 0; i < d->B; ++i) longest = std::max(longest, (int)(seq_start[i + 1] - seq_start[i]));
-  ChunkPlan one = make_chunk_plan(1, (int)std::min<long long>(total, 0x7fffffc0LL), d->Hq, d->Hkv, d->dk, d->carry_mode, d->segment);
+  ChunkPlan one = make_chunk_plan(1, (int)std::min<long long>(total, 0x7fffffc0LL), d->Hq, d->Hkv, d->dk, d->carry_mode, d->segment, false, 0);
   ChunkPlan p{};
   const int whole = (longest + 63) / 64 * 64;
   p.seg_len = std::min(one.seg_len, whole);
@@ -275,7 +276,7 @@ int lawcat_gla_prefill(const lawcat_desc* desc, const void* q, const void* k, co
     c.S_out = S_out; c.z_out = z_out; c.workspace = workspace;
     c.B = desc->B; c.T = desc->T; c.Hq = desc->Hq; c.Hkv = desc->Hkv; c.d = desc->dk;
     c.W = 1; c.phi = LAWCAT_PHI_IDENTITY; c.fuse_conv = 0;
-    c.gate_scale = desc->gate_scale; c.eps = desc->eps; c.plan = plan_for(desc);
+    c.gate_scale = desc->gate_scale; c.eps = desc->eps; c.plan = plan_for(desc, false, workspace_bytes);
     return hip_status(launch_gla_chunk(c, hs));
   }
   RecurrentParams r{};
@@ -338,7 +339,7 @@ int layer_prefill_impl(const lawcat_desc* desc, const void* Q, const void* K, co
       !aligned16(O) || !den_ok || !aligned16(S_out) || !aligned16(z_out) ||
       !aligned16(q_tail_out) || !aligned16(k_tail_out) || !aligned16(workspace))
     return LAWCAT_E_ALIGN;
-  const size_t need = workspace_bytes_checked(desc, LAWCAT_CALL_LAYER_PREFILL);
+  const size_t need = workspace_bytes_checked(desc, LAWCAT_CALL_LAYER_PREFILL, 0);
   if (need > 0 && (workspace == nullptr || workspace_bytes < need)) return LAWCAT_E_WORKSPACE;
   hipStream_t hs = static_cast<hipStream_t>(stream);
   const int bf16 = desc->dtype == LAWCAT_DTYPE_BF16;
@@ -350,7 +351,7 @@ int layer_prefill_impl(const lawcat_desc* desc, const void* Q, const void* K, co
     c.workspace = workspace;
     c.B = desc->B; c.T = desc->T; c.Hq = desc->Hq; c.Hkv = desc->Hkv; c.d = desc->dk;
     c.W = desc->conv_width; c.phi = desc->feature_map; c.fuse_conv = 1;
-    c.gate_scale = desc->gate_scale; c.eps = desc->eps; c.plan = plan_for(desc);
+    c.gate_scale = desc->gate_scale; c.eps = desc->eps; c.plan = plan_for(desc, true, workspace_bytes);
     c.q_tail = q_tail_out; c.k_tail = k_tail_out;
     c.ev_start = ev_start; c.ev_stop = ev_stop;
     return hip_status(launch_gla_chunk(c, hs));
@@ -448,7 +449,7 @@ int lawcat_layer_prefill_varlen(const lawcat_desc* desc, const int32_t* seq_star
     const long long len = (long long)seq_start[i + 1] - seq_start[i];
     lawcat_desc one = *desc;
     one.B = 1; one.T = (int32_t)len;
-    const size_t need = workspace_bytes_checked(&one, LAWCAT_CALL_LAYER_PREFILL);
+    const size_t need = workspace_bytes_checked(&one, LAWCAT_CALL_LAYER_PREFILL, 0);
     if (need > 0 && (workspace == nullptr || workspace_bytes < need)) return LAWCAT_E_WORKSPACE;
   }
   const size_t qrow = (size_t)desc->Hq * desc->dk * eb, krow = (size_t)desc->Hkv * desc->dk * eb;
@@ -513,7 +514,7 @@ int lawcat_layer_prefill_static(const lawcat_desc* desc, const void* Q, const vo
                                 float* S_out, float* z_out, void* q_tail_out, void* k_tail_out, void* stream) {
   const int st = check_desc(desc, true);
   if (st != LAWCAT_OK) return st;
-  if (workspace_bytes_checked(desc, LAWCAT_CALL_LAYER_PREFILL) > (size_t)LAWCAT_STATIC_WORKSPACE_BYTES)
+  if (workspace_bytes_checked(desc, LAWCAT_CALL_LAYER_PREFILL, 0) > (size_t)LAWCAT_STATIC_WORKSPACE_BYTES)
     return LAWCAT_E_STATIC_LIMIT;
   if (!Q || !K || !V || !gate_logits || !wq || !wk || !O || !S_out || !z_out) return LAWCAT_E_NULL;
   void* ws = nullptr;

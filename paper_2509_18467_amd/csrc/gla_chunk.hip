@@ -15,10 +15,16 @@ static int fold_most(int heads, int group, int d) {
   return d == 64 ? std::min(chunk::kFoldMost<64> + 1, 9 + heads / 4) : std::min(group < 8 ? chunk::kFoldMost<128> + 1 : 7, 4 + heads / 8);
 }
 
-ChunkPlan make_chunk_plan(int B, int T, int Hq, int Hkv, int d, int carry_mode, int segment) {
+ChunkPlan make_chunk_plan(int B, int T, int Hq, int Hkv, int d, int carry_mode, int segment, bool conv, size_t room) {
   ChunkPlan p{};
   const int heads = B * Hkv;
   int seg_len;
+  auto cut = [&](int len) {
+    p.seg_len = len;
+    p.nseg = (T + len - 1) / len;
+    // per (head, segment): contribution or start state S | z | total decay, then one flag word each
+    p.workspace_bytes = p.nseg > 1 ? (size_t)heads * p.nseg * ((d * d + 2 * d) * sizeof(float) + sizeof(int)) : 0;
+  };
   if (carry_mode == 1) {
     seg_len = (T + 63) / 64 * 64;
   } else if (segment > 0) {
@@ -28,6 +34,20 @@ ChunkPlan make_chunk_plan(int B, int T, int Hq, int Hkv, int d, int carry_mode, 
     // 64, one 8-wave team at 128), in segments of two granules (128 tokens) at least ...
     const int slots = d == 64 ? 512 : 256;
     const long long groups = (long long)heads * std::max(1, Hq / Hkv / 4);   // workgroups per segment
+    // Head dim 128 with conv: two 4-wave teams per unit (gla_wide.h), in twice as many segments, where those are long enough that the
+    // state pass, which reads up to 192 tokens of each, costs less than the output pass gains, and if the workspace has the slots.  us a
+    // call, eight waves / four (segments of .. tokens): 32 on 8 heads, 8192 tokens (128) 76.6 / 90.9, 16384 (256) 128.0 / 129.3, 18000 (320) 133.7 /
+    // 131.4, 24000 165.1 / 159.9, 65536 402.6 / 363.1, 131072 777 / 686, x 16, 2000 (512) 205.0 / 193.0, x 32, 700 145.7 / 144.5; two heads a
+    // workgroup, 20000 (320) 116.6 / 116.2, 30000 150.9 / 146.3; one, 30000 (512) 124.1 / 125.3, 36000 (576) 144.9 / 140.2; groups of more than one
+    // workgroup, whose state pass is half as many, 32 on 4, 8192 (128) 71.2 / 71.7, 12000 (192) 92.5 / 85.2.  Without conv, where there is less
+    // beside the MFMA stage to run, 16384 tokens of the feature-map layer 224.8 / 240.0.
+    if (d == 128 && conv) {
+      const int group = std::max(1, Hq / Hkv), most = (int)((512 + groups - 1) / groups);
+      const int len = ((T + most - 1) / most + 63) / 64 * 64;
+      cut(len);
+      p.wide = len >= (group >= 8 ? 192 : group == 1 ? 576 : 320) && p.workspace_bytes <= room;
+      if (p.wide) return p;
+    }
     const int want = (int)((slots + groups - 1) / groups);
     seg_len = (T + want - 1) / want;
     seg_len = (seg_len + 63) / 64 * 64;
@@ -47,10 +67,7 @@ ChunkPlan make_chunk_plan(int B, int T, int Hq, int Hkv, int d, int carry_mode, 
       seg_len = two > 1 && one * groups <= slots && pays ? 64 : 128;
     }
   }
-  p.seg_len = seg_len;
-  p.nseg = (T + seg_len - 1) / seg_len;
-  // per (head, segment): contribution or start state S | z | total decay, then one flag word each
-  p.workspace_bytes = p.nseg > 1 ? (size_t)heads * p.nseg * ((d * d + 2 * d) * sizeof(float) + sizeof(int)) : 0;
+  cut(seg_len);
   return p;
 }
 
@@ -66,7 +83,7 @@ hipError_t launch_gla_chunk(const ChunkParams& p, hipStream_t stream) {
   a.per_head = p.plan.per_head; a.inv_len = 1.0 / p.plan.seg_len;
   a.seg_live = reinterpret_cast<int*>(a.ws + (size_t)p.B * p.Hkv * p.plan.nseg * (p.d * p.d + 2 * p.d));
   a.B = p.B; a.T = p.T; a.Hq = p.Hq; a.Hkv = p.Hkv; a.W = p.W;
-  a.seg_len = p.plan.seg_len; a.nseg = p.plan.nseg;
+  a.seg_len = p.plan.seg_len; a.nseg = p.plan.nseg; a.wide = p.plan.wide;
   // A workgroup of the output pass takes four query heads of a group, or two or one where that still gives no more workgroups than
   // compute units: each is a serial walk, and those for two heads or one are shorter, at the price of forming the keys' side again.
   // us a call with four / two / one, 8 kv heads: of 64, 32 query heads, 64 tokens 13.7 / 11.9 / 10.7, 517 20.4 / 19.1 / -; 1500, where

@@ -1,5 +1,5 @@
 // Head dimension 128 instantiations of the matrix-core prefill kernels.
-#include "gla_chunk_impl.h"
+#include "gla_wide.h"
 namespace lawcat {
 namespace chunk {
 hipError_t launch_d128(const ChunkArgs& a, int group, int mode, hipStream_t stream, const TraceEvents& ev) {

@@ -33,6 +33,7 @@
 // while the others waited, z in all waves' registers).  Its stages do not overlap: the compute stage (5.9 of 14.3 us a granule) is
 // bound by the vector ALUs, outputs and state (5.7) by LDS, 26 KB a wave and chunk.  Granules of 32 tokens in two sets of operands, the
 // two waves of a SIMD in opposite stages, took 151 us.
+// Long sequences with conv take a form of its own there (gla_wide.h: two workgroups of four waves a compute unit).
 //
 // Per-step decay is floored at 2^-13 so that eight steps of 1/alpha stay below 2^104; the floor changes
 // a state by at most 2^-13 of what the step before it held.
@@ -92,6 +93,7 @@ struct ChunkArgs {
   int per_head;     // packed batches: workgroups per kv head
   double inv_len;   // 1 / seg_len
   int places;       // which workgroup takes which segment
+  int wide;    // head dim 128: the output pass in its form for many workgroups (gla_wide.h)
   int fold;    // few segments: the output pass folds its predecessors' contributions itself, there is no scan
   float gate_scale, eps;
 };
@@ -118,7 +120,7 @@ struct Geo {
   static constexpr int TRS = NTG * 2 + 8;    // LDS row stride (bytes) of channel-major bf16 rows
   // OWN: a wave keeps its chunk's Q', K' (see the top); S at each chunk's start, in MFMA operands, [chunk][16 value columns][k-step]
   // [64 lanes] x 16 B.
-  static constexpr bool OWN = D == 64 && GR > 0;
+  static constexpr bool OWN = D == 64 && GR > 0, WIDE = false;
   static constexpr int kSn = 0;
   static constexpr int kSnChunk = D * D * 2;
   static constexpr int kQp = 0;
@@ -241,6 +243,33 @@ struct Chunk {
   uint4 p[NQ];
 };
 
+// Head dim 128, output pass, four waves: granules of 32 tokens, 32 value columns of the state a wave.  Two workgroups share a compute
+// unit, so that one's loads and vector instructions run beside the other's MFMA stage; see gla_wide.h.
+template <int GR, int MODE>
+struct WideGeo {
+  static constexpr int D = 128, NW = 4, TEAM = 64 * NW, CH = 2, NTG = 32, MCG = NTG / kChunk;
+  static constexpr int RT = D / 16, KS = D / 32, CT = 2;      // CT: tiles of value columns a wave
+  static constexpr int QRS = D * 2 + 8, TRS = NTG * 2 + 8;
+  static constexpr bool OWN = false, WIDE = true;
+  static constexpr int HW = (GR + 1) / 2;                     // heads whose scores a wave sums up
+  static constexpr int kQp = 0;
+  static constexpr int kKd = kQp + GR * NTG * QRS;            // (K' passes through the last head's Q' rows)
+  static constexpr int kVt = kKd + D * TRS;
+  static constexpr int kEb = kVt + D * TRS;
+  static constexpr int kEf = kEb + MCG * D * 4;
+  static constexpr int kWl = kEf + MCG * D * 4;
+  static constexpr int kPs = kWl + (MODE == kPlain ? 0 : (GR + 1) * D * 16);   // parts of scores, then scores: [chunk][head][64 lanes] x 16 B
+  static constexpr int kZs = kPs + MCG * GR * 1024;
+  static constexpr int kDn = kZs + MCG * D * 2;               // denominators: [chunk][head][16 queries] fp32
+  static constexpr int kFl = kDn + MCG * GR * 64;
+  static constexpr int kBytes = kFl + 32;
+  static constexpr int kSlot = D * D + 2 * D;
+  static_assert(2 * ((kBytes + 1279) / 1280 * 1280) <= 160 * 1024);
+};
+// Scores of a chunk over the wave's 64 channels, of the heads that it sums up
+template <int GR>
+struct Part { floatx4 p[(GR + 1) / 2]; };
+
 // Causal scores of a chunk, P^T[key 4 g4 + i][query n] for key <= query, as a k = 32 operand: slots 0..3 the high parts, 4..7 the
 // residuals of this lane's 4 keys.  The weights of the few nearest keys dominate the output, so their bf16 rounding would not
 // average out.
@@ -253,9 +282,9 @@ __device__ inline uint4 pack_scores(floatx4 pt, int g4, int n) {
   return make_uint4(ph0, ph1, pl0, pl1);
 }
 
-template <int D, int GR, int MODE, bool OUTPUT>
+template <int D, int GR, int MODE, bool OUTPUT, typename GEO = Geo<D, GR, MODE>>
 struct Kernel {
-  using G = Geo<D, GR, MODE>;
+  using G = GEO;
   static constexpr bool OWN = OUTPUT && G::OWN;
   static constexpr bool CONV = MODE != kPlain;
   static constexpr int NQ = OUTPUT ? GR : 1;
@@ -282,15 +311,18 @@ struct Kernel {
   }
 
   // ---- registers -> LDS operands: gate products, conv + phi, scaling by the decay, bf16 packing
-  template <bool EDGE, bool GS1>
+  template <bool EDGE, bool GS1, typename OWN_T>
   __device__ static inline void compute(Raw<NQ>& raw, const RowSrc& srcQ, unsigned coff, int W, unsigned char* smem,
                                         const float* wl, int t0, int s1, int tl0, int c0, int mcw, int th,
-                                        float gate_scale, Chunk<D, NQ>& own) {
+                                        float gate_scale, OWN_T& own) {
     const int tok0 = t0 + tl0;
     const int idx32 = (int)(((threadIdx.x & 63) ^ 32) << 2);  // the lane that holds the other half of the chunk
     // OWN: rows of the wave's chunk in LDS on their way from patches to operands, where S of the same chunk will be: nothing else
     // reads either
-    unsigned char* rows = smem + G::kSn + mcw * G::kSnChunk;
+    // WIDE: this wave's part, 64 channels of its chunk, of the last head's Q' rows
+    unsigned char* rows;
+    if constexpr (G::WIDE) rows = smem + G::kQp + ((GR - 1) * G::NTG + kChunk * mcw) * G::QRS;
+    else rows = smem + G::kSn + mcw * G::kSnChunk;
     // query heads are fetched two heads ahead of their use
     if (OUTPUT) fetch_head<EDGE>(raw, srcQ, 0, t0, tl0, coff, W);
     if (OUTPUT && NQ > 1) fetch_head<EDGE>(raw, srcQ, 1, t0, tl0, coff, W);
@@ -357,7 +389,9 @@ struct Kernel {
     }
     __builtin_amdgcn_sched_barrier(0);  // keep the sections apart: bounds live registers
     // keys: K' = k/E (in-chunk scores) and Kdec = k E_last/E (state update)
-    unsigned char* kp = (OWN ? rows + 8 * th * G::QRS : smem + G::kKp + tl0 * G::QRS) + c0 * 2;
+    unsigned char* kp;
+    if constexpr (OWN || G::WIDE) kp = rows + 8 * th * G::QRS + c0 * 2;
+    else kp = smem + G::kKp + tl0 * G::QRS + c0 * 2;
     float kdv[8][2];
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
@@ -392,23 +426,33 @@ struct Kernel {
     *reinterpret_cast<uint2*>(vp + G::TRS + 8) = make_uint2(v1[2], v1[3]);
     if (OUTPUT) {
       const int g4 = (threadIdx.x >> 4) & 3, n = threadIdx.x & 15;
-      bf16x8 kop[G::KS];
-      auto operands = [&](bf16x8 (&o)[G::KS]) {
+      constexpr int KO = G::WIDE ? 2 : G::KS;      // k-steps over what the wave holds
+      bf16x8 kop[KO], qop[G::WIDE ? 2 : 1][KO];
+      const int slab = G::WIDE ? __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) % G::CH : 0;
+      auto operands = [&](bf16x8 (&o)[KO], const unsigned char* rows) {
         __builtin_amdgcn_wave_barrier();   // LDS serves one wave's requests in order: the rows are complete here, and read before they change
 #pragma unroll
-        for (int ks = 0; ks < G::KS; ++ks) {
-          const unsigned char* p = rows + n * G::QRS + g4 * 8 + 64 * ks;
+        for (int ks = 0; ks < KO; ++ks) {
+          const unsigned char* p = rows + n * G::QRS + g4 * 8 + 64 * ks + (G::WIDE ? 128 * slab : 0);
           o[ks] = make8(*reinterpret_cast<const uint2*>(p), *reinterpret_cast<const uint2*>(p + 32));
         }
         __builtin_amdgcn_wave_barrier();
       };
       auto scores = [&](int hh) {
         floatx4 pt = {0.f, 0.f, 0.f, 0.f};
+        if constexpr (G::WIDE) {
+          // over the wave's 64 channels: one of the two waves of a chunk sums a head's up, the other hands it its part
 #pragma unroll
-        for (int ks = 0; ks < G::KS; ++ks) pt = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kop[ks], own.q[hh][ks], pt, 0, 0, 0);
-        own.p[hh] = pack_scores(pt, g4, n);
+          for (int ks = 0; ks < KO; ++ks) pt = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kop[ks], qop[hh & 1][ks], pt, 0, 0, 0);
+          if (hh / G::HW == slab) own.p[hh % G::HW] = pt;
+          else *reinterpret_cast<floatx4*>(smem + G::kPs + (mcw * GR + hh) * 1024 + (threadIdx.x & 63) * 16) = pt;
+        } else {
+#pragma unroll
+          for (int ks = 0; ks < G::KS; ++ks) pt = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kop[ks], own.q[hh][ks], pt, 0, 0, 0);
+          own.p[hh] = pack_scores(pt, g4, n);
+        }
       };
-      if constexpr (OWN) operands(kop);
+      if constexpr (OWN || G::WIDE) operands(kop, rows);
       // queries: conv + phi, times E
 #pragma unroll
       for (int hh = 0; hh < NQ; ++hh) {
@@ -421,11 +465,14 @@ struct Kernel {
         for (int i = 0; i < 8; ++i)
           *reinterpret_cast<uint32_t*>(qp + i * G::QRS) = pack2(qf[i][0] * E[i][0], qf[i][1] * E[i][1]);
         if constexpr (OWN) {
-          operands(own.q[hh]);
+          operands(own.q[hh], rows);
+          if (hh > 0) scores(hh - 1);
+        } else if constexpr (G::WIDE) {
+          operands(qop[hh & 1], smem + G::kQp + (hh * G::NTG + kChunk * mcw) * G::QRS);
           if (hh > 0) scores(hh - 1);
         }
       }
-      if constexpr (OWN) scores(NQ - 1);
+      if constexpr (OWN || G::WIDE) scores(NQ - 1);
     }
     // vmcnt(0): every row has been used, nothing is in flight; said so that the compiler, which merges what is in flight in the four
     // forms of this function, does not wait after it, or before the last of them, for the next granule's rows and for all stores.  (The
@@ -585,6 +632,26 @@ __device__ inline Place find_place(const ChunkArgs& a, int l) {
   p.T = __builtin_amdgcn_readlane(end, lane) - p.row0;
   cut_place(a, p);
   return p;
+}
+
+// The conv cache of a workgroup's heads: the last W - 1 raw rows of [halo ; x].
+template <int D>
+__device__ inline void store_tails(const ChunkArgs& a, int b, int hk, int qh0, int heads, bool keeps, int T, size_t row0, int tid, int threads) {
+  const int Wm = a.W - 1;
+  for (int e = tid; e < (heads + (keeps ? 1 : 0)) * Wm * D; e += threads) {
+    const int c = e % D, r = (e / D) % Wm, hh = e / (D * Wm);
+    const bool isq = hh < heads;
+    bf16_t* dst = isq ? a.q_tail : a.k_tail;
+    if (dst == nullptr) continue;
+    const int H = isq ? a.Hq : a.Hkv, head = isq ? hk * a.group + qh0 + hh : hk;
+    const bf16_t* x = isq ? a.q : a.k;
+    const bf16_t* halo = isq ? a.q_halo : a.k_halo;
+    const int src = T - Wm + r;
+    bf16_t val = 0;
+    if (src >= 0) val = x[((row0 + src) * H + head) * D + c];
+    else if (halo != nullptr) val = halo[(((size_t)b * Wm + (Wm + src)) * H + head) * D + c];
+    dst[(((size_t)b * Wm + r) * H + head) * D + c] = val;
+  }
 }
 
 // One or two query heads, no conv: registers and LDS for three workgroups a compute unit.  Calls of more than 512 workgroups, three / two
@@ -1215,25 +1282,11 @@ __global__ void __launch_bounds__(D * 4, D == 64 ? (three_share<D, GR, MODE, OUT
     if (ddst != nullptr && mcw == 0 && th == 0) *reinterpret_cast<float2*>(ddst + c0) = make_float2(rgran[0], rgran[1]);
     if (!OUTPUT && tid == 0) a.seg_live[slot0 + seg] = dead ? 0 : 1;
   }
-  // ---- conv cache out: the last W-1 raw rows of [halo ; x] for this workgroup's heads
-  if (OUTPUT && CONV && seg == nseg - 1 && a.W > 1) {
-    const int Wm = a.W - 1;
-    for (int e = tid; e < (GR + (keeps ? 1 : 0)) * Wm * D; e += G::TEAM) {
-      const int c = e % D, r = (e / D) % Wm, hh = e / (D * Wm);
-      const bool isq = hh < GR;
-      bf16_t* dst = isq ? a.q_tail : a.k_tail;
-      if (dst == nullptr) continue;
-      const int H = isq ? a.Hq : a.Hkv, head = isq ? hk * a.group + qh0 + hh : hk;
-      const bf16_t* x = isq ? a.q : a.k;
-      const bf16_t* halo = isq ? a.q_halo : a.k_halo;
-      const int src = T - Wm + r;
-      bf16_t val = 0;
-      if (src >= 0) val = x[((row0 + src) * H + head) * D + c];
-      else if (halo != nullptr) val = halo[(((size_t)b * Wm + (Wm + src)) * H + head) * D + c];
-      dst[(((size_t)b * Wm + r) * H + head) * D + c] = val;
-    }
-  }
+  if (OUTPUT && CONV && seg == nseg - 1 && a.W > 1) store_tails<D>(a, b, hk, qh0, GR, keeps, T, row0, tid, G::TEAM);
 }
+
+template <int GR, int MODE>
+__global__ void gla_wide_kernel(const ChunkArgs a);     // gla_wide.h
 
 template <int D, int GR, int MODE>
 hipError_t launch_all(const ChunkArgs& a, int parts, hipStream_t stream, bool with_state_pass, const TraceEvents& ev) {
@@ -1258,15 +1311,23 @@ hipError_t launch_all(const ChunkArgs& a, int parts, hipStream_t stream, bool wi
       if (e != hipSuccess) return e;
     }
   }
-  auto k3 = gla_chunk_kernel<D, GR, MODE, true>;
-  e = set_lds<gla_chunk_kernel<D, GR, MODE, true>>(G::kBytes);
-  if (e != hipSuccess) return e;
   // measurement entry point: the two events take the kernel's own start and stop timestamps (no dispatch gaps)
-  if (ev.start != nullptr && ev.stop != nullptr)
-    hipExtLaunchKernelGGL(k3, dim3(x, y, parts), dim3(G::TEAM), G::kBytes, stream, ev.start, ev.stop, 0, a);
-  else
-    hipLaunchKernelGGL(k3, dim3(x, y, parts), dim3(G::TEAM), G::kBytes, stream, a);
-  return hipGetLastError();
+  auto output = [&](auto kernel, int team, int bytes) {
+    if (ev.start != nullptr && ev.stop != nullptr)
+      hipExtLaunchKernelGGL(kernel, dim3(x, y, parts), dim3(team), bytes, stream, ev.start, ev.stop, 0, a);
+    else
+      hipLaunchKernelGGL(kernel, dim3(x, y, parts), dim3(team), bytes, stream, a);
+    return hipGetLastError();
+  };
+  if constexpr (D == 128) {
+    if constexpr (MODE != kPlain) if (a.wide) {
+      using W = WideGeo<GR, MODE>;
+      e = set_lds<gla_wide_kernel<GR, MODE>>(W::kBytes);
+      return e != hipSuccess ? e : output(gla_wide_kernel<GR, MODE>, W::TEAM, W::kBytes);
+    }
+  }
+  e = set_lds<gla_chunk_kernel<D, GR, MODE, true>>(G::kBytes);
+  return e != hipSuccess ? e : output(gla_chunk_kernel<D, GR, MODE, true>, G::TEAM, G::kBytes);
 }
 
 // A group of any size is covered by output-pass launches whose workgroups take 4, 2 or 1 of its query heads each; they

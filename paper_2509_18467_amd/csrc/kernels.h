@@ -99,10 +99,12 @@ struct ChunkPlan {
   int seg_len;
   int nseg;
   size_t workspace_bytes;
+  int wide;           // head dim 128: the output pass in its form for many workgroups
   int segments;       // packed batches: segments per kv head, and a bound of them whatever the lengths; elsewhere 0
   int per_head;
 };
-ChunkPlan make_chunk_plan(int B, int T, int Hq, int Hkv, int d, int carry_mode, int segment);
+// room: bytes of workspace that there are (one that needs less is chosen where they are fewer than the quickest plan's)
+ChunkPlan make_chunk_plan(int B, int T, int Hq, int Hkv, int d, int carry_mode, int segment, bool conv, size_t room);
 bool chunk_path_supports(int group);  // query heads per kv head the kernel is built for
 
 struct ChunkParams {
