@@ -128,25 +128,29 @@ __global__ void __launch_bounds__(4 * D) bwd_state_kernel(const BwdArgs a) {
   __shared__ int flags[NW];
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l = threadIdx.x & 63, g = l >> 4, n = l & 15;
   const Lanes ln = make_lanes(l);
-  const Quad qd = make_quad(l);
+  const Turn qd = make_turn(l);
   const int seg = blockIdx.x, bh = blockIdx.y, b = bh / a.Hkv, hk = bh % a.Hkv;
   const int s0 = seg * a.seg_len, rows = min(a.T, s0 + a.seg_len) - s0;
   const unsigned stride = (unsigned)a.Hkv * D * St::kBytes;
   const size_t first = (((size_t)b * a.T + s0) * a.Hkv + hk) * D * St::kBytes;
   const Rows K = make_rows(a.k, first, stride, rows, D * St::kBytes), V = make_rows(a.v, first, stride, rows, D * St::kBytes),
              Gt = make_rows(a.g, first, stride, rows, D * St::kBytes);
-  const unsigned off = St::offset(K, g, n, 16 * w);
+  const unsigned off = St::row_offset(K, g, n, 16 * w);
   floatx4 X[D / 16];
 #pragma unroll
   for (int jt = 0; jt < D / 16; ++jt) X[jt] = floatx4{0.f, 0.f, 0.f, 0.f};
   float z = 0.f, run = 1.f;
-  typename St::Raw rk[NM], rv[NM], rg[NM];
+  constexpr bool kRows = sizeof(T) == 2;        // v as whole rows
+  typename St::Raw rk[NM], rv[kRows ? 1 : NM], rg[NM];
+  WholeRows<D, 1> wv[kRows ? NM : 1];
+  const unsigned offv = WholeRows<D, 1>::offset(V, threadIdx.x);
   auto fetch = [&](int t0) {
 #pragma unroll
     for (int m = 0; m < NM; ++m) {
       rg[m] = St::load(Gt, off, t0 + kC * m);
       rk[m] = St::load(K, off, t0 + kC * m);
-      rv[m] = St::load(V, off, t0 + kC * m);
+      if constexpr (kRows) wv[m].load(V, offv, t0 + kC * m);
+      else rv[m] = St::load(V, off, t0 + kC * m);
     }
   };
   int t0 = (rows - 1) / (NM * kC) * (NM * kC);
@@ -156,10 +160,11 @@ __global__ void __launch_bounds__(4 * D) bwd_state_kernel(const BwdArgs a) {
     float kd[NM][4];
 #pragma unroll
     for (int m = NM - 1; m >= 0; --m) {
-      St::template to_lds<D>(vrows + m * kC * St::template row_bytes<D>(), g, n, 16 * w, rv[m]);
+      if constexpr (kRows) wv[m].to_lds(vrows + m * kC * St::template row_bytes<D>(), St::template row_bytes<D>(), threadIdx.x);
+      else St::template to_lds<D>(vrows + m * kC * St::template row_bytes<D>(), g, n, 16 * w, rv[m]);
       float gl[4], kk[4], al[4];
-      St::patch(qd, rg[m], gl);
-      St::patch(qd, rk[m], kk);
+      St::row_patch(qd, rg[m], gl);
+      St::row_patch(qd, rk[m], kk);
       alphas_of(gl, a.gate_scale, rows - (t0 + kC * m + 4 * g), al);
       const float s2 = al[3], s1 = al[2] * s2, s0x = al[1] * s1, tot = al[0] * s0x;
       const float x1 = lane_get(ln.x1, tot), x2 = lane_get(ln.x2, tot), x3 = lane_get(ln.x3, tot);
@@ -183,7 +188,7 @@ __global__ void __launch_bounds__(4 * D) bwd_state_kernel(const BwdArgs a) {
     __syncthreads();
   }
   float* slot = a.slots_f + ((size_t)bh * (a.nseg - 1) + seg) * slot_floats<D>();
-  const int c = 16 * w + n;
+  const int c = 16 * w + St::channel(n);
 #pragma unroll
   for (int jt = 0; jt < D / 16; ++jt) *reinterpret_cast<floatx4*>(slot + (size_t)c * D + 16 * jt + 4 * g) = X[jt];
   z += lane_get(ln.x1, z);
@@ -273,7 +278,7 @@ __global__ void __launch_bounds__(4 * D, 2) bwd_forward_kernel(const BwdArgs a) 
   const int tid = threadIdx.x;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63, g = l >> 4, n = l & 15;
   const Lanes ln = make_lanes(l);
-  const Quad qd = make_quad(l);
+  const Turn qd = make_turn(l);
   constexpr bool kWide = sizeof(T) == 4;      // fp32 storage: contractions summed in 64 bits
   const int row = kWide ? strided(n) : n;     // the A operand's row in this lane
   const int seg = blockIdx.x, bh = blockIdx.y, b = bh / a.Hkv, hk = bh % a.Hkv;
@@ -285,8 +290,8 @@ __global__ void __launch_bounds__(4 * D, 2) bwd_forward_kernel(const BwdArgs a) 
   const Rows K = make_rows(a.k, kv1, kvs, rows, D * St::kBytes), V = make_rows(a.v, kv1, kvs, rows, D * St::kBytes),
              Gt = make_rows(a.g, kv1, kvs, rows, D * St::kBytes), Q = make_rows(a.q, q1, qs, rows, a.group * D * St::kBytes),
              O = make_rows(a.dO, q1, qs, rows, a.group * D * St::kBytes), dQ = make_rows(a.dq, q1, qs, rows, a.group * D * St::kBytes);
-  const unsigned offk = St::offset(K, g, n, 16 * w), offq = St::offset(Q, g, n, 16 * w);
-  const int c = 16 * w + n;
+  const unsigned offk = St::row_offset(K, g, n, 16 * w), offq = St::row_offset(Q, g, n, 16 * w);
+  const int c = 16 * w + St::channel(n);
 
   // state before the next chunk's first token (to be decayed by f), normalizer; gradient contribution
   floatx4 X[D / 16], R[D / 16];
@@ -350,8 +355,8 @@ __global__ void __launch_bounds__(4 * D, 2) bwd_forward_kernel(const BwdArgs a) 
     // ---- rows to LDS, gates
     if (hb == 0) {
       float gl[4];
-      St::patch(qd, rg, gl);
-      St::patch(qd, rk, kk);
+      St::row_patch(qd, rg, gl);
+      St::row_patch(qd, rk, kk);
       alphas_of(gl, a.gate_scale, rows - (row0 + 4 * g), d.al);
       bool tame = true;
 #pragma unroll
@@ -381,7 +386,7 @@ __global__ void __launch_bounds__(4 * D, 2) bwd_forward_kernel(const BwdArgs a) 
     }
     float qq[HB][4];
 #pragma unroll
-    for (int h = 0; h < HB; ++h) St::patch(qd, rq[h], qq[h]);
+    for (int h = 0; h < HB; ++h) St::row_patch(qd, rq[h], qq[h]);
     float top = 0.f;       // largest |q|
 #pragma unroll
     for (int h = 0; h < HB; ++h)
@@ -562,7 +567,7 @@ __global__ void __launch_bounds__(4 * D, 2) bwd_forward_kernel(const BwdArgs a) 
           qw[h][i] = qe * rd[i];
         }
       }
-      St::store(dQ, qd, offq + (unsigned)(hb * HB + h) * D * St::kBytes, row0, g, n, 0, kC, dq);
+      St::row_store(dQ, qd, offq + (unsigned)(hb * HB + h) * D * St::kBytes, row0, g, n, dq);
     }
     Rz += rz;
     // q and dO reach rz through dden, and a denominator of zero does: what is not finite in any of them shows here
@@ -619,7 +624,8 @@ __device__ __forceinline__ void reverse_sweep(const BwdArgs& a) {
   const int tid = threadIdx.x;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63, g = l >> 4, n = l & 15;
   const Lanes ln = make_lanes(l);
-  const Quad qd = make_quad(l);
+  const Turn qd = make_turn(l);
+  const Quad qv = make_quad(l);      // (dv: lanes are value columns as they come)
   constexpr bool kWide = sizeof(T) == 4;      // fp32 storage: contractions summed in 64 bits
   const int row = kWide ? strided(n) : n;     // the A operand's row in this lane
   const int seg = blockIdx.x, bh = blockIdx.y, b = bh / a.Hkv, hk = bh % a.Hkv;
@@ -632,8 +638,8 @@ __device__ __forceinline__ void reverse_sweep(const BwdArgs& a) {
              Gt = make_rows(a.g, kv1, kvs, rows, D * St::kBytes), Q = make_rows(a.q, q1, qs, rows, a.group * D * St::kBytes),
              O = make_rows(a.dO, q1, qs, rows, a.group * D * St::kBytes), dK = make_rows(a.dk, kv1, kvs, rows, D * St::kBytes),
              dV = make_rows(a.dv, kv1, kvs, rows, D * St::kBytes), dG = make_rows(a.dg, kv1, kvs, rows, D * St::kBytes);
-  const unsigned offk = St::offset(K, g, n, 16 * w), offq = St::offset(Q, g, n, 16 * w);
-  const int c = 16 * w + n;
+  const unsigned offk = St::row_offset(K, g, n, 16 * w), offq = St::row_offset(Q, g, n, 16 * w);
+  const int c = 16 * w + St::channel(n), vc = 16 * w + n;      // this lane's key channel, and value column
 
   // the gradient flowing into the segment's end, and the gate's sum over everything after it
   floatx4 R[D / 16];
@@ -734,8 +740,8 @@ __device__ __forceinline__ void reverse_sweep(const BwdArgs& a) {
     // ---- once per chunk: decays, K', R~; rows to LDS
     if (hb == 0) {
       float gl[4];
-      St::patch(qd, rg, gl);
-      St::patch(qd, rk, kk);
+      St::row_patch(qd, rg, gl);
+      St::row_patch(qd, rk, kk);
       alphas_of(gl, a.gate_scale, rows - (row0 + 4 * g), d.al);
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
@@ -772,7 +778,7 @@ __device__ __forceinline__ void reverse_sweep(const BwdArgs& a) {
             rs[jt] = split4(R[jt][0], R[jt][1], R[jt][2], R[jt][3]);
             state_terms_to_lds(sm + L::rR, D * D * 2, g, n, 16 * w, jt, rs[jt]);
           } else {
-            *reinterpret_cast<floatx4*>(sm + L::rR + c * f32_row_bytes<D>() + (16 * jt + 4 * g) * 4) = R[jt];
+            *reinterpret_cast<floatx4*>(sm + L::rR + vc * f32_row_bytes<D>() + (16 * jt + 4 * g) * 4) = R[jt];      // (a row per lane, as K')
           }
         }
       }
@@ -799,7 +805,7 @@ __device__ __forceinline__ void reverse_sweep(const BwdArgs& a) {
     Wide<T> rzt[4] = {0, 0, 0, 0};
 #pragma unroll
     for (int h = 0; h < HB; ++h) {
-      St::patch(qd, rq[h], qp[h]);
+      St::row_patch(qd, rq[h], qp[h]);
 #pragma unroll
       for (int i = 0; i < 4; ++i) qp[h][i] *= d.E[i];
       if constexpr (kAhead) {
@@ -889,7 +895,7 @@ __device__ __forceinline__ void reverse_sweep(const BwdArgs& a) {
       for (int i = 0; i < 4; ++i) {
         Wide<T> s = 0;
 #pragma unroll
-        for (int j = 0; j < NW; ++j) s += dvp[(j * kC + 4 * g + i) * D + c];
+        for (int j = 0; j < NW; ++j) s += dvp[(j * kC + 4 * g + i) * D + vc];
         if (kWide) dvw[i] += s;
         else dv[i] += s;
       }
@@ -913,7 +919,7 @@ __device__ __forceinline__ void reverse_sweep(const BwdArgs& a) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
           fa[i] = f[i];
-          r[i] = *reinterpret_cast<const float*>(sm + L::rR + (16 * ct + 4 * g + i) * f32_row_bytes<D>() + c * 4);
+          r[i] = *reinterpret_cast<const float*>(sm + L::rR + (16 * ct + 4 * g + i) * f32_row_bytes<D>() + vc * 4);
         }
         if constexpr (kWide) {
 #pragma unroll
@@ -1090,9 +1096,9 @@ __device__ __forceinline__ void reverse_sweep(const BwdArgs& a) {
 #pragma unroll
       for (int i = 0; i < 4; ++i) dgv[i] = (float)(x[i] + rest) * a.gate_scale * sig[i];
       later = lane_get(ln.n4, (float)(x[0] + rest));
-      St::store(dK, qd, offk, row0, g, n, 0, kC, dkv);
-      St::store(dV, qd, offk, row0, g, n, 0, kC, dvv);
-      St::store(dG, qd, offk, row0, g, n, 0, kC, dgv);
+      St::row_store(dK, qd, offk, row0, g, n, dkv);
+      St::store(dV, qv, St::offset(dV, g, n, 16 * w), row0, g, n, 0, kC, dvv);
+      St::row_store(dG, qd, offk, row0, g, n, dgv);
     }
     // What is read after the barrier before dv (the scores, dO . v, dO) is written next after the first barrier of the next chunk, or in the other
     // turn's rows; everything else was read before it.  (One turn of rows, parts, and tokens one by one, are read up to here.)
