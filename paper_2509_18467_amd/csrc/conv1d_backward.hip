@@ -54,18 +54,23 @@ constexpr int kGroup = 4;   // rows fetched together, one group ahead of the ari
 
 // grid (ceil(row / (1024 / NSUB)), strips, B), 256 threads = 256 / NSUB groups of four channels x NSUB runs of a strip's tokens;
 // row = H * d channels of a token.
-template <typename T, int W, int PHI, int NSUB>
-__global__ void __launch_bounds__(256) conv_bwd_kernel(const T* __restrict__ x, const T* __restrict__ w,
+// WHOLE (up to four strips in all): grid (ceil(row / 32)), 512 threads = 8 groups of four channels x all strips' runs of 4 tokens; `partial` is
+// dw itself, added up in the order of the two kernels (the same bits).  A second launch for so few sums took as long as the first:
+// 100 tokens of two heads, fp32, the training pass 83.3 -> 79.7 us, 256 96.0 -> 94.3; 200 of 32 / 8, bf16, 80.7 -> 79.4.  For more strips a
+// workgroup's columns are too narrow for its 512 threads: 8 strips, 500 tokens of 4 / 2 125.0 / 126.8, 16, 1000 of 32 / 8 98.3 / 117.6.
+template <typename T, int W, int PHI, int NSUB, bool WHOLE = false>
+__global__ void __launch_bounds__(WHOLE ? 512 : 256) conv_bwd_kernel(const T* __restrict__ x, const T* __restrict__ w,
                                                       const T* __restrict__ halo, const T* __restrict__ dy,
                                                       T* __restrict__ dx, T* __restrict__ dhalo,
-                                                      float* __restrict__ partial, int Tn, int row) {
-  constexpr int COLS = 256 / NSUB, RUN = kStrip / NSUB;
+                                                      float* __restrict__ partial, int Tn, int row, int strips = 0, int n_partial = 0) {
+  constexpr int COLS = WHOLE ? 8 : 256 / NSUB, RUN = kStrip / NSUB;
   typedef typename RawOf<T>::type Raw;
   const int col = threadIdx.x % COLS, sub = threadIdx.x / COLS;
   const int e0 = (blockIdx.x * COLS + col) * 4;
-  const int strip = blockIdx.y, b = blockIdx.z;
-  const int t0 = strip * kStrip + sub * RUN, t1 = min(Tn, t0 + RUN);
-  const bool active = e0 < row && t0 < Tn;
+  const int all = WHOLE ? sub / NSUB : 0;      // of all sequences' strips
+  const int b = WHOLE ? all / strips : blockIdx.z, strip = WHOLE ? all - b * strips : blockIdx.y;
+  const int t0 = strip * kStrip + (WHOLE ? sub % NSUB : sub) * RUN, t1 = min(Tn, t0 + RUN);
+  const bool active = e0 < row && t0 < Tn && (!WHOLE || all < n_partial);
 
   float dw[4][W];
 #pragma unroll
@@ -169,6 +174,30 @@ __global__ void __launch_bounds__(256) conv_bwd_kernel(const T* __restrict__ x, 
       }
     }
   }
+  if constexpr (WHOLE) {
+    constexpr int N = COLS * 4 * W;      // sums
+    __shared__ float sums[512 * 4 * W], strip_sums[4 * N];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int dl = 0; dl < W; ++dl) sums[threadIdx.x * 4 * W + i * W + dl] = dw[i][dl];
+    __syncthreads();
+    for (int k = threadIdx.x; k < n_partial * N; k += 512) {
+      const int q = k / N, e = k % N;
+      float acc = 0.f;
+#pragma unroll
+      for (int j = 0; j < NSUB; ++j) acc += sums[(q * NSUB + j) * N + e];
+      strip_sums[k] = acc;
+    }
+    __syncthreads();
+    const int first = blockIdx.x * N + threadIdx.x;
+    if (threadIdx.x < N && first < row * W) {
+      float acc = strip_sums[threadIdx.x];
+      for (int q = 1; q < n_partial; ++q) acc += strip_sums[q * N + threadIdx.x];
+      partial[first] = acc;
+    }
+    return;
+  }
   float* out = partial + ((size_t)b * gridDim.y + strip) * row * W;
   if constexpr (NSUB == 1) {      // a thread's own 4 W sums are contiguous
     if (!active) return;
@@ -248,7 +277,7 @@ template <typename T, int W, int PHI, int NSUB>
 void launch_kernel(const ConvBackwardParams& p, float* partial, int row, int strips, hipStream_t stream) {
   const int cols = 256 / NSUB;
   hipLaunchKernelGGL((conv_bwd_kernel<T, W, PHI, NSUB>), dim3((row / 4 + cols - 1) / cols, strips, p.B), dim3(256), 0, stream,
-                     (const T*)p.x, (const T*)p.w, (const T*)p.halo, (const T*)p.dy, (T*)p.dx, (T*)p.dhalo, partial, p.T, row);
+                     (const T*)p.x, (const T*)p.w, (const T*)p.halo, (const T*)p.dy, (T*)p.dx, (T*)p.dhalo, partial, p.T, row, 0, 0);
 }
 
 template <typename T, int W, int PHI>
@@ -263,6 +292,11 @@ hipError_t launch_phi(const ConvBackwardParams& p, hipStream_t stream) {
   // whole strip, where that fills the chip: short sequences leave most runs empty (256 sequences, 2048 channels, bf16, 17 and 32
   // tokens 19.6 and 30.2 us, in runs of 16 26.1 and 33.4; from 64 on the same).
   const long long work = (long long)row * n_partial;
+  if (p.T > 4 && n_partial > 1 && n_partial <= 4 && work < 96 * 1024) {
+    hipLaunchKernelGGL((conv_bwd_kernel<T, W, PHI, 16, true>), dim3((row / 4 + 7) / 8), dim3(512), 0, stream, (const T*)p.x, (const T*)p.w,
+                       (const T*)p.halo, (const T*)p.dy, (T*)p.dx, (T*)p.dhalo, p.dw, p.T, row, strips, n_partial);
+    return hipGetLastError();
+  }
   if (p.T <= 4 || (p.T < kStrip && work * (int)sizeof(T) >= 1 << 20)) launch_kernel<T, W, PHI, 1>(p, partial, row, strips, stream);
   else if (work >= 96 * 1024) launch_kernel<T, W, PHI, 4>(p, partial, row, strips, stream);
   else launch_kernel<T, W, PHI, 16>(p, partial, row, strips, stream);
