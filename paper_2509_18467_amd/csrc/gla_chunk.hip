@@ -108,7 +108,8 @@ hipError_t launch_gla_chunk(const ChunkParams& p, hipStream_t stream) {
   // of 64, 128 x 200 tokens 96 / 122 / 120, 30 x 333 47 / 65 / 52, 12 of 60 to 280 24.2 / 26.4 / 29.3; 4 short ones beside one of 2000 47.5 /
   // 29.8 / 30.9, 12 of 88 to 1439 54.9 / 39.2 / 41.8; 24 of 101 to 3364 190 / 115 / 95, 48 of 204 to 691 135 / 120 / 97.  Of 128, 16 of 480 to
   // 520 84 / 128 / 88; 3 of 337 to 855 63 / 47 / 48; 24 of 300 to 498 161 / 146 / 106.  (At head dim 64 a few workgroups too many, which leave
-  // at once, cost less than to order them: 24 of 300 to 498, 9/8 of the chip, 48.8 / 50.1 / 51.1; of 128, 12 of 208 to 352, 63 / 71 / 50.)
+  // at once, cost less than to order them, while a walk is short: 24 of 300 to 498, 9/8 of the chip, 48.8 / 50.1 / 51.1, but 8 of 4111 to
+  // 7197, segments of 832, 172 / 140 / 140; of 128, 12 of 208 to 352, 63 / 71 / 50.)
   a.places = chunk::kDirect;
   if (p.seq_start) {
     const long long places = p.d == 64 ? 512 : 256, parts = in_place ? 1 : std::max(1, group / a.most);     // at once on the chip; workgroups per segment
@@ -116,7 +117,7 @@ hipError_t launch_gla_chunk(const ChunkParams& p, hipStream_t stream) {
     if (direct <= p.plan.segments || direct * p.Hkv * parts <= places) a.places = chunk::kDirect;
     else if (p.B > 64) a.places = direct <= in_order ? chunk::kDirect : chunk::kInOrder;
     else if (in_order * p.Hkv * parts <= places) a.places = chunk::kInOrder;
-    else a.places = p.d == 64 && direct * p.Hkv * parts <= places * 9 / 8 ? chunk::kDirect : chunk::kByLength;
+    else a.places = p.d == 64 && p.plan.seg_len <= 256 && direct * p.Hkv * parts <= places * 9 / 8 ? chunk::kDirect : chunk::kByLength;
   }
   const int passes = group % 4 == 0 || a.most == 1 ? 1 : group / 4 + (group % 4 + 1) / 2;
   a.fold = !in_place && nseg > 1 && nseg * passes <= fold_most(heads, group, p.d);
