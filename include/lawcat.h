@@ -234,7 +234,7 @@ LAWCAT_API int lawcat_layer_prefill(const lawcat_desc* desc, const void* Q, cons
  * that the workgroups are about as many as the chip holds whatever the mix of lengths.  Otherwise (no device
  * copy, or fp32 storage): one lawcat_layer_prefill with B = 1 per sequence, enqueued in order on `stream`,
  * sharing `workspace`.  Workspace size for either form: lawcat_varlen_workspace_bytes (one_launch = whether
- * seq_start_dev will be passed).  All sequences are checked on the host before anything is enqueued: a length
+ * seq_start_dev will be passed); a smaller one is taken if a plan with fewer segments fits it.  All sequences are checked on the host before anything is enqueued: a length
  * below 1 or above desc->T is LAWCAT_E_BAD_DESC.
  */
 LAWCAT_API size_t lawcat_varlen_workspace_bytes(const lawcat_desc* desc, const int32_t* seq_start, int one_launch);

@@ -113,43 +113,77 @@ size_t workspace_bytes_checked(const lawcat_desc* d, int which, size_t room = SI
 
 // Segments of a packed batch of sequences (one set of launches): cut as for ONE sequence of all the tokens, so that
 // the workgroups are about as many as the chip holds and about equally long whatever the mix of lengths; slots are
-// laid out for the longest sequence.
-ChunkPlan varlen_plan(const lawcat_desc* d, const int32_t* seq_start) {
+// laid out for the longest sequence.  room: bytes of the workspace; if it is too small, the plan is the one that needs least (`roomy` false):
+// eight waves a workgroup at head dim 128, one round of workgroups.
+ChunkPlan varlen_plan(const lawcat_desc* d, const int32_t* seq_start, size_t room, bool roomy = true) {
   const long long total = seq_start[d->B];
   int longest = 1;
   for (int i = 0; i < d->B; ++i) longest = std::max(longest, (int)(seq_start[i + 1] - seq_start[i]));
-  ChunkPlan one = make_chunk_plan(1, (int)std::min<long long>(total, 0x7fffffc0LL), d->Hq, d->Hkv, d->dk, d->carry_mode, d->segment, false, 0);
+  const int tokens = (int)std::min<long long>(total, 0x7fffffc0LL), whole = (longest + 63) / 64 * 64;
+  const bool cut = d->segment == 0 && d->carry_mode != LAWCAT_CARRY_SEQUENTIAL;
+  const long long parts = std::max(1, d->Hq / d->Hkv / 4), lanes = d->Hkv * parts;   // workgroups take up to four query heads
+  ChunkPlan one = make_chunk_plan(1, tokens, d->Hq, d->Hkv, d->dk, d->carry_mode, d->segment, roomy, SIZE_MAX);
   ChunkPlan p{};
-  const int whole = (longest + 63) / 64 * 64;
+  // Head dim 128, two workgroups a unit (gla_wide.h): as for one sequence (groups of eight from 320 tokens a segment like the others), and where even
+  // uncut sequences are an eighth more workgroups than units, which one a unit takes in two rounds.  us a call, eight waves / four, 32 heads on 8: 24
+  // of 100 to 3269 tokens 224 / 195, 40 of 16 to 1244 130 / 111, 48 of 200 to 299 119 / 93; 32 on 4, 40 of 30 to 264 63 / 58.
+  if (d->dk == 128 && roomy && cut) {
+    p.wide = one.wide && one.seg_len >= 320;
+    if (d->B * lanes > 288) {
+      const long long most = (512 + lanes - 1) / lanes;
+      one.seg_len = (int)std::max<long long>(128, ((tokens + most - 1) / most + 63) / 64 * 64);
+      p.wide = 1;
+    } else if (one.wide && !p.wide) {
+      one = make_chunk_plan(1, tokens, d->Hq, d->Hkv, d->dk, d->carry_mode, d->segment, false, SIZE_MAX);
+    }
+  }
   p.seg_len = std::min(one.seg_len, whole);
   if (d->carry_mode == LAWCAT_CARRY_SEQUENTIAL) p.seg_len = whole;
-  if (d->segment == 0 && d->carry_mode != LAWCAT_CARRY_SEQUENTIAL) {
+  if (cut) {
     // every sequence rounds its segment count up: lengthen the segments until the workgroups fit the chip in one
     // round (a few too many would double the time of the pass), or, where a group takes several workgroups, in as many rounds as
     // cost least (a few long sequences among many short ones: 32 of 20 to 1405 tokens, 32 query heads on 4 of 128, one round / two
     // 259 / 161 us)
-    const long long slots = d->dk == 64 ? 512 : 256, parts = std::max(1, d->Hq / d->Hkv / 4);   // workgroups take up to four query heads
-    auto rounds = [&](int seg_len) {
+    const bool shared = d->dk == 64 || p.wide;   // two workgroups a unit
+    const long long slots = shared ? 512 : 256;
+    auto workgroups = [&](int seg_len) {
       long long n = 0;
       for (int i = 0; i < d->B; ++i) n += (seq_start[i + 1] - seq_start[i] + seg_len - 1) / seg_len;
-      return (n * d->Hkv * parts + slots - 1) / slots;
+      return n * lanes;
     };
-    long long cost = LLONG_MAX;
+    // Where two workgroups share a unit, up to a third too many, the longest first (up to 64 sequences, find_place), cost two thirds of a round
+    // more at most: they are the shortest ones and begin as others end, and who is left alone in a unit is faster.  32 heads on 8 of 128, 64
+    // of 16 to 681 tokens, uncut for one round / in segments of 256 166 / 136 us.  (Lengths that are nearly alike leave a second round, and take one: 8
+    // of 4111 to 7197 375 / 292.)
+    const bool spill = roomy && shared && d->B > 1 && d->B <= 64;
+    long long cost = LLONG_MAX, r;
     int len = p.seg_len;
     for (long long most = parts; most >= 1; --most) {
-      long long r = rounds(len);
-      while (len < whole && r > most) r = rounds(len += 64);
+      for (;; len += 64) {
+        const long long n = workgroups(len);
+        r = (n + slots - 1) / slots;
+        if (spill && r == 2 && 3 * n <= 4 * slots) {
+          if (len * 5LL / 3 < cost) {
+            cost = len * 5LL / 3;
+            p.seg_len = len;
+          }
+        }
+        if (len >= whole || r <= most) break;
+      }
       if (r * len <= cost) {
         cost = r * len;
         p.seg_len = len;
       }
     }
+    // uncut, there is no state pass, which takes about as long as 128 tokens (32 on 4 of 128, 100 of 50 to 198 tokens, segments of 192 / uncut
+    // 125 / 105 us)
+    if (roomy && shared && (d->B * lanes + slots - 1) / slots * longest <= cost + 128) p.seg_len = whole;
   }
   p.nseg = cut_sequence(longest, p.seg_len).nseg;
   for (int i = 0; i < d->B; ++i) p.segments += cut_sequence(seq_start[i + 1] - seq_start[i], p.seg_len).nseg;
   p.per_head = (int)((total + p.seg_len - 1) / p.seg_len) + d->B - 1;
   p.workspace_bytes = p.nseg > 1 ? (size_t)d->B * d->Hkv * p.nseg * ((d->dk * d->dk + 2 * d->dk) * sizeof(float) + sizeof(int)) : 0;
-  return p;
+  return roomy && p.workspace_bytes > room ? varlen_plan(d, seq_start, room, false) : p;
 }
 
 int hip_status(hipError_t e) { return e == hipSuccess ? LAWCAT_OK : LAWCAT_E_HIP; }
@@ -399,7 +433,7 @@ size_t lawcat_varlen_workspace_bytes(const lawcat_desc* desc, const int32_t* seq
     const long long len = (long long)seq_start[i + 1] - seq_start[i];
     if (len < 1 || len > desc->T) return 0;
   }
-  if (one_launch && prefill_path(desc) == Path::kChunkBf16) return varlen_plan(desc, seq_start).workspace_bytes;
+  if (one_launch && prefill_path(desc) == Path::kChunkBf16) return varlen_plan(desc, seq_start, SIZE_MAX).workspace_bytes;
   size_t need = 0;
   for (int i = 0; i < desc->B; ++i) {
     lawcat_desc one = *desc;
@@ -433,7 +467,7 @@ int lawcat_layer_prefill_varlen(const lawcat_desc* desc, const int32_t* seq_star
   if (seq_start_dev != nullptr && prefill_path(desc) == Path::kChunkBf16) {
     // one set of launches for the whole batch: the kernels take every sequence's first row and length from
     // the device copy of the offsets; segments are cut for the longest sequence
-    const ChunkPlan plan = varlen_plan(desc, seq_start);
+    const ChunkPlan plan = varlen_plan(desc, seq_start, workspace == nullptr ? 0 : workspace_bytes);
     if (plan.workspace_bytes > 0 && (workspace == nullptr || workspace_bytes < plan.workspace_bytes)) return LAWCAT_E_WORKSPACE;
     ChunkParams c{};
     c.q = Q; c.k = K; c.v = V; c.g = gate_logits; c.wq = wq; c.wk = wk; c.q_halo = q_halo; c.k_halo = k_halo;

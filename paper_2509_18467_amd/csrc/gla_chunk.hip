@@ -112,7 +112,7 @@ hipError_t launch_gla_chunk(const ChunkParams& p, hipStream_t stream) {
   // 7197, segments of 832, 172 / 140 / 140; of 128, 12 of 208 to 352, 63 / 71 / 50.)
   a.places = chunk::kDirect;
   if (p.seq_start) {
-    const long long places = p.d == 64 ? 512 : 256, parts = in_place ? 1 : std::max(1, group / a.most);     // at once on the chip; workgroups per segment
+    const long long places = p.d == 64 || p.plan.wide ? 512 : 256, parts = in_place ? 1 : std::max(1, group / a.most);     // at once on the chip; workgroups per segment
     const long long direct = (long long)p.B * nseg, in_order = p.plan.per_head;
     if (direct <= p.plan.segments || direct * p.Hkv * parts <= places) a.places = chunk::kDirect;
     else if (p.B > 64) a.places = direct <= in_order ? chunk::kDirect : chunk::kInOrder;
