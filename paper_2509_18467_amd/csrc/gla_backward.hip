@@ -31,15 +31,16 @@
 // The gate's sum over all later tokens is split at segment ends, where it equals sum_j S^[c, j] Gr[c, j], the states on the two
 // sides of the boundary: no pass over the sequence is needed for it.
 //
-// What it measures (32768 tokens, 32 query heads on 8 kv heads, d = 64, bf16), a call back to back with itself: 406 us.  Kernel by
-// kernel under a profiler, at their quickest: state 17, scans 4 each, forward sweep 190, reverse sweep 215.  The two sweeps move
-// 0.57 and 0.54 GB (q, dO, k, v, g once each, the gate term in fp32, the gradients), 105 us each at the rate of a large copy.  A chunk
-// takes a workgroup 6.1 us (two share a compute unit), spread over all of its sections (timestamps, us: forward, gates and rows 1.3, K' and z 1.1, u 1.3,
-// reduction of q . u 0.4, dden and dq 0.7, gradients' and state's update 1.1; reverse, gates, rows and decays 1.1, R~ v and K' R~ 2.0,
-// scores 0.6, dk 0.8, update 0.8, dv and outputs 0.6; barriers 0.1 each): dependent chains at two waves per SIMD, whose
-// registers (239 and 231) leave room for no third, and a limit of 168 spilled (forward 636 us, reverse 423).  With one chunk's rows
-// written only when all waves were done with the chunk before (three barriers a chunk in the forward sweep, five in the
-// reverse one, now two each) and the four gates of a lane formed one after the other: 418.
+// What it measures (32768 tokens, 32 query heads on 8 kv heads, d = 64, bf16), kernel by kernel in a training pass under a profiler, at their
+// quickest / on average: state 14 / 15, scans 4, forward sweep 155 / 172, reverse sweep 152 / 171.  The two sweeps move 0.57 and 0.54 GB (q, dO,
+// k, v, g once each, the gate term in fp32, the gradients), 105 us each at the rate of a large copy; what bounds them is a workgroup's dependent
+// chain through a chunk's sections between two barriers, at two waves per SIMD, whose registers leave room for no third (a limit of
+// 168 spilled: forward 636 us, reverse 423).  The training pass, us, step by step: 645; the reverse sweep's products of two fp32 operands as bf16 terms
+// (chunk_f32.h) 638; dO and v, which only go to LDS, loaded as whole rows (a load of a patch touched 16 rows for 32 bytes, and the
+// issue of a chunk's twelve took a sixth of it) 613; no branch around the reverse sweep's loads, whose join waited for all of them,
+// 599; 32-bit offsets and the operands of the state's update read together 597; patches with a row's four lanes side by side, whose loads
+// then are 16 accesses and not 64, 586.  Nothing or worse: patches transposed through LDS (667), rows a chunk ahead through LDS (624), loads spread over the
+// stage (627), a denominator load per wave (623).
 //
 // fp32 storage: the sums of every contraction are fp64 MFMAs and decays are multiplied up in 64 bits, rounded per chunk, because
 // chains of fp32 MFMAs alone were up to 2.4 times further from 64-bit arithmetic than sums token by token.  2-norm errors of
