@@ -373,8 +373,8 @@ int layer_prefill_impl(const lawcat_desc* desc, const void* Q, const void* K, co
       !aligned16(O) || !den_ok || !aligned16(S_out) || !aligned16(z_out) ||
       !aligned16(q_tail_out) || !aligned16(k_tail_out) || !aligned16(workspace))
     return LAWCAT_E_ALIGN;
-  const size_t need = workspace_bytes_checked(desc, LAWCAT_CALL_LAYER_PREFILL, 0);
-  if (need > 0 && (workspace == nullptr || workspace_bytes < need)) return LAWCAT_E_WORKSPACE;
+  const size_t room = workspace == nullptr ? 0 : workspace_bytes;
+  if (workspace_bytes_checked(desc, LAWCAT_CALL_LAYER_PREFILL, 0) > room) return LAWCAT_E_WORKSPACE;
   hipStream_t hs = static_cast<hipStream_t>(stream);
   const int bf16 = desc->dtype == LAWCAT_DTYPE_BF16;
 
@@ -385,7 +385,7 @@ int layer_prefill_impl(const lawcat_desc* desc, const void* Q, const void* K, co
     c.workspace = workspace;
     c.B = desc->B; c.T = desc->T; c.Hq = desc->Hq; c.Hkv = desc->Hkv; c.d = desc->dk;
     c.W = desc->conv_width; c.phi = desc->feature_map; c.fuse_conv = 1;
-    c.gate_scale = desc->gate_scale; c.eps = desc->eps; c.plan = plan_for(desc, true, workspace_bytes);
+    c.gate_scale = desc->gate_scale; c.eps = desc->eps; c.plan = plan_for(desc, true, room);
     c.q_tail = q_tail_out; c.k_tail = k_tail_out;
     c.ev_start = ev_start; c.ev_stop = ev_stop;
     return hip_status(launch_gla_chunk(c, hs));

@@ -1,0 +1,27 @@
+"""Which launches a prefill makes of the workspace that it is given, read from the launches themselves (see launches.py).  CPU only."""
+import pytest
+
+from paper_2509_18467_amd import lawcat
+
+import launches as L
+
+SLOT = (128 * 128 + 2 * 128) * 4 + 4
+
+
+@pytest.fixture(scope="module")
+def directory(tmp_path_factory):
+    return str(tmp_path_factory.mktemp("launches"))
+
+
+def test_no_workspace_has_no_room(directory):
+    """Head dim 128, more uncut workgroups than compute units: the quickest plan cuts sequences, and one that needs no workspace is taken as
+    well.  Without a pointer it is the one that runs, whatever size is passed beside it."""
+    d = lawcat.make_desc(40, 700, 32, 8, 128)
+    room = lawcat.workspace_bytes(d, lawcat.CALL_LAYER_PREFILL)
+    assert room == 40 * 8 * 2 * SLOT
+    one = lawcat.make_desc(1, 128 * 300, 64, 1, 128)
+    quick, bare, null, sized, missing = L.run([L.prefill(d, L.AT, room), L.prefill(d, L.AT, 0), L.prefill(d, L.NULL, 0), L.prefill(d, L.NULL, room),
+                                               L.prefill(one, L.NULL, 1 << 30)], directory)
+    assert quick == (0, [(1, 320, 1, 512), (2, 320, 1, 256)])     # state pass, output pass with four waves
+    assert bare == null == sized == (0, [(1, 320, 1, 512)])       # one segment each, eight waves
+    assert missing == (-4, [])
