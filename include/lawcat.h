@@ -95,7 +95,7 @@ typedef struct lawcat_desc {
  * Returns 0 for an invalid desc as well (the call itself reports the error).
  * lawcat_layer_prefill, head dimension 128, long sequences: the quickest form's; about half of it is taken, too
  * (LAWCAT_E_WORKSPACE below that): the sequence is then cut into segments twice as long and the call takes up to a seventh
- * longer, its results the same to rounding.  lawcat_layer_prefill_static takes whichever form its buffer holds. */
+ * longer, its results the same to rounding. */
 LAWCAT_API size_t lawcat_workspace_bytes(const lawcat_desc* desc, int which_call);
 
 /*
@@ -266,9 +266,9 @@ LAWCAT_API int lawcat_layer_prefill_fm(const lawcat_desc* desc, const void* Q, c
 /*
  * lawcat_layer_prefill for callers that cannot allocate device memory or hold a workspace: code under HIP
  * graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments and same results as
- * lawcat_layer_prefill, without `workspace`: the scratch is a buffer of LAWCAT_STATIC_WORKSPACE_BYTES that
+ * lawcat_layer_prefill with the workspace that lawcat_workspace_bytes asks for, without `workspace`: the scratch is a buffer that
  * lives inside the library, one copy per GPU that loads it, until the process ends.  The call allocates and
- * frees nothing.  A desc whose least workspace (see lawcat_workspace_bytes) exceeds the buffer
+ * frees nothing.  A desc whose least workspace (see lawcat_workspace_bytes) exceeds LAWCAT_STATIC_WORKSPACE_BYTES
  * returns LAWCAT_E_STATIC_LIMIT before anything is enqueued (24 MiB covers the two-level carry of every
  * single-sequence shape with up to 8 kv heads of dimension 128; fp32 storage stages q-dot and k-dot there and
  * fits only short sequences).  Every call on a GPU uses that GPU's one buffer: calls that overlap in time on

@@ -16,8 +16,11 @@ namespace {
 
 // Scratch of lawcat_layer_prefill_static: one copy per GPU that loads the library, kept until the process ends.
 // In host code the array's name is only a handle for hipGetSymbolAddress; kernels receive the device address
-// that static_scratch() looks up once per device.
-__device__ __align__(256) unsigned char scratch[LAWCAT_STATIC_WORKSPACE_BYTES];
+// that static_scratch() looks up once per device.  A call is taken if its least plan fits LAWCAT_STATIC_WORKSPACE_BYTES, and then runs the plan
+// that it would run with the workspace it asks for: the four-wave form at head dim 128 (gla_wide.h) has fewer than 512 + heads slots, of
+// fewer than 512 heads, 66564 bytes each (64.95 MiB).
+constexpr size_t kStaticRoom = (size_t)65 << 20;
+__device__ __align__(256) unsigned char scratch[kStaticRoom];
 
 hipError_t static_scratch(void** out) {
   constexpr int kMaxDev = 64;
@@ -554,7 +557,7 @@ int lawcat_layer_prefill_static(const lawcat_desc* desc, const void* Q, const vo
   void* ws = nullptr;
   if (static_scratch(&ws) != hipSuccess) return LAWCAT_E_HIP;
   return layer_prefill_impl(desc, Q, K, V, gate_logits, wq, wk, S0, z0, q_halo, k_halo, O, den_out, S_out, z_out,
-                            q_tail_out, k_tail_out, ws, LAWCAT_STATIC_WORKSPACE_BYTES, stream, nullptr, nullptr);
+                            q_tail_out, k_tail_out, ws, kStaticRoom, stream, nullptr, nullptr);
 }
 
 int lawcat_layer_prefill_timed(const lawcat_desc* desc, const void* Q, const void* K, const void* V,

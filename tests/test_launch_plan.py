@@ -25,3 +25,12 @@ def test_no_workspace_has_no_room(directory):
     assert quick == (0, [(1, 320, 1, 512), (2, 320, 1, 256)])     # state pass, output pass with four waves
     assert bare == null == sized == (0, [(1, 320, 1, 512)])       # one segment each, eight waves
     assert missing == (-4, [])
+
+
+@pytest.mark.parametrize("d,Hq,Hkv,B,T", [
+    # head dim 128: the four-wave form's slots, more than the limit of the least plan; the same within it; the most slots there are; eight waves
+    (128, 32, 8, 1, 18000), (128, 32, 8, 1, 131072), (128, 32, 4, 8, 1025), (128, 4, 1, 511, 700), (128, 32, 8, 1, 16384), (64, 32, 8, 1, 32768)])
+def test_static_scratch_has_room_for_the_same_plan(directory, d, Hq, Hkv, B, T):
+    desc = lawcat.make_desc(B, T, Hq, Hkv, d)
+    static, prefill = L.run([L.static(desc), L.prefill(desc, L.AT, lawcat.workspace_bytes(desc, lawcat.CALL_LAYER_PREFILL))], directory)
+    assert static == prefill and static[0] == 0 and len(static[1]) >= 2

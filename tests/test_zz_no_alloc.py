@@ -17,7 +17,7 @@ def _bits(t):
     return t.view(torch.int16) if t.dtype == torch.bfloat16 else t.view(torch.int32)
 
 
-def _both(wl, seed):
+def _both(wl, seed, quick=False):
     dt = H.tdtype(wl)
     x = make_inputs(wl, seed=seed, halo=True, state=True)
     desc = H.desc_for(wl, feature_map=1)
@@ -34,7 +34,10 @@ def _both(wl, seed):
                 torch.full((wl.B, wl.W - 1, wl.Hkv, wl.d), float("nan"), dtype=dt, device="cuda")]
 
     need = lawcat.workspace_bytes(desc, lawcat.CALL_LAYER_PREFILL)
-    assert 0 < need <= lawcat.STATIC_WORKSPACE_BYTES, "the case must use the scratch buffer and fit it"
+    if quick:      # (only the least plan has to fit the limit)
+        assert need > lawcat.STATIC_WORKSPACE_BYTES
+    else:
+        assert 0 < need <= lawcat.STATIC_WORKSPACE_BYTES, "the case must use the scratch buffer and fit it"
     ref = outputs()
     ws = lawcat.alloc_workspace(desc, lawcat.CALL_LAYER_PREFILL)
     lawcat.layer_prefill(desc, *ins, S0, z0, qh, kh, *ref, ws)
@@ -50,3 +53,8 @@ def test_static_scratch_entry_point_matches_on_two_calls_in_a_row():
     print("no-alloc entry point: mistral7b shape T=9000, then llama1b shape T=3000", flush=True)
     _both(WORKLOADS["mistral7b_16k"].with_T(9000), seed=31)
     _both(WORKLOADS["llama1b_8k"].with_T(3000), seed=32)
+
+
+def test_static_scratch_entry_point_matches_where_the_quickest_plan_needs_more_than_the_limit():
+    print("no-alloc entry point: mistral7b shape T=18000", flush=True)
+    _both(WORKLOADS["mistral7b_16k"].with_T(18000), seed=33, quick=True)
