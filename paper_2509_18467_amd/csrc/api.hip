@@ -123,64 +123,71 @@ ChunkPlan varlen_plan(const lawcat_desc* d, const int32_t* seq_start, size_t roo
   int longest = 1;
   for (int i = 0; i < d->B; ++i) longest = std::max(longest, (int)(seq_start[i + 1] - seq_start[i]));
   const int tokens = (int)std::min<long long>(total, 0x7fffffc0LL), whole = (longest + 63) / 64 * 64;
-  const bool cut = d->segment == 0 && d->carry_mode != LAWCAT_CARRY_SEQUENTIAL;
-  const long long parts = std::max(1, d->Hq / d->Hkv / 4), lanes = d->Hkv * parts;   // workgroups take up to four query heads
-  ChunkPlan one = make_chunk_plan(1, tokens, d->Hq, d->Hkv, d->dk, d->carry_mode, d->segment, roomy, SIZE_MAX);
-  ChunkPlan p{};
-  // Head dim 128, two workgroups a unit (gla_wide.h): as for one sequence (groups of eight from 320 tokens a segment like the others), and where even
-  // uncut sequences are an eighth more workgroups than units, which one a unit takes in two rounds.  us a call, eight waves / four, 32 heads on 8: 24
-  // of 100 to 3269 tokens 224 / 195, 40 of 16 to 1244 130 / 111, 48 of 200 to 299 119 / 93; 32 on 4, 40 of 30 to 264 63 / 58.
-  if (d->dk == 128 && roomy && cut) {
-    p.wide = one.wide && one.seg_len >= 320;
-    if (d->B * lanes > 288) {
-      const long long most = (512 + lanes - 1) / lanes;
-      one.seg_len = (int)std::max<long long>(128, ((tokens + most - 1) / most + 63) / 64 * 64);
-      p.wide = 1;
-    } else if (one.wide && !p.wide) {
-      one = make_chunk_plan(1, tokens, d->Hq, d->Hkv, d->dk, d->carry_mode, d->segment, false, SIZE_MAX);
-    }
-  }
-  p.seg_len = std::min(one.seg_len, whole);
-  if (d->carry_mode == LAWCAT_CARRY_SEQUENTIAL) p.seg_len = whole;
-  if (cut) {
+  const long long parts = std::max(1, d->Hq / d->Hkv / 4), lanes = d->Hkv * parts, uncut = d->B * lanes;   // workgroups take up to four query heads
+  auto workgroups = [&](int seg_len) {
+    long long n = 0;
+    for (int i = 0; i < d->B; ++i) n += (seq_start[i + 1] - seq_start[i] + seg_len - 1) / seg_len;
+    return n * lanes;
+  };
+  // Segment length for so many places on the chip, from `len` on.  every: what the workspace may be too small for, too.
+  auto cut = [&](int len, long long slots, bool every) {
     // every sequence rounds its segment count up: lengthen the segments until the workgroups fit the chip in one
     // round (a few too many would double the time of the pass), or, where a group takes several workgroups, in as many rounds as
     // cost least (a few long sequences among many short ones: 32 of 20 to 1405 tokens, 32 query heads on 4 of 128, one round / two
     // 259 / 161 us)
-    const bool shared = d->dk == 64 || p.wide;   // two workgroups a unit
-    const long long slots = shared ? 512 : 256;
-    auto workgroups = [&](int seg_len) {
-      long long n = 0;
-      for (int i = 0; i < d->B; ++i) n += (seq_start[i + 1] - seq_start[i] + seg_len - 1) / seg_len;
-      return n * lanes;
-    };
-    // Where two workgroups share a unit, up to a third too many, the longest first (up to 64 sequences, find_place), cost two thirds of a round
-    // more at most: they are the shortest ones and begin as others end, and who is left alone in a unit is faster.  32 heads on 8 of 128, 64
-    // of 16 to 681 tokens, uncut for one round / in segments of 256 166 / 136 us.  (Lengths that are nearly alike leave a second round, and take one: 8
-    // of 4111 to 7197 375 / 292.)
-    const bool spill = roomy && shared && d->B > 1 && d->B <= 64;
     long long cost = LLONG_MAX, r;
-    int len = p.seg_len;
+    const int first = len = std::min(len, whole);
+    int best = len;
     for (long long most = parts; most >= 1; --most) {
       for (;; len += 64) {
-        const long long n = workgroups(len);
-        r = (n + slots - 1) / slots;
-        if (spill && r == 2 && 3 * n <= 4 * slots) {
-          if (len * 5LL / 3 < cost) {
-            cost = len * 5LL / 3;
-            p.seg_len = len;
-          }
-        }
+        r = (workgroups(len) + slots - 1) / slots;
         if (len >= whole || r <= most) break;
       }
       if (r * len <= cost) {
         cost = r * len;
-        p.seg_len = len;
+        best = len;
+      }
+    }
+    if (!every || best == whole) return best;
+    // Two workgroups a unit, longest first (up to 64 sequences, find_place): up to a third too many cost two thirds of a round more at most; they
+    // are the shortest ones and begin as others end, and who is left alone in a unit is faster.  Heads of 64, 16 on 8, 58 of 128 to 2923 tokens,
+    // segments of 2112 / 960 1.43 times as fast, 52 of 84 to 2623 1344 / 768 1.13; 8 on 8 of 128, 57 of 47 to 2893 2048 / 1088 1.34.  Not for segments
+    // that the state pass and the fold outweigh (of 64, 32 on 8, 6 of 482 to 858, 128 / 64 tokens 32.6 / 44.4 us, 16 on 8, 47 of 109 to 682, 448 / 256 55.2 / 60.8),
+    // nor in the place of uncut sequences, which have no state pass (32 on 32 of 128, 17 of 35 to 474, uncut / 384 79.9 / 104.8).
+    for (len = std::max(first, d->dk == 64 ? 512 : 192); d->B > 1 && d->B <= 64 && len < best && len * 5LL / 3 < cost; len += 64) {
+      const long long n = workgroups(len);
+      if (n > slots && 3 * n <= 4 * slots) {
+        cost = len * 5LL / 3;
+        best = len;
       }
     }
     // uncut, there is no state pass, which takes about as long as 128 tokens (32 on 4 of 128, 100 of 50 to 198 tokens, segments of 192 / uncut
     // 125 / 105 us)
-    if (roomy && shared && (d->B * lanes + slots - 1) / slots * longest <= cost + 128) p.seg_len = whole;
+    return (uncut + slots - 1) / slots * longest <= cost + 128 ? whole : best;
+  };
+  ChunkPlan p{};
+  const ChunkPlan one = make_chunk_plan(1, tokens, d->Hq, d->Hkv, d->dk, d->carry_mode, d->segment, false, SIZE_MAX);
+  if (d->carry_mode == LAWCAT_CARRY_SEQUENTIAL) {
+    p.seg_len = whole;
+  } else if (d->segment != 0) {
+    p.seg_len = std::min(one.seg_len, whole);
+  } else {
+    if (d->dk == 128 && roomy) {
+      // Head dim 128, two workgroups a unit (gla_wide.h).  us a call, eight waves / four, 32 heads on 8.  As for one sequence (groups of eight from 320
+      // tokens a segment like the others): 24 of 100 to 3269 tokens 224 / 195.
+      const ChunkPlan four = make_chunk_plan(1, tokens, d->Hq, d->Hkv, d->dk, d->carry_mode, d->segment, true, SIZE_MAX);
+      if (uncut <= 288) {
+        p.wide = four.wide && four.seg_len >= 320;
+        if (p.wide) p.seg_len = cut(four.seg_len, 512, true);
+      } else {
+        // Where even uncut sequences are an eighth more workgroups than units, which one a unit takes in two rounds: 40 of 16 to 1244 130 / 111, 48 of
+        // 200 to 299 119 / 93; 32 on 4, 40 of 30 to 264 63 / 58.
+        const long long most = (512 + lanes - 1) / lanes;
+        p.wide = 1;
+        p.seg_len = cut((int)std::max<long long>(128, ((tokens + most - 1) / most + 63) / 64 * 64), 512, true);
+      }
+    }
+    if (!p.wide) p.seg_len = cut(one.seg_len, d->dk == 64 ? 512 : 256, roomy && d->dk == 64);
   }
   p.nseg = cut_sequence(longest, p.seg_len).nseg;
   for (int i = 0; i < d->B; ++i) p.segments += cut_sequence(seq_start[i + 1] - seq_start[i], p.seg_len).nseg;
