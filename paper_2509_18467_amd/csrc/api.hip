@@ -122,8 +122,8 @@ ChunkPlan varlen_plan(const lawcat_desc* d, const int32_t* seq_start, size_t roo
   const long long total = seq_start[d->B];
   int longest = 1;
   for (int i = 0; i < d->B; ++i) longest = std::max(longest, (int)(seq_start[i + 1] - seq_start[i]));
-  const int tokens = (int)std::min<long long>(total, 0x7fffffc0LL), whole = (longest + 63) / 64 * 64;
-  const long long parts = std::max(1, d->Hq / d->Hkv / 4), lanes = d->Hkv * parts, uncut = d->B * lanes;   // workgroups take up to four query heads
+  const int tokens = (int)std::min<long long>(total, 0x7fffffc0LL), whole = (longest + 63) / 64 * 64, group = d->Hq / d->Hkv;
+  const long long parts = std::max(1, group / 4), lanes = d->Hkv * parts, uncut = d->B * lanes;   // workgroups take up to four query heads
   auto workgroups = [&](int seg_len) {
     long long n = 0;
     for (int i = 0; i < d->B; ++i) n += (seq_start[i + 1] - seq_start[i] + seg_len - 1) / seg_len;
@@ -161,9 +161,19 @@ ChunkPlan varlen_plan(const lawcat_desc* d, const int32_t* seq_start, size_t roo
         best = len;
       }
     }
-    // uncut, there is no state pass, which takes about as long as 128 tokens (32 on 4 of 128, 100 of 50 to 198 tokens, segments of 192 / uncut
-    // 125 / 105 us)
-    return (uncut + slots - 1) / slots * longest <= cost + 128 ? whole : best;
+    // Uncut, there is no state pass, which takes about as long as 128 tokens at head dim 128 (32 on 4, 100 of 50 to 198, segments of 192 / uncut
+    // 125 / 105 us); at 64 as 64 tokens a round (14 of 75 to 127 of 32 heads on 8 17.7 / 13.5, 8 of 59 to 97 of 2 on 1 13.6 / 11.6), or 128 for
+    // long segments (43 of 459 to 651 of 32 on 8 91 / 84) and from about 200 query heads' walks on (8 on 8, 5 of 148 to 172 in 120 segments of 64 tokens /
+    // uncut 0.95 times as fast, 8 of 150 to 185, 192, 0.97, 23 of 26 to 149, 248, 1.12, 14 of 88 to 191, 256, 1.10; 16 on 8, 4 of 22 to 148, 56, 0.92, 9 of 3
+    // to 170, 112, 1.04, 13 of 29 to 158, 176, 1.13; 32 on 8, 2 of 83 to 137, 40, 0.93, 7 of 33 to 153, 104, 1.11, 13 of 89 to 136, 216, 1.22), except where
+    // workgroups for four heads, which walk longest, are few and few sequences are cut (32 on 8, 20 of 2 to 185, 232 / 160, 0.90, 30 of 2 to 179, 328 /
+    // 240, 0.96, but 26 of 21 to 151, 328 / 208, 1.01, 39 of 4 to 187, 432 / 312, 1.15).  Each of a group's launches walks all of it.
+    const long long rounds = (uncut + slots - 1) / slots, now = workgroups(best);
+    if (d->dk == 128) return rounds * longest <= cost + 128 ? whole : best;
+    const GroupCover c = cover_group(group, now / parts), all = cover_group(group, uncut / parts);
+    const bool heavy = c.launches == 1 && all.launches == 1 && (now + slots - 1) / slots == rounds &&
+                       (best >= 320 || (now * std::min(group, 4) >= 200 && (group <= 2 || all.most < 4 || 5 * now >= 8 * uncut || now >= 400)));
+    return all.launches * rounds * whole <= c.launches * cost + rounds * (heavy ? 128 : 64) ? whole : best;
   };
   ChunkPlan p{};
   const ChunkPlan one = make_chunk_plan(1, tokens, d->Hq, d->Hkv, d->dk, d->carry_mode, d->segment, false, SIZE_MAX);

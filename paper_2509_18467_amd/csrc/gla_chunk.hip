@@ -15,6 +15,16 @@ static int fold_most(int heads, int group, int d) {
   return d == 64 ? std::min(chunk::kFoldMost<64> + 1, 9 + heads / 4) : std::min(group < 8 ? chunk::kFoldMost<128> + 1 : 7, 4 + heads / 8);
 }
 
+GroupCover cover_group(int group, long long walks) {
+  const int most = walks * group <= 256 ? 1 : walks * ((group + 1) / 2) <= 256 ? 2 : 4;     // (see launch_gla_chunk)
+  int launches = 0;
+  for (int left = group; left > 0; ++launches) {
+    const int heads = left >= most ? most : (left >= 2 ? 2 : 1);
+    left -= left / heads * heads;
+  }
+  return {most, launches};
+}
+
 ChunkPlan make_chunk_plan(int B, int T, int Hq, int Hkv, int d, int carry_mode, int segment, bool conv, size_t room) {
   ChunkPlan p{};
   const int heads = B * Hkv;
@@ -93,8 +103,7 @@ hipError_t launch_gla_chunk(const ChunkParams& p, hipStream_t stream) {
   const int nseg = p.plan.nseg, heads = p.B * p.Hkv, group = p.Hq / p.Hkv;
   const long long walks = p.seq_start ? (long long)p.Hkv * p.plan.segments : (long long)nseg * heads;
   const bool in_place = chunk::in_place(a);
-  a.most = 4;
-  if (!in_place) a.most = walks * group <= 256 ? 1 : walks * ((group + 1) / 2) <= 256 ? 2 : 4;
+  a.most = in_place ? 4 : cover_group(group, walks).most;
   // With few segments the output pass folds its predecessors' contributions itself instead of waiting for a scan: a launch less,
   // and, with many heads, less traffic, against a walk over the predecessors' slots in each of the output pass's launches (more than
   // one for groups that are no multiple of 4).  Scan / fold, us a call in segments of 128 tokens: of 64, 2 heads, 8 segments 23.3 / 22.6,

@@ -105,6 +105,10 @@ struct ChunkPlan {
 };
 // room: bytes of workspace that there are (one that needs less is chosen where they are fewer than the quickest plan's)
 ChunkPlan make_chunk_plan(int B, int T, int Hq, int Hkv, int d, int carry_mode, int segment, bool conv, size_t room);
+// How the output pass covers a group of query heads for so many walks of all of them (out of place): heads that a workgroup takes at most,
+// and launches.
+struct GroupCover { int most, launches; };
+GroupCover cover_group(int group, long long walks);
 bool chunk_path_supports(int group);  // query heads per kv head the kernel is built for
 
 struct ChunkParams {
