@@ -120,8 +120,13 @@ size_t workspace_bytes_checked(const lawcat_desc* d, int which, size_t room = SI
 // eight waves a workgroup at head dim 128, one round of workgroups.
 ChunkPlan varlen_plan(const lawcat_desc* d, const int32_t* seq_start, size_t room, bool roomy = true) {
   const long long total = seq_start[d->B];
+  long long granules = 0;      // of 64 tokens
   int longest = 1;
-  for (int i = 0; i < d->B; ++i) longest = std::max(longest, (int)(seq_start[i + 1] - seq_start[i]));
+  for (int i = 0; i < d->B; ++i) {
+    const int len = seq_start[i + 1] - seq_start[i];
+    longest = std::max(longest, len);
+    granules += (len + 63) / 64;
+  }
   const int tokens = (int)std::min<long long>(total, 0x7fffffc0LL), whole = (longest + 63) / 64 * 64, group = d->Hq / d->Hkv;
   const long long parts = std::max(1, group / 4), lanes = d->Hkv * parts, uncut = d->B * lanes;   // workgroups take up to four query heads
   auto workgroups = [&](int seg_len) {
@@ -129,8 +134,8 @@ ChunkPlan varlen_plan(const lawcat_desc* d, const int32_t* seq_start, size_t roo
     for (int i = 0; i < d->B; ++i) n += (seq_start[i + 1] - seq_start[i] + seg_len - 1) / seg_len;
     return n * lanes;
   };
-  // Segment length for so many places on the chip, from `len` on.  every: what the workspace may be too small for, too.
-  auto cut = [&](int len, long long slots, bool every) {
+  // Segment length for so many places on the chip, from `len` on.  every: what the workspace may be too small for, too; spill: see there.
+  auto cut = [&](int len, long long slots, bool every, bool spill = true) {
     // every sequence rounds its segment count up: lengthen the segments until the workgroups fit the chip in one
     // round (a few too many would double the time of the pass), or, where a group takes several workgroups, in as many rounds as
     // cost least (a few long sequences among many short ones: 32 of 20 to 1405 tokens, 32 query heads on 4 of 128, one round / two
@@ -154,7 +159,7 @@ ChunkPlan varlen_plan(const lawcat_desc* d, const int32_t* seq_start, size_t roo
     // segments of 2112 / 960 1.43 times as fast, 52 of 84 to 2623 1344 / 768 1.13; 8 on 8 of 128, 57 of 47 to 2893 2048 / 1088 1.34.  Not for segments
     // that the state pass and the fold outweigh (of 64, 32 on 8, 6 of 482 to 858, 128 / 64 tokens 32.6 / 44.4 us, 16 on 8, 47 of 109 to 682, 448 / 256 55.2 / 60.8),
     // nor in the place of uncut sequences, which have no state pass (32 on 32 of 128, 17 of 35 to 474, uncut / 384 79.9 / 104.8).
-    for (len = std::max(first, d->dk == 64 ? 512 : 192); d->B > 1 && d->B <= 64 && len < best && len * 5LL / 3 < cost; len += 64) {
+    for (len = std::max(first, d->dk == 64 ? 512 : 192); spill && d->B > 1 && d->B <= 64 && len < best && len * 5LL / 3 < cost; len += 64) {
       const long long n = workgroups(len);
       if (n > slots && 3 * n <= 4 * slots) {
         cost = len * 5LL / 3;
@@ -190,11 +195,36 @@ ChunkPlan varlen_plan(const lawcat_desc* d, const int32_t* seq_start, size_t roo
         p.wide = four.wide && four.seg_len >= 320;
         if (p.wide) p.seg_len = cut(four.seg_len, 512, true);
       } else {
-        // Where even uncut sequences are an eighth more workgroups than units, which one a unit takes in two rounds: 40 of 16 to 1244 130 / 111, 48 of
-        // 200 to 299 119 / 93; 32 on 4, 40 of 30 to 264 63 / 58.
-        const long long most = (512 + lanes - 1) / lanes;
-        p.wide = 1;
-        p.seg_len = cut((int)std::max<long long>(128, ((tokens + most - 1) / most + 63) / 64 * 64), 512, true);
+        // Where even uncut sequences are an eighth more workgroups than units, eight waves leave the sequences whole, and take as long as the longest
+        // one, or as a unit's share of all (only groups of eight and more cut them there, in several rounds, and are slower always, 44 of 22 to 202
+        // tokens of 32 on 4 71 / 64).  Four waves cut them if that makes the longest walk enough shorter, with the state pass as 128 tokens more.
+        // One or two heads a group, for which the state pass is as much work as the output pass, to 5/8: 47 of 28 to 1002 of 8 on 8 104 / 96 (to 3/4, 73 of 5
+        // to 1082 of 4 on 4, 117 / 149); where a unit's share is two thirds of the longest walk, which then is more than that with eight waves, to 3/4 and
+        // 5/6, 24 of 62 to 669 of 16 on 16 85 / 86, 57 of 385 to 1812 of 16 on 8 409 / 303, but 42 of 327 to 871 of 8 on 8 to 0.79 134 / 142.  More heads to 5/6, 40
+        // of 66 to 395 88 / 84 (to 7/8, 60 of 10 to 485, 97 / 121; in two launches to 2/3, 40 of 13 to 343 of 40 on 8 137 / 117, to 5/6, 27 of 9 to 342 of 48 on 16
+        // 96 / 103), and to 15/16, 46 of 390 to 980 318 / 235.  To half if it takes more than a round of
+        // them, 57 of 47 to 2893 of 8 on 8 379 / 254, 60 of 10 to 485, 5/8, 64 / 77; not where few sequences of many heads share the units evenly, 13 of 213
+        // to 1909 of 32 on 32 232 / 247.
+        // Or they leave them whole, too, where the share is most of the longest walk, which alone is a third quicker with eight waves: 48 of 250
+        // 104 / 84; share 0.68, 72 of 21 to 621 of 40 on 8 236 / 257, more than a round of both, 0.77, 40 of 13 to 543 of 64 on 16 146 / 152; two heads a group,
+        // whose workgroups gain less, 0.81, 25 of 66 to 461 of 32 on 16 100 / 95; one, 0.91, 55 of 61 to 269 of 8 on 8 57 / 51, 0.94, 62 of 80 to 550 88 / 91, 0.76,
+        // 58 of 80 to 898 131 / 146; up to 128 tokens 0.72, 38 of 9 to 95 of 16 on 8 33 / 30, 0.66, 38 of 1 to 98 of 8 on 8 23 / 27; few sequences of many
+        // heads 0.90, 13 of 96 to 571 of 32 on 32 77 / 92.
+        const long long most = (512 + lanes - 1) / lanes, share = granules * lanes, walk = 256LL * (whole / 64);
+        const int start = (int)std::max<long long>(128, ((tokens + most - 1) / most + 63) / 64 * 64);
+        if (parts > 1 && uncut <= 512) {
+          p.wide = 1;
+          p.seg_len = cut(start, 512, true);
+        } else {
+          const bool small = 3 * share < 2 * walk;
+          int len = uncut > 512 ? whole : cut(start, 512, true, small);
+          if (len < whole && workgroups(len) > 512 && 2 * (len + 128LL) > whole) len = cut(start, 512, true, false);
+          const int limit = small ? (group <= 2 ? 30 : group % 4 ? 32 : 40) : group == 1 ? 36 : group == 2 ? 40 : 45;      // forty-eighths
+          const bool shorter = len < whole && (small || lanes < 32) && 48 * (len + 128LL) <= (long long)limit * whole;
+          const int sixteenths = lanes >= 32 ? 16 : whole <= 128 ? 13 - std::min(group, 3) : uncut > 512 ? 14 : 15 - std::min(group, 3);
+          p.wide = shorter || 16 * share >= sixteenths * walk;
+          p.seg_len = shorter ? len : whole;
+        }
       }
     }
     if (!p.wide) p.seg_len = cut(one.seg_len, d->dk == 64 ? 512 : 256, roomy && d->dk == 64);

@@ -50,3 +50,38 @@ def test_more_than_a_round(directory, Hq, Hkv, lengths, segments):
     (20, 4, spread(27, 35, 192), 3), (32, 8, spread(43, 459, 651), 1)])
 def test_uncut(directory, Hq, Hkv, lengths, segments):
     assert plan(directory, 64, Hq, Hkv, lengths) == (segments, 4)
+
+
+# Head dim 128, more uncut workgroups than units: four waves a workgroup where they make the longest walk enough shorter, or have enough work
+@pytest.mark.parametrize("Hq,Hkv,lengths,segments,waves", [
+    # no more than an eighth more
+    (32, 8, [250] * 36, 1, 8), (32, 8, [250] * 37, 1, 4), (32, 8, [250] * 48, 1, 4),
+    # cut: one and two heads a group, four, three in two launches; more than a round of them; few sequences of many heads; groups of eight
+    (8, 8, spread(47, 28, 1002), 3, 4), (4, 4, spread(88, 22, 288), 1, 8), (8, 8, spread(42, 327, 871), 1, 8), (32, 8, spread(40, 66, 395), 3, 4),
+    (32, 8, spread(46, 390, 980), 2, 4), (24, 8, spread(39, 217, 662), 2, 4), (48, 16, spread(27, 9, 342), 1, 8), (8, 8, spread(57, 47, 2893), 4, 4),
+    (8, 8, spread(60, 10, 485), 1, 8), (32, 32, spread(13, 213, 1909), 1, 8), (32, 4, spread(44, 8, 1000), 4, 4),
+    # uncut: by a unit's share
+    (8, 8, spread(70, 4, 760), 1, 8), (40, 8, spread(72, 21, 621), 1, 8), (64, 16, spread(40, 13, 543), 1, 8), (64, 16, [250] * 40, 1, 4),
+    (64, 8, spread(36, 39, 345), 1, 4), (16, 8, spread(57, 385, 1812), 1, 4), (8, 8, spread(58, 80, 898), 1, 8), (8, 8, spread(55, 61, 269), 1, 4),
+    (16, 8, spread(38, 9, 95), 1, 4), (8, 8, spread(38, 1, 98), 1, 8), (32, 32, spread(13, 96, 571), 1, 8), (32, 32, [571] * 13, 1, 4)])
+def test_four_waves(directory, Hq, Hkv, lengths, segments, waves):
+    assert plan(directory, 128, Hq, Hkv, lengths) == (segments, waves)
+
+
+# A workspace too small for the quickest plan takes the one that needs least: its segments of the longest sequence, and its launches
+@pytest.mark.parametrize("d,Hq,Hkv,lengths,segments,launches", [
+    (128, 32, 8, spread(24, 100, 3269), 3, [(328, 1, 1, 512)] * 2), (128, 8, 8, spread(57, 47, 2893), 0, [(1, 456, 1, 512)]),
+    (64, 16, 8, spread(58, 128, 2923), 2, [(664, 1, 1, 256)] * 2)])
+def test_least_plan(directory, d, Hq, Hkv, lengths, segments, launches):
+    starts = [0]
+    for n in lengths:
+        starts.append(starts[-1] + n)
+    desc = lawcat.make_desc(len(lengths), max(lengths), Hq, Hkv, d)
+    slot = len(lengths) * Hkv * ((d * d + 2 * d) * 4 + 4)
+    need = lawcat.varlen_workspace_bytes(desc, starts, True)
+    assert need > segments * slot
+    quick, short, least, null, less = L.run([L.packed(desc, starts, L.AT, room) for room in (need, need - 1, segments * slot)] +
+                                            [L.packed(desc, starts, L.NULL, need), L.packed(desc, starts, L.AT, max(0, segments * slot - 1))], directory)
+    assert quick[0] == 0 and quick[1] != launches
+    assert short == least == (0, launches)
+    assert (null == less == (-4, [])) if segments else (null == less == (0, launches))
