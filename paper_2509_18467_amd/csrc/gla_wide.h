@@ -61,7 +61,7 @@ __global__ void __launch_bounds__(256, 2) gla_wide_kernel(const ChunkArgs a) {
   else
     for (int j = tid; j < nseg - 1; j += G::TEAM) live_any |= a.seg_live[slot0 + j];
   constexpr int kZd = (kFoldMost<D> * 2 * D + G::TEAM - 1) / G::TEAM;
-  static_assert(kFoldMost<D> * 2 * D * 4 <= G::kPs);
+  static_assert(kFoldMost<D> * 2 * D * 4 <= G::kWl);      // (the conv weights there are written before)
   float zraw[kZd];
   if (a.fold) {
 #pragma unroll
