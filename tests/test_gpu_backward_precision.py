@@ -116,3 +116,40 @@ def test_gradients(oracle, d, G, gate_scale, dtype):
         print(f"  {n}: {err[0]:.3e}, token by token {err[1]:.3e}", flush=True)
         # the norm of thousands of independent errors: known to one percent
         assert err[0] <= 1.02 * err[1], n
+
+
+@pytest.mark.parametrize("gate_scale", [1.0, 0.0625])
+@pytest.mark.parametrize("G", [2, 4, 8])
+def test_stored_gradients(oracle, G, gate_scale):
+    """bf16 storage, head dim 64, where products of two fp32 operands go through bf16 MFMAs as three terms each: how many of the stored
+    gradients differ from the rounded exact ones, which is in proportion to the mean error before their rounding."""
+    d = 64
+    wl = Workload("stored", B=16, T=170, Hq=2 * G, Hkv=2, d=d, dtype="bf16")
+    print("stored gradients", wl, gate_scale, flush=True)
+    rng = np.random.default_rng(73)
+
+    def store(a):
+        return H.host(H.dev(a.astype(np.float32), torch.bfloat16)).astype(np.float32)
+
+    def phi(a):
+        return np.where(a > 0, 1 + a, np.exp(np.minimum(a, 0)))
+
+    q, k = (store(phi(rng.standard_normal((wl.B, wl.T, h, d)) * 0.125)) for h in (wl.Hq, 2))
+    v, g, dO = (store(rng.standard_normal((wl.B, wl.T, h, d)) * s) for h, s in ((2, 0.125), (2, 1.0), (wl.Hq, 0.5)))
+    S0 = (rng.standard_normal((wl.B, 2, d, d)) * 0.25).astype(np.float32)
+    z0 = (np.abs(rng.standard_normal((wl.B, 2, d)) * 2) + 4).astype(np.float32)
+    den = oracle.gla_prefill(q, k, v, g, gate_scale, 0.0, S0, z0)["den"].astype(np.float32)
+    ref = oracle.gla_backward(q, k, v, g, dO, gate_scale, 0.0, S0, z0)
+    ins = [H.dev(a, torch.bfloat16) for a in (q, k, v, g)]
+    outs = [torch.empty_like(t) for t in ins]
+    desc = H.desc_for(wl, gate_scale=gate_scale)
+    lawcat.gla_backward(desc, *ins, H.dev(den), H.dev(dO, torch.bfloat16), H.dev(S0), H.dev(z0), *outs, None, None,
+                        lawcat.alloc_workspace(desc, lawcat.CALL_GLA_BACKWARD))
+    torch.cuda.synchronize()
+    rec = _token_by_token(*(H.dev(a) for a in (q, k, v, g, dO, den)), gate_scale, H.dev(S0), H.dev(z0))
+    for n, t in zip(("dq", "dk", "dv", "dg"), outs):
+        exact = store(ref[n])
+        wrong = [int((H.host(a) != exact).sum()) for a in (t, rec[n].to(torch.bfloat16))]
+        print(f"  {n}: {wrong[0]} of {exact.size} differ, token by token {wrong[1]}", flush=True)
+        # counts of independent events: known to their square roots, four of which are allowed
+        assert wrong[0] <= wrong[1] + 4 * (wrong[0] + wrong[1]) ** 0.5, n

@@ -61,6 +61,28 @@ def test_repeated_calls_are_bit_identical(d, group, mode):
                               f"{int((_bits(cur[name]) != _bits(first[name])).sum())} elements")
 
 
+@pytest.mark.parametrize("B,Hkv,group,T", [(1, 8, 8, 16500), (8, 8, 4, 2050), (16, 32, 2, 290), (16, 32, 1, 530)])
+@pytest.mark.parametrize("feature_map", [0, 1])
+def test_four_wave_form_is_bit_identical(B, Hkv, group, T, feature_map):
+    """Head dim 128, two workgroups of four waves a compute unit, which hand parts of scores, keys, the normalizer and denominators to each
+    other through LDS: four, two and one heads a workgroup, with a state pass and without, several workgroups per unit."""
+    wl = Workload("det_wide", B=B, T=T, Hq=Hkv * group, Hkv=Hkv, d=128)
+    x = make_inputs(wl, seed=7, state=True, halo=True)
+    Q, K, V, G, wq, wk, qh, kh = (H.dev(x[n], torch.bfloat16) for n in ("Q", "K", "V", "G", "wq", "wk", "q_halo", "k_halo"))
+    S0, z0 = H.dev(x["S0"]), H.dev(x["z0"])
+    desc = H.desc_for(wl, feature_map=feature_map)
+    ws = lawcat.alloc_workspace(desc, lawcat.CALL_LAYER_PREFILL)
+    first = None
+    for it in range(RUNS):
+        cur = {"o": torch.empty_like(Q), "den": torch.empty(B, T, wl.Hq, device="cuda"), "S": torch.empty_like(S0), "z": torch.empty_like(z0)}
+        ws.fill_(0xFF)     # NaN patterns: nothing is read before it is written
+        lawcat.layer_prefill(desc, Q, K, V, G, wq, wk, S0, z0, qh, kh, cur["o"], cur["den"], cur["S"], cur["z"], None, None, ws)
+        torch.cuda.synchronize()
+        first = first or cur
+        for name in cur:
+            assert torch.equal(_bits(cur[name]), _bits(first[name])), f"{wl}: {name} of call {it} differs from call 0"
+
+
 @pytest.mark.parametrize("d", [64, 128])
 def test_matrix_core_side_kernels_are_bit_identical(d):
     """The conv + feature-matrix kernel and the gate projection reduce in a fixed order too (the gate projection

@@ -57,6 +57,30 @@ def test_wide(oracle, B, Hkv, group, T, W, gate_scale, nseg):
     check(oracle, wl, x, run(wl, x, gate_scale, nseg=nseg), gate_scale)
 
 
+@pytest.mark.parametrize("group,Hkv,T", [(8, 4, 1057), (2, 32, 290), (1, 32, 530)])
+@pytest.mark.parametrize("W", [4, 1])
+def test_identity_map_from_nothing(oracle, group, Hkv, T, W):
+    """No feature map (positive queries and keys), no start state and no rows before the first token; one tap as well."""
+    wl = Workload("wide", 8 if group == 8 else 16, T, Hkv * group, Hkv, 128, W, "bf16")
+    x = make_inputs(wl, seed=96)
+    for n in ("Q", "K", "wq", "wk"):
+        x[n] = np.abs(x[n])
+    print("wide, identity map", wl, flush=True)
+    D = H.desc_for(wl, feature_map=0, gate_scale=0.5)
+    Q, K, V, G, wq, wk = (H.dev(x[n], torch.bfloat16) for n in ("Q", "K", "V", "G", "wq", "wk"))
+    O, den = torch.full_like(Q, float("nan")), torch.full((wl.B, wl.T, wl.Hq), float("nan"), device="cuda")
+    S, z = torch.full((wl.B, Hkv, 128, 128), float("nan"), device="cuda"), torch.full((wl.B, Hkv, 128), float("nan"), device="cuda")
+    lawcat.layer_prefill(D, Q, K, V, G, wq, wk, None, None, None, None, O, den, S, z, None, None, lawcat.alloc_workspace(D, lawcat.CALL_LAYER_PREFILL))
+    torch.cuda.synchronize()
+    ref = oracle.layer_prefill(x["Q"], x["K"], x["V"], x["G"], x["wq"], x["wk"], 0, 0.5, 0.0)
+    # Keys are products with a channel's weights, several times the RMS in some channels: beside the bar a half-ulp of bf16 on one factor of
+    # each product, which sums up to that of the sum of their absolute values (that of S is the state of |V|; o is a mean of values, den and z add
+    # positive terms up)
+    terms = {"S": oracle.layer_prefill(x["Q"], x["K"], np.abs(x["V"]), x["G"], x["wq"], x["wk"], 0, 0.5, 0.0)["S"]}
+    for n, t in (("o", O), ("den", den), ("S", S), ("z", z)):
+        H.assert_close(H.host(t), ref[n], wl, n, 1, terms.get(n))
+
+
 @pytest.mark.parametrize("inplace", [False, True])
 def test_closing_gates(oracle, inplace):
     """Channels that close in the middle of a chunk and of a segment, and stay open elsewhere."""
@@ -83,13 +107,14 @@ def test_least_workspace(oracle):
 MIXED = (1, 15, 16, 17, 31, 32, 33, 64, 700, 65, 95, 96, 97, 129, 300, 257) * 3
 
 
-@pytest.mark.parametrize("Hkv,group,lengths,nseg,inplace", [
+# short: what becomes of a workspace a little too small; None where none is needed
+@pytest.mark.parametrize("Hkv,group,lengths,nseg,inplace,short", [
     # more than an eighth more sequences than units: by length, longest first; uncut, a grid by sequences; more than 64
-    (8, 4, MIXED, 4, False), (8, 4, MIXED, 4, True), (32, 1, MIXED, 1, False), (4, 8, (97, 130, 700) * 14, 2, False), (4, 8, (97, 40, 130, 5) * 25, 1, False),
+    (8, 4, MIXED, 4, False, "taken"), (8, 4, MIXED, 4, True, "taken"), (32, 1, MIXED, 1, False, None), (4, 8, (97, 130, 700) * 14, 2, False, "refused"),
+    (4, 8, (97, 40, 130, 5) * 25, 1, False, None),
     # a few long ones: folded, and scanned in place
-    (32, 1, (5000, 700, 3600), 8, False), (32, 1, (5000, 700, 3600), 8, True)])
-@pytest.mark.parametrize("least", [False, True])
-def test_packed(oracle, Hkv, group, lengths, nseg, inplace, least):
+    (32, 1, (5000, 700, 3600), 8, False, "taken"), (32, 1, (5000, 700, 3600), 8, True, "taken")])
+def test_packed(oracle, Hkv, group, lengths, nseg, inplace, short):
     B, starts = len(lengths), np.concatenate([[0], np.cumsum(lengths)]).astype(np.int32)
     wl = Workload("wide", 1, int(starts[-1]), Hkv * group, Hkv, 128, 4, "bf16")
     x = make_inputs(wl, seed=94)
@@ -97,36 +122,39 @@ def test_packed(oracle, Hkv, group, lengths, nseg, inplace, least):
     D = lawcat.make_desc(B, max(lengths), wl.Hq, Hkv, 128, feature_map=1, gate_scale=0.5)
     need = lawcat.varlen_workspace_bytes(D, starts, True)
     assert need == (B * Hkv * nseg * SLOT if nseg > 1 else 0)
-    print("wide packed", wl, B, inplace, least, flush=True)
+    print("wide packed", wl, B, inplace, flush=True)
     Q, K, V, G, wq, wk = (H.dev(x[n], torch.bfloat16) for n in ("Q", "K", "V", "G", "wq", "wk"))
-    qh, kh, S0, z0 = H.dev(ext["q_halo"], torch.bfloat16), H.dev(ext["k_halo"], torch.bfloat16), H.dev(ext["S0"]), H.dev(ext["z0"])
-    O, qt, kt = (torch.full_like(t, float("nan")) for t in (Q, qh, kh))
-    S, z = (S0, z0) if inplace else (torch.full_like(S0, float("nan")), torch.full_like(z0, float("nan")))
-    den = torch.full((wl.T, wl.Hq), float("nan"), device="cuda")
+    qh, kh = H.dev(ext["q_halo"], torch.bfloat16), H.dev(ext["k_halo"], torch.bfloat16)
 
     def call(room):
+        S0, z0 = H.dev(ext["S0"]), H.dev(ext["z0"])
+        O, qt, kt = (torch.full_like(t, float("nan")) for t in (Q, qh, kh))
+        S, z = (S0, z0) if inplace else (torch.full_like(S0, float("nan")), torch.full_like(z0, float("nan")))
+        den = torch.full((wl.T, wl.Hq), float("nan"), device="cuda")
         ws = torch.full((max(room, 16) + 256,), 0x5A, dtype=torch.uint8, device="cuda")
         lawcat.layer_prefill_varlen(D, starts, Q, K, V, G, wq, wk, S0, z0, qh, kh, O, den, S, z, qt, kt, ws[:max(room, 16)],
                                     seq_start_dev=torch.from_numpy(starts).cuda())
         torch.cuda.synchronize()
         assert bool((ws[max(room, 16):] == 0x5A).all())
+        return {"o": H.host(O)[0], "den": H.host(den), "S": H.host(S), "z": H.host(z), "q_tail": H.host(qt), "k_tail": H.host(kt)}
 
-    if least and need > 0:
-        # a little less than the size it asks for: what the eight-wave form needs, if that is less, or an error
-        try:
+    calls = [call(need)]
+    if short == "taken":        # what the eight-wave form needs is less
+        calls.append(call(need - 16))
+        assert not np.array_equal(calls[0]["o"], calls[1]["o"])      # (the other form, which rounds elsewhere)
+    elif short == "refused":
+        with pytest.raises(lawcat.LawcatError):
             call(need - 16)
-        except lawcat.LawcatError:
-            return
     else:
-        call(need)
-    got = {"o": H.host(O)[0], "den": H.host(den), "S": H.host(S), "z": H.host(z)}
+        assert need == 0
     for i, (a, b) in enumerate(zip(starts[:-1], starts[1:])):
         if B > 20 and i % 5 and i != B - 1 and lengths[i] != 700:      # (the oracle's time)
             continue
         ref = oracle.layer_prefill(x["Q"][:, a:b], x["K"][:, a:b], x["V"][:, a:b], x["G"][:, a:b], x["wq"], x["wk"], 1, 0.5, 0.0,
                                    ext["S0"][i:i + 1], ext["z0"][i:i + 1], ext["q_halo"][i:i + 1], ext["k_halo"][i:i + 1])
-        for n in got:
-            # (a few tokens are too few for an RMS: a half-ulp of the stored value beside it)
-            H.assert_close((got[n][a:b] if n in ("o", "den") else got[n][i])[None], ref[n], wl, f"sequence {i} of {B - 1} {n}", 1 if n == "o" else 0)
-        for tail, raw, halo in ((qt, "Q", "q_halo"), (kt, "K", "k_halo")):
-            assert np.array_equal(H.host(tail[i]), np.concatenate([ext[halo][i], x[raw][0, a:b]])[-3:].astype(np.float64)), i
+        for got in calls:
+            for n in ("o", "den", "S", "z"):
+                # (a few tokens are too few for an RMS: a half-ulp of the stored value beside it)
+                H.assert_close((got[n][a:b] if n in ("o", "den") else got[n][i])[None], ref[n], wl, f"sequence {i} of {B - 1} {n}", 1 if n == "o" else 0)
+            for tail, raw, halo in (("q_tail", "Q", "q_halo"), ("k_tail", "K", "k_halo")):
+                assert np.array_equal(got[tail][i], np.concatenate([ext[halo][i], x[raw][0, a:b]])[-3:].astype(np.float64)), i
