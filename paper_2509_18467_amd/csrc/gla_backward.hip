@@ -231,8 +231,8 @@ struct Sweep {
   // bf16 storage, reverse: products of two fp32 operands, too, go through the matrix cores as bf16 terms (mfma_terms(), 192 cycles
   // where fp32 MFMAs take 512): q E / den is split once, for the update of R~, dk and the scores, R~ for dk and dv, a head's dO . v by the
   // wave that forms it.  The matrix cores are busy for 1184 cycles a wave and chunk instead of 2144, 32768 tokens of 32 / 8 heads of 64, the
-  // training pass, 649 -> 638 us, 9001 of 16 / 8 heads 217.3 -> 210.4; bf16 results that differ from rounded exact ones: dk 0.89, dv 0.72,
-  // dg 0.96 times as many.  Head dim 128, whose terms do not fit the LDS (dk alone: 389 -> 395 us for 6000 tokens, registers), and one query
+  // training pass, 649 -> 638 us, 9001 of 16 / 8 heads 217.3 -> 210.4; bf16 results that differ from rounded exact ones, 3001 to
+  // 65536 tokens of 32 / 8, 16 / 8 and 32 / 4 heads, N(0, 1) and slow gates: dk 0.75 to 0.97, dv 0.58 to 0.77, dg 0.80 to 0.97 times as many.  Head dim 128, whose terms do not fit the LDS (dk alone: 389 -> 395 us for 6000 tokens, registers), and one query
   // head a pass (three workgroups a compute unit) keep fp32 MFMAs.
   static constexpr bool kScoreTerms = kDaOnce && D == 64;
   static constexpr int kDaWave = NW >= 2 * HB ? HB : 0;           // the first of these waves, after those with the scores where there are
@@ -911,7 +911,7 @@ __device__ __forceinline__ void reverse_sweep(const BwdArgs& a) {
       dvw = kZero64;
       if constexpr (L::kScoreTerms) {
         dv0 = mfma_terms(terms_frag(sm + L::rK, D * 32, g, n, 0), state_terms_frag(sm + L::rR, D * D * 2, g, n, w, 0),
-                         terms_frag(sm + L::rK, D * 32, g, n, 1), state_terms_frag(sm + L::rR, D * D * 2, g, n, w, 1), dv0);
+                         terms_frag(sm + L::rK, D * 32, g, n, 1), state_terms_frag(sm + L::rR, D * D * 2, g, n, w, 1));
       } else
 #pragma unroll
       for (int ct = 0; ct < D / 16; ++ct) {
@@ -939,7 +939,7 @@ __device__ __forceinline__ void reverse_sweep(const BwdArgs& a) {
         floatx4 sc = {0.f, 0.f, 0.f, 0.f};       // [s][`row`]
         if constexpr (L::kScoreTerms) {
           sc = mfma_terms(terms_frag(sm + L::rQ + w * L::kTerms, D * 32, g, n, 0), terms_frag(sm + L::rK, D * 32, g, n, 0),
-                          terms_frag(sm + L::rQ + w * L::kTerms, D * 32, g, n, 1), terms_frag(sm + L::rK, D * 32, g, n, 1), sc);
+                          terms_frag(sm + L::rQ + w * L::kTerms, D * 32, g, n, 1), terms_frag(sm + L::rK, D * 32, g, n, 1));
 #pragma unroll
           for (int i = 0; i < 4; ++i) sc[i] = row <= 4 * g + i ? sc[i] : 0.f;
         } else {
@@ -1028,10 +1028,9 @@ __device__ __forceinline__ void reverse_sweep(const BwdArgs& a) {
       auto term = [&](int h, int k) { return *reinterpret_cast<const uint2*>(das + h * L::kDa + k * 512 + l * 8); };
       auto da = [&](int h) { return Terms{make8(term(h, 0), term(h + 1, 0)), make8(term(h, 1), term(h + 1, 1)), make8(term(h, 2), term(h + 1, 2))}; };
       if constexpr (HB == 4) {
-        dk = mfma_terms(da(0), pair_terms(qs[0], qs[1]), da(2), pair_terms(qs[2], qs[3]), dk);
+        dk += mfma_terms(da(0), pair_terms(qs[0], qs[1]), da(2), pair_terms(qs[2], qs[3]));
       } else {
-        const Terms a0 = da(0), q0 = pair_terms(qs[0], qs[1]);
-        dk = mfma_bf16(a0.t0, q0.t0, mfma_small_terms(a0, q0, dk));
+        dk += mfma_terms(da(0), pair_terms(qs[0], qs[1]));
       }
     } else if constexpr (L::kDaOnce) {
 #pragma unroll

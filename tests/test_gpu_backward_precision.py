@@ -153,3 +153,38 @@ def test_stored_gradients(oracle, G, gate_scale):
         print(f"  {n}: {wrong[0]} of {exact.size} differ, token by token {wrong[1]}", flush=True)
         # counts of independent events: known to their square roots, four of which are allowed
         assert wrong[0] <= wrong[1] + 4 * (wrong[0] + wrong[1]) ** 0.5, n
+
+
+@pytest.mark.parametrize("Hq,Hkv,T,gate_scale", [(32, 8, 1500, 1.0), (16, 8, 512, 1.0), (32, 4, 300, 1.0), (8, 8, 203, 1.0), (32, 8, 512, 0.25)])
+def test_gate_gradient_adds_up(Hq, Hkv, T, gate_scale):
+    """From no state the first token's gate changes nothing: its gradient, a sum over all tokens, is exactly 0.  What is left of it is the sum's
+    error, which no rounding of the stored value hides; token by token, without a bias, it grows with the root of the length."""
+    B, d = 64, 64
+    wl = Workload("adds_up", B=B, T=T, Hq=Hq, Hkv=Hkv, d=d, dtype="bf16")
+    print("adds up", wl, gate_scale, flush=True)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(74)
+
+    def normal(scale, heads):
+        return torch.randn((B, T, heads, d), generator=gen, device="cuda") * scale
+
+    def phi(a):
+        return torch.where(a > 0, 1 + a, torch.exp(a.clamp(max=0)))
+
+    q, k = phi(normal(0.125, Hq)).bfloat16(), phi(normal(0.125, Hkv)).bfloat16()
+    v, g, dO = normal(0.125, Hkv).bfloat16(), normal(1.0, Hkv).bfloat16(), normal(0.5, Hq).bfloat16()
+    al = torch.exp(gate_scale * torch.nn.functional.logsigmoid(g.double()))
+    z, den = torch.zeros_like(al[:, 0]), torch.empty(B, T, Hq, device="cuda")
+    for t in range(T):
+        z = z * al[:, t] + k[:, t].double()
+        den[:, t] = (q[:, t].double().reshape(B, Hkv, -1, d) * z[:, :, None]).sum(-1).reshape(B, Hq)
+    outs = [torch.empty_like(x) for x in (q, k, v, g)]
+    desc = H.desc_for(wl, gate_scale=gate_scale)
+    lawcat.gla_backward(desc, q, k, v, g, den, dO, None, None, *outs, None, None, lawcat.alloc_workspace(desc, lawcat.CALL_GLA_BACKWARD))
+    torch.cuda.synchronize()
+    zero = torch.zeros(B, Hkv, d, d, device="cuda")
+    rec = _token_by_token(*(x.float() for x in (q, k, v, g, dO)), den, gate_scale, zero, zero[..., 0])
+    err = [x[:, 0].double().pow(2).mean().sqrt().item() for x in (outs[3], rec["dg"])]
+    print(f"  first token's dg {err[0]:.3e}, token by token {err[1]:.3e}", flush=True)
+    # the RMS of 16 thousand values and more, those of a head alike: known to a few percent
+    assert err[0] <= 1.05 * err[1]
