@@ -54,7 +54,7 @@ constexpr int kGroup = 4;   // rows fetched together, one group ahead of the ari
 
 // grid (ceil(row / (1024 / NSUB)), strips, B), 256 threads = 256 / NSUB groups of four channels x NSUB runs of a strip's tokens;
 // row = H * d channels of a token.
-// WHOLE (up to four strips in all): grid (ceil(row / 32)), 512 threads = 8 groups of four channels x all strips' runs of 4 tokens; `partial` is
+// WHOLE (up to four strips in all, as launch_phi() says): grid (ceil(row / 32)), 512 threads = 8 groups of four channels x all strips' runs of 4 tokens; `partial` is
 // dw itself, added up in the order of the two kernels (the same bits).  A second launch for so few sums took as long as the first:
 // 100 tokens of two heads, fp32, the training pass 83.3 -> 79.7 us, 256 96.0 -> 94.3; 200 of 32 / 8, bf16, 80.7 -> 79.4.  For more strips a
 // workgroup's columns are too narrow for its 512 threads: 8 strips, 500 tokens of 4 / 2 125.0 / 126.8, 16, 1000 of 32 / 8 98.3 / 117.6.
@@ -292,7 +292,10 @@ hipError_t launch_phi(const ConvBackwardParams& p, hipStream_t stream) {
   // whole strip, where that fills the chip: short sequences leave most runs empty (256 sequences, 2048 channels, bf16, 17 and 32
   // tokens 19.6 and 30.2 us, in runs of 16 26.1 and 33.4; from 64 on the same).
   const long long work = (long long)row * n_partial;
-  if (p.T > 4 && n_partial > 1 && n_partial <= 4 && work < 96 * 1024) {
+  // One launch as long as its workgroups find a place at once: one a compute unit with three taps or four, two with one or two.  us, two
+  // launches / one: 8192 channels, 4 taps, 250 tokens 8.5 / 7.1, 9216 9.7 / 11.9, 24576, 128 tokens 10.1 / 15.8; 16384, 2 taps, 250 tokens 8.9 / 8.7,
+  // 24576, 190 tokens 9.8 / 12.4.
+  if (p.T > 4 && n_partial > 1 && n_partial <= 4 && work < 96 * 1024 && row <= (W <= 2 ? 16384 : 8192)) {
     hipLaunchKernelGGL((conv_bwd_kernel<T, W, PHI, 16, true>), dim3((row / 4 + 7) / 8), dim3(512), 0, stream, (const T*)p.x, (const T*)p.w,
                        (const T*)p.halo, (const T*)p.dy, (T*)p.dx, (T*)p.dhalo, p.dw, p.T, row, strips, n_partial);
     return hipGetLastError();

@@ -57,6 +57,11 @@ def packed(d, starts, workspace, room, one_launch=True):
                                            NULL, NULL, workspace, size(room), NULL]
 
 
+def conv_adjoint(d, heads, workspace, room):
+    """Arguments of lawcat_conv1d_backward"""
+    return "lawcat_conv1d_backward", [desc(d), ("pointer", heads), AT, AT, NULL, AT, AT, AT, NULL, workspace, size(room), NULL]
+
+
 def run(calls, directory):
     """[(status, [(grid x, grid y, grid z, threads)])] of the calls"""
     recorder = os.path.join(directory, "launch_recorder.so")

@@ -34,3 +34,14 @@ def test_static_scratch_has_room_for_the_same_plan(directory, d, Hq, Hkv, B, T):
     desc = lawcat.make_desc(B, T, Hq, Hkv, d)
     static, prefill = L.run([L.static(desc), L.prefill(desc, L.AT, lawcat.workspace_bytes(desc, lawcat.CALL_LAYER_PREFILL))], directory)
     assert static == prefill and static[0] == 0 and len(static[1]) >= 2
+
+
+@pytest.mark.parametrize("heads,d,B,T,W,one", [
+    # as many workgroups as compute units with three taps or four, twice as many with fewer
+    (64, 128, 1, 128, 4, True), (65, 128, 1, 128, 4, False), (128, 64, 2, 33, 3, True), (96, 128, 4, 30, 3, False),
+    (128, 128, 4, 20, 2, True), (129, 128, 1, 128, 2, False), (128, 128, 3, 50, 1, True), (192, 128, 3, 50, 1, False)])
+def test_conv_adjoint_in_one_launch(directory, heads, d, B, T, W, one):
+    desc = lawcat.make_desc(B, T, heads, heads, d, conv_width=W)
+    (status, launches), = L.run([L.conv_adjoint(desc, heads, L.AT, 1 << 30)], directory)
+    assert status == 0 and len(launches) == (1 if one else 2)
+    assert not one or launches == [(heads * d // 32, 1, 1, 512)]
