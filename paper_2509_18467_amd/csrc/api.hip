@@ -134,6 +134,16 @@ ChunkPlan varlen_plan(const lawcat_desc* d, const int32_t* seq_start, size_t roo
     for (int i = 0; i < d->B; ++i) n += (seq_start[i + 1] - seq_start[i] + seg_len - 1) / seg_len;
     return n * lanes;
   };
+  // the shortest segments from `len` on (a multiple of 64) that are so few workgroups; whole sequences if none are.  (They never get more with the
+  // length: by steps that double, then by halves.  One length after the other, 64 sequences of 100 to 131072 tokens of 32 heads on 8 of 128 took the
+  // host 299 us instead of 7.)
+  auto shortest = [&](int len, long long most) {
+    int too_many = len / 64 - 1, enough = whole / 64;
+    auto look = [&](int at) { return (workgroups(at * 64) <= most ? enough : too_many) = at; };
+    for (int step = 1; too_many + step < enough; step *= 2) look(too_many + step);
+    while (enough - too_many > 1) look((too_many + enough) / 2);
+    return enough * 64;
+  };
   // Segment length for so many places on the chip, from `len` on.  every: what the workspace may be too small for, too; spill: see there.
   auto cut = [&](int len, long long slots, bool every, bool spill = true) {
     // every sequence rounds its segment count up: lengthen the segments until the workgroups fit the chip in one
@@ -144,10 +154,8 @@ ChunkPlan varlen_plan(const lawcat_desc* d, const int32_t* seq_start, size_t roo
     const int first = len = std::min(len, whole);
     int best = len;
     for (long long most = parts; most >= 1; --most) {
-      for (;; len += 64) {
-        r = (workgroups(len) + slots - 1) / slots;
-        if (len >= whole || r <= most) break;
-      }
+      len = shortest(len, most * slots);
+      r = (workgroups(len) + slots - 1) / slots;
       if (r * len <= cost) {
         cost = r * len;
         best = len;
@@ -159,9 +167,10 @@ ChunkPlan varlen_plan(const lawcat_desc* d, const int32_t* seq_start, size_t roo
     // segments of 2112 / 960 1.43 times as fast, 52 of 84 to 2623 1344 / 768 1.13; 8 on 8 of 128, 57 of 47 to 2893 2048 / 1088 1.34.  Not for segments
     // that the state pass and the fold outweigh (of 64, 32 on 8, 6 of 482 to 858, 128 / 64 tokens 32.6 / 44.4 us, 16 on 8, 47 of 109 to 682, 448 / 256 55.2 / 60.8),
     // nor in the place of uncut sequences, which have no state pass (32 on 32 of 128, 17 of 35 to 474, uncut / 384 79.9 / 104.8).
-    for (len = std::max(first, d->dk == 64 ? 512 : 192); spill && d->B > 1 && d->B <= 64 && len < best && len * 5LL / 3 < cost; len += 64) {
-      const long long n = workgroups(len);
-      if (n > slots && 3 * n <= 4 * slots) {
+    len = std::max(first, d->dk == 64 ? 512 : 192);
+    if (spill && d->B > 1 && d->B <= 64 && len < best) {
+      len = shortest(len, 4 * slots / 3);
+      if (len < best && len * 5LL / 3 < cost && workgroups(len) > slots) {
         cost = len * 5LL / 3;
         best = len;
       }

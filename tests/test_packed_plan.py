@@ -1,5 +1,7 @@
 """How the one-launch plan of a packed batch cuts its sequences, on both sides of every line of its rules: segments of the longest sequence, from
 the workspace that the batch asks for, and waves of a workgroup of the output pass, from its launch (see launches.py).  CPU only."""
+import time
+
 import pytest
 
 from paper_2509_18467_amd import lawcat
@@ -85,3 +87,18 @@ def test_least_plan(directory, d, Hq, Hkv, lengths, segments, launches):
     assert quick[0] == 0 and quick[1] != launches
     assert short == least == (0, launches)
     assert (null == less == (-4, [])) if segments else (null == less == (0, launches))
+
+
+@pytest.mark.parametrize("d,Hq,Hkv", [(64, 32, 8), (128, 8, 8), (128, 32, 8), (128, 40, 8)])
+def test_time(d, Hq, Hkv):
+    """A plan does not look at the lengths of a segment one after the other (up to 420 us, 7 by halves): 64 sequences up to 131072 tokens."""
+    starts = [0]
+    for n in spread(64, 100, 131072):
+        starts.append(starts[-1] + n)
+    desc = lawcat.make_desc(64, 131072, Hq, Hkv, d)
+    best = 1.0
+    for _ in range(20):
+        t = time.perf_counter()
+        lawcat.varlen_workspace_bytes(desc, starts, True)
+        best = min(best, time.perf_counter() - t)
+    assert best < 1e-4
