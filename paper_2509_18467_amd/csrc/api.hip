@@ -161,16 +161,21 @@ ChunkPlan varlen_plan(const lawcat_desc* d, const int32_t* seq_start, size_t roo
         best = len;
       }
     }
-    if (!every || best == whole) return best;
+    if (!every || (best == whole && uncut > slots)) return best;
     // Two workgroups a unit, longest first (up to 64 sequences, find_place): up to a third too many cost two thirds of a round more at most; they
     // are the shortest ones and begin as others end, and who is left alone in a unit is faster.  Heads of 64, 16 on 8, 58 of 128 to 2923 tokens,
     // segments of 2112 / 960 1.43 times as fast, 52 of 84 to 2623 1344 / 768 1.13; 8 on 8 of 128, 57 of 47 to 2893 2048 / 1088 1.34.  Not for segments
     // that the state pass and the fold outweigh (of 64, 32 on 8, 6 of 482 to 858, 128 / 64 tokens 32.6 / 44.4 us, 16 on 8, 47 of 109 to 682, 448 / 256 55.2 / 60.8),
-    // nor in the place of uncut sequences, which have no state pass (32 on 32 of 128, 17 of 35 to 474, uncut / 384 79.9 / 104.8).
+    // nor in the place of uncut sequences, which have no state pass, of more than a round (32 on 32 of 128, 17 of 35 to 474, uncut / 384 79.9 / 104.8), or
+    // if they stay longer than two fifths (16 on 16 of 64, 32 of 135 to 1947, 0.52, 133 / 140, 24 on 24, 21 of 69 to 2074, 0.45, 121 / 130, 8 on 8, 64 of
+    // 244 to 2522, 0.47, 158 / 175; 24 on 24, 21 of 20 to 1385, 0.36, 92 / 60, 10 on 10, 51 of 50 to 1475, 0.33, 90 / 87, 32 on 8, 64 of 100 to 7743
+    // 722 / 386); at head dim 128 than half (16 on 16, 32 of 41 to 2087, 0.42, 260 / 208).  A sequence's workgroups go round the eight dies: where
+    // they are no multiple of that, gains are uneven (20 on 20 of 128, 25 of 29 to 1762 201 / 226, 26 to 1611 172 / 148; 10 on 10, 51 of 11 to 1030 113 / 127).
     len = std::max(first, d->dk == 64 ? 512 : 192);
     if (spill && d->B > 1 && d->B <= 64 && len < best) {
       len = shortest(len, 4 * slots / 3);
-      if (len < best && len * 5LL / 3 < cost && workgroups(len) > slots) {
+      if (len < best && len * 5LL / 3 < cost && workgroups(len) > slots &&
+          (best < whole || (lanes % 8 == 0 && (d->dk == 64 ? 5 * len <= 2 * whole : 2 * len < whole)))) {
         cost = len * 5LL / 3;
         best = len;
       }
