@@ -187,12 +187,15 @@ ChunkPlan varlen_plan(const lawcat_desc* d, const int32_t* seq_start, size_t roo
     // to 170, 112, 1.04, 13 of 29 to 158, 176, 1.13; 32 on 8, 2 of 83 to 137, 40, 0.93, 7 of 33 to 153, 104, 1.11, 13 of 89 to 136, 216, 1.22), except where
     // workgroups for four heads, which walk longest, are few and few sequences are cut (32 on 8, 20 of 2 to 185, 232 / 160, 0.90, 30 of 2 to 179, 328 /
     // 240, 0.96, but 26 of 21 to 151, 328 / 208, 1.01, 39 of 4 to 187, 432 / 312, 1.15).  Each of a group's launches walks all of it.
+    // Nothing where cutting takes a round more, from 512 tokens on: those rounds overlap (32 on 4, 64 of 77 to 386, 448 tokens at most in one round / 192 in
+    // two 63 / 73, but 128 on 16, 16 of 172 to 641, 704 / 320 93 / 83, 64 on 8, 32 of 61 to 525, 576 / 256 77 / 79, of 69 to 534 78 / 70).
     const long long rounds = (uncut + slots - 1) / slots, now = workgroups(best);
     if (d->dk == 128) return rounds * longest <= cost + 128 ? whole : best;
     const GroupCover c = cover_group(group, now / parts), all = cover_group(group, uncut / parts);
     const bool heavy = c.launches == 1 && all.launches == 1 && (now + slots - 1) / slots == rounds &&
                        (best >= 320 || (now * std::min(group, 4) >= 200 && (group <= 2 || all.most < 4 || 5 * now >= 8 * uncut || now >= 400)));
-    return all.launches * rounds * whole <= c.launches * cost + rounds * (heavy ? 128 : 64) ? whole : best;
+    const int state = (now + slots - 1) / slots > rounds && whole > 448 ? 0 : heavy ? 128 : 64;
+    return all.launches * rounds * whole <= c.launches * cost + rounds * state ? whole : best;
   };
   ChunkPlan p{};
   const ChunkPlan one = make_chunk_plan(1, tokens, d->Hq, d->Hkv, d->dk, d->carry_mode, d->segment, false, SIZE_MAX);

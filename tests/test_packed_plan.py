@@ -59,7 +59,9 @@ def test_full_round(directory, d, Hq, Hkv, lengths, segments, waves):
     # by how many sequences are cut where workgroups take four heads
     (32, 8, spread(20, 2, 185), 3), (16, 4, spread(33, 19, 145), 3), (16, 2, spread(78, 10, 250), 2), (32, 8, spread(39, 4, 187), 1),
     # in two launches; long segments
-    (20, 4, spread(27, 35, 192), 3), (32, 8, spread(43, 459, 651), 1)])
+    (20, 4, spread(27, 35, 192), 3), (32, 8, spread(43, 459, 651), 1),
+    # in a round more
+    (32, 4, spread(64, 70, 448), 1), (128, 16, spread(16, 80, 641), 3), (64, 8, spread(32, 69, 534), 3)])
 def test_uncut(directory, Hq, Hkv, lengths, segments):
     assert plan(directory, 64, Hq, Hkv, lengths) == (segments, 4)
 
