@@ -169,13 +169,13 @@ ChunkPlan varlen_plan(const lawcat_desc* d, const int32_t* seq_start, size_t roo
     // nor in the place of uncut sequences, which have no state pass, of more than a round (32 on 32 of 128, 17 of 35 to 474, uncut / 384 79.9 / 104.8), or
     // if they stay longer than two fifths (16 on 16 of 64, 32 of 135 to 1947, 0.52, 133 / 140, 24 on 24, 21 of 69 to 2074, 0.45, 121 / 130, 8 on 8, 64 of
     // 244 to 2522, 0.47, 158 / 175; 24 on 24, 21 of 20 to 1385, 0.36, 92 / 60, 10 on 10, 51 of 50 to 1475, 0.33, 90 / 87, 32 on 8, 64 of 100 to 7743
-    // 722 / 386); at head dim 128 than half (16 on 16, 32 of 41 to 2087, 0.42, 260 / 208).  A sequence's workgroups go round the eight dies: where
-    // they are no multiple of that, gains are uneven (20 on 20 of 128, 25 of 29 to 1762 201 / 226, 26 to 1611 172 / 148; 10 on 10, 51 of 11 to 1030 113 / 127).
+    // 722 / 386; 16 on 16 of 128, 32 of 36 to 1966 257 / 213).  A sequence's workgroups go round the eight dies: where they are no multiple of that, gains
+    // are uneven (20 on 20 of 128, 25 of 29 to 1762 201 / 226, 26 to 1611 172 / 148; 10 on 10, 51 of 11 to 1030 113 / 127).
     len = std::max(first, d->dk == 64 ? 512 : 192);
     if (spill && d->B > 1 && d->B <= 64 && len < best) {
       len = shortest(len, 4 * slots / 3);
       if (len < best && len * 5LL / 3 < cost && workgroups(len) > slots &&
-          (best < whole || (lanes % 8 == 0 && (d->dk == 64 ? 5 * len <= 2 * whole : 2 * len < whole)))) {
+          (best < whole || (lanes % 8 == 0 && 5 * len <= 2 * whole))) {
         cost = len * 5LL / 3;
         best = len;
       }

@@ -39,11 +39,11 @@ def test_more_than_a_round(directory, Hq, Hkv, lengths, segments):
     assert plan(directory, 64, Hq, Hkv, lengths) == (segments, 4)
 
 
-# Where uncut sequences are a full round: cut if that leaves two fifths of the longest, at head dim 128 half; not of more than a round, nor where there are
-# more than 64, nor where a sequence's workgroups are no multiple of eight
+# Where uncut sequences are a full round: cut if that leaves two fifths of the longest; not of more than a round, nor where there are more than
+# 64, nor where a sequence's workgroups are no multiple of eight
 @pytest.mark.parametrize("d,Hq,Hkv,lengths,segments,waves", [
     (64, 32, 8, spread(64, 100, 7743), 3, 4), (64, 16, 16, spread(32, 15, 1500), 3, 4), (64, 16, 16, spread(32, 135, 1947), 1, 4),
-    (64, 32, 8, spread(65, 100, 7743), 1, 4), (128, 16, 16, spread(32, 41, 2087), 3, 4), (128, 10, 10, spread(51, 11, 1030), 1, 8),
+    (64, 32, 8, spread(65, 100, 7743), 1, 4), (128, 16, 16, spread(32, 36, 1966), 3, 4), (128, 16, 16, spread(32, 174, 2087), 1, 8), (128, 10, 10, spread(51, 11, 1030), 1, 8),
     (64, 20, 20, spread(25, 20, 1500), 1, 4), (128, 8, 8, spread(64, 10, 1114), 3, 4), (128, 32, 32, spread(17, 35, 474), 1, 8)])
 def test_full_round(directory, d, Hq, Hkv, lengths, segments, waves):
     assert plan(directory, d, Hq, Hkv, lengths) == (segments, waves)
