@@ -437,7 +437,7 @@ def main():
     }
     if r["kernel_ms"]:
         ach = r["bytes_step"] / (r["kernel_ms"] * 1e-3) / 1e9
-        out["roofline"] = {"bound": "hbm", "kernel": "gla_chunk_kernel (output pass)", "achieved": ach,
+        out["roofline"] = {"bound": "hbm", "kernel": "output pass", "achieved": ach,
                            "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": ach / HBM_PEAK_GBS,
                            "traffic": read_traffic(wl.name), "kernel_ms": r["kernel_ms"],
                            "algorithmic_bytes_per_launch": r["bytes_step"],

@@ -93,9 +93,9 @@ typedef struct lawcat_desc {
 
 /* Bytes of device scratch `which_call` (LAWCAT_CALL_*) needs for this desc; 0 if none.
  * Returns 0 for an invalid desc as well (the call itself reports the error).
- * lawcat_layer_prefill, head dimension 128, long sequences: the quickest form's; about half of it is taken, too
- * (LAWCAT_E_WORKSPACE below that): the sequence is then cut into segments twice as long and the call takes up to a seventh
- * longer, its results the same to rounding. */
+ * lawcat_layer_prefill, head dimension 128, long sequences: the quickest form's; what its other form needs is taken, too
+ * (LAWCAT_E_WORKSPACE below that): half of it or more for one sequence, none where whole sequences are workgroups enough.  The call
+ * then takes up to a quarter longer, its results the same to rounding. */
 LAWCAT_API size_t lawcat_workspace_bytes(const lawcat_desc* desc, int which_call);
 
 /*

@@ -32,7 +32,7 @@
 // sides of the boundary: no pass over the sequence is needed for it.
 //
 // What it measures (32768 tokens, 32 query heads on 8 kv heads, d = 64, bf16), kernel by kernel in a training pass under a profiler, at their
-// quickest / on average: state 14 / 15, scans 4, forward sweep 155 / 172, reverse sweep 152 / 171.  The two sweeps move 0.57 and 0.54 GB (q, dO,
+// quickest / on average: state 14 / 15, scans 4, forward sweep 155 / 172, reverse sweep 152 / 171 (on a slower card 164 / 181, 163 / 182).  The two sweeps move 0.57 and 0.54 GB (q, dO,
 // k, v, g once each, the gate term in fp32, the gradients), 105 us each at the rate of a large copy; what bounds them is a workgroup's dependent
 // chain through a chunk's sections between two barriers, at two waves per SIMD, whose registers leave room for no third (a limit of
 // 168 spilled: forward 636 us, reverse 423).  The training pass, us, step by step: 645; the reverse sweep's products of two fp32 operands as bf16 terms
